@@ -6,16 +6,21 @@
 //
 // Selecting the `heavy` largest under the order (score, then position) is the
 // same as repeatedly evicting the smallest (score, position) pair, the rule the
-// generation steps use.  One workgroup per head: an exact 4x8-bit radix select
-// on the order-preserving integer image of the scores finds the threshold, the
-// positions of equal-score tokens break the tie at the threshold, a block scan
-// assigns slots, then all threads copy rows with 128-bit accesses.
+// generation steps use.  An exact radix select on the order-preserving integer
+// image of the scores finds the threshold, the positions of equal-score tokens
+// break the tie at the threshold, ballots and a scan over the waves assign slots,
+// then all threads copy rows with 128-bit accesses.
 #include "wave_ops.h"
 
 namespace {
 
 constexpr int SG_NT = 512;
 constexpr int SG_NW = SG_NT / 64;
+constexpr int SG_BITS = 11;                 // radix digit: 11 + 11 + 10 bits
+constexpr int SG_BINS = 1 << SG_BITS;
+constexpr int SG_LDS_KEYS = 30720;          // ranking keys kept in LDS up to this many candidates (120 KiB)
+// where the ranking keys live during the selection
+constexpr int SG_KEYS_NONE = 0, SG_KEYS_LDS = 1;   // (any larger value: that many registers per thread)
 
 __device__ inline unsigned order_key(float x)
 {
@@ -23,9 +28,23 @@ __device__ inline unsigned order_key(float x)
     return (u & 0x80000000u) ? ~u : (u | 0x80000000u);   // monotone in x
 }
 
-// Exclusive prefix sum of one int per thread over the workgroup; `total`
-// receives the sum.  `scratch` holds SG_NW + 1 ints.
-__device__ inline int block_exclusive_scan(int v, int *scratch, int &total)
+// Sum over the workgroup of one int per thread (every thread gets it).  `scratch`
+// holds SG_NW ints.
+__device__ inline int block_sum(int v, int *scratch)
+{
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+    __syncthreads();                       // scratch may still be read from a previous use
+    if ((threadIdx.x & 63) == 0) scratch[threadIdx.x >> 6] = v;
+    __syncthreads();
+    int tot = 0;
+#pragma unroll
+    for (int w = 0; w < SG_NW; ++w) tot += scratch[w];
+    return tot;
+}
+
+// Exclusive prefix sum of one int per thread over the workgroup.  `scratch` holds SG_NW ints.
+__device__ inline int block_exclusive_scan(int v, int *scratch)
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     int inc = v;
@@ -37,14 +56,10 @@ __device__ inline int block_exclusive_scan(int v, int *scratch, int &total)
     __syncthreads();                       // scratch may still be read from a previous scan
     if (lane == 63) scratch[wave] = inc;
     __syncthreads();
-    int base = 0, tot = 0;
+    int base = 0;
 #pragma unroll
-    for (int w = 0; w < SG_NW; ++w) {
-        const int s = scratch[w];
-        if (w < wave) base += s;
-        tot += s;
-    }
-    total = tot;
+    for (int w = 0; w < SG_NW; ++w)
+        if (w < wave) base += scratch[w];
     return base + inc - v;
 }
 
@@ -55,20 +70,37 @@ __device__ inline int block_exclusive_scan(int v, int *scratch, int &total)
 // type: the cache stores 4-bit codes and the kept rows (ROWB bytes of QDT
 // elements) are quantised on their way in.  PAT: built for a sparse-attention
 // pattern as the protected set (the recent-window build carries none of that code).
-template <int ROWB, int QDT, bool PAT>
+//
+// `parts` workgroups share a head: each makes the whole selection for itself and
+// fills its own share of the slots (positions, scores, rows), so they need nothing
+// from each other.  What bounds the kernel is the row copy; one workgroup per head
+// left most of the chip idle at few heads, and a head's copy then runs at the rate
+// of one CU.  The selection is a few microseconds of latency: a wave works on a
+// contiguous run of entries, 64 at a time, so that reads are coalesced and ranks come
+// from ballots; the ranking keys are formed once and kept in KEYS registers per
+// thread (all reads in flight at once, no LDS latency in the sweeps), in LDS for
+// longer prompts, and beyond SG_LDS_KEYS candidates formed again for every sweep.
+// Measured, one workgroup per head and byte digits -> this: 32 heads, 3277 of 16 384
+// tokens, f16 d = 128: 134 -> 45 us (keys in LDS: 54) for 110 MB; 128 heads, 819 of
+// 4096: 42 -> 29 us; 512 heads, 410 of 2048: 48 -> 45 us (a copy's rate: 4.9 TB/s).
+template <int ROWB, int QDT, bool PAT, int KEYS>
 __global__ __launch_bounds__(SG_NT) void select_gather_kernel(
     const char *__restrict__ Kp, const char *__restrict__ Vp, const float *__restrict__ score,
     const float *__restrict__ base, const int32_t *__restrict__ pos_in, int n, int t_new,
     char *__restrict__ Kc, char *__restrict__ Vc, float *__restrict__ acc_g,
-    int32_t *__restrict__ pos_g, int k, int heavy, int recent, int rank, int protect, int stride)
+    int32_t *__restrict__ pos_g, int k, int heavy, int recent, int rank, int protect, int stride,
+    int parts, int part_slots)
 {
     extern __shared__ __align__(16) unsigned char smem[];
-    int *sel_l = reinterpret_cast<int *>(smem);        // [k] slot -> prompt position
-    __shared__ unsigned hist[256];
+    int *sel_l = reinterpret_cast<int *>(smem);        // [part_slots] slot -> candidate
+    unsigned *key_l = reinterpret_cast<unsigned *>(sel_l + part_slots);   // [n] (SG_KEYS_LDS)
+    __shared__ unsigned hist[SG_BINS];
     __shared__ unsigned sh_prefix, sh_need;
-    __shared__ int scan_l[SG_NW + 1];
+    __shared__ int scan_l[2 * SG_NW];
 
-    const int head = blockIdx.x, tid = threadIdx.x;
+    const int head = blockIdx.x / parts, tid = threadIdx.x;
+    const int sb = (blockIdx.x % parts) * part_slots;  // this workgroup's slots [sb, se)
+    const int se = min(k, sb + part_slots);
     const float *sc_in = score + (size_t)head * n;
     const float *bs = base ? base + (size_t)head * n : nullptr;
     const int32_t *pin = pos_in ? pos_in + (size_t)head * n : nullptr;
@@ -82,13 +114,49 @@ __global__ __launch_bounds__(SG_NT) void select_gather_kernel(
     auto ranked = [&](float v, int j) {
         return rank == H2O_RANK_AVERAGED ? __fdiv_rn(v, (float)(t_new - pos_of(j))) : v;
     };
+    // this wave's run of entries
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int run = ((n + SG_NW - 1) / SG_NW + 63) & ~63;
+    const int j0 = min(n, wave * run), j1 = min(n, j0 + run);
+    constexpr bool IN_REGS = KEYS > SG_KEYS_LDS;
+    unsigned key_r[IN_REGS ? KEYS : 1];
+    // f(entry, its key) for every entry of the wave's run, one per lane, ascending; lanes
+    // past the run's end get entry n
+    auto sweep = [&](auto f) {
+        if constexpr (IN_REGS) {
+#pragma unroll
+            for (int i = 0; i < KEYS; ++i) {
+                if (j0 + i * 64 >= j1) break;          // wave-uniform
+                const int j = j0 + i * 64 + lane;
+                f(j < j1 ? j : n, key_r[i]);
+            }
+        } else {
+            for (int b = j0; b < j1; b += 64) {
+                const int j = b + lane;
+                unsigned key = 0;
+                if (j < j1) {
+                    if constexpr (KEYS == SG_KEYS_LDS) key = key_l[j];
+                    else key = order_key(ranked(sc_of(j), j));
+                }
+                f(j < j1 ? j : n, key);
+            }
+        }
+    };
 
-    for (int s = tid; s < k; s += SG_NT) sel_l[s] = -1;
+    for (int s = sb + tid; s < se; s += SG_NT) sel_l[s - sb] = n <= k && s < n ? s : -1;
 
-    if (n <= k) {
-        __syncthreads();
-        for (int s = tid; s < n; s += SG_NT) sel_l[s] = s;
-    } else {
+    if (n > k) {
+        if constexpr (IN_REGS) {
+#pragma unroll
+            for (int i = 0; i < KEYS; ++i) {
+                const int j = min(j0 + i * 64 + lane, n - 1);
+                key_r[i] = order_key(ranked(sc_of(j), j));
+            }
+        } else if constexpr (KEYS == SG_KEYS_LDS) {
+            // (written and read by the same wave)
+#pragma unroll 8
+            for (int j = j0 + lane; j < j1; j += 64) key_l[j] = order_key(ranked(sc_of(j), j));
+        }
         // Which entries compete.  With the recent window (protect 0) the candidates are
         // the entries in front of the last `recent` positions; positions ascend, so they
         // are a prefix [0, older) and `heavy` of them are kept.  With a sparse-attention
@@ -104,18 +172,13 @@ __global__ __launch_bounds__(SG_NT) void select_gather_kernel(
         if constexpr (PAT) {
             int cnt = 0;
             for (int j = tid; j < n; j += SG_NT) cnt += covered(j);
-            int total;
-            block_exclusive_scan(cnt, scan_l, total);
+            const int total = block_sum(cnt, scan_l);
             overflow = total > k;
             want = overflow ? k : k - total;
-            __syncthreads();
         } else if (pin) {
             int cnt = 0;
             for (int j = tid; j < n; j += SG_NT) cnt += pin[j] < t_new - recent;
-            int total;
-            block_exclusive_scan(cnt, scan_l, total);
-            older = total;
-            __syncthreads();
+            older = block_sum(cnt, scan_l);
         }
         auto is_cand = [&](int j) {
             if constexpr (PAT) return covered(j) == overflow;
@@ -125,79 +188,101 @@ __global__ __launch_bounds__(SG_NT) void select_gather_kernel(
             if constexpr (PAT) return !overflow && covered(j);
             else return j >= older;
         };
-        const int cand_end = PAT ? n : older;          // candidates lie in [0, cand_end)
         unsigned thr = 0, need = 0;                    // keep keys > thr, and `need` of those == thr
         if (want > 0) {
             // radix select: the want-th largest key among the candidates (there are more
-            // than `want` of them: n exceeds the budget)
+            // than `want` of them: n exceeds the budget).  Three digits of 11, 11 and 10
+            // bits: the first one (sign, exponent, two mantissa bits) already spreads
+            // scores over dozens of bins, where 8 bits had put nearly all of them, and the
+            // LDS atomics with them, into a handful.
             unsigned prefix = 0, mask = 0;
             need = (unsigned)want;
-            for (int shift = 24; shift >= 0; shift -= 8) {
-                for (int b = tid; b < 256; b += SG_NT) hist[b] = 0;
+#pragma unroll 1
+            for (int d = 0; d < 3; ++d) {
+                const int shift = d == 0 ? 21 : d == 1 ? 10 : 0;
+                const unsigned dmask = d == 2 ? 1023u : 2047u;
+                for (int b = tid; b < SG_BINS; b += SG_NT) hist[b] = 0;
                 __syncthreads();
-                for (int j = tid; j < cand_end; j += SG_NT) {
-                    if (!is_cand(j)) continue;
-                    const unsigned key = order_key(ranked(sc_of(j), j));
-                    if ((key & mask) == prefix) atomicAdd(&hist[(key >> shift) & 255u], 1u);
-                }
+                sweep([&](int j, unsigned key) {
+                    if (j < n && (key & mask) == prefix && is_cand(j))
+                        atomicAdd(&hist[(key >> shift) & dmask], 1u);
+                });
                 __syncthreads();
-                // the bin in which the count from the top reaches `need`: thread r looks
-                // at bin 255 - r, the scan gives it the count of all higher bins
+                // the bin in which the count from the top reaches `need`: thread r looks at
+                // the bins SG_BINS - 1 - 4r and the three below, the scan gives it the count
+                // of all higher bins
                 {
-                    const int bin = 255 - tid;
-                    const int cnt = tid < 256 ? (int)hist[bin] : 0;
-                    int total;
-                    const int above = block_exclusive_scan(cnt, scan_l, total);
-                    if (tid < 256 && (unsigned)above < need && (unsigned)(above + cnt) >= need) {
-                        sh_prefix = prefix | ((unsigned)bin << shift);
-                        sh_need = need - (unsigned)above;   // still needed inside that bin
+                    static_assert(SG_BINS == 4 * SG_NT, "four bins per thread");
+                    const int top = SG_BINS - 4 - 4 * tid;
+                    const uint4 h = *reinterpret_cast<const uint4 *>(hist + top);
+                    const unsigned c[4] = {h.w, h.z, h.y, h.x};
+                    unsigned above = (unsigned)block_exclusive_scan((int)(c[0] + c[1] + c[2] + c[3]), scan_l);
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        if (above < need && above + c[i] >= need) {
+                            sh_prefix = prefix | ((unsigned)(top + 3 - i) << shift);
+                            sh_need = need - above;     // still needed inside that bin
+                        }
+                        above += c[i];
                     }
                 }
                 __syncthreads();
                 prefix = sh_prefix;
                 need = sh_need;
-                mask |= 255u << shift;
-                __syncthreads();
+                mask |= dmask << shift;
             }
             thr = prefix;
         }
-        // each thread owns a contiguous run of positions so that ranks follow position order
-        const int per = (n + SG_NT - 1) / SG_NT;
-        const int j0 = min(n, tid * per), j1 = min(n, j0 + per);
-        int eq_cnt = 0;
-        if (want > 0)
-            for (int j = j0; j < min(j1, cand_end); ++j)
-                eq_cnt += is_cand(j) && order_key(ranked(sc_of(j), j)) == thr;
-        int eq_total;
-        int eq_before = block_exclusive_scan(eq_cnt, scan_l, eq_total);
-        // among equal scores the higher positions are kept: the last `need` of them
-        const int eq_first_kept = eq_total - (int)need;
-        auto kept = [&](int j, int &e) {
-            if (always(j)) return true;
-            if (want <= 0 || !is_cand(j)) return false;
-            const unsigned key = order_key(ranked(sc_of(j), j));
-            if (key > thr) return true;
-            if (key == thr) { const bool keep = e >= eq_first_kept; ++e; return keep; }
-            return false;
+        // Ranks in position order.  A wave first counts, in its run, the entries that are kept
+        // outright and those at the threshold, then (knowing how many of both the waves in
+        // front have) it assigns slots.
+        auto look = [&](int j, unsigned key, bool &sure, bool &equal) {
+            sure = equal = false;
+            if (j < n) {
+                sure = always(j);
+                if (!sure && want > 0 && is_cand(j)) {
+                    sure = key > thr;
+                    equal = key == thr;
+                }
+            }
         };
-        int keep_cnt = 0;
-        {
-            int e = eq_before;
-            for (int j = j0; j < j1; ++j) keep_cnt += kept(j, e);
+        int sure_cnt = 0, eq_cnt = 0;
+        sweep([&](int j, unsigned key) {
+            bool sure, equal;
+            look(j, key, sure, equal);
+            sure_cnt += __popcll(__ballot(sure));
+            eq_cnt += __popcll(__ballot(equal));
+        });
+        __syncthreads();
+        if (lane == 0) { scan_l[wave] = sure_cnt; scan_l[SG_NW + wave] = eq_cnt; }
+        __syncthreads();
+        int slot = 0, e = 0, eq_total = 0;
+#pragma unroll
+        for (int w = 0; w < SG_NW; ++w) {
+            if (w < wave) { slot += scan_l[w]; e += scan_l[SG_NW + w]; }
+            eq_total += scan_l[SG_NW + w];
         }
-        int kept_total;
-        int slot = block_exclusive_scan(keep_cnt, scan_l, kept_total);
-        {
-            int e = eq_before;
-            for (int j = j0; j < j1; ++j)
-                if (kept(j, e)) { if (slot < k) sel_l[slot] = j; ++slot; }
-        }
+        // among equal scores the higher positions are kept: the last `need` of them
+        const int eq_first = eq_total - (int)need;
+        slot += max(0, e - eq_first);
+        const unsigned long long below = (1ull << lane) - 1ull;
+        sweep([&](int j, unsigned key) {
+            bool sure, equal;
+            look(j, key, sure, equal);
+            const unsigned long long eqs = __ballot(equal);
+            const bool keep = sure || (equal && e + __popcll(eqs & below) >= eq_first);
+            const unsigned long long kept = __ballot(keep);
+            const int mine = slot + __popcll(kept & below);
+            if (keep && mine >= sb && mine < se) sel_l[mine - sb] = j;
+            slot += __popcll(kept);
+            e += __popcll(eqs);
+        });
     }
     __syncthreads();
 
-    // bookkeeping of every slot
-    for (int s = tid; s < k; s += SG_NT) {
-        const int j = sel_l[s];
+    // bookkeeping of this workgroup's slots
+    for (int s = sb + tid; s < se; s += SG_NT) {
+        const int j = sel_l[s - sb];
         pos_g[hoff + s] = j >= 0 ? pos_of(j) : -1;
         acc_g[hoff + s] = j >= 0 ? sc_of(j) : 0.f;
     }
@@ -214,9 +299,9 @@ __global__ __launch_bounds__(SG_NT) void select_gather_kernel(
         const size_t pbase = (size_t)head * n * ROWB;
         typedef float f32x2 __attribute__((ext_vector_type(2)));
         // every lane runs every round (the reductions inside the quantiser span lanes)
-        for (int s0 = 0; s0 < k; s0 += RPR) {
+        for (int s0 = sb; s0 < se; s0 += RPR) {
             const int s = s0 + rsub;
-            const int j = s < k ? sel_l[s] : -1;
+            const int j = s < se ? sel_l[s - sb] : -1;
             const size_t off = pbase + (size_t)max(j, 0) * ROWB;
             float kx[8], vx[8];
             load8<QDT>(reinterpret_cast<const T *>(Kp + off) + l * 8, kx);
@@ -244,13 +329,13 @@ __global__ __launch_bounds__(SG_NT) void select_gather_kernel(
     // four rows per thread in flight (unconditional loads of a clamped row, so that
     // the requests of a batch leave back to back)
     constexpr int UNR = 4;
-    for (int s0 = rsub; s0 < k; s0 += UNR * ROWS_PER_ROUND) {
+    for (int s0 = sb + rsub; s0 < se; s0 += UNR * ROWS_PER_ROUND) {
         int j[UNR];
         uint4 kv[UNR], vv[UNR];
 #pragma unroll
         for (int u = 0; u < UNR; ++u) {
             const int s = s0 + u * ROWS_PER_ROUND;
-            j[u] = s < k ? sel_l[s] : -1;
+            j[u] = s < se ? sel_l[s - sb] : -1;
             const size_t off = pbase + (size_t)max(j[u], 0) * ROWB + li * 16;
             kv[u] = *reinterpret_cast<const uint4 *>(Kp + off);
             vv[u] = *reinterpret_cast<const uint4 *>(Vp + off);
@@ -301,17 +386,46 @@ hipError_t h2o_launch_select_gather(const h2o_cache &c, const void *K, const voi
 {
     const int heads = c.cfg.batch * c.cfg.heads;
     const int rowb = c.cfg.head_dim * c.esize;
-    const size_t smem = (size_t)c.k * sizeof(int);
     const char *Kp = static_cast<const char *>(K), *Vp = static_cast<const char *>(V);
-#define H2O_SG_ARGS                                                                             \
-    dim3(heads), dim3(SG_NT), smem, st, Kp, Vp, score, base, pos_in, n, t_new, c.K, c.V, c.acc,     \
-        c.pos, c.k, c.cfg.heavy, c.cfg.recent, c.cfg.rank, c.cfg.protect, c.cfg.stride
+    // Workgroups per head: enough to give every CU two, but at least 32 slots each
+    // (one round of the row copy).
+    int parts = (2 * 256 + heads - 1) / heads;
+    if (const int most = (c.k + 31) / 32; parts > most) parts = most;
+    const int part_slots = (c.k + parts - 1) / parts;
+    parts = (c.k + part_slots - 1) / part_slots;
+    // Keys in registers: 8 per thread up to 4096 candidates, 32 up to 16 384 (window mode;
+    // the pattern modes, whose sweeps also test the pattern, keep them in LDS).
+    const bool window = c.cfg.protect == H2O_PROTECT_RECENT;
+    const int keys = window && n <= 8 * SG_NT    ? 8
+                     : window && n <= 32 * SG_NT ? 32
+                     : n <= SG_LDS_KEYS          ? SG_KEYS_LDS
+                                                 : SG_KEYS_NONE;
+    const size_t smem = (size_t)part_slots * sizeof(int) + (keys == SG_KEYS_LDS && n > c.k ? (size_t)n * 4 : 0);
+    auto launch = [&](auto kern, bool &raised) -> hipError_t {
+        if (smem > 40 * 1024 && !raised) {
+            const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, 140 * 1024);
+            if (e != hipSuccess) return e;
+            raised = true;
+        }
+        hipLaunchKernelGGL(kern, dim3((unsigned)heads * parts), dim3(SG_NT), smem, st, Kp, Vp, score, base,
+                           pos_in, n, t_new, c.K, c.V, c.acc, c.pos, c.k, c.cfg.heavy, c.cfg.recent,
+                           c.cfg.rank, c.cfg.protect, c.cfg.stride, parts, part_slots);
+        return hipGetLastError();
+    };
+#define H2O_SG1(RB, QDT, PAT, KEYS)                                                             \
+    do {                                                                                        \
+        static bool raised = false;                                                             \
+        return launch(select_gather_kernel<RB, QDT, PAT, KEYS>, raised);                        \
+    } while (0)
 #define H2O_SG(RB, QDT)                                                                         \
     do {                                                                                        \
-        if (c.cfg.protect == H2O_PROTECT_RECENT)                                                \
-            hipLaunchKernelGGL((select_gather_kernel<RB, QDT, false>), H2O_SG_ARGS);            \
-        else                                                                                    \
-            hipLaunchKernelGGL((select_gather_kernel<RB, QDT, true>), H2O_SG_ARGS);             \
+        if (window && keys == 8) H2O_SG1(RB, QDT, false, 8);                                    \
+        if (window && keys == 32) H2O_SG1(RB, QDT, false, 32);                                  \
+        if (window && keys == SG_KEYS_LDS) H2O_SG1(RB, QDT, false, SG_KEYS_LDS);                \
+        if (window) H2O_SG1(RB, QDT, false, SG_KEYS_NONE);                                      \
+        if (keys == SG_KEYS_LDS) H2O_SG1(RB, QDT, true, SG_KEYS_LDS);                           \
+        H2O_SG1(RB, QDT, true, SG_KEYS_NONE);                                                   \
     } while (0)
     if (c.cfg.kv_bits == 4) {
         const int d = c.cfg.head_dim;
@@ -320,7 +434,6 @@ hipError_t h2o_launch_select_gather(const h2o_cache &c, const void *K, const voi
         case H2O_F16: if (d == 64) H2O_SG(128, H2O_F16); else H2O_SG(256, H2O_F16); break;
         default: if (d == 64) H2O_SG(128, H2O_BF16); else H2O_SG(256, H2O_BF16); break;
         }
-        return hipGetLastError();
     }
     switch (rowb) {
     case 128: H2O_SG(128, -1); break;
@@ -329,8 +442,7 @@ hipError_t h2o_launch_select_gather(const h2o_cache &c, const void *K, const voi
     default: return hipErrorInvalidValue;
     }
 #undef H2O_SG
-#undef H2O_SG_ARGS
-    return hipGetLastError();
+#undef H2O_SG1
 }
 
 // ---- cache + chunk -> one candidate list per head ---------------------------------
