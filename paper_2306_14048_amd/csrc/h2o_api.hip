@@ -214,7 +214,7 @@ size_t h2o_prefill_attention_workspace_bytes(const h2o_config *cfg, int32_t n)
 {
     if (check_config(cfg) != H2O_OK || n < 1 || n > H2O_MAX_PROMPT) return 0;
     if (cfg->dtype == H2O_F32) return 0;
-    return align_up(h2o_attn_vt_bytes(*cfg, n), 256) + h2o_prefill_workspace_bytes(cfg, n);
+    return align_up(h2o_attn_vcopy_bytes(*cfg, n), 256) + h2o_prefill_workspace_bytes(cfg, n);
 }
 
 int h2o_prefill_attention(const h2o_config *cfg, const void *Q, const void *K, const void *V,
@@ -230,7 +230,7 @@ int h2o_prefill_attention(const h2o_config *cfg, const void *Q, const void *K, c
     if (n > H2O_MAX_PROMPT || cfg->dtype == H2O_F32) return H2O_EUNSUPPORTED;
     if (ws_bytes < h2o_prefill_attention_workspace_bytes(cfg, n)) return H2O_ENOMEM;
     char *ws = static_cast<char *>(workspace);
-    float *lse2 = reinterpret_cast<float *>(ws + align_up(h2o_attn_vt_bytes(*cfg, n), 256));
+    float *lse2 = reinterpret_cast<float *>(ws + align_up(h2o_attn_vcopy_bytes(*cfg, n), 256));
     return hip_rc(h2o_launch_prefill_attention(*cfg, h2o_scale_of(*cfg), Q, K, V, n, n, ws, lse2,
                                                lse_out, out, static_cast<hipStream_t>(hip_stream)));
 }
@@ -247,7 +247,7 @@ int h2o_prefill_attention_scores(h2o_cache *cache, const void *Q, const void *K,
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
     char *ws = static_cast<char *>(workspace);
     const size_t half = h2o_prefill_workspace_bytes(cfg, n) / 2;
-    float *lse2 = reinterpret_cast<float *>(ws + align_up(h2o_attn_vt_bytes(*cfg, n), 256));
+    float *lse2 = reinterpret_cast<float *>(ws + align_up(h2o_attn_vcopy_bytes(*cfg, n), 256));
     float *sums = colsum_out ? colsum_out : reinterpret_cast<float *>(reinterpret_cast<char *>(lse2) + half);
     const hipError_t e = h2o_launch_prefill_colsum(*cfg, h2o_scale_of(*cfg), Q, K, n, n, lse2, sums, st);
     if (e != hipSuccess) return H2O_EHIP;
@@ -264,11 +264,11 @@ size_t h2o_prefill_chunk_workspace_bytes(const h2o_config *cfg, int32_t m, int32
     const size_t rows = align_up(heads * ncat * cfg->head_dim * h2o_esize(cfg->dtype), 256);
     const size_t vec = align_up(heads * ncat * sizeof(float), 256);
     // K and V of cache + chunk, old scores, positions, column sums, row statistics,
-    // the slots in position order (+ the transposed V of cache + chunk when the
+    // the slots in position order (+ room for a copy of V of cache + chunk when the
     // attention output is wanted)
     return 2 * rows + 3 * vec + align_up(heads * (size_t)m * sizeof(float), 256) +
            align_up(heads * k * sizeof(int32_t), 256) +
-           (with_output ? align_up(h2o_attn_vt_bytes(*cfg, (int)ncat), 256) : 0);
+           (with_output ? align_up(h2o_attn_vcopy_bytes(*cfg, (int)ncat), 256) : 0);
 }
 
 int h2o_prefill_chunk(h2o_cache *cache, const void *Q, const void *K, const void *V, int32_t m,
@@ -295,7 +295,7 @@ int h2o_prefill_chunk(h2o_cache *cache, const void *Q, const void *K, const void
     float *lse = reinterpret_cast<float *>(ws + 2 * rows + 3 * vec);
     int32_t *order = reinterpret_cast<int32_t *>(ws + 2 * rows + 3 * vec +
                                                  align_up(heads * (size_t)m * sizeof(float), 256));
-    char *vt = reinterpret_cast<char *>(order) + align_up(heads * (size_t)cache->k * sizeof(int32_t), 256);
+    char *vcopy = reinterpret_cast<char *>(order) + align_up(heads * (size_t)cache->k * sizeof(int32_t), 256);
     const int ncat = occ + m;
     const double scale = h2o_scale_of(cfg);
     // after generation steps have evicted, the slots are first put in position order
@@ -303,7 +303,7 @@ int h2o_prefill_chunk(h2o_cache *cache, const void *Q, const void *K, const void
                                      base, pos_cat, st);
     if (e != hipSuccess) return H2O_EHIP;
     // row statistics: a by-product of the attention output when that is wanted
-    e = out ? h2o_launch_prefill_attention(cfg, scale, Q, Kcat, Vcat, m, ncat, vt, lse, nullptr, out, st)
+    e = out ? h2o_launch_prefill_attention(cfg, scale, Q, Kcat, Vcat, m, ncat, vcopy, lse, nullptr, out, st)
             : h2o_launch_prefill_lse(cfg, scale, Q, Kcat, m, ncat, lse, st);
     if (e != hipSuccess) return H2O_EHIP;
     e = h2o_launch_prefill_colsum(cfg, scale, Q, Kcat, m, ncat, lse, colsum, st);

@@ -23,12 +23,14 @@
 // the output accumulator are per-lane scalars; the only cross-lane traffic is
 // one exchange of the tile maximum between the two lane halves that share a
 // query.  V is needed with the key index innermost (A operand of the second
-// product); it is transposed once per call into the workspace ([head][d][n],
-// zero padded to whole tiles), after which its tiles are copied and read
-// exactly like key tiles.  The key rows of a tile are visited in an order that
-// makes the 8 probabilities a lane holds for one MFMA step belong to 8
-// consecutive keys, so P^T goes from the accumulator registers into the second
-// product without any shuffle and the V^T fragment is one 128-bit LDS read.
+// product): its tiles are copied into LDS row by row, exactly like key tiles, and
+// read with the transposing LDS read, in which 16 lanes fetch 4 keys x 16 dims and
+// each lane receives the 4 keys of one dim.  (A first version transposed V in global
+// memory once per call: 49-52 us of the 650 + 50 us that 128 heads x 4096 tokens x 128
+// take, and 20 of 160 us on a 1024-token chunk.)  The key rows of a tile are visited
+// in an order that makes the 8 probabilities a lane holds for one MFMA step belong to
+// 8 consecutive keys, so P^T goes from the accumulator registers into the second
+// product without any shuffle and the V^T fragment is two 64-bit LDS reads.
 //
 // Schedule: as in the scoring passes, two groups of four waves run one barrier
 // apart; one group's matrix phase (P.V of the previous tile, then Q.K of this
@@ -84,41 +86,20 @@ constexpr int ANW = 8;       // waves per workgroup
 constexpr int ANS = 3;       // stages (key tile + value tile each); copies run two tiles ahead
 constexpr int ABN = 64;      // keys per tile
 
-// ---- V -> V^T ([head][n][d] -> [head][d][npad]), zero padded ----------------------
-template <int D>
-__global__ __launch_bounds__(256) void transpose_v_kernel(const uint16_t *__restrict__ V,
-                                                          uint16_t *__restrict__ Vt, int n, int npad)
+// the 4 consecutive keys of one dim out of a row-major tile in LDS (transposing read: see above)
+__device__ inline uint2 read_keys4(const unsigned char *lds)
 {
-    // rows go into LDS in 32-bit pieces; the pitch of D + 2 elements (an odd number of
-    // words) spreads the column reads below over the banks
-    constexpr int PITCH = D + 2;
-    __shared__ __align__(4) uint16_t tile[ABN * PITCH];
-    const int head = blockIdx.x, j0 = blockIdx.y * ABN, tid = threadIdx.x;
-    const uint16_t *Vh = V + (size_t)head * n * D;
-    uint16_t *Vth = Vt + (size_t)head * D * npad;
-    constexpr int CPR = D / 8;                       // 16-byte chunks per row
-    for (int q = tid; q < ABN * CPR; q += 256) {
-        const int r = q / CPR, c = q % CPR;
-        uint4 v = make_uint4(0, 0, 0, 0);
-        if (j0 + r < n) v = *reinterpret_cast<const uint4 *>(Vh + (size_t)(j0 + r) * D + c * 8);
-        unsigned *dst = reinterpret_cast<unsigned *>(tile + r * PITCH + c * 8);
-        dst[0] = v.x; dst[1] = v.y; dst[2] = v.z; dst[3] = v.w;
-    }
-    __syncthreads();
-    for (int q = tid; q < D * (ABN / 8); q += 256) {
-        const int d = q / (ABN / 8), c = q % (ABN / 8);
-        uint16_t e[8];
-#pragma unroll
-        for (int i = 0; i < 8; ++i) e[i] = tile[(c * 8 + i) * PITCH + d];
-        *reinterpret_cast<uint4 *>(Vth + (size_t)d * npad + j0 + c * 8) = *reinterpret_cast<const uint4 *>(e);
-    }
+    typedef short s16x4 __attribute__((ext_vector_type(4)));
+    typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+    const s16x4 r = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)lds);
+    return __builtin_bit_cast(uint2, r);
 }
 
 // ---- attention -------------------------------------------------------------------
 template <int DT, int D>
 __global__ __launch_bounds__(ANW * 64, 2) void prefill_attn_kernel(
-    const char *__restrict__ Qg, const char *__restrict__ Kg, const char *__restrict__ Vtg, int nq,
-    int nk, int npad, int heads, float c2, float *__restrict__ lse2, float *__restrict__ lse_nat,
+    const char *__restrict__ Qg, const char *__restrict__ Kg, const char *__restrict__ Vg, int nq,
+    int nk, int heads, float c2, float *__restrict__ lse2, float *__restrict__ lse_nat,
     char *__restrict__ Og)
 {
     const int off = nk - nq;               // key position of query 0
@@ -128,17 +109,17 @@ __global__ __launch_bounds__(ANW * 64, 2) void prefill_attn_kernel(
     constexpr int NDB = D / 32;            // 32-dim blocks of the output
     constexpr int KS = ABN / 16;           // MFMA steps of the second product per tile
     constexpr int TILEK = ABN * ROWB;      // key tile bytes
-    constexpr int VROWB = ABN * 2;         // bytes per V^T tile row (128)
-    constexpr int TILEV = D * VROWB;       // value tile bytes
-    constexpr int STAGE = TILEK + TILEV;
+    constexpr int STAGE = 2 * TILEK;       // key tile + value tile
     // XOR swizzle of 16-byte chunks inside a row (see the scoring passes)
     constexpr int CPRK = ROWB / 16, RSHK = ROWB >= 256 ? 0 : 1, KMASKK = (CPRK < 16 ? CPRK : 16) - 1;
-    constexpr int CPRV = VROWB / 16, RSHV = 1, KMASKV = CPRV - 1;
+    // Value rows are swizzled by 64-byte groups: a transposing read touches 4 consecutive
+    // rows x 64 bytes per 32 lanes, which have to fall into four different bank groups.
+    constexpr int VSH = ROWB >= 256 ? 0 : 1, VMASK = ROWB >= 256 ? 3 : 1;
     constexpr int NT = ANW * 64;
     constexpr int SROWS = ANW * 32;
-    constexpr int CPTK = ABN * CPRK / NT, CPTV = D * CPRV / NT;
-    constexpr int CPF = CPTK + CPTV;       // copy instructions per wave per stage
-    static_assert(ABN * CPRK % NT == 0 && D * CPRV % NT == 0 && CPTK >= 1 && CPTV >= 1, "copy split");
+    constexpr int CPTK = ABN * CPRK / NT;
+    constexpr int CPF = 2 * CPTK;          // copy instructions per wave per stage
+    static_assert(ABN * CPRK % NT == 0 && CPTK >= 1, "copy split");
 
     extern __shared__ __align__(16) unsigned char smem[];   // [ANS][STAGE]
 
@@ -159,7 +140,7 @@ __global__ __launch_bounds__(ANW * 64, 2) void prefill_attn_kernel(
     const int s0 = blk * SROWS;
     const char *Qh = Qg + (size_t)head * nq * ROWB;
     const char *Kh = Kg + (size_t)head * nk * ROWB;
-    const char *Vth = Vtg + (size_t)head * D * npad * 2;
+    const char *Vh = Vg + (size_t)head * nk * ROWB;
 
     const int srow = s0 + wave * 32 + l32;           // this lane's query
     uint4 st[NF];
@@ -175,22 +156,17 @@ __global__ __launch_bounds__(ANW * 64, 2) void prefill_attn_kernel(
     const int T = min((nk + ABN - 1) / ABN, (off + s0 + SROWS + ABN - 1) / ABN);
 
     // copy plan: instruction c of wave w fills LDS chunks [(c*ANW + w)*64, +64)
-    unsigned koff[CPTK], kchunk[CPTK], voff[CPTV];
+    unsigned koff[CPTK], kchunk[CPTK], vchunk[CPTK];
 #pragma unroll
     for (int c = 0; c < CPTK; ++c) {
         const unsigned q = (unsigned)(c * ANW + wave) * 64u + lane;
         const unsigned r = q / CPRK, pos = q % CPRK;
         koff[c] = r * ROWB;
         kchunk[c] = (pos ^ ((r >> RSHK) & KMASKK)) * 16u;
-    }
-#pragma unroll
-    for (int c = 0; c < CPTV; ++c) {
-        const unsigned q = (unsigned)(c * ANW + wave) * 64u + lane;
-        const unsigned r = q / CPRV, pos = q % CPRV;
-        voff[c] = r * (unsigned)npad * 2u + (pos ^ ((r >> RSHV) & KMASKV)) * 16u;
+        vchunk[c] = (pos ^ (((r >> VSH) & VMASK) << 2)) * 16u;
     }
     const i32x4 rsrc_k = make_rsrc(Kh, (unsigned)nk * ROWB);
-    const i32x4 rsrc_v = make_rsrc(Vth, (unsigned)D * (unsigned)npad * 2u);
+    const i32x4 rsrc_v = make_rsrc(Vh, (unsigned)nk * ROWB);
     const unsigned lds_w = __builtin_amdgcn_readfirstlane(
         (unsigned)reinterpret_cast<size_t>(smem) + wave * 1024);
     const unsigned last_row_off = (unsigned)(nk - 1) * ROWB;
@@ -199,19 +175,21 @@ __global__ __launch_bounds__(ANW * 64, 2) void prefill_attn_kernel(
     // last stage's key tile are never read)
     auto fetch = [&](int u, int stg) {
         const int kt = min(u, T - 1), vt = min(max(u - 1, 0), T - 1);
-        const unsigned t0 = (unsigned)kt * (ABN * ROWB);
         const unsigned base = lds_w + stg * STAGE;
-        if (t0 + ABN * ROWB <= (unsigned)nk * ROWB) {
+        // (rows past the end, only in a ragged last tile, repeat row nk-1: masked)
+        auto tile = [&](const i32x4 &rsrc, int t, const unsigned *chunk, unsigned lds) {
+            const unsigned t0 = (unsigned)t * (ABN * ROWB);
+            if (t0 + ABN * ROWB <= (unsigned)nk * ROWB) {
 #pragma unroll
-            for (int c = 0; c < CPTK; ++c) dma16(rsrc_k, koff[c] + kchunk[c], t0, base + c * ANW * 1024);
-        } else {                                       // ragged last tile: rows past nk repeat row nk-1
+                for (int c = 0; c < CPTK; ++c) dma16(rsrc, koff[c] + chunk[c], t0, lds + c * ANW * 1024);
+            } else {
 #pragma unroll
-            for (int c = 0; c < CPTK; ++c)
-                dma16(rsrc_k, min(t0 + koff[c], last_row_off) + kchunk[c], 0u, base + c * ANW * 1024);
-        }
-#pragma unroll
-        for (int c = 0; c < CPTV; ++c)
-            dma16(rsrc_v, voff[c], (unsigned)vt * VROWB, base + TILEK + c * ANW * 1024);
+                for (int c = 0; c < CPTK; ++c)
+                    dma16(rsrc, min(t0 + koff[c], last_row_off) + chunk[c], 0u, lds + c * ANW * 1024);
+            }
+        };
+        tile(rsrc_k, kt, kchunk, base);
+        tile(rsrc_v, vt, vchunk, base + TILEK);
     };
 
     // LDS read offsets.  Key rows are visited so that MFMA row 16a + 8b + 4c + e
@@ -220,7 +198,7 @@ __global__ __launch_bounds__(ANW * 64, 2) void prefill_attn_kernel(
     // 16s + 8h + (0..7) of the block, which is exactly what the second
     // product's B operand needs.
     const int krow = (l32 & ~12) | ((l32 & 4) << 1) | ((l32 & 8) >> 1);
-    unsigned ka[NF][MB], va[NDB][KS];
+    unsigned ka[NF][MB], va[NDB];
 #pragma unroll
     for (int f = 0; f < NF; ++f)
 #pragma unroll
@@ -228,13 +206,22 @@ __global__ __launch_bounds__(ANW * 64, 2) void prefill_attn_kernel(
             const int row = mb * 32 + krow;
             ka[f][mb] = row * ROWB + (((2 * f + half) ^ ((row >> RSHK) & KMASKK)) * 16);
         }
+    // Value fragments: lane 4q + i of a group of 16 fetches dims 4i..4i+3 of key q (and,
+    // second read, of key 4 + q); lane halves take keys 0..7 / 8..15 of an MFMA step, the
+    // two groups of a half dims 0..15 / 16..31 of a 32-dim block.
+    {
+        const int q = (lane & 15) >> 2, i = lane & 3;
+        const int row = 8 * half + q;                    // (steps of 4 and 16 rows leave the swizzle alone)
 #pragma unroll
-    for (int db = 0; db < NDB; ++db)
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-            const int row = db * 32 + l32;
-            va[db][ks] = TILEK + row * VROWB + (((2 * ks + half) ^ ((row >> RSHV) & KMASKV)) * 16);
-        }
+        for (int db = 0; db < NDB; ++db)
+            va[db] = TILEK + row * ROWB +
+                     (((4 * db) ^ (((row >> VSH) & VMASK) << 2)) + 2 * ((lane >> 4) & 1) + (i >> 1)) * 16 + 8 * (i & 1);
+    }
+    auto value_fragment = [&](const unsigned char *sb, int db, int ks) {
+        const uint2 lo = read_keys4(sb + va[db] + ks * 16 * ROWB);
+        const uint2 hi = read_keys4(sb + va[db] + ks * 16 * ROWB + 4 * ROWB);
+        return make_uint4(lo.x, lo.y, hi.x, hi.y);
+    };
 
     float m_run = -INFINITY, l_run = 0.f;   // running maximum of the raw products / normaliser part
     f32x16 oacc[NDB];
@@ -278,14 +265,14 @@ __global__ __launch_bounds__(ANW * 64, 2) void prefill_attn_kernel(
             uint4 ring[PF];
 #pragma unroll
             for (int i = 0; i < PF; ++i)
-                ring[i] = *reinterpret_cast<const uint4 *>(sb + va[i % NDB][i / NDB]);
+                ring[i] = value_fragment(sb, i % NDB, i / NDB);
 #pragma unroll
             for (int i = 0; i < N; ++i) {
                 const int ks = i / NDB, db = i % NDB;
                 __builtin_amdgcn_sched_barrier(0);      // keep the reads PF ahead (the scheduler would pull them back)
                 oacc[db] = mma16<DT>(ring[i % PF], pfrag[ks], oacc[db]);
                 if (i + PF < N)
-                    ring[i % PF] = *reinterpret_cast<const uint4 *>(sb + va[(i + PF) % NDB][(i + PF) / NDB]);
+                    ring[i % PF] = value_fragment(sb, (i + PF) % NDB, (i + PF) / NDB);
             }
             __builtin_amdgcn_sched_barrier(0);
         }
@@ -404,16 +391,20 @@ __global__ __launch_bounds__(ANW * 64, 2) void prefill_attn_kernel(
 
 template <int DT, int D>
 hipError_t launch_attn(const h2o_config &cfg, double scale, const void *Q, const void *K,
-                       const void *V, int nq, int nk, void *vt, float *lse2, float *lse_nat, void *out,
+                       const void *V, int nq, int nk, void *vcopy, float *lse2, float *lse_nat, void *out,
                        hipStream_t st)
 {
     const int heads = cfg.batch * cfg.heads;
-    const int npad = (nk + ABN - 1) / ABN * ABN;
-    hipLaunchKernelGGL((transpose_v_kernel<D>), dim3(heads, npad / ABN), dim3(256), 0, st,
-                       static_cast<const uint16_t *>(V), static_cast<uint16_t *>(vt), nk, npad);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    constexpr size_t smem = (size_t)ANS * (ABN * D * 2 + D * ABN * 2);
+    hipError_t e = hipSuccess;
+    // V is read until the last workgroup ends: an output written over it (in place) needs a copy
+    const char *v0 = static_cast<const char *>(V), *o0 = static_cast<const char *>(out);
+    const size_t vbytes = (size_t)heads * nk * D * 2, obytes = (size_t)heads * nq * D * 2;
+    if (v0 < o0 + obytes && o0 < v0 + vbytes) {
+        e = hipMemcpyAsync(vcopy, V, vbytes, hipMemcpyDeviceToDevice, st);
+        if (e != hipSuccess) return e;
+        V = vcopy;
+    }
+    constexpr size_t smem = (size_t)ANS * 2 * ABN * D * 2;
     auto kern = prefill_attn_kernel<DT, D>;
     static bool raised = false;
     if (smem > 48 * 1024 && !raised) {
@@ -426,28 +417,28 @@ hipError_t launch_attn(const h2o_config &cfg, double scale, const void *Q, const
     const float c2 = (float)(scale * 1.4426950408889634);
     hipLaunchKernelGGL(kern, dim3((unsigned)((heads + 63) / 64) * 64 * nblk), dim3(ANW * 64), smem, st,
                        static_cast<const char *>(Q), static_cast<const char *>(K),
-                       static_cast<const char *>(vt), nq, nk, npad, heads, c2, lse2, lse_nat,
+                       static_cast<const char *>(V), nq, nk, heads, c2, lse2, lse_nat,
                        static_cast<char *>(out));
     return hipGetLastError();
 }
 
 }  // namespace
 
-size_t h2o_attn_vt_bytes(const h2o_config &cfg, int n)
+size_t h2o_attn_vcopy_bytes(const h2o_config &cfg, int n)
 {
-    const size_t npad = ((size_t)n + ABN - 1) / ABN * ABN;
+    const size_t npad = ((size_t)n + ABN - 1) / ABN * ABN;      // (whole tiles: part of the ABI's scratch sizes)
     return (size_t)cfg.batch * cfg.heads * cfg.head_dim * npad * 2;
 }
 
 hipError_t h2o_launch_prefill_attention(const h2o_config &cfg, double scale, const void *Q,
-                                        const void *K, const void *V, int nq, int nk, void *vt,
+                                        const void *K, const void *V, int nq, int nk, void *vcopy,
                                         float *lse2, float *lse_nat, void *out, hipStream_t st)
 {
     const int d = cfg.head_dim;
     if (nq < 1 || nq > nk) return hipErrorInvalidValue;
     if (cfg.dtype == H2O_F16)
-        return d == 64 ? launch_attn<H2O_F16, 64>(cfg, scale, Q, K, V, nq, nk, vt, lse2, lse_nat, out, st)
-                       : launch_attn<H2O_F16, 128>(cfg, scale, Q, K, V, nq, nk, vt, lse2, lse_nat, out, st);
-    return d == 64 ? launch_attn<H2O_BF16, 64>(cfg, scale, Q, K, V, nq, nk, vt, lse2, lse_nat, out, st)
-                   : launch_attn<H2O_BF16, 128>(cfg, scale, Q, K, V, nq, nk, vt, lse2, lse_nat, out, st);
+        return d == 64 ? launch_attn<H2O_F16, 64>(cfg, scale, Q, K, V, nq, nk, vcopy, lse2, lse_nat, out, st)
+                       : launch_attn<H2O_F16, 128>(cfg, scale, Q, K, V, nq, nk, vcopy, lse2, lse_nat, out, st);
+    return d == 64 ? launch_attn<H2O_BF16, 64>(cfg, scale, Q, K, V, nq, nk, vcopy, lse2, lse_nat, out, st)
+                   : launch_attn<H2O_BF16, 128>(cfg, scale, Q, K, V, nq, nk, vcopy, lse2, lse_nat, out, st);
 }
