@@ -302,7 +302,8 @@ int h2o_prefill_attention_scores(h2o_cache *cache, const void *Q, const void *K,
                                  void *hip_stream);
 
 /*
- * One generation step for the token at position t, one fused kernel launch
+ * One generation step for the token at position t, one fused kernel launch (two where
+ * the step is split, see h2o_cache_set_step_scratch)
  * (Definition 2.2, Algorithm 2, App. A decode commentary), per head:
  *   1. logits  s_j = scale * <q, K[slot j]> for every occupied slot, and
  *      s_self = scale * <q, k_new>;
@@ -327,6 +328,23 @@ int h2o_prefill_attention_scores(h2o_cache *cache, const void *Q, const void *K,
  */
 int h2o_decode_step(h2o_cache *cache, const void *q, const void *k_new,
                     const void *v_new, void *out, void *hip_stream);
+
+/*
+ * Optional scratch for generation steps with few heads and a long budget.  With fewer
+ * heads than the GPU has compute units, one workgroup per head leaves the rest idle;
+ * given scratch, a step splits every head over several workgroups and joins the parts
+ * in a second launch (same results to the order of float64 sums).
+ *   h2o_step_scratch_bytes      device bytes a cache of this configuration can use;
+ *                               0 where steps are never split
+ *   h2o_cache_set_step_scratch  hands the cache a buffer of at least that size (16-byte
+ *                               aligned, contents arbitrary), which has to live as long
+ *                               as the cache memory and belongs to this cache alone;
+ *                               NULL takes it away again.  Without it steps run on one
+ *                               workgroup per head.
+ * Errors: EINVAL, ENOMEM (bytes too small).
+ */
+size_t h2o_step_scratch_bytes(const h2o_config *cfg);
+int h2o_cache_set_step_scratch(h2o_cache *cache, void *dev_mem, size_t bytes);
 
 /* Copies pos / acc (each [batch, heads, k], device pointers, either may be
  * NULL) out of the cache, ordered after earlier work on the stream. */

@@ -35,7 +35,7 @@ EXPORTS = (
     "h2o_cache_regions", "h2o_status_str", "h2o_prefill_attention_workspace_bytes",
     "h2o_prefill_attention", "h2o_prefill_attention_scores", "h2o_prefill_chunk_workspace_bytes",
     "h2o_prefill_chunk", "h2o_cache_rolled_positions", "h2o_prefill_scores_noalloc",
-    "h2o_cache_validate",
+    "h2o_cache_validate", "h2o_step_scratch_bytes", "h2o_cache_set_step_scratch",
 )
 
 
@@ -84,6 +84,9 @@ _lib.h2o_decode_step.argtypes = [_vp, _vp, _vp, _vp, _vp, _vp]
 _lib.h2o_cache_snapshot.argtypes = [_vp, _vp, _vp, _vp]
 _lib.h2o_cache_restore.argtypes = [_vp, _vp, _vp, _vp, _vp, _i32, _vp]
 _lib.h2o_cache_tokens_seen.argtypes = [_vp]
+_lib.h2o_step_scratch_bytes.restype = _sz
+_lib.h2o_step_scratch_bytes.argtypes = [_cfgp]
+_lib.h2o_cache_set_step_scratch.argtypes = [_vp, _vp, _sz]
 _lib.h2o_cache_regions.argtypes = [_vp] + [ctypes.POINTER(_vp)] * 4
 _lib.h2o_status_str.restype = ctypes.c_char_p
 _lib.h2o_status_str.argtypes = [ctypes.c_int]
@@ -243,6 +246,14 @@ def h2o_cache_validate(cache, flags_out, stream=None) -> None:
     _check(_lib.h2o_cache_validate(cache, _ptr(flags_out), _stream(stream)), "h2o_cache_validate")
 
 
+def h2o_step_scratch_bytes(cfg: h2o_config) -> int:
+    return int(_lib.h2o_step_scratch_bytes(ctypes.byref(cfg)))
+
+
+def h2o_cache_set_step_scratch(cache, dev_mem, nbytes: int) -> None:
+    _check(_lib.h2o_cache_set_step_scratch(cache, _ptr(dev_mem), int(nbytes)), "h2o_cache_set_step_scratch")
+
+
 def h2o_cache_tokens_seen(cache) -> int:
     return int(_lib.h2o_cache_tokens_seen(cache))
 
@@ -273,6 +284,11 @@ class H2OCache:
         self.mem = torch.empty(nbytes, dtype=torch.uint8, device=self.device)
         self.handle = h2o_cache_init(self.cfg, self.mem, nbytes, stream)
         self._ws = None
+        # scratch for steps that are split over several workgroups per head (0 for most shapes)
+        scratch = h2o_step_scratch_bytes(self.cfg)
+        self._step_ws = torch.empty(scratch, dtype=torch.uint8, device=self.device) if scratch else None
+        if scratch:
+            h2o_cache_set_step_scratch(self.handle, self._step_ws, scratch)
 
     def close(self):
         if getattr(self, "handle", None):

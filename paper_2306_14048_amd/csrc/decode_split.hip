@@ -1,0 +1,433 @@
+// The generation step for few heads with long budgets: several workgroups per head.
+//
+// One workgroup per head leaves most of the chip idle when there are fewer heads
+// than CUs, and a head's cache then streams at the rate of one CU (about 130 GB/s):
+// 64 heads x 3277 slots (bf16, d = 128, 110 MB) took 41.5 us, 2.6 TB/s; split it takes
+// 26.4 us: 19-21 us for the parts (5.1-5.8 TB/s) and 5 us for joining them.  Here `parts`
+// workgroups share a head, each with a run of its slots, and a second, short launch
+// puts the parts together.  What one part needs of the others (the softmax normaliser)
+// is only needed for the scores and for the final scale of the output, so nothing in
+// the first launch waits for anything:
+//
+//   decode_part_kernel    logits of the part's slots, e_j = exp(s_j - shift) and their
+//                         sum (all fp64), output of the part normalised by the part's
+//                         own sum (fp32 like the one-workgroup kernels)
+//   decode_finish_kernel  one workgroup per head: the common normaliser, every slot's
+//                         probability (rounded once to binary32), scores, eviction,
+//                         overwrite, weighted sum of the parts' outputs (fp64)
+//
+// The shift is the token's own logit in every part, as in the one-workgroup kernels
+// (its own maximum in a part whose sum overflows), so e_j, the normaliser and with
+// them the probabilities and scores are the same numbers, to the order of the fp64 sum.
+#include "wave_ops.h"
+
+namespace {
+
+constexpr int SPLIT_MAX_PARTS = 32;
+constexpr int PNW = 8;                 // waves per workgroup (parts)
+constexpr int FNT = 1024;              // threads per workgroup (finish)
+constexpr int FSPT = H2O_MAX_BUDGET / FNT;
+
+struct PartStat { double shift, sum, s_self, unused; };
+
+// Scratch of one cache: e[heads][k], stat[heads][32], o[heads][32][d]
+struct Scratch { double *e; PartStat *stat; float *o; };
+
+// The one-workgroup kernel's body without the bookkeeping: see decode_resident_kernel
+// for the plan of the loads (all requests first, straight-line, none conditional) and
+// for slot ownership.  Requires per <= U * RPI and 1 <= slots of every part.
+template <int DT, int D, int U>
+__global__ __launch_bounds__(PNW * 64, 4) void decode_part_kernel(
+    const char *__restrict__ Kc, const char *__restrict__ Vc, const char *__restrict__ q_g,
+    const char *__restrict__ kn_g, int k, int n_occ, int per, int parts, double scale,
+    double *__restrict__ e_g, PartStat *__restrict__ stat_g, float *__restrict__ o_g)
+{
+    using E = Elem<DT>;
+    using T = typename E::T;
+    constexpr int EPL = E::EPL;
+    constexpr int LPR = D / EPL;
+    constexpr int RPW = 64 / LPR;
+    constexpr int RPI = PNW * RPW;
+    constexpr int OWN = U * RPW;
+    constexpr int PITCH = LPR + 1;
+    constexpr unsigned ROWB = D * sizeof(T);
+    static_assert(OWN <= 64, "one slot per lane");
+
+    const int head = blockIdx.x / parts, part = blockIdx.x % parts;
+    const int first = part * per, n_loc = min(per, n_occ - first);
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int sub = lane / LPR, li = lane % LPR;
+
+    __shared__ double part_l[PNW * OWN * PITCH];
+    __shared__ double red_sum[PNW], red_max[PNW];
+    __shared__ float p_l[PNW * OWN];
+    __shared__ float o_l[PNW * D];
+    double *part_w = part_l + wave * OWN * PITCH;
+    float *p_w = p_l + wave * OWN;
+
+    const size_t hoff = (size_t)head * k + first;
+    const char *Kb = Kc + hoff * ROWB;
+    const char *Vb = Vc + hoff * ROWB;
+    const T *qh = reinterpret_cast<const T *>(q_g) + (size_t)head * D;
+    const T *knh = reinterpret_cast<const T *>(kn_g) + (size_t)head * D;
+
+    const int row0 = wave * RPW + sub, last = n_loc - 1;
+    const int my_slot = (lane / RPW) * RPI + wave * RPW + (lane % RPW);
+    const bool owner = lane < OWN && my_slot < n_loc;
+
+    const uint4 qraw = *reinterpret_cast<const uint4 *>(qh + li * EPL);
+    const uint4 kraw = *reinterpret_cast<const uint4 *>(knh + li * EPL);
+    unsigned off[U];
+    uint4 buf[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        off[u] = (unsigned)min(u * RPI + row0, last) * ROWB + (unsigned)li * 16u;
+        buf[u] = load_stream(Kb + off[u]);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+
+    double qd[EPL];
+    double s_self;
+    {
+        const T *qe = reinterpret_cast<const T *>(&qraw);
+        const T *ke = reinterpret_cast<const T *>(&kraw);
+        double a = 0.0;
+#pragma unroll
+        for (int i = 0; i < EPL; ++i) {
+            qd[i] = (double)E::to_f(qe[i]);
+            a = fma((double)E::to_f(ke[i]), qd[i], a);
+        }
+        s_self = group_sum<LPR>(a) * scale;
+    }
+
+    // ---- logits
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const T *x = reinterpret_cast<const T *>(&buf[u]);
+        double a0 = 0.0, a1 = 0.0;
+#pragma unroll
+        for (int i = 0; i < EPL; i += 2) {
+            a0 = fma((double)E::to_f(x[i]), qd[i], a0);
+            a1 = fma((double)E::to_f(x[i + 1]), qd[i + 1], a1);
+        }
+        buf[u] = load_stream(Vb + off[u]);
+        part_w[(u * RPW + sub) * PITCH + li] = a0 + a1;
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    __builtin_amdgcn_wave_barrier();
+
+    // ---- exponentials and the part's sum
+    double s_j = 0.0;
+    if (lane < OWN) {
+        const double *pr = part_w + lane * PITCH;
+        double a = pr[0], b = pr[1];
+#pragma unroll
+        for (int c = 2; c < LPR; c += 2) { a += pr[c]; b += pr[c + 1]; }
+        s_j = (a + b) * scale;
+    }
+    double shift = s_self;
+    double e_j = owner ? exp(s_j - shift) : 0.0;
+    {
+        const double dw = wave_sum(e_j);
+        if (lane == 0) red_sum[wave] = dw;
+    }
+    lds_barrier();
+    double den = 0.0;
+#pragma unroll
+    for (int w = 0; w < PNW; ++w) den += red_sum[w];
+    if (!(den <= 1.79769313486231570815e+308)) {
+        // some logit is > ~709 above the token's own: this part takes its maximum
+        const double mw = wave_max(owner ? s_j : -INFINITY);
+        if (lane == 0) red_max[wave] = mw;
+        lds_barrier();
+#pragma unroll
+        for (int w = 0; w < PNW; ++w) shift = fmax(shift, red_max[w]);
+        e_j = owner ? exp(s_j - shift) : 0.0;
+        const double dw = wave_sum(e_j);
+        if (lane == 0) red_sum[wave] = dw;
+        lds_barrier();
+        den = 0.0;
+#pragma unroll
+        for (int w = 0; w < PNW; ++w) den += red_sum[w];
+    }
+    if (owner) e_g[hoff + my_slot] = e_j;
+    // (a part whose logits all lie > ~745 below the token's own has weight zero)
+    const float p_j = den == 0.0 ? 0.f : (float)(e_j / den);
+    if (lane < OWN) p_w[lane] = p_j;
+    __builtin_amdgcn_wave_barrier();
+
+    // ---- output of the part
+    float o[EPL];
+#pragma unroll
+    for (int i = 0; i < EPL; ++i) o[i] = 0.f;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const float p = p_w[u * RPW + sub];
+        const T *x = reinterpret_cast<const T *>(&buf[u]);
+#pragma unroll
+        for (int i = 0; i < EPL; ++i) o[i] = fmaf(p, E::to_f(x[i]), o[i]);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    wave_output_to_lds<EPL, LPR, D>(o, o_l, wave, sub, li);
+    lds_barrier();
+    const size_t po = (size_t)head * SPLIT_MAX_PARTS + part;
+    if (tid < D) {
+        float r = 0.f;
+#pragma unroll
+        for (int w = 0; w < PNW; ++w) r += o_l[w * D + tid];
+        o_g[po * D + tid] = r;
+    }
+    if (tid == 0) {
+        stat_g[po].shift = shift;
+        stat_g[po].sum = den;
+        stat_g[po].s_self = s_self;
+    }
+}
+
+// One workgroup per head; a thread has the slots tid, tid + 1024, ...  Latency-bound
+// (20 bytes per slot): every load is requested before the first use, and what depends on
+// the parts (factors, normaliser) is worked out by one lane per part.
+template <int DT, int D, bool PAT>
+__global__ __launch_bounds__(FNT) void decode_finish_kernel(
+    char *__restrict__ Kc, char *__restrict__ Vc, float *__restrict__ acc_g,
+    int32_t *__restrict__ pos_g, const char *__restrict__ kn_g, const char *__restrict__ vn_g,
+    char *__restrict__ out_g, int k, int n_occ, int t, int recent, int rank, int protect, int stride,
+    int per, int parts, const double *__restrict__ e_g, const PartStat *__restrict__ stat_g,
+    const float *__restrict__ o_g)
+{
+    using E = Elem<DT>;
+    using T = typename E::T;
+    constexpr int EPL = E::EPL, LPR = D / EPL;
+    constexpr unsigned ROWB = D * sizeof(T);
+    constexpr int FNW = FNT / 64;
+
+    const int head = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const size_t hoff = (size_t)head * k, po = (size_t)head * SPLIT_MAX_PARTS;
+    __shared__ double w_l[SPLIT_MAX_PARTS];      // factor of a part's exponentials
+    __shared__ float ow_l[SPLIT_MAX_PARTS];      // weight of its output
+    __shared__ double red_key[FNW], red_all[FNW];
+    static_assert(SPLIT_MAX_PARTS <= 64, "one lane per part");
+
+    double e_j[FSPT];
+    float acc_j[FSPT];
+    int pos_j[FSPT];
+#pragma unroll
+    for (int i = 0; i < FSPT; ++i) {
+        if (i * FNT >= n_occ) break;
+        const int s = min(tid + i * FNT, n_occ - 1);
+        e_j[i] = e_g[hoff + s];
+        acc_j[i] = acc_g[hoff + s];
+        pos_j[i] = pos_g[hoff + s];
+    }
+    const T v_self = reinterpret_cast<const T *>(vn_g)[(size_t)head * D + tid % D];
+    const int li = lane % LPR;
+    const uint4 row = *reinterpret_cast<const uint4 *>(((lane / LPR) & 1 ? vn_g : kn_g) + (size_t)head * ROWB + li * 16);
+
+    // the outputs of the parts (column tid % D; the first D threads use them)
+    constexpr int OPF = 8;
+    float o_p[OPF];
+#pragma unroll
+    for (int p = 0; p < OPF; ++p) o_p[p] = o_g[(po + min(p, parts - 1)) * D + tid % D];
+
+    // the common normaliser: sums of the parts (lane p of every wave has part p), brought to
+    // one shift by factors that are exactly one unless a part overflowed
+    const bool has = lane < parts;
+    const PartStat st = stat_g[po + min(lane, parts - 1)];
+    const double s_self = lane_value(st.s_self, 0);
+    double ref = fmax(s_self, wave_max(st.shift));
+    double f = exp(st.shift - ref), e_self = exp(s_self - ref);
+    double den = e_self + wave_sum(has ? st.sum * f : 0.0);
+    if (!(den <= 1.79769313486231570815e+308)) {     // finite parts, infinite sum
+        ref += 32.0;
+        f = exp(st.shift - ref);
+        e_self = exp(s_self - ref);
+        den = e_self + wave_sum(has ? st.sum * f : 0.0);
+    }
+    const float p_self = (float)(e_self / den);
+    if (wave == 0 && has) {
+        w_l[lane] = f;
+        ow_l[lane] = (float)(st.sum * f / den);
+    }
+    const bool plain = __ballot(f != 1.0) == 0;      // (every wave finds the same)
+    __syncthreads();
+
+    // ---- scores and the eviction candidates (as in the one-workgroup kernels)
+    unsigned long long key = NO_CANDIDATE, key_all = NO_CANDIDATE;
+    int key_slot = -1, key_all_slot = -1;
+#pragma unroll
+    for (int i = 0; i < FSPT; ++i) {
+        if (i * FNT >= n_occ) break;
+        const int s = tid + i * FNT;
+        if (s < n_occ) {
+            const float p_j = (float)((plain ? e_j[i] : e_j[i] * w_l[s / per]) / den);
+            acc_j[i] += p_j;                                         // binary32 accumulate
+            acc_g[hoff + s] = acc_j[i];
+            const unsigned long long c =
+                ((unsigned long long)__float_as_uint(rank_value(acc_j[i], pos_j[i], t, rank)) << 32) |
+                (unsigned)pos_j[i];
+            if (PAT ? !is_protected(pos_j[i], t, recent, protect, stride) : pos_j[i] <= t - recent) {
+                if (c < key) { key = c; key_slot = s; }
+            }
+            if (PAT && c < key_all) { key_all = c; key_all_slot = s; }
+        }
+    }
+    {
+        const double kw = wave_min_f64(__longlong_as_double((long long)key));
+        if (lane == 0) red_key[wave] = kw;
+        if constexpr (PAT) {
+            const double ka = wave_min_f64(__longlong_as_double((long long)key_all));
+            if (lane == 0) red_all[wave] = ka;
+        }
+    }
+    // ---- output
+    if (tid < D) {
+        double r = (double)p_self * (double)E::to_f(v_self);
+#pragma unroll
+        for (int p = 0; p < OPF; ++p)
+            if (p < parts) r = fma((double)ow_l[p], (double)o_p[p], r);
+        for (int p = OPF; p < parts; ++p) r = fma((double)ow_l[p], (double)o_g[(po + p) * D + tid], r);
+        reinterpret_cast<T *>(out_g)[(size_t)head * D + tid] = E::from_f((float)r);
+    }
+    __syncthreads();
+
+    int tslot = -1;
+    if (n_occ < k) {
+        if (wave == 0) tslot = n_occ;
+    } else {
+        double wd = red_key[0];
+#pragma unroll
+        for (int w = 1; w < FNW; ++w) wd = fmin(wd, red_key[w]);
+        if constexpr (PAT) {
+            if (wd != wd) {                                          // the pattern covers every slot
+                wd = red_all[0];
+#pragma unroll
+                for (int w = 1; w < FNW; ++w) wd = fmin(wd, red_all[w]);
+                key = key_all;
+                key_slot = key_all_slot;
+            }
+        }
+        const unsigned long long win = (unsigned long long)__double_as_longlong(wd);
+        const unsigned long long self_key =
+            ((unsigned long long)__float_as_uint(p_self) << 32) | (unsigned)t;
+        const bool evict = wd == wd && (PAT || recent != 0 || win < self_key);
+        const unsigned long long b = __ballot(evict && key == win && key != NO_CANDIDATE);
+        if (b != 0) tslot = __builtin_amdgcn_readlane(key_slot, __ffsll((long long)b) - 1);
+    }
+    if (tslot >= 0) {
+        // (the lane that holds the winner also wrote that slot's old score above: the new
+        // one goes out from the same lane, behind it)
+        if (n_occ < k ? lane == 0 : key_slot == tslot) {
+            pos_g[hoff + tslot] = t;
+            acc_g[hoff + tslot] = p_self;
+        }
+        if (lane < 2 * LPR)
+            *reinterpret_cast<uint4 *>((lane < LPR ? Kc : Vc) + (hoff + tslot) * ROWB + li * 16) = row;
+    }
+}
+
+// How a step over n_occ slots is split (parts <= 1: it is not).  Rows of `rpw` per
+// wave and load; a part holds at most `umax` rounds.
+struct Plan { int parts, per; };
+
+Plan plan_of(int heads, int n_occ, int rpw)
+{
+    const int rpi = PNW * rpw, umax = rpw * 13 <= 64 ? 13 : 8;
+    // Where the line lies.  A budget that the one-workgroup kernel holds in registers is
+    // bound by the latency of one pass over it, which a second launch (4.5 us) only adds
+    // to.  Beyond it, measured (us per step, one workgroup / split):
+    //   rows of 256 B   32 heads: 520 slots 9.7 / 9.1, 4096 47 / 17;  64: 520 9.5 / 10.5,
+    //                   1000 14.6 / 11.5;  128: 520 10.4 / 12.3, 1000 16.2 / 15.4,
+    //                   4096 55 / 51;  192: 1000 18 / 23, 4096 63 / 73
+    //   rows of 512 B   64: 520 13.9 / 11.4;  128: 520 15.9 / 15.6, 4096 110 / 91;  192: 127 / 136
+    //   rows of 128 B   96: 700 8.0 / 10.7;  128: 1000 18 / 11.5;  255: 1000 20 / 16, 4096 78 / 54
+    const int resident = rpi * (umax > 8 ? 15 : 8);
+    const int most_heads = rpw == 8 ? 255 : 128;
+    const int least_slots = heads <= 32 ? resident + 1 : rpw == 2 ? 450 : 900;
+    if (heads > most_heads || n_occ <= resident || n_occ < least_slots) return {1, n_occ};
+    int parts = 512 / heads;                                     // two workgroups per CU
+    const int least = (n_occ + rpi * umax - 1) / (rpi * umax), most = (n_occ + rpi * 4 - 1) / (rpi * 4);
+    if (parts > most) parts = most;
+    if (parts < least) parts = least;
+    if (parts > SPLIT_MAX_PARTS) parts = SPLIT_MAX_PARTS;
+    if (parts < least) return {1, n_occ};
+    const int per = ((n_occ + parts - 1) / parts + rpi - 1) / rpi * rpi;    // whole rounds
+    return {(n_occ + per - 1) / per, per};
+}
+
+Scratch carve(const h2o_cache &c)
+{
+    const size_t heads = (size_t)c.cfg.batch * c.cfg.heads;
+    Scratch s;
+    s.e = static_cast<double *>(c.step_scratch);
+    s.stat = reinterpret_cast<PartStat *>(s.e + heads * c.k);
+    s.o = reinterpret_cast<float *>(s.stat + heads * SPLIT_MAX_PARTS);
+    return s;
+}
+
+template <int DT, int D>
+hipError_t launch(const h2o_cache &c, const void *q, const void *kn, const void *vn, void *out,
+                  Plan p, hipStream_t st)
+{
+    constexpr int RPW = 64 / (D / Elem<DT>::EPL);
+    constexpr int RPI = PNW * RPW;
+    const int heads = c.cfg.batch * c.cfg.heads, occ = c.t < c.k ? c.t : c.k;
+    const Scratch s = carve(c);
+    auto part = [&](auto kern) {
+        hipLaunchKernelGGL(kern, dim3((unsigned)heads * p.parts), dim3(PNW * 64), 0, st, c.K, c.V,
+                           static_cast<const char *>(q), static_cast<const char *>(kn), c.k, occ, p.per, p.parts,
+                           c.scale, s.e, s.stat, s.o);
+    };
+    const int rounds = p.per / RPI;
+    if (rounds <= 4) part(decode_part_kernel<DT, D, 4>);
+    else if (rounds <= 6) part(decode_part_kernel<DT, D, 6>);
+    else if (rounds <= 8) part(decode_part_kernel<DT, D, 8>);
+    else if constexpr (RPW * 13 <= 64) {
+        if (rounds <= 10) part(decode_part_kernel<DT, D, 10>);
+        else part(decode_part_kernel<DT, D, 13>);
+    }
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    auto finish = [&](auto kern) {
+        hipLaunchKernelGGL(kern, dim3(heads), dim3(FNT), 0, st, c.K, c.V, c.acc, c.pos,
+                           static_cast<const char *>(kn), static_cast<const char *>(vn), static_cast<char *>(out),
+                           c.k, occ, c.t, c.cfg.recent, c.cfg.rank, c.cfg.protect, c.cfg.stride, p.per, p.parts, s.e,
+                           s.stat, s.o);
+    };
+    if (c.cfg.protect == H2O_PROTECT_RECENT) finish(decode_finish_kernel<DT, D, false>);
+    else finish(decode_finish_kernel<DT, D, true>);
+    return hipGetLastError();
+}
+
+inline int rows_per_wave(const h2o_config &c) { return 1024 / (c.head_dim * h2o_esize(c.dtype)); }
+
+}  // namespace
+
+size_t h2o_split_scratch_bytes(const h2o_config &c)
+{
+    const size_t heads = (size_t)c.batch * c.heads, k = (size_t)c.heavy + c.recent;
+    if (c.kv_bits != 0 || heads > 255 || plan_of((int)heads, (int)k, rows_per_wave(c)).parts <= 1) return 0;
+    return heads * (k * sizeof(double) + SPLIT_MAX_PARTS * (sizeof(PartStat) + c.head_dim * sizeof(float)));
+}
+
+bool h2o_split_wanted(const h2o_cache &c)
+{
+    return c.step_scratch && plan_of(c.cfg.batch * c.cfg.heads, c.t < c.k ? c.t : c.k, rows_per_wave(c.cfg)).parts > 1;
+}
+
+hipError_t h2o_launch_decode_split(const h2o_cache &c, const void *q, const void *k_new,
+                                   const void *v_new, void *out, hipStream_t st)
+{
+    const int d = c.cfg.head_dim;
+    const Plan p = plan_of(c.cfg.batch * c.cfg.heads, c.t < c.k ? c.t : c.k, rows_per_wave(c.cfg));
+    switch (c.cfg.dtype) {
+    case H2O_F32:
+        return d == 64 ? launch<H2O_F32, 64>(c, q, k_new, v_new, out, p, st)
+                       : launch<H2O_F32, 128>(c, q, k_new, v_new, out, p, st);
+    case H2O_F16:
+        return d == 64 ? launch<H2O_F16, 64>(c, q, k_new, v_new, out, p, st)
+                       : launch<H2O_F16, 128>(c, q, k_new, v_new, out, p, st);
+    default:
+        return d == 64 ? launch<H2O_BF16, 64>(c, q, k_new, v_new, out, p, st)
+                       : launch<H2O_BF16, 128>(c, q, k_new, v_new, out, p, st);
+    }
+}

@@ -31,24 +31,6 @@
 
 namespace {
 
-// ---- pieces shared by the two kernels -------------------------------------------
-
-// Adds this lane's fp32 partial output (EPL columns of row group `sub`) into the
-// workgroup's output row, multiplies nothing: o_l[wave][column] gets the wave's sum.
-template <int EPL, int LPR, int D>
-__device__ inline void wave_output_to_lds(float (&o)[EPL], float *o_l, int wave, int sub, int li)
-{
-#pragma unroll
-    for (int m = LPR; m < 64; m <<= 1) {
-#pragma unroll
-        for (int i = 0; i < EPL; ++i) o[i] += __shfl_xor(o[i], m, 64);
-    }
-    if (sub == 0) {
-#pragma unroll
-        for (int i = 0; i < EPL; ++i) o_l[wave * D + li * EPL + i] = o[i];
-    }
-}
-
 // ---- register-resident kernel: every row of the head fits the ring -----------------
 //
 // Requires n_occ <= U * RPI and U * RPW <= 64.  Straight-line code: the U key

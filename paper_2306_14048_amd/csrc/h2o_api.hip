@@ -116,6 +116,7 @@ int h2o_cache_init(const h2o_config *cfg, void *dev_mem, size_t bytes, void *hip
     c->rowb = h2o_row_bytes(*cfg);
     c->t = 0;
     c->sorted = true;
+    c->step_scratch = nullptr;
     char *base = static_cast<char *>(dev_mem);
     c->K = base;
     c->V = base + l.kv;
@@ -323,13 +324,27 @@ int h2o_decode_step(h2o_cache *cache, const void *q, const void *k_new, const vo
         return H2O_EINVAL;
     if (cache->t >= 0x7ffffff0) return H2O_EUNSUPPORTED;
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
-    const hipError_t e = cache->cfg.kv_bits == 4 ? h2o_launch_decode_q4(*cache, q, k_new, v_new, out, st)
-                                                 : h2o_launch_decode(*cache, q, k_new, v_new, out, st);
+    const hipError_t e = cache->cfg.kv_bits == 4  ? h2o_launch_decode_q4(*cache, q, k_new, v_new, out, st)
+                         : h2o_split_wanted(*cache) ? h2o_launch_decode_split(*cache, q, k_new, v_new, out, st)
+                                                    : h2o_launch_decode(*cache, q, k_new, v_new, out, st);
     if (e != hipSuccess) return H2O_EHIP;
     // free slots fill in index order (positions stay ascending); an eviction
     // overwrites a slot in the middle
     if (cache->t >= cache->k) cache->sorted = false;
     cache->t += 1;
+    return H2O_OK;
+}
+
+size_t h2o_step_scratch_bytes(const h2o_config *cfg)
+{
+    return check_config(cfg) == H2O_OK ? h2o_split_scratch_bytes(*cfg) : 0;
+}
+
+int h2o_cache_set_step_scratch(h2o_cache *cache, void *dev_mem, size_t bytes)
+{
+    if (!cache || !aligned16(dev_mem)) return H2O_EINVAL;
+    if (dev_mem && bytes < h2o_split_scratch_bytes(cache->cfg)) return H2O_ENOMEM;
+    cache->step_scratch = h2o_split_scratch_bytes(cache->cfg) ? dev_mem : nullptr;
     return H2O_OK;
 }
 

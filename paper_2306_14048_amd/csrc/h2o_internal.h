@@ -18,6 +18,7 @@ struct h2o_cache {
     float *acc;        // [B*Hh][k]
     int32_t *pos;      // [B*Hh][k]
     size_t kv_bytes;   // bytes of the K (= V) region
+    void *step_scratch;   // the caller's scratch for split steps, or nullptr (h2o_cache_set_step_scratch)
 };
 
 static inline int h2o_esize(int dtype) { return dtype == H2O_F32 ? 4 : 2; }
@@ -34,6 +35,12 @@ static inline double h2o_scale_of(const h2o_config &c)
 hipError_t h2o_launch_mark_free(const h2o_cache &c, hipStream_t st);
 hipError_t h2o_launch_decode(const h2o_cache &c, const void *q, const void *k_new,
                              const void *v_new, void *out, hipStream_t st);
+// the same step with several workgroups per head (few heads, long budgets), on the
+// cache's step scratch; h2o_split_scratch_bytes: 0 for a configuration it is not used for
+size_t h2o_split_scratch_bytes(const h2o_config &c);
+bool h2o_split_wanted(const h2o_cache &c);
+hipError_t h2o_launch_decode_split(const h2o_cache &c, const void *q, const void *k_new,
+                                   const void *v_new, void *out, hipStream_t st);
 // the same step over a cache that stores 4-bit codes
 hipError_t h2o_launch_decode_q4(const h2o_cache &c, const void *q, const void *k_new,
                                 const void *v_new, void *out, hipStream_t st);

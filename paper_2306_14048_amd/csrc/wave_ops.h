@@ -125,6 +125,22 @@ __device__ inline double wave_sum(double v)
     v = group_sum<16>(v);
     return (lane_value(v, 0) + lane_value(v, 16)) + (lane_value(v, 32) + lane_value(v, 48));
 }
+// Adds this lane's fp32 partial output (EPL columns of row group `sub`) into the
+// workgroup's output row, multiplies nothing: o_l[wave][column] gets the wave's sum.
+template <int EPL, int LPR, int D>
+__device__ inline void wave_output_to_lds(float (&o)[EPL], float *o_l, int wave, int sub, int li)
+{
+#pragma unroll
+    for (int m = LPR; m < 64; m <<= 1) {
+#pragma unroll
+        for (int i = 0; i < EPL; ++i) o[i] += __shfl_xor(o[i], m, 64);
+    }
+    if (sub == 0) {
+#pragma unroll
+        for (int i = 0; i < EPL; ++i) o_l[wave * D + li * EPL + i] = o[i];
+    }
+}
+
 constexpr unsigned long long NO_CANDIDATE = ~0ull;
 
 // What ranks a slot for eviction after the query at position t: its accumulated

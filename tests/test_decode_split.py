@@ -1,0 +1,99 @@
+"""Generation steps split over several workgroups per head, against the one-workgroup
+kernels on the same inputs (a cache whose step scratch is taken away), over every form the
+split rule accepts: element types, head dimensions, edges of the part sizes, a cache that
+is still filling, no window, no heavy hitters, both rankings, both patterns, logits that
+overflow a part's shift.  (The parity tests with long budgets and few heads compare the
+split steps with the oracle; this file also keeps the one-workgroup kernels in use there.)"""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+# Both sides accumulate p * v in binary32 over at most 4096 slots in different groupings: a
+# few roundings of 2^-24 of the largest partial sum, then one rounding to the element type,
+# which may fall on the other side of a tie (one unit in the last place).
+OUT_TOL = {torch.float32: 2e-6, torch.float16: 2 ** -10, torch.bfloat16: 2 ** -7}
+DT = {"f32": torch.float32, "f16": torch.float16, "bf16": torch.bfloat16}
+
+
+@pytest.mark.parametrize("dt,d,batch,heads,n,heavy,recent,more", [
+    ("f16", 128, 1, 3, 481, 241, 240, {}),              # first budget past one workgroup's registers
+    ("bf16", 128, 2, 32, 3277, 1639, 1638, {}),         # eight parts
+    ("f16", 128, 1, 8, 4096, 2048, 2048, {}),           # the largest budget, most parts
+    ("bf16", 128, 4, 32, 1000, 500, 500, {}),           # most heads of this row size
+    ("f16", 64, 1, 255, 1000, 500, 500, {}),            # ... and of 128-byte rows
+    ("f32", 128, 1, 5, 1001, 500, 501, {}),
+    ("f32", 64, 1, 5, 1217, 609, 608, {}),
+    ("f16", 64, 3, 7, 513, 257, 256, {}),
+    ("bf16", 64, 1, 2, 4095, 2000, 2095, {}),
+    ("f16", 128, 1, 4, 479, 1000, 1000, {}),            # filling: crosses from one workgroup to the split
+    ("f16", 128, 1, 4, 1500, 1500, 0, {}),              # no window: the newcomer competes
+    ("f16", 128, 1, 4, 1500, 0, 1500, {}),              # sliding window
+    ("bf16", 128, 1, 4, 1500, 750, 750, dict(rank=1)),
+    ("f16", 128, 1, 4, 1500, 1200, 300, dict(protect=1, stride=7)),
+    ("f16", 64, 1, 4, 1500, 1200, 30, dict(protect=2, stride=100, rank=1)),
+    ("f16", 128, 1, 4, 1500, 1300, 200, dict(protect=1, stride=1)),      # covers every slot
+    ("f32", 64, 1, 4, 1500, 750, 750, dict(far=1)),     # logits ~2000 above the token's own
+    ("f32", 64, 1, 4, 1500, 750, 750, dict(far=-1)),    # ... and ~2000 below: parts of weight zero
+])
+def test_split_step_matches_one_workgroup(dt, d, batch, heads, n, heavy, recent, more):
+    from paper_2306_14048_amd import binding as hb
+    dev, dtype, T = torch.device("cuda:0"), DT[dt], 6
+    more = dict(more)
+    far = more.pop("far", 0)
+    g = torch.Generator().manual_seed(n + d)
+    rand = lambda *s: torch.randn(s, generator=g)  # noqa: E731
+    K = (rand(batch, heads, n, d) * torch.exp(rand(batch, heads, n, 1))).to(dtype).to(dev)
+    V = rand(batch, heads, n, d).to(dtype).to(dev)
+    score = (torch.exp(1.5 * rand(batch, heads, n))).to(dev)
+    qs, ks, vs = (rand(T, batch, heads, d).to(dtype).to(dev) for _ in range(3))
+    if far:
+        qs.fill_(1.0)
+        ks.fill_(0.0)
+        K[:, :, 7:n // 2] = 250.0 * far
+        if far < 0:
+            K[:] = -250.0
+    caches = []
+    for split in (True, False):
+        c = hb.H2OCache(batch, heads, d, heavy, recent, dtype, device=dev, **more)
+        assert hb.h2o_step_scratch_bytes(c.cfg) > 0
+        if not split:
+            hb.h2o_cache_set_step_scratch(c.handle, None, 0)
+        c.prefill_select(K, V, score)
+        caches.append(c)
+    for t in range(T):
+        outs = []
+        for c in caches:
+            out = torch.full((batch, heads, d), 7.0, dtype=dtype, device=dev)
+            c.decode_step(qs[t], ks[t], vs[t], out)
+            outs.append(out)
+        torch.cuda.synchronize()
+        (Ka, Va, aa, pa), (Kb, Vb, ab, pb) = (c.views() for c in caches)
+        occ = pa >= 0
+        assert torch.equal(pa, pb), "step %d: positions differ" % t
+        # the probabilities are rounded from float64 values that agree to ~1e-15
+        assert float(((aa - ab).abs() / ab.clamp_min(1e-30)).max()) <= 1.2e-7
+        assert torch.equal(Ka[occ].view(torch.uint8), Kb[occ].view(torch.uint8))
+        assert torch.equal(Va[occ].view(torch.uint8), Vb[occ].view(torch.uint8))
+        a, b = outs[0].double(), outs[1].double()
+        scale = b.abs().amax(-1, keepdim=True).clamp_min(1e-30)
+        assert bool(torch.isfinite(a).all())
+        assert float(((a - b).abs() / scale).max()) <= OUT_TOL[dtype]
+    for c in caches:
+        c.close()
+
+
+def test_scratch_sizes_and_refusals():
+    from paper_2306_14048_amd import binding as hb
+    assert hb.h2o_step_scratch_bytes(hb.make_config(16, 32, 128, 1000, 1000, hb.H2O_F16)) == 0   # many heads
+    assert hb.h2o_step_scratch_bytes(hb.make_config(1, 32, 128, 205, 205, hb.H2O_F16)) == 0      # short budget
+    assert hb.h2o_step_scratch_bytes(hb.make_config(1, 4, 128, 500, 500, hb.H2O_F16, kv_bits=4)) == 0
+    c = hb.H2OCache(1, 4, 128, 1000, 1000, torch.float16, device="cuda:0")
+    need = hb.h2o_step_scratch_bytes(c.cfg)
+    buf = torch.empty(need + 16, dtype=torch.uint8, device="cuda:0")
+    lib = hb._lib
+    assert lib.h2o_cache_set_step_scratch(c.handle, buf.data_ptr(), need - 1) == hb.H2O_ENOMEM
+    assert lib.h2o_cache_set_step_scratch(c.handle, buf.data_ptr() + 8, need) == hb.H2O_EINVAL
+    assert lib.h2o_cache_set_step_scratch(None, buf.data_ptr(), need) == hb.H2O_EINVAL
+    assert lib.h2o_cache_set_step_scratch(c.handle, buf.data_ptr(), need) == hb.H2O_OK
+    c.close()
