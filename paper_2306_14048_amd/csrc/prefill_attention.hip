@@ -12,7 +12,7 @@
 // every row falls out of it: with this kernel the scoring costs one extra
 // matrix pass (the column sums) instead of two.
 //
-// Shape of the computation.  A workgroup of 8 waves owns 256 queries (32 per
+// Shape of the computation.  A workgroup of 4 waves owns 128 queries (32 per
 // wave, kept in registers as MFMA B-operand fragments) and streams 64-key
 // tiles.  Per tile and wave:
 //     S^T (keys x queries)  = K_tile . Q^T          16 MFMAs 32x32x16
@@ -32,9 +32,15 @@
 // 8 consecutive keys, so P^T goes from the accumulator registers into the second
 // product without any shuffle and the V^T fragment is two 64-bit LDS reads.
 //
-// Schedule: as in the scoring passes, two groups of four waves run one barrier
-// apart; one group's matrix phase (P.V of the previous tile, then Q.K of this
-// one: 32 MFMAs) overlaps the other group's vector phase (softmax of its tile).
+// Schedule.  One barrier per tile; the copy of tile u+1 into the other stage runs while
+// tile u is worked on.  Two workgroups share a CU (64 KB of LDS and 2 x 4 waves at ~200
+// registers each), and drift apart by themselves: while one multiplies the other is in
+// its softmax.  A first version had 8 waves and 256 queries per workgroup, one
+// workgroup per CU, its two wave groups held one phase apart by the barriers; measured
+// against it (us, attention only, d = 128, f16): 8 heads x 300 tokens 14.8 -> 10.5, 32 x
+// 1531 46 -> 41, 32 x 4096 153 -> 148, 128 x 4096 574 -> 563 (976 TFLOP/s), 3584 x 256 242 -> 191:
+// short and few prompts gain most (half the work on the longest block), long ones lose
+// nothing.
 #include "h2o_internal.h"
 #include "lds_copy.h"
 #include <type_traits>
@@ -82,8 +88,8 @@ __device__ inline float other_half(float x)
     return __uint_as_float(r[0] == own ? r[1] : r[0]);
 }
 
-constexpr int ANW = 8;       // waves per workgroup
-constexpr int ANS = 3;       // stages (key tile + value tile each); copies run two tiles ahead
+constexpr int ANW = 4;       // waves per workgroup
+constexpr int ANS = 2;       // stages (key tile + value tile each); copies run one tile ahead
 constexpr int ABN = 64;      // keys per tile
 
 // the 4 consecutive keys of one dim out of a row-major tile in LDS (transposing read: see above)
@@ -118,7 +124,6 @@ __global__ __launch_bounds__(ANW * 64, 2) void prefill_attn_kernel(
     constexpr int NT = ANW * 64;
     constexpr int SROWS = ANW * 32;
     constexpr int CPTK = ABN * CPRK / NT;
-    constexpr int CPF = 2 * CPTK;          // copy instructions per wave per stage
     static_assert(ABN * CPRK % NT == 0 && CPTK >= 1, "copy split");
 
     extern __shared__ __align__(16) unsigned char smem[];   // [ANS][STAGE]
@@ -128,7 +133,6 @@ __global__ __launch_bounds__(ANW * 64, 2) void prefill_attn_kernel(
     // too, which otherwise keeps a second copy of the accumulators around them)
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int half = lane >> 5, l32 = lane & 31;
-    const int grp = wave >> 2;
     const int nblk = (nq + SROWS - 1) / SROWS;
     // a head lives on one XCD (one L2); heaviest (last) row blocks first
     constexpr int HG = 8;
@@ -233,13 +237,11 @@ __global__ __launch_bounds__(ANW * 64, 2) void prefill_attn_kernel(
     bool live_prev = false;
 
     fetch(0, 0);
-    fetch(1, 1);
-    dma_wait_upto<CPF>();
+    dma_wait_upto<0>();
 #pragma unroll
     for (int f = 0; f < NF; ++f)
         asm volatile("" ::"v"(st[f].x), "v"(st[f].y), "v"(st[f].z), "v"(st[f].w));
     wg_barrier();
-    if (grp == 1) wg_barrier();            // second group runs one phase behind
 
     int stg = 0;
     // Iteration u: matrix phase = P.V of tile u-1 and Q.K of tile u, vector phase
@@ -248,7 +250,7 @@ __global__ __launch_bounds__(ANW * 64, 2) void prefill_attn_kernel(
     auto step = [&](int u, auto masked_tag, auto last_tag) {
         constexpr bool MASKED = decltype(masked_tag)::value;
         constexpr bool LAST = decltype(last_tag)::value;
-        fetch(u + 2, stg == 0 ? ANS - 1 : stg - 1);          // into the stage of iteration u-1
+        fetch(u + 1, stg ^ 1);                               // into the stage of iteration u-1
         const unsigned char *sb = smem + stg * STAGE;
         const int r0 = u * ABN;
         const int w0 = s0 + wave * 32;
@@ -297,8 +299,6 @@ __global__ __launch_bounds__(ANW * 64, 2) void prefill_attn_kernel(
             __builtin_amdgcn_sched_barrier(0);
         }
         __builtin_amdgcn_s_setprio(0);
-        dma_wait_upto<CPF>();
-        wg_barrier();
 
         if (live) {
             if constexpr (MASKED) {
@@ -353,8 +353,8 @@ __global__ __launch_bounds__(ANW * 64, 2) void prefill_attn_kernel(
             l_run += sum0 + sum1;
         }
         live_prev = live;
-        stg = stg == ANS - 1 ? 0 : stg + 1;
-        dma_wait_upto<CPF>();
+        stg ^= 1;
+        dma_wait_upto<0>();                    // the next iteration's stage has landed
         wg_barrier();
     };
     {
@@ -363,8 +363,6 @@ __global__ __launch_bounds__(ANW * 64, 2) void prefill_attn_kernel(
         for (int u = t_diag0; u < T; ++u) step(u, std::true_type{}, std::false_type{});
         step(T, std::false_type{}, std::true_type{});
     }
-    if (grp == 0) wg_barrier();
-    dma_wait_upto<0>();                    // trailing requests land before the LDS is released
 
     // ---- normalise and store ------------------------------------------------------
     const float l_tot = l_run + other_half(l_run);
@@ -436,9 +434,9 @@ hipError_t h2o_launch_prefill_attention(const h2o_config &cfg, double scale, con
 {
     const int d = cfg.head_dim;
     if (nq < 1 || nq > nk) return hipErrorInvalidValue;
-    if (cfg.dtype == H2O_F16)
-        return d == 64 ? launch_attn<H2O_F16, 64>(cfg, scale, Q, K, V, nq, nk, vcopy, lse2, lse_nat, out, st)
-                       : launch_attn<H2O_F16, 128>(cfg, scale, Q, K, V, nq, nk, vcopy, lse2, lse_nat, out, st);
-    return d == 64 ? launch_attn<H2O_BF16, 64>(cfg, scale, Q, K, V, nq, nk, vcopy, lse2, lse_nat, out, st)
-                   : launch_attn<H2O_BF16, 128>(cfg, scale, Q, K, V, nq, nk, vcopy, lse2, lse_nat, out, st);
+#define H2O_ATTN(DT, D) \
+    launch_attn<DT, D>(cfg, scale, Q, K, V, nq, nk, vcopy, lse2, lse_nat, out, st)
+    if (cfg.dtype == H2O_F16) return d == 64 ? H2O_ATTN(H2O_F16, 64) : H2O_ATTN(H2O_F16, 128);
+    return d == 64 ? H2O_ATTN(H2O_BF16, 64) : H2O_ATTN(H2O_BF16, 128);
+#undef H2O_ATTN
 }

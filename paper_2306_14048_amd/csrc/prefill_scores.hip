@@ -55,7 +55,6 @@ __device__ inline f32x16 mma(const uint4 &a, const uint4 &b, f32x16 acc)
     }
 }
 
-constexpr int NWV = 8;         // waves per workgroup
 constexpr int NTB = 3;         // streamed-tile buffers (copies run two tiles ahead)
 constexpr int NLB = 4;         // row-statistic buffers (pass 2; read one phase later than the tile)
 
@@ -71,8 +70,13 @@ constexpr int NLB = 4;         // row-statistic buffers (pass 2; read one phase 
 // the barriers themselves: the second group enters the loop one barrier late,
 // so whenever one group is in its matrix phase the other is in its vector
 // phase ("ping-pong").  s_setprio lets the matrix phase win the issue slot.
-template <int DT, int D, int MB, bool COLSUM>
-__global__ __launch_bounds__(NWV * 64, 4) void prefill_pass_kernel(
+//
+// NWV: waves per workgroup.  Eight (256 stationary rows, two workgroups per CU) is
+// the shape for a full chip.  Four (128 rows, one group, one barrier per tile, the
+// overlap left to the workgroups that share a CU) is for grids that do not fill it:
+// the longest block then has half the work per tile.
+template <int DT, int D, int MB, int NWV, bool COLSUM>
+__device__ __forceinline__ void prefill_pass(
     const char *__restrict__ Qg, const char *__restrict__ Kg, int nq, int nk, int heads, float c2,
     float *__restrict__ lse2, float *__restrict__ colsum)
 {
@@ -106,7 +110,8 @@ __global__ __launch_bounds__(NWV * 64, 4) void prefill_pass_kernel(
     // (the wave index as a scalar: branches on it are then uniform for the compiler too)
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int half = lane >> 5, l32 = lane & 31;
-    const int grp = wave >> 2;            // ping-pong group
+    constexpr bool SKEW = NWV == 8;       // two wave groups one phase apart
+    const int grp = SKEW ? wave >> 2 : 0; // ping-pong group
     // The nq queries are the LAST nq positions of the nk keys (nq == nk for a whole
     // prompt; nq < nk when a chunk of new tokens attends to nk - nq cached tokens in
     // front of it): query row i sits at key position off + i and sees keys <= off + i.
@@ -289,8 +294,10 @@ __global__ __launch_bounds__(NWV * 64, 4) void prefill_pass_kernel(
             }
             __builtin_amdgcn_s_setprio(0);
         }
-        dma_wait_upto<CPF>();
-        wg_barrier();
+        if constexpr (SKEW) {
+            dma_wait_upto<CPF>();
+            wg_barrier();
+        }
 
         if (live) {
             if constexpr (!COLSUM) {
@@ -384,7 +391,7 @@ __global__ __launch_bounds__(NWV * 64, 4) void prefill_pass_kernel(
         for (int tile = t_diag1; tile < t_rag; ++tile) tile_step(tile, std::false_type{});
         for (int tile = t_rag; tile < t_end; ++tile) tile_step(tile, std::true_type{});
     }
-    if (grp == 0) wg_barrier();            // the barrier the second group spent at the start
+    if (SKEW && grp == 0) wg_barrier();    // the barrier the second group spent at the start
     dma_wait_upto<0>();                    // trailing repeat requests land before the LDS is released
 
     if constexpr (!COLSUM) {
@@ -399,7 +406,23 @@ __global__ __launch_bounds__(NWV * 64, 4) void prefill_pass_kernel(
     }
 }
 
-template <int DT, int D, bool COLSUM>
+template <int DT, int D, int MB, bool COLSUM>
+__global__ __launch_bounds__(8 * 64, 4) void prefill_pass_kernel(
+    const char *__restrict__ Qg, const char *__restrict__ Kg, int nq, int nk, int heads, float c2,
+    float *__restrict__ lse2, float *__restrict__ colsum)
+{
+    prefill_pass<DT, D, MB, 8, COLSUM>(Qg, Kg, nq, nk, heads, c2, lse2, colsum);
+}
+
+template <int DT, int D, int MB, bool COLSUM>
+__global__ __launch_bounds__(4 * 64, 4) void prefill_pass4_kernel(
+    const char *__restrict__ Qg, const char *__restrict__ Kg, int nq, int nk, int heads, float c2,
+    float *__restrict__ lse2, float *__restrict__ colsum)
+{
+    prefill_pass<DT, D, MB, 4, COLSUM>(Qg, Kg, nq, nk, heads, c2, lse2, colsum);
+}
+
+template <int DT, int D, int NWV, bool COLSUM>
 hipError_t launch_pass(const h2o_config &cfg, double scale, const void *Q, const void *K, int nq,
                        int nk, float *lse2, float *colsum, hipStream_t st)
 {
@@ -411,7 +434,7 @@ hipError_t launch_pass(const h2o_config &cfg, double scale, const void *Q, const
     const int heads = cfg.batch * cfg.heads;
     const int nblk = ((COLSUM ? nk : nq) + SROWS - 1) / SROWS;
     const float c2 = (float)(scale * 1.4426950408889634);
-    auto kern = prefill_pass_kernel<DT, D, MB, COLSUM>;
+    auto kern = NWV == 8 ? prefill_pass_kernel<DT, D, MB, COLSUM> : prefill_pass4_kernel<DT, D, MB, COLSUM>;
     if (smem > 48 * 1024) {
         static bool raised = false;
         if (!raised) {
@@ -428,6 +451,25 @@ hipError_t launch_pass(const h2o_config &cfg, double scale, const void *Q, const
     return hipGetLastError();
 }
 
+template <int DT, int D, bool COLSUM>
+hipError_t pick_waves(const h2o_config &cfg, double scale, const void *Q, const void *K, int nq,
+                      int nk, float *lse2, float *colsum, hipStream_t st)
+{
+    // Eight waves pay off when the grid fills the chip several times over with long streams:
+    // the line is drawn on blocks x streamed rows.  Both passes, us, eight / four waves:
+    //   16-bit, d = 128   32 heads x 512: 26.5 / 19.7, 32 x 1531: 59 / 51, 32 x 4096 (2.1 M):
+    //                     198 / 186, 128 x 2048 (2.1 M): 181 / 178, 64 x 4096 (4.2 M): 286 / 302,
+    //                     512 x 2048 (8.4 M): 655 / 670, 128 x 4096 (8.4 M): 566 / 586
+    //   16-bit, d = 64    128 x 2048: 127 / 120, 128 x 4096 (8.4 M): 396 / 394, 128 x 8192 (34 M): 1420 / 1448
+    //   binary32          d = 64, 64 x 2048: 382 / 304, 128 x 4096 (8.4 M): 2197 / 2172;
+    //                     d = 128, 128 x 1024: 489 / 336, 128 x 4096: 4187 / 4173
+    const long long blocks8 = (long long)cfg.batch * cfg.heads * (((COLSUM ? nk : nq) + 255) / 256);
+    constexpr long long LINE = DT != H2O_F32 && D == 128 ? 3000000 : 16000000;
+    if (blocks8 * (COLSUM ? nq : nk) > LINE)
+        return launch_pass<DT, D, 8, COLSUM>(cfg, scale, Q, K, nq, nk, lse2, colsum, st);
+    return launch_pass<DT, D, 4, COLSUM>(cfg, scale, Q, K, nq, nk, lse2, colsum, st);
+}
+
 template <bool COLSUM>
 hipError_t dispatch(const h2o_config &cfg, double scale, const void *Q, const void *K, int nq,
                     int nk, float *lse2, float *colsum, hipStream_t st)
@@ -435,14 +477,14 @@ hipError_t dispatch(const h2o_config &cfg, double scale, const void *Q, const vo
     const int d = cfg.head_dim;
     switch (cfg.dtype) {
     case H2O_F32:
-        return d == 64 ? launch_pass<H2O_F32, 64, COLSUM>(cfg, scale, Q, K, nq, nk, lse2, colsum, st)
-                       : launch_pass<H2O_F32, 128, COLSUM>(cfg, scale, Q, K, nq, nk, lse2, colsum, st);
+        return d == 64 ? pick_waves<H2O_F32, 64, COLSUM>(cfg, scale, Q, K, nq, nk, lse2, colsum, st)
+                       : pick_waves<H2O_F32, 128, COLSUM>(cfg, scale, Q, K, nq, nk, lse2, colsum, st);
     case H2O_F16:
-        return d == 64 ? launch_pass<H2O_F16, 64, COLSUM>(cfg, scale, Q, K, nq, nk, lse2, colsum, st)
-                       : launch_pass<H2O_F16, 128, COLSUM>(cfg, scale, Q, K, nq, nk, lse2, colsum, st);
+        return d == 64 ? pick_waves<H2O_F16, 64, COLSUM>(cfg, scale, Q, K, nq, nk, lse2, colsum, st)
+                       : pick_waves<H2O_F16, 128, COLSUM>(cfg, scale, Q, K, nq, nk, lse2, colsum, st);
     default:
-        return d == 64 ? launch_pass<H2O_BF16, 64, COLSUM>(cfg, scale, Q, K, nq, nk, lse2, colsum, st)
-                       : launch_pass<H2O_BF16, 128, COLSUM>(cfg, scale, Q, K, nq, nk, lse2, colsum, st);
+        return d == 64 ? pick_waves<H2O_BF16, 64, COLSUM>(cfg, scale, Q, K, nq, nk, lse2, colsum, st)
+                       : pick_waves<H2O_BF16, 128, COLSUM>(cfg, scale, Q, K, nq, nk, lse2, colsum, st);
     }
 }
 

@@ -1,0 +1,63 @@
+"""The two workgroup shapes of the scoring passes (four and eight waves) on either side of
+the line between them, and lengths around the four-wave shapes' blocks of 128 rows:
+column sums and attention rows against float64."""
+import pytest
+import torch
+
+from tests.test_prefill_parity import COLSUM_ATOL, COLSUM_RTOL
+
+pytestmark = pytest.mark.gpu
+DT = {"f32": torch.float32, "f16": torch.float16, "bf16": torch.bfloat16}
+# attention rows: the probabilities and the result are each rounded once to the element type
+# (half a unit in the last place of 1 each, the former averaged over the row)
+ROW_TOL = {"f16": 2 * 2.0 ** -11, "bf16": 2 * 2.0 ** -8}
+
+
+@pytest.mark.parametrize("dt,d,heads,n", [
+    ("f32", 64, 64, 8209), ("f32", 128, 64, 8209), ("f16", 64, 64, 8209),     # eight waves, ragged
+    ("bf16", 128, 64, 4101),                                                  # eight waves
+    ("bf16", 128, 64, 2999),                                                  # four waves, just below
+    ("f16", 128, 3, 1), ("f16", 64, 3, 127), ("bf16", 128, 9, 128), ("f16", 128, 2, 129),
+    ("f32", 64, 2, 130), ("f32", 128, 2, 257), ("bf16", 64, 2, 513),
+])
+def test_column_sums_and_rows(dt, d, heads, n):
+    from paper_2306_14048_amd import binding as hb, synth
+    dev, dtype = torch.device("cuda:0"), DT[dt]
+    Q, K, V = synth.make_prompt(1, heads, n, d, dtype, 1.0, dev, seed=n)
+    cfg = hb.make_config(1, heads, d, 1, 1, dtype)
+    got = hb.prefill_colsum(cfg, Q, K)[0]
+    attn = None
+    if dt != "f32":
+        need = hb.h2o_prefill_attention_workspace_bytes(cfg, n)
+        ws = torch.empty(need, dtype=torch.uint8, device=dev)
+        attn = torch.empty_like(Q)
+        hb.h2o_prefill_attention(cfg, Q, K, V, n, ws, need, attn)
+    hidden = torch.ones(n, n, dtype=torch.bool, device=dev).triu(1)
+    for h in sorted({0, heads // 2, heads - 1}):
+        s = (Q[0, h].double() @ K[0, h].double().t()).mul_(d ** -0.5).masked_fill_(hidden, float("-inf"))
+        p = torch.softmax(s, -1)
+        ref = p.sum(0)
+        assert float(((got[h].double() - ref).abs() / (COLSUM_RTOL * ref + COLSUM_ATOL)).max()) <= 1.0
+        if attn is not None:
+            rows = p @ V[0, h].double()
+            err = (attn[0, h].double() - rows).norm(dim=-1) / rows.norm(dim=-1)
+            assert float(err.max()) <= ROW_TOL[dt]
+        del s, p
+
+
+def test_attention_in_place():
+    """An output that lies over V, or over Q, gives what a separate output gives."""
+    from paper_2306_14048_amd import binding as hb, synth
+    dev, n, d = torch.device("cuda:0"), 700, 128
+    Q, K, V = synth.make_prompt(1, 3, n, d, torch.float16, 1.0, dev, seed=9)
+    cfg = hb.make_config(1, 3, d, 1, 1, torch.float16)
+    need = hb.h2o_prefill_attention_workspace_bytes(cfg, n)
+    ws = torch.empty(need, dtype=torch.uint8, device=dev)
+    ref = torch.empty_like(Q)
+    hb.h2o_prefill_attention(cfg, Q, K, V, n, ws, need, ref)
+    over_v = V.clone()
+    hb.h2o_prefill_attention(cfg, Q, K, over_v, n, ws, need, over_v)
+    over_q = Q.clone()
+    hb.h2o_prefill_attention(cfg, over_q, K, V, n, ws, need, over_q)
+    torch.cuda.synchronize()
+    assert torch.equal(over_v, ref) and torch.equal(over_q, ref)
