@@ -103,8 +103,15 @@ def _ptr(x):
     return x.data_ptr()
 
 
+# The current stream's handle without a Stream object around it (2.8 us per call, as long as
+# a small generation step takes on the GPU; this takes 0.1 us).
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(stream):
     if stream is None:
+        if _raw_stream is not None:
+            return _raw_stream(torch.cuda.current_device())
         stream = torch.cuda.current_stream()
     if isinstance(stream, int):
         return stream
@@ -277,6 +284,7 @@ class H2OCache:
         self.dtype = dtype if isinstance(dtype, torch.dtype) else TORCH_DTYPES[dtype]
         self.device = torch.device(device)
         self.budget = int(heavy) + int(recent)
+        self._step_shape = (int(batch), int(heads), int(head_dim))
         nbytes = h2o_cache_bytes(self.cfg)
         if nbytes == 0:
             raise H2OError(H2O_EINVAL, "h2o_cache_bytes")
@@ -375,9 +383,22 @@ class H2OCache:
         h2o_prefill_select(self.handle, K, V, score, n, stream)
 
     def decode_step(self, q, k_new, v_new, out, stream=None):
-        shape = (*self.shape_heads, self.cfg.head_dim)
+        # The call every generated token makes.  The checks of _expect in one condition, and
+        # the entry point called with the pointers right away: 9.7 -> 5.3 us of host time per
+        # step, of which the launch is 4 (a step of 8 heads x 64 slots is 3.8 us on the GPU).
+        shape, dtype, device = self._step_shape, self.dtype, self.mem.device
+        for x in (q, k_new, v_new, out):
+            if not (isinstance(x, torch.Tensor) and x.dtype == dtype and x.shape == shape
+                    and x.device == device and x.is_contiguous()):
+                break
+        else:
+            rc = _lib.h2o_decode_step(self.handle, q.data_ptr(), k_new.data_ptr(), v_new.data_ptr(),
+                                      out.data_ptr(), _stream(stream))
+            if rc != H2O_OK:
+                raise H2OError(rc, "h2o_decode_step")
+            return
         for x, nm in ((q, "q"), (k_new, "k_new"), (v_new, "v_new"), (out, "out")):
-            self._expect(x, shape, self.dtype, nm)
+            self._expect(x, shape, dtype, nm)                 # says what is wrong
         h2o_decode_step(self.handle, q, k_new, v_new, out, stream)
 
     def snapshot(self, stream=None):
