@@ -8,74 +8,120 @@
 // x = min + code * scale; the new token attends to itself with its key and value
 // as given and is quantised when it is written into its slot.
 //
-// Memory plan.  A stored row is D/2 bytes of codes followed by D/64 (scale, min)
-// pairs.  LPR = D/32 neighbouring lanes read a row's codes with one 128-bit load
-// each (32 codes per lane) and the pair of the group they fall in with one
-// 64-bit load, so a wave covers RPW = 64/LPR rows per round.  All U key rounds
-// of a wave are requested up front; a round's registers are refilled with the
-// value row of the same slot as soon as the key has been used, so the value
-// stream is in flight during the softmax.  Nothing is dequantised into memory.
+// Both contractions run on the integer matrix cores, exactly.  With the row's
+// (scale s_g, min m_g) per group g of 64 elements,
+//     <q, x>  = sum_g  s_g * sum_{e in g} q_e c_e  +  m_g * sum_{e in g} q_e
+//     out_e   = sum_j (p_j s_gj) c_je  +  sum_j p_j m_gj .
+// The codes c (0..15) are one operand as bytes; the other is q, respectively
+// w_j = p_j s_gj, as a fixed-point number cut into signed 8-bit digits (base 256, digits
+// -128..127): q_e * 2^(54-E) with max|q| < 2^E in eight digits, w_j * 2^(30-E') with
+// the largest w of 64 slots < 2^E' in four.  v_mfma_i32_16x16x64_i8 then forms the digit
+// sums without rounding and they are put together in float64: a logit is off by at most
+// 64 * 15 * 2^-55 of max|q| per group (the float64 sums before: the same order), a
+// weight by 2^-31 of the largest one (before: binary32 products and sums).
+//   logits   A = digits of q (row = digit; rows 0-7 group 0, rows 8-15 group 1, zero where a
+//            row's group is not the lane's piece of the head dimension), B = 16 cached rows
+//   output   A = digits of w (rows 0-3 group 0, 4-7 group 1), B = 64 rows x 16 elements,
+//            read from the row-major codes with the 4-bit transposing LDS read
+// Turning codes into bytes takes three vector instructions per eight codes.  The kernel
+// before this one formed both sums on the vector ALU (an AND-OR and an fp64 or mixed fma
+// per code, 6.3 k vector instructions per head of 410 slots; now 4.9 k, most of them the
+// softmax and bookkeeping of each wave).  Measured, before -> this, f16, d = 128: 512 heads
+// x 410 slots 11.5 -> 9.9 us (36.7 MB), x 2048 45.6 -> 32.2; 3584 x 205 35.1 -> 30.1 (4.3 TB/s),
+// x 64 25.6 -> 14.7; 4096 x 410 72 -> 57 (5.1 TB/s); 32 x 2000 18.1 -> 12.2; binary32
+// elements 512 x 410 13.2 -> 10.4.
 //
-// Arithmetic.  Logits: with the row's (scale s_g, min m_g) per group g,
-//     <q, x> = sum_g  s_g * sum_{e in g} q_e c_e  +  m_g * sum_{e in g} q_e .
-// The inner sums are formed in fp64 without converting the codes: a code placed
-// in mantissa bits [p, p+4) of the high word of a double whose exponent makes
-// that field's unit 1 IS the number 2^(20-p) + c, one bit-field insert per code;
-// the surplus sum_e q_e 2^(20-p_e) is a per-lane constant taken off afterwards
-// (fp64 keeps 2^20 |q| + q c to ~1e-9 absolute, far below what the scores need).
-// Output: the same idea in half precision, (c << 6) | 0x4C00 is the half 16 + c,
-// two codes per AND-OR, multiplied by the fp32 weight p * s_g in a mixed-precision
-// fma with fp32 accumulation; 16 * sum p s_g and sum p m_g are settled once per lane.
+// Memory plan.  A wave owns blocks of 64 consecutive slots, one slot per lane.  A
+// block's stored rows are one contiguous image of 64 * 80 (or 48) bytes; the K images of a
+// wave's blocks followed by the V images are copied straight into a ring of LDS buffers of
+// its own (no registers, no barriers), all of them up front when the ring holds them
+// (budgets up to 512: two workgroups per CU), with the slots' bookkeeping behind them.
+// Every global read of the kernel is such a copy, so that each wait names exactly the
+// copies it needs (a load that the compiler waits for would wait for all of them).
 #include "wave_ops.h"
+#include "lds_copy.h"
 #include <type_traits>
 
 namespace {
 
-template <int CTRL> __device__ inline float dpp_f(float v)
-{
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, true));
-}
-constexpr int DPP_ROR2 = 0x122, DPP_ROR4 = 0x124, DPP_ROR8 = 0x128;   // rotate inside 16 lanes
-
-// sum over the LANES (2 or 4) neighbouring lanes of a row; every one of them gets it
-template <int LANES> __device__ inline double row_lanes_sum(double a)
-{
-    a += dpp<DPP_XOR1>(a);
-    if (LANES >= 4) a += dpp<DPP_XOR2>(a);
-    return a;
-}
-
-// Streaming loads addressed as uniform base + 32-bit lane offset (the form that
-// needs one address register per lane instead of a 64-bit pair).
 typedef float f32x2 __attribute__((ext_vector_type(2)));
-__device__ inline f32x2 load_pair_stream(const char *base, unsigned byte_off)
+typedef int i32x2 __attribute__((ext_vector_type(2)));
+
+// streaming form of dma16: the cache is read once per step
+__device__ inline void dma16_stream(i32x4 rsrc, unsigned voff, unsigned lds_base)
 {
-    return __builtin_nontemporal_load(reinterpret_cast<const f32x2 *>(base + byte_off));
-}
-__device__ inline uint4 load_codes_stream(const char *base, unsigned byte_off)
-{
-    return load_stream(base + byte_off);
+    asm volatile("s_nop 0\n\tbuffer_load_dwordx4 %0, %1, 0 offen nt lds"
+                 :
+                 : "v"(voff), "s"(rsrc), "{m0}"(lds_base)
+                 : "memory");
 }
 
-// Bit position of code j (0..7) of a word inside the high word of the double it is
-// turned into: codes 0..4 stay where they are (bits 0, 4, .., 16), codes 5..7 are
-// taken from the word shifted right by 12 (bits 8, 12, 16).
-__host__ __device__ constexpr int code_bit(int j) { return j < 5 ? 4 * j : 4 * (j - 3); }
+// 16 codes (two words) as 16 bytes: codes 0,2,4,6 | 1,3,5,7 of each word
+__device__ inline i32x4 codes_to_bytes(unsigned w0, unsigned w1)
+{
+    constexpr unsigned M = 0x0F0F0F0Fu;
+    return i32x4{(int)(w0 & M), (int)((w0 >> 4) & M), (int)(w1 & M), (int)((w1 >> 4) & M)};
+}
 
-// Registers: a lane keeps its 32 elements of q as doubles (64 registers) next to
-// the rounds in flight (7 registers each), which is why everything that is only
-// needed after the key pass (slot bookkeeping, the new token once more) is
-// requested after it, and why no loaded value may ever be spilled: a spill of a
-// register a load is still writing waits for the whole stream.  Four-wave
-// workgroups: 256 slots fit 128 registers (four workgroups per CU), 512 slots 168
-// (three per CU); deeper rings run at two waves per SIMD.  Eight waves per head
-// with half the rounds each were measured slower (more waves redo the softmax and
-// bookkeeping than the shorter rounds save).
-// PAT: built for a sparse-attention pattern as the protected set (the plain recent
-// window's build carries none of that code).
-template <int DT, int D, int NW, int U, bool PAT>
-__global__ __launch_bounds__(NW * 64, U * (64 / (D / 32)) == 64 ? 4 : (NW == 4 && U * (64 / (D / 32)) == 128) ? 3 : 2)
-void decode_q4_kernel(
+// sum of a over the lanes l, l ^ 32 (result: a's in lanes 0..31, b's in lanes 32..63)
+__device__ inline double fold32(double a, double b)
+{
+    const auto hi = __builtin_amdgcn_permlane32_swap((unsigned)__double2hiint(a), (unsigned)__double2hiint(b), false, false);
+    const auto lo = __builtin_amdgcn_permlane32_swap((unsigned)__double2loint(a), (unsigned)__double2loint(b), false, false);
+    return __hiloint2double((int)hi[0], (int)lo[0]) + __hiloint2double((int)hi[1], (int)lo[1]);
+}
+// sum over the lanes l, l ^ 16 (result: a's in the even rows of 16 lanes, b's in the odd ones)
+__device__ inline double fold16(double a, double b)
+{
+    const auto hi = __builtin_amdgcn_permlane16_swap((unsigned)__double2hiint(a), (unsigned)__double2hiint(b), false, false);
+    const auto lo = __builtin_amdgcn_permlane16_swap((unsigned)__double2loint(a), (unsigned)__double2loint(b), false, false);
+    return __hiloint2double((int)hi[0], (int)lo[0]) + __hiloint2double((int)hi[1], (int)lo[1]);
+}
+__device__ inline float wave_max_f32(float v)
+{
+    v = fmaxf(v, __int_as_float(dpp<DPP_XOR1>(__float_as_int(v))));
+    v = fmaxf(v, __int_as_float(dpp<DPP_XOR2>(__float_as_int(v))));
+    v = fmaxf(v, __int_as_float(dpp<DPP_HALF_MIRROR>(__float_as_int(v))));
+    v = fmaxf(v, __int_as_float(dpp<DPP_MIRROR>(__float_as_int(v))));
+    const int i = __float_as_int(v);
+    return fmaxf(fmaxf(__int_as_float(__builtin_amdgcn_readlane(i, 0)), __int_as_float(__builtin_amdgcn_readlane(i, 16))),
+                 fmaxf(__int_as_float(__builtin_amdgcn_readlane(i, 32)), __int_as_float(__builtin_amdgcn_readlane(i, 48))));
+}
+// smallest E with |x| < 2^E for a finite x (at least -126)
+__device__ inline int exponent_above(float x) { return (int)((__float_as_uint(x) >> 23) & 255u) - 126; }
+// exact power of two, |n| <= 1022
+__device__ inline double pow2(int n) { return __hiloint2double((1023 + n) << 20, 0); }
+
+// Four digit sums: sum_i v[i] 256^i = lo + 65536 hi.  (One MFMA's or two MFMAs' sums are below
+// 2 * 64 * 128 * 15 < 2^18, so neighbours fit one 32-bit integer.)
+__device__ inline i32x2 digit_pairs(const i32x4 &v) { return i32x2{v[0] + (v[1] << 8), v[2] + (v[3] << 8)}; }
+__device__ inline double joined(const i32x2 &v) { return fma((double)v.y, 65536.0, (double)v.x); }
+
+constexpr int MAX_WAVES = 8;
+
+// LDS of a workgroup: the shared part, then one part per wave
+template <int D> struct Shared {
+    unsigned char raw[3][512];                 // q, the new key, the new value as given
+    signed char digit[8][D];                   // q's digits; elements in the byte order of codes_to_bytes
+    double red_sum[MAX_WAVES], red_max[MAX_WAVES], red_key[MAX_WAVES];
+    double min_sum[2][MAX_WAVES];              // sum p m_g over a wave's slots
+    double s_self, qsum[2];                    // the token's own logit; scale * sum q per group
+    unsigned new_row[96];                      // the new token as stored: words, scales, mins
+};
+template <int D, int SPL> struct Ring {
+    static constexpr int IMG = 64 * H2O_Q4_ROW_BYTES(D);       // one block's rows
+    static constexpr int NB = SPL == 1 ? 2 : 3;                // buffers
+    // images | positions and scores of the wave's slots | digits of the weights of one
+    // block (one block per wave: in the K image, which is done with by then)
+    static constexpr int META = NB * IMG, REC = SPL == 1 ? 0 : META + SPL * 512;
+    static constexpr int BYTES = META + SPL * 512 + (SPL == 1 ? 0 : 512);
+};
+
+// SPL: blocks of 64 slots per wave (block s of wave w: s * waves + w).  PAT: built for
+// a sparse-attention pattern as the protected set (the plain recent window's build
+// carries none of that code).
+template <int DT, int D, int SPL, bool PAT>
+__global__ __launch_bounds__(MAX_WAVES * 64, 4) void decode_q4_kernel(
     char *__restrict__ Kc, char *__restrict__ Vc, float *__restrict__ acc_g,
     int32_t *__restrict__ pos_g, const char *__restrict__ q_g,
     const char *__restrict__ kn_g, const char *__restrict__ vn_g,
@@ -84,195 +130,226 @@ void decode_q4_kernel(
 {
     using E = Elem<DT>;
     using T = typename E::T;
+    using L = Ring<D, SPL>;
     constexpr int CODEB = D / 2;                // bytes of codes per row
     constexpr unsigned ROWB = H2O_Q4_ROW_BYTES(D);
-    constexpr int LPR = D / 32;                 // lanes per row, 32 codes each
-    constexpr int RPW = 64 / LPR;               // rows per wave per round
-    constexpr int RPI = NW * RPW;               // rows per workgroup-wide round
-    constexpr int OWN = U * RPW;                // slots a wave owns
-    constexpr int SPL = OWN / 64;               // ... per lane
+    constexpr int NG = D / 64;                  // groups per row = MFMAs per 16 rows
+    constexpr int IPB = L::IMG / 1024;          // copy instructions per image
+    constexpr int NB = L::NB;
     constexpr int QL = D / 8;                   // lanes holding the new key, 8 elements each
-    constexpr int QPITCH = 34;                  // doubles per 32-element slice of q in LDS (bank spread)
-    constexpr int OPITCH = D + 4;               // floats per row of partial outputs in LDS (bank spread)
-    static_assert(NW * 64 >= D, "one thread per element of q");
-    static_assert(OWN % 64 == 0 && SPL >= 1, "whole slots per lane");
-    static_assert(D == 64 || D == 128, "head dimension");
+    constexpr int META_COPIES = 2 * SPL;
+    static_assert(L::IMG % 1024 == 0 && (D == 64 || D == 128), "whole copies");
 
     const int head = blockIdx.x;
-    const int tid = threadIdx.x, lane = tid & 63;
+    const int tid = threadIdx.x, lane = tid & 63, nthr = blockDim.x, nw = nthr >> 6;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int sub = lane / LPR, li = lane % LPR;
+    const int l16 = lane & 15, quarter = lane >> 4;
 
     extern __shared__ __align__(16) unsigned char smem[];
-    double *s_l = reinterpret_cast<double *>(smem);                    // [NW][OWN] logits
-    double *red_sum = s_l + NW * OWN;                                  // [NW]
-    double *red_max = red_sum + NW;                                    // [NW] (overflow path)
-    double *red_key = red_max + NW;                                    // [NW]
-    double *qd_l = red_key + NW;                                       // [LPR][QPITCH] q as doubles
-    float *p_l = reinterpret_cast<float *>(qd_l + LPR * QPITCH);       // [NW][OWN]
-    float *fix_l = p_l + NW * OWN;                                     // [NW][4]
-    unsigned *new_l = reinterpret_cast<unsigned *>(fix_l + NW * 4);    // [3][32] the new token as stored
-    float *o_l = reinterpret_cast<float *>(new_l + 96);                // [NW * RPW][OPITCH]
-    double *s_w = s_l + wave * OWN;
-    float *p_w = p_l + wave * OWN;
+    Shared<D> &sh = *reinterpret_cast<Shared<D> *>(smem);
+    unsigned char *mine_l = smem + ((sizeof(Shared<D>) + 15) & ~(size_t)15) + (size_t)wave * L::BYTES;
+    const unsigned raw_b = (unsigned)reinterpret_cast<size_t>(smem);
+    const unsigned mine_b = __builtin_amdgcn_readfirstlane((unsigned)reinterpret_cast<size_t>(mine_l));
 
     const size_t hoff = (size_t)head * k;
     char *Kb = Kc + hoff * ROWB;
     char *Vb = Vc + hoff * ROWB;
-    const T *qh = reinterpret_cast<const T *>(q_g) + (size_t)head * D;
-    const T *knh = reinterpret_cast<const T *>(kn_g) + (size_t)head * D;
-    const T *vnh = reinterpret_cast<const T *>(vn_g) + (size_t)head * D;
 
-    const int row0 = wave * RPW + sub;          // this lane's row inside a round
-    const int last = max(n_occ, 1) - 1;         // clamp target
+    // ---- requests: q and the new token (wave 0), then the wave's images in the order they
+    // are used, then the bookkeeping.  Pieces past the occupied slots repeat the last
+    // occupied piece (in bounds; what they hold is masked).
+    if (wave == 0) {
+        constexpr unsigned RB = D * sizeof(T);
+        const i32x4 rq = make_rsrc(q_g + (size_t)head * RB, RB);
+        const i32x4 rk = make_rsrc(kn_g + (size_t)head * RB, RB);
+        const i32x4 rv = make_rsrc(vn_g + (size_t)head * RB, RB);
+        if (lane < (int)RB / 16) {
+            dma16(rq, lane * 16u, 0u, raw_b);
+            dma16(rk, lane * 16u, 0u, raw_b + 512);
+            dma16(rv, lane * 16u, 0u, raw_b + 1024);
+        }
+    }
+    const unsigned occ_bytes = (unsigned)max(n_occ, 1) * ROWB;
+    const i32x4 rsrc_k = make_rsrc(Kb, (unsigned)k * ROWB);
+    const i32x4 rsrc_v = make_rsrc(Vb, (unsigned)k * ROWB);
+    auto fetch = [&](int item) {                // item: K of blocks 0..SPL-1, then V of them
+        const int s = item % SPL;
+        const unsigned first = (unsigned)(s * nw + wave) * L::IMG + lane * 16u;
+#pragma unroll
+        for (int i = 0; i < IPB; ++i)
+            dma16_stream(item < SPL ? rsrc_k : rsrc_v, min(first + i * 1024u, occ_bytes - 16u),
+                         mine_b + (item % NB) * L::IMG + i * 1024);
+    };
+#pragma unroll
+    for (int i = 0; i < NB; ++i) fetch(i);
     int my_slot[SPL];
     bool owner[SPL];
-#pragma unroll
-    for (int s = 0; s < SPL; ++s) {
-        const int o = lane + 64 * s;            // entry of the wave's tile: round o / RPW, row o % RPW
-        my_slot[s] = (o / RPW) * RPI + wave * RPW + (o % RPW);
-        owner[s] = my_slot[s] < n_occ;
-    }
-
-    // ---- requests: q, the new token, then the whole key stream ------------------
-    const T q_elem = qh[tid % D];               // threads [0, D) widen q once for the workgroup
-    // 8 elements of q and of the new key per lane (lanes [0, QL) cover the row): the token's own logit
-    const int e8 = (lane % QL) * 8;
-    float q8[8], k8[8];
-    load8<DT>(qh + e8, q8);
-    load8<DT>(knh + e8, k8);
-
-    unsigned off[U];                            // byte offset of this lane's 16 bytes of codes
-    const unsigned to_pair = (unsigned)CODEB + (unsigned)(li / 2) * 8u - (unsigned)li * 16u;   // ... on to its group's pair
-    uint4 buf[U];
-    f32x2 par[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-        off[u] = __umul24((unsigned)min(u * RPI + row0, last), ROWB) + (unsigned)li * 16u;
-        buf[u] = load_codes_stream(Kb, off[u]);
-        par[u] = load_pair_stream(Kb, off[u] + to_pair);
-    }
-    __builtin_amdgcn_sched_barrier(0);
-
-    // ---- the token's own logit (while the stream arrives) ------------------------
-    double s_self;
     {
+        const i32x4 rsrc_p = make_rsrc(pos_g + hoff, (unsigned)k * 4u);
+        const i32x4 rsrc_a = make_rsrc(acc_g + hoff, (unsigned)k * 4u);
+#pragma unroll
+        for (int s = 0; s < SPL; ++s) {
+            my_slot[s] = (s * nw + wave) * 64 + lane;
+            owner[s] = my_slot[s] < n_occ;
+            const unsigned off = (unsigned)min(my_slot[s], max(n_occ, 1) - 1) * 4u;
+            dma4(rsrc_p, off, 0u, mine_b + L::META + s * 512);
+            dma4(rsrc_a, off, 0u, mine_b + L::META + s * 512 + 256);
+        }
+    }
+
+    // ---- q: the token's own logit, group sums, digits --------------------------------
+    dma_wait_upto<NB * IPB + META_COPIES>();    // (wave 0: its three copies have landed)
+    lds_barrier();
+    const T *q_l = reinterpret_cast<const T *>(sh.raw[0]), *kn_l = reinterpret_cast<const T *>(sh.raw[1]),
+            *vn_l = reinterpret_cast<const T *>(sh.raw[2]);
+    // Sums over the head dimension and the new token as it will be stored are each worked
+    // out by one wave (in the wait for the first image), the digits by the first D threads.
+    if (tid < MAX_WAVES) {                      // entries of waves that do not exist
+        sh.red_sum[tid] = 0.0;
+        sh.red_max[tid] = -INFINITY;
+        sh.red_key[tid] = __longlong_as_double((long long)NO_CANDIDATE);
+        sh.min_sum[0][tid] = sh.min_sum[1][tid] = 0.0;
+    }
+    auto job = [&](int j) { return wave == (j + 2) % nw; };      // (waves 0 and 1 cut the digits)
+    if (job(0)) {
         double a = 0.0;
 #pragma unroll
-        for (int i = 0; i < 8; ++i) a = fma((double)q8[i], (double)k8[i], a);
-        s_self = lane_value(group_sum<QL>(a), 0) * scale;     // lanes [0, QL) hold q.k_new
+        for (int g = 0; g < NG; ++g)
+            a = fma((double)E::to_f(q_l[64 * g + lane]), (double)E::to_f(kn_l[64 * g + lane]), a);
+        a = wave_sum(a);
+        if (lane == 0) sh.s_self = a * scale;
     }
-
-    // ---- this lane's 32 elements of q, widened exactly (once per workgroup, via LDS) ---
-    if (tid < D) qd_l[(tid / 32) * QPITCH + (tid % 32)] = (double)E::to_f(q_elem);
-    lds_barrier();
-    double qd[32];
-    double qsum = 0.0, surplus = 0.0;           // sum q_e and sum q_e 2^(20 - bit(e))
+    if (job(1)) {
+        const double a = wave_sum((double)E::to_f(q_l[lane]));
+        if (lane == 0) sh.qsum[0] = a * scale;
+    }
+    if (job(2)) {
+        const double a = NG == 2 ? wave_sum((double)E::to_f(q_l[D - 64 + lane])) : 0.0;
+        if (lane == 0) sh.qsum[1] = a * scale;
+    }
+    if (job(3)) {
+        float n8[8];
+        load8<DT>(((lane / QL) == 1 ? vn_l : kn_l) + (lane % QL) * 8, n8);
+        float new_scale, new_min;
+        const unsigned new_word = q4_quantise8(n8, new_scale, new_min);
+        if (lane < 32) {
+            sh.new_row[lane] = new_word;
+            sh.new_row[32 + lane] = __float_as_uint(new_scale);
+            sh.new_row[64 + lane] = __float_as_uint(new_min);
+        }
+    }
+    int qe;                                     // |q| < 2^qe
     {
-#pragma unroll
-        for (int i = 0; i < 32; i += 2) {
-            const double2 two = *reinterpret_cast<const double2 *>(qd_l + li * QPITCH + i);
-            qd[i] = two.x;
-            qd[i + 1] = two.y;
-        }
-        double by_bit[5] = {0.0, 0.0, 0.0, 0.0, 0.0};        // codes that sit at bit 0, 4, 8, 12, 16
-#pragma unroll
-        for (int e = 0; e < 32; ++e) by_bit[code_bit(e % 8) / 4] += qd[e];
-#pragma unroll
-        for (int b = 0; b < 5; ++b) {
-            qsum += by_bit[b];
-            surplus = fma(by_bit[b], (double)(1 << (20 - 4 * b)), surplus);
-        }
+        float m = fabsf(E::to_f(q_l[lane]));
+        if (NG == 2) m = fmaxf(m, fabsf(E::to_f(q_l[D - 64 + lane])));
+        qe = exponent_above(wave_max_f32(m));
     }
-
-    // The constants that are OR-ed around a code live in vector registers: the fused
-    // AND-OR instruction takes one scalar operand only (the mask), and a constant the
-    // compiler can see would be split off into an instruction of its own.
-    unsigned exp_bits[5];                       // exponent of 2^(20 - bit) for bit = 0, 4, .., 16
+    for (int e = tid; e < D; e += nthr) {
+        const double x = (double)E::to_f(q_l[e]) * pow2(54 - qe);
+        const double hi = floor(x * 0x1p-32);
+        const unsigned lo = (unsigned)rint(fma(hi, -0x1p32, x));
+        const unsigned long long bias = 0x0080808080808080ull;
+        const unsigned long long d =
+            ((((unsigned long long)(unsigned)(int)hi << 32) | lo) + bias) ^ bias;
+        const int at = (e & ~7) | ((e & 1) << 2) | ((e & 7) >> 1);
 #pragma unroll
-    for (int b = 0; b < 5; ++b) {
-        exp_bits[b] = (1023u + 20u - 4u * (unsigned)b) << 20;
-        asm volatile("" : "+v"(exp_bits[b]));
+        for (int i = 0; i < 8; ++i) sh.digit[i][at] = (signed char)(d >> (8 * i));
     }
+    lds_barrier();
+    i32x4 aq[NG];
+#pragma unroll
+    for (int m = 0; m < NG; ++m) {
+        const bool in_group = (l16 >> 3) == (NG == 2 ? quarter >> 1 : 0);
+        const i32x4 v = *reinterpret_cast<const i32x4 *>(&sh.digit[l16 & 7][quarter * 16 * NG + 16 * m]);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) aq[m][i] = in_group ? v[i] : 0;
+    }
+    // a lane's digit sums: quarter 0 / 1 = digits 0-3 / 4-7 of group 0, quarters 2 / 3 of group 1
+    const int my_group = NG == 2 ? quarter >> 1 : 0;
+    const bool used = NG == 2 || quarter < 2;
+    const double s_self = sh.s_self, qsum[2] = {sh.qsum[0], sh.qsum[1]};
+    // (digits cannot hold an infinity or a NaN in q: the logits are then not numbers)
+    const bool q_finite = fabs(qsum[0] + qsum[1]) <= 1.79769313486231570815e+308;
+    const double digit_unit = !q_finite ? (double)NAN : used ? pow2(qe - 54 + ((quarter & 1) ? 32 : 0)) * scale : 0.0;
+    const double min_unit = used && !(quarter & 1) ? qsum[my_group] : 0.0;
 
-    // ---- logits: one pass over the cached keys ------------------------------------
+    // ---- logits ------------------------------------------------------------------------
+    double s_j[SPL];
+    auto refill = [&](int item) {               // after item's buffer has been read
+        if (item + NB < 2 * SPL) {
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            fetch(item + NB);
+        }
+    };
+    auto for_blocks = [&](auto f) {
+        f(std::integral_constant<int, 0>{});
+        if constexpr (SPL > 1) f(std::integral_constant<int, 1>{});
+        if constexpr (SPL > 2) {
+            f(std::integral_constant<int, 2>{});
+            f(std::integral_constant<int, 3>{});
+        }
+    };
+    // copies issued behind item i by the time it is waited for
+    constexpr auto behind = [](int i) {
+        const int last = i + NB - 1 < 2 * SPL - 1 ? i + NB - 1 : 2 * SPL - 1;
+        return (last - i) * IPB + (i < NB ? META_COPIES : 0);
+    };
+    for_blocks([&](auto tag) {
+        constexpr int s = decltype(tag)::value;
+        dma_wait_upto<behind(s)>();
+        const unsigned char *img = mine_l + (s % NB) * L::IMG;
+        double part[4];
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-        if (u * RPI + wave * RPW < n_occ) {     // wave-uniform: rounds past the occupied slots cost no arithmetic
-            pin(buf[u]);
-            const unsigned w[4] = {buf[u].x, buf[u].y, buf[u].z, buf[u].w};
-            double a0 = 0.0, a1 = 0.0;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const unsigned hi12 = w[i] >> 12;
-#pragma unroll
-                for (int j = 0; j < 8; ++j) {
-                    const int b = code_bit(j);
-                    const unsigned src = j < 5 ? w[i] : hi12;
-                    const unsigned hi = (src & (0xFu << b)) | exp_bits[b / 4];
-                    const double c = __hiloint2double((int)hi, 0);      // 2^(20-b) + code
-                    if (j & 1) a1 = fma(c, qd[i * 8 + j], a1);
-                    else a0 = fma(c, qd[i * 8 + j], a0);
+        for (int tl = 0; tl < 4; ++tl) {
+            part[tl] = 0.0;
+            if ((s * nw + wave) * 64 + tl * 16 < n_occ) {      // wave-uniform
+                const unsigned char *row = img + (tl * 16 + l16) * ROWB;
+                i32x4 sums = {0, 0, 0, 0};
+                if constexpr (NG == 2) {
+                    const uint4 w = *reinterpret_cast<const uint4 *>(row + quarter * 16);
+                    sums = __builtin_amdgcn_mfma_i32_16x16x64_i8(aq[0], codes_to_bytes(w.x, w.y), sums, 0, 0, 0);
+                    sums = __builtin_amdgcn_mfma_i32_16x16x64_i8(aq[1], codes_to_bytes(w.z, w.w), sums, 0, 0, 0);
+                } else {
+                    const uint2 w = *reinterpret_cast<const uint2 *>(row + quarter * 8);
+                    sums = __builtin_amdgcn_mfma_i32_16x16x64_i8(aq[0], codes_to_bytes(w.x, w.y), sums, 0, 0, 0);
                 }
+                const f32x2 sm = *reinterpret_cast<const f32x2 *>(row + CODEB + 8 * my_group);
+                part[tl] = fma(joined(digit_pairs(sums)) * digit_unit, (double)sm.x, (double)sm.y * min_unit);
             }
-            const double part = fma((double)par[u].x, (a0 + a1) - surplus, (double)par[u].y * qsum);
-            const double tot = row_lanes_sum<LPR>(part);
-            if (li == 0) s_w[u * RPW + sub] = tot * scale;
         }
-        // the value row takes the registers; the pair's offset is worked out here, from a
-        // copy the compiler cannot see through, so that it is not kept for every round
-        unsigned o = off[u];
-        asm volatile("" : "+v"(o));
-        buf[u] = load_codes_stream(Vb, o);
-        par[u] = load_pair_stream(Vb, o + to_pair);
-        __builtin_amdgcn_sched_barrier(0);
-    }
-    // What is needed after the value pass, requested behind the value stream (loads
-    // complete in order): the owned slots' bookkeeping, the new token once more (lanes
-    // [0, QL): 8 elements of its key, lanes [QL, 2 QL): of its value) and the column of
-    // its value this thread adds to the output.  All unconditional: a load behind a
-    // branch would be waited for on the spot.
-    int pos_j[SPL];
-    float acc_j[SPL];
-#pragma unroll
-    for (int s = 0; s < SPL; ++s) {
-        pos_j[s] = pos_g[hoff + min(my_slot[s], last)];
-        acc_j[s] = acc_g[hoff + min(my_slot[s], last)];
-    }
-    float n8[8];
-    load8<DT>((lane / QL) == 1 ? vnh + e8 : knh + e8, n8);
-    const T v_self_raw = vnh[tid % D];
-    __builtin_amdgcn_wave_barrier();
+        // the four quarters' parts of a row added up; lane l gets row l of the block
+        s_j[s] = fold16(fold32(part[0], part[2]), fold32(part[1], part[3]));
+        refill(s);
+    });
 
     // ---- exact softmax over the occupied slots + the token itself -------------------
-    double s_j[SPL], e_j[SPL];
+    double e_j[SPL];
     double e_sum = 0.0;
 #pragma unroll
     for (int s = 0; s < SPL; ++s) {
-        s_j[s] = owner[s] ? s_w[lane + 64 * s] : 0.0;
         e_j[s] = owner[s] ? exp(s_j[s] - s_self) : 0.0;
         e_sum += e_j[s];
     }
     double e_self = 1.0;
     {
         const double dw = wave_sum(e_sum);
-        if (lane == 0) red_sum[wave] = dw;
+        if (lane == 0) sh.red_sum[wave] = dw;
     }
     lds_barrier();
     double den = e_self;
 #pragma unroll
-    for (int w = 0; w < NW; ++w) den += red_sum[w];
+    for (int w = 0; w < MAX_WAVES; ++w) den += sh.red_sum[w];
     if (!(den <= 1.79769313486231570815e+308)) {
         // some logit is > ~709 above the token's own: redo with the true maximum
         double m = -INFINITY;
 #pragma unroll
         for (int s = 0; s < SPL; ++s) m = fmax(m, owner[s] ? s_j[s] : -INFINITY);
         const double mw = wave_max(m);
-        if (lane == 0) red_max[wave] = mw;
+        if (lane == 0) sh.red_max[wave] = mw;
         lds_barrier();
         double mx = s_self;
 #pragma unroll
-        for (int w = 0; w < NW; ++w) mx = fmax(mx, red_max[w]);
+        for (int w = 0; w < MAX_WAVES; ++w) mx = fmax(mx, sh.red_max[w]);
         e_sum = 0.0;
 #pragma unroll
         for (int s = 0; s < SPL; ++s) {
@@ -281,112 +358,106 @@ void decode_q4_kernel(
         }
         e_self = exp(s_self - mx);
         const double dw = wave_sum(e_sum);
-        if (lane == 0) red_sum[wave] = dw;
+        if (lane == 0) sh.red_sum[wave] = dw;
         lds_barrier();
         den = e_self;
 #pragma unroll
-        for (int w = 0; w < NW; ++w) den += red_sum[w];
+        for (int w = 0; w < MAX_WAVES; ++w) den += sh.red_sum[w];
     }
     const float p_self = (float)(e_self / den);
-
-    // ---- probabilities to the lanes that read the value rows ------------------------
     float p_j[SPL];
 #pragma unroll
-    for (int s = 0; s < SPL; ++s) {
-        p_j[s] = (float)(e_j[s] / den);
-        p_w[lane + 64 * s] = p_j[s];                         // 0 for unoccupied rows
-    }
-    __builtin_amdgcn_wave_barrier();
+    for (int s = 0; s < SPL; ++s) p_j[s] = (float)(e_j[s] / den);          // 0 for unoccupied rows
 
-    // ---- output: one pass over the cached values --------------------------------------
-    // Accumulated in fp32, except for binary32 element types: there the output has to
-    // hold 1e-5 relative, and the sums of p s_g (16 + c) are an order of magnitude larger
-    // than the output they leave once 16 sum p s_g and sum p m_g are taken off (a
-    // dequantised value is itself the small difference of m_g and c s_g), so fp32
-    // rounding of the large sums would show.  fp64 then, settled per lane before the
-    // columns meet in LDS.
-    using OT = typename std::conditional<DT == H2O_F32, double, float>::type;
-    OT o[32];
+    // ---- output ------------------------------------------------------------------------
+    // (the weights of a block have an exponent of their own: the scales of later blocks may
+    // not have arrived yet)
+    constexpr int NDT = D / 16;                 // 16-element tiles of the output
+    double o[NDT / NG];                         // lanes of quarter g: group g's elements 16 dt + l16
 #pragma unroll
-    for (int i = 0; i < 32; ++i) o[i] = (OT)0;
-    unsigned half16 = 0x4C004C00u;              // two halves of value 16 (in a vector register, as above)
-    asm volatile("" : "+v"(half16));
-    OT wsum = (OT)0, msum = (OT)0;              // sum p s_g and sum p m_g over this lane's rows
+    for (int i = 0; i < NDT / NG; ++i) o[i] = 0.0;
+    double msum[2] = {0.0, 0.0};
+    for_blocks([&](auto tag) {
+        constexpr int s = decltype(tag)::value;
+        dma_wait_upto<behind(SPL + s)>();
+        const unsigned char *img = mine_l + ((SPL + s) % NB) * L::IMG;
+        if ((s * nw + wave) * 64 < n_occ) {                    // wave-uniform
+            // this lane's weights, one per group, as fixed-point digits (p is 0 for a slot that
+            // is not occupied; it takes the last occupied row's scales)
+            const unsigned char *meta = img + min(lane, n_occ - 1 - (s * nw + wave) * 64) * ROWB + CODEB;
+            double w[2] = {0.0, 0.0};
+            bool fine[2] = {true, true};
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-        if (u * RPI + wave * RPW < n_occ) {
-            pin(buf[u]);
-            // rows past the occupied slots repeat the last occupied row with p = 0
-            const float p = p_w[u * RPW + sub];
-            OT wgt;
-            if constexpr (DT == H2O_F32) {
-                wgt = (double)p * (double)par[u].x;
-                msum = fma((double)p, (double)par[u].y, msum);
-            } else {
-                wgt = p * par[u].x;
-                msum = fmaf(p, par[u].y, msum);
+            for (int g = 0; g < NG; ++g) {
+                const f32x2 sm = *reinterpret_cast<const f32x2 *>(meta + 8 * g);
+                w[g] = (double)p_j[s] * (double)sm.x;
+                msum[g] = fma((double)p_j[s], (double)sm.y, msum[g]);
+                // infinite or not a number: so is the group's output
+                fine[g] = __ballot(!(w[g] <= 1.79769313486231570815e+308)) == 0;
             }
-            wsum += wgt;
-            const unsigned w[4] = {buf[u].x, buf[u].y, buf[u].z, buf[u].w};
+            const int we = exponent_above(wave_max_f32((float)fmax(w[0], w[1])));
+            const double up = pow2(30 - we);
+            const double down = (quarter & 1 ? fine[NG - 1] : fine[0]) ? pow2(we - 30) : (double)NAN;
+            unsigned char *rec = mine_l + L::REC;
+            {
+                const unsigned bias = 0x00808080u;
+                uint2 d;
+                d.x = ((unsigned)rint(w[0] * up) + bias) ^ bias;
+                d.y = NG == 2 ? ((unsigned)rint(w[1] * up) + bias) ^ bias : 0u;
+                *reinterpret_cast<uint2 *>(rec + lane * 8) = d;
+            }
+            __builtin_amdgcn_wave_barrier();
+            asm volatile("" ::: "memory");
+            // A operand: digit l16 (0-3 group 0, 4-7 group 1) of the quarter's 16 rows, in the
+            // byte order of codes_to_bytes.  (8-bit transposing read: lane i < 8 of 16 receives
+            // byte i of the records that the even lanes point at.)
+            i32x4 aw;
+            {
+                typedef __attribute__((address_space(3))) i32x2 lds_i32x2;
+                const int i = l16 >> 1, r = ((i & 3) << 1) | (i >> 2);       // 0 2 4 6 1 3 5 7
+                const unsigned char *at = rec + (quarter * 16 + r) * 8;
+                const i32x2 a = __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_i32x2 *)at);
+                const i32x2 b = __builtin_amdgcn_ds_read_tr8_b64_v2i32((lds_i32x2 *)(at + 64));
+                aw = i32x4{a.x, a.y, b.x, b.y};
+            }
+            // B operand: lane = element 16 dt + l16 of the quarter's 16 rows (4-bit transposing read)
+            const unsigned char *row = img + lane * ROWB;
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                // codes (j, j + 4) of the word as the two halves 16 + c of one register
-                const unsigned x[4] = {w[i] << 6, w[i] << 2, w[i] >> 2, w[i] >> 6};
+            for (int i = 0; i < NDT / NG; ++i) {
+                i32x4 sums[NG];
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const unsigned h2 = (x[j] & 0x03C003C0u) | half16;
-                    const _Float16 lo = __builtin_bit_cast(_Float16, (unsigned short)(h2 & 0xffffu));
-                    const _Float16 hi = __builtin_bit_cast(_Float16, (unsigned short)(h2 >> 16));
-                    if constexpr (DT == H2O_F32) {
-                        o[i * 8 + j] = fma(wgt, (double)(float)lo, o[i * 8 + j]);
-                        o[i * 8 + j + 4] = fma(wgt, (double)(float)hi, o[i * 8 + j + 4]);
-                    } else {
-                        o[i * 8 + j] = fmaf(wgt, (float)lo, o[i * 8 + j]);
-                        o[i * 8 + j + 4] = fmaf(wgt, (float)hi, o[i * 8 + j + 4]);
-                    }
+                for (int g = 0; g < NG; ++g) {
+                    typedef __attribute__((address_space(3))) i32x2 lds_i32x2;
+                    const int dt = g * (NDT / NG) + i;
+                    const i32x2 c = __builtin_amdgcn_ds_read_tr4_b64_v2i32((lds_i32x2 *)(row + 8 * dt));
+                    sums[g] = __builtin_amdgcn_mfma_i32_16x16x64_i8(
+                        aw, codes_to_bytes((unsigned)c.x, (unsigned)c.y), i32x4{0, 0, 0, 0}, 0, 0, 0);
                 }
+                // rows 4g..4g+3 of a group's tile are its digits: quarter g of the lanes has them
+                i32x2 v = digit_pairs(sums[0]);
+                if constexpr (NG == 2) {
+                    const i32x2 v1 = digit_pairs(sums[1]);
+                    if (quarter & 1) v = v1;
+                }
+                o[i] = fma(joined(v), down, o[i]);
             }
         }
-        __builtin_amdgcn_sched_barrier(0);
-    }
+        refill(SPL + s);
+    });
+    dma_wait_upto<0>();                         // the bookkeeping as well
     {
-        // every lane hands its 32 partial columns to LDS (o_l[row of the round][column]);
-        // the two constants, which belong to all 32 columns alike, are added up over
-        // the wave's rows first: fix_l[wave][li] (fp64 accumulation: taken off per lane)
-        float *dst = o_l + (wave * RPW + sub) * OPITCH + li * 32;
-        float fix;
-        if constexpr (DT == H2O_F32) {
-            const double fixd = msum - 16.0 * wsum;
+        // the wave's columns, in its first buffer (every image has been read)
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        double *o_w = reinterpret_cast<double *>(mine_l);
+        if (quarter < NG) {
 #pragma unroll
-            for (int i = 0; i < 32; i += 4)
-                *reinterpret_cast<float4 *>(dst + i) =
-                    make_float4((float)(o[i] + fixd), (float)(o[i + 1] + fixd), (float)(o[i + 2] + fixd),
-                                (float)(o[i + 3] + fixd));
-            fix = 0.f;
-        } else {
-#pragma unroll
-            for (int i = 0; i < 32; i += 4)
-                *reinterpret_cast<float4 *>(dst + i) = make_float4(o[i], o[i + 1], o[i + 2], o[i + 3]);
-            fix = msum - 16.f * wsum;
+            for (int i = 0; i < NDT / NG; ++i) o_w[(quarter * (NDT / NG) + i) * 16 + l16] = o[i];
         }
-        fix += dpp_f<DPP_ROR8>(fix);
-        fix += dpp_f<DPP_ROR4>(fix);
-        if (LPR == 2) fix += dpp_f<DPP_ROR2>(fix);
-        fix += __shfl_xor(fix, 16, 64);
-        fix += __shfl_xor(fix, 32, 64);
-        if (lane < LPR) fix_l[wave * 4 + lane] = fix;
-    }
-
-    // ---- the new token as it will be stored (one wave works it out for whichever
-    // wave turns out to own the slot) ---------------------------------------------------
-    if (wave == 0) {
-        float new_scale, new_min;
-        const unsigned new_word = q4_quantise8(n8, new_scale, new_min);
-        if (lane < 32) {
-            new_l[lane] = new_word;
-            new_l[32 + lane] = __float_as_uint(new_scale);
-            new_l[64 + lane] = __float_as_uint(new_min);
-        }
+        // lanes 0..31 add up group 0, lanes 32..63 group 1 (d = 64: a second copy)
+        double mg = fold32(msum[0], msum[NG - 1]);
+        mg = group_sum<16>(mg);
+        mg = fold16(mg, mg);
+        if ((lane & 31) == 0 && (lane >> 5) < NG) sh.min_sum[lane >> 5][wave] = mg;
     }
 
     // ---- score update (Algorithm 2, accumulate line: binary32 add of the binary32
@@ -397,14 +468,17 @@ void decode_q4_kernel(
     // that it covers them all, in the LDS words of the overflow path, idle by now)
     unsigned long long key = NO_CANDIDATE, key_all = NO_CANDIDATE;
     int key_slot = -1, key_all_slot = -1;
+    float acc_j[SPL];
 #pragma unroll
     for (int s = 0; s < SPL; ++s) {
+        const int pos_j = *reinterpret_cast<const int *>(mine_l + L::META + s * 512 + lane * 4);
+        acc_j[s] = *reinterpret_cast<const float *>(mine_l + L::META + s * 512 + 256 + lane * 4);
         acc_j[s] += p_j[s];
         if (owner[s]) {
             const unsigned long long c =
-                ((unsigned long long)__float_as_uint(rank_value(acc_j[s], pos_j[s], t, rank)) << 32) |
-                (unsigned)pos_j[s];
-            if (PAT ? !is_protected(pos_j[s], t, recent, protect, stride) : pos_j[s] <= t - recent) {
+                ((unsigned long long)__float_as_uint(rank_value(acc_j[s], pos_j, t, rank)) << 32) |
+                (unsigned)pos_j;
+            if (PAT ? !is_protected(pos_j, t, recent, protect, stride) : pos_j <= t - recent) {
                 if (c < key) { key = c; key_slot = my_slot[s]; }
             }
             if (PAT && c < key_all) { key_all = c; key_all_slot = my_slot[s]; }
@@ -412,38 +486,34 @@ void decode_q4_kernel(
     }
     {
         const double kw = wave_min_f64(__longlong_as_double((long long)key));
-        if (lane == 0) red_key[wave] = kw;
+        if (lane == 0) sh.red_key[wave] = kw;
     }
     if constexpr (PAT) {
         const double ka = wave_min_f64(__longlong_as_double((long long)key_all));
-        if (lane == 0) red_max[wave] = ka;
+        if (lane == 0) sh.red_max[wave] = ka;
     }
     lds_barrier();
 
     // ---- write-back ---------------------------------------------------------------------
-    if (tid < D) {
-        float r0 = p_self * E::to_f(v_self_raw), r1 = 0.f;
+    for (int e = tid; e < D; e += nthr) {
+        double r = (double)p_self * (double)E::to_f(vn_l[e]);
 #pragma unroll
-        for (int w = 0; w < NW; ++w) r1 += fix_l[w * 4 + tid / 32];
-#pragma unroll 8
-        for (int row = 0; row < NW * RPW; row += 2) {
-            r0 += o_l[row * OPITCH + tid];
-            r1 += o_l[(row + 1) * OPITCH + tid];
-        }
-        reinterpret_cast<T *>(out_g)[(size_t)head * D + tid] = E::from_f(r0 + r1);
+        for (int w = 0; w < MAX_WAVES; ++w) r += sh.min_sum[e / 64][w];
+        const unsigned char *w0 = smem + ((sizeof(Shared<D>) + 15) & ~(size_t)15) + (size_t)e * 8;
+        for (int w = 0; w < nw; ++w) r += *reinterpret_cast<const double *>(w0 + (size_t)w * L::BYTES);
+        reinterpret_cast<T *>(out_g)[(size_t)head * D + e] = E::from_f((float)r);
     }
     int tslot = -1;          // wave-uniform: the slot this wave has to fill, if any
     int lost_slot = -1;      // per lane: its slot that has just been evicted
     if (n_occ < k) {
         if (wave == 0) tslot = n_occ;
     } else {
-        double wd = red_key[0];
+        double wd = sh.red_key[0];
 #pragma unroll
-        for (int w = 1; w < NW; ++w) wd = fmin(wd, red_key[w]);
+        for (int w = 1; w < MAX_WAVES; ++w) wd = fmin(wd, sh.red_key[w]);
         if (PAT && wd != wd) {                               // the pattern covers every slot
-            wd = red_max[0];
-#pragma unroll
-            for (int w = 1; w < NW; ++w) wd = fmin(wd, red_max[w]);
+            wd = sh.red_max[0];
+            for (int w = 1; w < nw; ++w) wd = fmin(wd, sh.red_max[w]);
             key = key_all;
             key_slot = key_all_slot;
         }
@@ -465,12 +535,17 @@ void decode_q4_kernel(
         if (lane < 2 * QL) {
             char *row = (lane < QL ? Kb : Vb) + (size_t)tslot * ROWB;
             const int l = lane % QL;
-            *reinterpret_cast<unsigned *>(row + l * 4) = new_l[lane];
+            *reinterpret_cast<unsigned *>(row + l * 4) = sh.new_row[lane];
             if ((l & 7) == 0)
                 *reinterpret_cast<f32x2 *>(row + CODEB + (l / 8) * 8) =
-                    f32x2{__uint_as_float(new_l[32 + lane]), __uint_as_float(new_l[64 + lane])};
+                    f32x2{__uint_as_float(sh.new_row[32 + lane]), __uint_as_float(sh.new_row[64 + lane])};
         }
     }
+}
+
+template <int D, int SPL> constexpr size_t lds_of(int waves)
+{
+    return ((sizeof(Shared<D>) + 15) & ~(size_t)15) + (size_t)waves * Ring<D, SPL>::BYTES;
 }
 
 #define H2O_DECODE_ARGS                                                                         \
@@ -478,14 +553,11 @@ void decode_q4_kernel(
         static_cast<const char *>(vn), static_cast<char *>(out), c.k, (c.t < c.k ? c.t : c.k),  \
         c.t, c.cfg.recent, c.scale, c.cfg.rank, c.cfg.protect, c.cfg.stride
 
-template <int DT, int D, int NW, int U>
-hipError_t launch_q4(const h2o_cache &c, const void *q, const void *kn, const void *vn, void *out,
-                     hipStream_t st)
+template <int DT, int D, int SPL>
+hipError_t launch_q4(const h2o_cache &c, int waves, const void *q, const void *kn, const void *vn,
+                     void *out, hipStream_t st)
 {
-    constexpr int LPR = D / 32, RPW = 64 / LPR, OWN = U * RPW;
-    constexpr size_t smem = (size_t)NW * OWN * 8 + (size_t)NW * 24 + (size_t)LPR * 34 * 8 +
-                            (size_t)NW * OWN * 4 + (size_t)NW * 16 + 384 +
-                            (size_t)NW * RPW * (D + 4) * 4 + 16;
+    const size_t smem = lds_of<D, SPL>(waves);
     auto launch = [&](auto kern, bool &raised) -> hipError_t {
         if (smem > 48 * 1024 && !raised) {
             const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
@@ -493,26 +565,32 @@ hipError_t launch_q4(const h2o_cache &c, const void *q, const void *kn, const vo
             if (e != hipSuccess) return e;
             raised = true;
         }
-        hipLaunchKernelGGL(kern, dim3(c.cfg.batch * c.cfg.heads), dim3(NW * 64), smem, st, H2O_DECODE_ARGS);
+        hipLaunchKernelGGL(kern, dim3(c.cfg.batch * c.cfg.heads), dim3(waves * 64), smem, st, H2O_DECODE_ARGS);
         return hipGetLastError();
     };
     static bool raised_window = false, raised_pattern = false;
-    if (c.cfg.protect == H2O_PROTECT_RECENT) return launch(decode_q4_kernel<DT, D, NW, U, false>, raised_window);
-    return launch(decode_q4_kernel<DT, D, NW, U, true>, raised_pattern);
+    if (c.cfg.protect == H2O_PROTECT_RECENT) return launch(decode_q4_kernel<DT, D, SPL, false>, raised_window);
+    return launch(decode_q4_kernel<DT, D, SPL, true>, raised_pattern);
 }
 
-// Rounds per wave follow the number of occupied slots (capacity NW * U * RPW).
+// Blocks per wave: as few as leave room for two workgroups in a CU's LDS (512 heads, d =
+// 128, us: 480 slots 1 / 2 blocks per wave 12.8 / 9.8; 600 2 / 4 blocks 16.1 / 12.3; 1000
+// 19.8 / 15.3; below that line more waves win: 205 slots 1 / 2 blocks 7.1 / 8.4).
 template <int DT, int D>
 hipError_t pick_q4(const h2o_cache &c, const void *q, const void *kn, const void *vn, void *out,
                    hipStream_t st)
 {
-    constexpr int RPW = 64 / (D / 32);
-    constexpr int U0 = 64 / RPW;                // fewest rounds that give every lane a slot
+    constexpr size_t HALF = 80 * 1024;
     const int occ = c.t < c.k ? c.t : c.k;
-    if (occ <= 4 * U0 * RPW) return launch_q4<DT, D, 4, U0>(c, q, kn, vn, out, st);           // 256 slots
-    if (occ <= 4 * 2 * U0 * RPW) return launch_q4<DT, D, 4, 2 * U0>(c, q, kn, vn, out, st);   // 512
-    if (occ <= 4 * 4 * U0 * RPW) return launch_q4<DT, D, 4, 4 * U0>(c, q, kn, vn, out, st);   // 1024
-    if (occ <= 8 * 4 * U0 * RPW) return launch_q4<DT, D, 8, 4 * U0>(c, q, kn, vn, out, st);   // 2048
+    const int blocks = occ > 64 ? (occ + 63) / 64 : 1;
+    // (a second wave shares the work on q and the new token where all heads run at once:
+    // 8 heads x 64 slots 5.6 -> 5.2 us; with more heads it only takes a place: 3584 x 64 14.7 / 18.1)
+    const int least = c.cfg.batch * c.cfg.heads <= 512 ? 2 : 1;
+    if (blocks <= MAX_WAVES && lds_of<D, 1>(blocks) <= HALF)
+        return launch_q4<DT, D, 1>(c, blocks < least ? least : blocks, q, kn, vn, out, st);
+    if (const int w = (blocks + 1) / 2; w <= MAX_WAVES && lds_of<D, 2>(w) <= HALF)
+        return launch_q4<DT, D, 2>(c, w, q, kn, vn, out, st);
+    if (blocks <= 4 * MAX_WAVES) return launch_q4<DT, D, 4>(c, (blocks + 3) / 4, q, kn, vn, out, st);
     return hipErrorInvalidValue;               // beyond H2O_Q4_MAX_BUDGET: refused at configuration time
 }
 

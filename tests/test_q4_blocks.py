@@ -1,0 +1,91 @@
+"""The 4-bit step at the edges of its dispatch (blocks of 64 slots, one to four per wave) and
+of its fixed-point digits: queries whose elements span many orders of magnitude, logits
+that overflow the shift, values with one huge row, and inputs that are not finite."""
+import pytest
+import torch
+
+from tests.test_q4_parity import q4_case, torch_dt
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("d,k,heads,dt", [
+    (128, 63, 2, "f16"), (128, 64, 2, "bf16"), (128, 65, 2, "f16"),        # one block, two
+    (128, 60, 520, "f16"),                                                 # one wave per head
+    (128, 448, 2, "f16"), (128, 449, 2, "f16"), (128, 512, 2, "f32"),      # seven blocks; eight: two per wave
+    (128, 513, 2, "bf16"), (128, 1025, 1, "f16"),                          # four per wave
+    (64, 512, 2, "f16"), (64, 513, 2, "f16"), (64, 896, 2, "bf16"), (64, 897, 2, "f32"), (64, 2047, 1, "f16"),
+])
+def test_q4_block_edges(d, k, heads, dt):
+    q4_case(1, heads, d, k + 3, 5, (k + 1) // 2, k // 2, torch_dt[dt], 1.0, 80 + k)
+    if heads < 10:
+        q4_case(1, heads, d, k - 3, 6, (k + 1) // 2, k // 2, torch_dt[dt], 1.0, 81 + k)   # fills, then evicts
+
+
+def dequantised(x):
+    g = x.float().unflatten(-1, (-1, 64))
+    mn, mx = g.amin(-1, keepdim=True), g.amax(-1, keepdim=True)
+    sc = (mx - mn) / torch.full_like(mx, 15.0)
+    code = torch.where(sc > 0, ((g - mn) / sc).round().clamp(0, 15), torch.zeros_like(g))
+    return (mn.double() + code.double() * sc.double()).flatten(-2)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("dt", ["f16", "bf16", "f32"])
+@pytest.mark.parametrize("kind", ["spread", "tiny", "above", "below", "one huge row"])
+def test_q4_digits(dt, d, kind):
+    """One step against float64 on the stored (dequantised) rows, on the CPU."""
+    from paper_2306_14048_amd import binding as hb
+    dev, dtype, heads, k = torch.device("cuda:0"), torch_dt[dt], 3, 150
+    g = torch.Generator().manual_seed(len(kind) + d)
+    rand = lambda *s: torch.randn(s, generator=g)  # noqa: E731
+    K, V = rand(1, heads, k, d), rand(1, heads, k, d)
+    q, kn, vn = rand(1, heads, d), rand(1, heads, d), rand(1, heads, d)
+    if kind == "spread":                        # six orders of magnitude inside one query
+        q = q * 10.0 ** (torch.randint(-5, 2, (1, heads, d), generator=g).float())
+    elif kind == "tiny":
+        q = q * 3e-5
+    elif kind == "above":                       # logits some 2000 above the token's own
+        q, kn, K = q.abs() + 1, torch.zeros_like(kn), K + (500 if d == 64 else 350) * (torch.arange(k) % 3 == 0)[:, None]
+    elif kind == "below":
+        q, kn, K = q.abs() + 1, torch.zeros_like(kn), K - 500
+    else:
+        V[:, :, 17] *= 1000.0
+    K, V, q, kn, vn = (x.to(dtype) for x in (K, V, q, kn, vn))
+    cache = hb.H2OCache(1, heads, d, k // 2, k // 2, dtype, device=dev, kv_bits=4)
+    score = torch.rand(1, heads, k, generator=g)
+    cache.prefill_select(K.to(dev), V.to(dev), score.to(dev))
+    out = torch.empty(1, heads, d, dtype=dtype, device=dev)
+    cache.decode_step(q.to(dev), kn.to(dev), vn.to(dev), out)
+    acc = cache.views()[2].cpu()
+    Kd, Vd = dequantised(K), dequantised(V)
+    s = (Kd @ q.double().unsqueeze(-1)).squeeze(-1) * d ** -0.5
+    own = (q.double() * kn.double()).sum(-1, keepdim=True) * d ** -0.5
+    p = torch.softmax(torch.cat([s, own], -1), -1)
+    ref = (p[..., None, :-1] @ Vd).squeeze(-2) + p[..., -1:] * vn.double()
+    # one rounding of the probability to binary32 and one of its sum with the score
+    want = (score.double() + p[..., :-1]).float()
+    hit = (cache.views()[3].cpu() == k)                      # the slot that was given up
+    assert int(hit.sum()) == heads
+    assert bool(((acc.double() - want.double()).abs() <= 1.2e-7 * want.double()).logical_or(hit).all())
+    # probabilities in binary32, then one rounding to the element type
+    tol = {"f32": 3e-7, "f16": 2.0 ** -11 + 3e-7, "bf16": 2.0 ** -8}[dt]
+    size = (p[..., None, :-1] @ Vd.abs()).squeeze(-2) + p[..., -1:] * vn.double().abs()
+    assert bool(((out.cpu().double() - ref).abs() <= tol * size + 1e-9 * size.amax()).all())
+    cache.close()
+
+
+def test_q4_not_finite():
+    """An infinity in the query makes the head's output not a number; other heads are untouched."""
+    from paper_2306_14048_amd import binding as hb
+    dev, d, k = torch.device("cuda:0"), 128, 100
+    g = torch.Generator().manual_seed(1)
+    K, V = (torch.randn(1, 2, k, d, generator=g).half().to(dev) for _ in range(2))
+    q, kn, vn = (torch.randn(1, 2, d, generator=g).half().to(dev) for _ in range(3))
+    q[0, 1, 5] = float("inf")
+    cache = hb.H2OCache(1, 2, d, 50, 50, torch.float16, device=dev, kv_bits=4)
+    cache.prefill_select(K, V, torch.rand(1, 2, k, generator=g).to(dev))
+    out = torch.empty(1, 2, d, dtype=torch.float16, device=dev)
+    cache.decode_step(q, kn, vn, out)
+    assert bool(torch.isfinite(out[0, 0]).all()) and bool(torch.isnan(out[0, 1]).all())
+    cache.close()
