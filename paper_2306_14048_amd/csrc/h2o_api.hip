@@ -154,9 +154,9 @@ int h2o_prefill_colsum(const h2o_config *cfg, const void *Q, const void *K, int3
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
     float *lse = static_cast<float *>(workspace);
     const double scale = h2o_scale_of(*cfg);
-    hipError_t e = h2o_launch_prefill_lse(*cfg, scale, Q, K, n, n, lse, st);
+    hipError_t e = h2o_launch_prefill_lse(*cfg, scale, Q, K, {}, n, n, lse, st);
     if (e != hipSuccess) return H2O_EHIP;
-    e = h2o_launch_prefill_colsum(*cfg, scale, Q, K, n, n, lse, colsum_out, st);
+    e = h2o_launch_prefill_colsum(*cfg, scale, Q, K, {}, n, n, lse, colsum_out, st);
     return hip_rc(e);
 }
 
@@ -232,7 +232,7 @@ int h2o_prefill_attention(const h2o_config *cfg, const void *Q, const void *K, c
     if (ws_bytes < h2o_prefill_attention_workspace_bytes(cfg, n)) return H2O_ENOMEM;
     char *ws = static_cast<char *>(workspace);
     float *lse2 = reinterpret_cast<float *>(ws + align_up(h2o_attn_vcopy_bytes(*cfg, n), 256));
-    return hip_rc(h2o_launch_prefill_attention(*cfg, h2o_scale_of(*cfg), Q, K, V, n, n, ws, lse2,
+    return hip_rc(h2o_launch_prefill_attention(*cfg, h2o_scale_of(*cfg), Q, K, V, {}, {}, n, n, ws, lse2,
                                                lse_out, out, static_cast<hipStream_t>(hip_stream)));
 }
 
@@ -250,7 +250,7 @@ int h2o_prefill_attention_scores(h2o_cache *cache, const void *Q, const void *K,
     const size_t half = h2o_prefill_workspace_bytes(cfg, n) / 2;
     float *lse2 = reinterpret_cast<float *>(ws + align_up(h2o_attn_vcopy_bytes(*cfg, n), 256));
     float *sums = colsum_out ? colsum_out : reinterpret_cast<float *>(reinterpret_cast<char *>(lse2) + half);
-    const hipError_t e = h2o_launch_prefill_colsum(*cfg, h2o_scale_of(*cfg), Q, K, n, n, lse2, sums, st);
+    const hipError_t e = h2o_launch_prefill_colsum(*cfg, h2o_scale_of(*cfg), Q, K, {}, n, n, lse2, sums, st);
     if (e != hipSuccess) return H2O_EHIP;
     return h2o_prefill_select(cache, K, V, sums, n, hip_stream);
 }
@@ -299,15 +299,43 @@ int h2o_prefill_chunk(h2o_cache *cache, const void *Q, const void *K, const void
     char *vcopy = reinterpret_cast<char *>(order) + align_up(heads * (size_t)cache->k * sizeof(int32_t), 256);
     const int ncat = occ + m;
     const double scale = h2o_scale_of(cfg);
-    // after generation steps have evicted, the slots are first put in position order
-    hipError_t e = h2o_launch_concat(*cache, K, V, m, occ, cache->sorted ? nullptr : order, Kcat, Vcat,
-                                     base, pos_cat, st);
+    // Slots in position order: the cached rows are used where they are, in front of the
+    // chunk's, and the compression moves rows inside the cache.  (An output over the
+    // chunk's keys or values, which later passes still read, or a chunk that lies in the
+    // cache itself takes the copying way below.)
+    const size_t cbytes = heads * (size_t)m * cfg.head_dim * cache->esize;
+    auto meet = [](const void *a, size_t na, const void *b, size_t nb) {
+        const char *x = static_cast<const char *>(a), *y = static_cast<const char *>(b);
+        return x < y + nb && y < x + na;
+    };
+    const size_t cache_bytes = layout_of(cfg).total;
+    const bool over = (out && (meet(out, cbytes, K, cbytes) || meet(out, cbytes, V, cbytes))) ||
+                      meet(K, cbytes, cache->K, cache_bytes) || meet(V, cbytes, cache->K, cache_bytes);
+    hipError_t e;
+    if (cache->sorted && !over) {
+        const FrontRows kf{cache->K, occ, cache->k}, vf{cache->V, occ, cache->k};
+        e = out ? h2o_launch_prefill_attention(cfg, scale, Q, K, V, kf, vf, m, ncat, vcopy, lse, nullptr, out, st)
+                : h2o_launch_prefill_lse(cfg, scale, Q, K, kf, m, ncat, lse, st);
+        if (e != hipSuccess) return H2O_EHIP;
+        e = h2o_launch_prefill_colsum(cfg, scale, Q, K, kf, m, ncat, lse, colsum, st);
+        if (e != hipSuccess) return H2O_EHIP;
+        // (an empty cache: nothing to move, and several workgroups may share a head)
+        e = occ == 0 && cache->t == 0
+                ? h2o_launch_select_gather(*cache, K, V, colsum, nullptr, nullptr, m, m, st)
+                : h2o_launch_compact(*cache, K, V, colsum, m, occ, st);
+        if (e != hipSuccess) return H2O_EHIP;
+        cache->t += m;
+        return H2O_OK;
+    }
+    // Else (generation steps have evicted, or the state was restored) cached and chunk
+    // tokens are first copied together, the slots in position order.
+    e = h2o_launch_concat(*cache, K, V, m, occ, cache->sorted ? nullptr : order, Kcat, Vcat, base, pos_cat, st);
     if (e != hipSuccess) return H2O_EHIP;
     // row statistics: a by-product of the attention output when that is wanted
-    e = out ? h2o_launch_prefill_attention(cfg, scale, Q, Kcat, Vcat, m, ncat, vcopy, lse, nullptr, out, st)
-            : h2o_launch_prefill_lse(cfg, scale, Q, Kcat, m, ncat, lse, st);
+    e = out ? h2o_launch_prefill_attention(cfg, scale, Q, Kcat, Vcat, {}, {}, m, ncat, vcopy, lse, nullptr, out, st)
+            : h2o_launch_prefill_lse(cfg, scale, Q, Kcat, {}, m, ncat, lse, st);
     if (e != hipSuccess) return H2O_EHIP;
-    e = h2o_launch_prefill_colsum(cfg, scale, Q, Kcat, m, ncat, lse, colsum, st);
+    e = h2o_launch_prefill_colsum(cfg, scale, Q, Kcat, {}, m, ncat, lse, colsum, st);
     if (e != hipSuccess) return H2O_EHIP;
     e = h2o_launch_select_gather(*cache, Kcat, Vcat, colsum, base, pos_cat, ncat, cache->t + m, st);
     if (e != hipSuccess) return H2O_EHIP;

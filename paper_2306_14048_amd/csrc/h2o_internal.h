@@ -44,12 +44,19 @@ hipError_t h2o_launch_decode_split(const h2o_cache &c, const void *q, const void
 // the same step over a cache that stores 4-bit codes
 hipError_t h2o_launch_decode_q4(const h2o_cache &c, const void *q, const void *k_new,
                                 const void *v_new, void *out, hipStream_t st);
+// Keys (or values) in front of the ones a caller passes: the first `rows` of a head's nk
+// rows sit at front + head * stride * row bytes (the cache), the rest in the caller's
+// array [heads][nk - rows].  {} = none.
+struct FrontRows {
+    const char *front = nullptr;
+    int rows = 0, stride = 0;
+};
 // prompt scoring: the nq queries (rows of Q) are the last nq positions of the nk
 // keys; lse [B*Hh][nq] = log2 of the row normalisers, colsum [B*Hh][nk]
 hipError_t h2o_launch_prefill_lse(const h2o_config &cfg, double scale, const void *Q,
-                                  const void *K, int nq, int nk, float *lse, hipStream_t st);
+                                  const void *K, const FrontRows &Kf, int nq, int nk, float *lse, hipStream_t st);
 hipError_t h2o_launch_prefill_colsum(const h2o_config &cfg, double scale, const void *Q,
-                                     const void *K, int nq, int nk, const float *lse,
+                                     const void *K, const FrontRows &Kf, int nq, int nk, const float *lse,
                                      float *colsum, hipStream_t st);
 // causal attention of nq queries (the last nq of nk key positions) over nk keys: V
 // ([nk][d] per head) is copied to `vcopy` (h2o_attn_vcopy_bytes(cfg, nk) bytes) first if
@@ -58,13 +65,18 @@ hipError_t h2o_launch_prefill_colsum(const h2o_config &cfg, double scale, const 
 // `lse_nat` (nullable) the natural-log row log-sum-exp; 16-bit element types only
 size_t h2o_attn_vcopy_bytes(const h2o_config &cfg, int nk);
 hipError_t h2o_launch_prefill_attention(const h2o_config &cfg, double scale, const void *Q,
-                                        const void *K, const void *V, int nq, int nk, void *vcopy,
-                                        float *lse2, float *lse_nat, void *out, hipStream_t st);
+                                        const void *K, const void *V, const FrontRows &Kf, const FrontRows &Vf,
+                                        int nq, int nk, void *vcopy, float *lse2, float *lse_nat, void *out,
+                                        hipStream_t st);
 // compression of n candidates per head (entry j: position pos_in[j] or j, score
 // base[j] + score[j] or score[j]) into the cache; t_new = tokens seen afterwards
 hipError_t h2o_launch_select_gather(const h2o_cache &c, const void *K, const void *V,
                                     const float *score, const float *base, const int32_t *pos_in,
                                     int n, int t_new, hipStream_t st);
+// compression in place: the n_occ cached tokens (slots in position order) followed by the
+// m tokens Kn, Vn at positions t.. are the candidates, with column sums score[heads][n_occ + m]
+hipError_t h2o_launch_compact(const h2o_cache &c, const void *Kn, const void *Vn, const float *score,
+                              int m, int n_occ, hipStream_t st);
 // the n_occ cached tokens in position order followed by the m chunk tokens as one
 // candidate list; `order` (heads * k ints of scratch) is needed when the slots are
 // not in position order, nullptr when they are

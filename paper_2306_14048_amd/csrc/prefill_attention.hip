@@ -102,10 +102,12 @@ __device__ inline uint2 read_keys4(const unsigned char *lds)
 }
 
 // ---- attention -------------------------------------------------------------------
-template <int DT, int D>
+// TWO: the first kf.rows keys and values of a head sit elsewhere (FrontRows): a tile is
+// copied from one place or the other, and row by row in the one tile that has rows of both.
+template <int DT, int D, bool TWO>
 __global__ __launch_bounds__(ANW * 64, 2) void prefill_attn_kernel(
-    const char *__restrict__ Qg, const char *__restrict__ Kg, const char *__restrict__ Vg, int nq,
-    int nk, int heads, float c2, float *__restrict__ lse2, float *__restrict__ lse_nat,
+    const char *__restrict__ Qg, const char *__restrict__ Kg, const char *__restrict__ Vg,
+    FrontRows kf, FrontRows vf, int nq, int nk, int heads, float c2, float *__restrict__ lse2, float *__restrict__ lse_nat,
     char *__restrict__ Og)
 {
     const int off = nk - nq;               // key position of query 0
@@ -143,8 +145,9 @@ __global__ __launch_bounds__(ANW * 64, 2) void prefill_attn_kernel(
     const int blk = nblk - 1 - idx / HG;
     const int s0 = blk * SROWS;
     const char *Qh = Qg + (size_t)head * nq * ROWB;
-    const char *Kh = Kg + (size_t)head * nk * ROWB;
-    const char *Vh = Vg + (size_t)head * nk * ROWB;
+    const int nf = TWO ? kf.rows : 0;
+    const char *Kh = Kg + (size_t)head * (nk - nf) * ROWB;
+    const char *Vh = Vg + (size_t)head * (nk - nf) * ROWB;
 
     const int srow = s0 + wave * 32 + l32;           // this lane's query
     uint4 st[NF];
@@ -169,8 +172,11 @@ __global__ __launch_bounds__(ANW * 64, 2) void prefill_attn_kernel(
         kchunk[c] = (pos ^ ((r >> RSHK) & KMASKK)) * 16u;
         vchunk[c] = (pos ^ (((r >> VSH) & VMASK) << 2)) * 16u;
     }
-    const i32x4 rsrc_k = make_rsrc(Kh, (unsigned)nk * ROWB);
-    const i32x4 rsrc_v = make_rsrc(Vh, (unsigned)nk * ROWB);
+    const i32x4 rsrc_k = make_rsrc(Kh, (unsigned)(nk - nf) * ROWB);
+    const i32x4 rsrc_v = make_rsrc(Vh, (unsigned)(nk - nf) * ROWB);
+    const i32x4 rsrc_kf = TWO ? make_rsrc(kf.front + (size_t)head * kf.stride * ROWB, (unsigned)nf * ROWB) : rsrc_k;
+    const i32x4 rsrc_vf = TWO ? make_rsrc(vf.front + (size_t)head * vf.stride * ROWB, (unsigned)nf * ROWB) : rsrc_v;
+    const unsigned edge = (unsigned)nf * ROWB;
     const unsigned lds_w = __builtin_amdgcn_readfirstlane(
         (unsigned)reinterpret_cast<size_t>(smem) + wave * 1024);
     const unsigned last_row_off = (unsigned)(nk - 1) * ROWB;
@@ -181,19 +187,31 @@ __global__ __launch_bounds__(ANW * 64, 2) void prefill_attn_kernel(
         const int kt = min(u, T - 1), vt = min(max(u - 1, 0), T - 1);
         const unsigned base = lds_w + stg * STAGE;
         // (rows past the end, only in a ragged last tile, repeat row nk-1: masked)
-        auto tile = [&](const i32x4 &rsrc, int t, const unsigned *chunk, unsigned lds) {
+        auto tile = [&](const i32x4 &rsrc, const i32x4 &rsrc_f, int t, const unsigned *chunk, unsigned lds) {
             const unsigned t0 = (unsigned)t * (ABN * ROWB);
-            if (t0 + ABN * ROWB <= (unsigned)nk * ROWB) {
+            if (TWO && t0 < edge) {
+                if (t0 + ABN * ROWB <= edge) {                 // whole tile in front
 #pragma unroll
-                for (int c = 0; c < CPTK; ++c) dma16(rsrc, koff[c] + chunk[c], t0, lds + c * ANW * 1024);
+                    for (int c = 0; c < CPTK; ++c) dma16(rsrc_f, koff[c] + chunk[c], t0, lds + c * ANW * 1024);
+                } else {                                       // rows of both
+#pragma unroll
+                    for (int c = 0; c < CPTK; ++c) {
+                        const unsigned off = min(t0 + koff[c], last_row_off);
+                        if (off < edge) dma16(rsrc_f, off + chunk[c], 0u, lds + c * ANW * 1024);
+                        else dma16(rsrc, off - edge + chunk[c], 0u, lds + c * ANW * 1024);
+                    }
+                }
+            } else if (t0 + ABN * ROWB <= (unsigned)nk * ROWB) {
+#pragma unroll
+                for (int c = 0; c < CPTK; ++c) dma16(rsrc, koff[c] + chunk[c], t0 - edge, lds + c * ANW * 1024);
             } else {
 #pragma unroll
                 for (int c = 0; c < CPTK; ++c)
-                    dma16(rsrc, min(t0 + koff[c], last_row_off) + chunk[c], 0u, lds + c * ANW * 1024);
+                    dma16(rsrc, min(t0 + koff[c], last_row_off) - edge + chunk[c], 0u, lds + c * ANW * 1024);
             }
         };
-        tile(rsrc_k, kt, kchunk, base);
-        tile(rsrc_v, vt, vchunk, base + TILEK);
+        tile(rsrc_k, rsrc_kf, kt, kchunk, base);
+        tile(rsrc_v, rsrc_vf, vt, vchunk, base + TILEK);
     };
 
     // LDS read offsets.  Key rows are visited so that MFMA row 16a + 8b + 4c + e
@@ -389,22 +407,23 @@ __global__ __launch_bounds__(ANW * 64, 2) void prefill_attn_kernel(
 
 template <int DT, int D>
 hipError_t launch_attn(const h2o_config &cfg, double scale, const void *Q, const void *K,
-                       const void *V, int nq, int nk, void *vcopy, float *lse2, float *lse_nat, void *out,
-                       hipStream_t st)
+                       const void *V, const FrontRows &kf, const FrontRows &vf, int nq, int nk, void *vcopy,
+                       float *lse2, float *lse_nat, void *out, hipStream_t st)
 {
     const int heads = cfg.batch * cfg.heads;
     hipError_t e = hipSuccess;
     // V is read until the last workgroup ends: an output written over it (in place) needs a copy
     const char *v0 = static_cast<const char *>(V), *o0 = static_cast<const char *>(out);
-    const size_t vbytes = (size_t)heads * nk * D * 2, obytes = (size_t)heads * nq * D * 2;
+    const size_t vbytes = (size_t)heads * (nk - vf.rows) * D * 2, obytes = (size_t)heads * nq * D * 2;
     if (v0 < o0 + obytes && o0 < v0 + vbytes) {
         e = hipMemcpyAsync(vcopy, V, vbytes, hipMemcpyDeviceToDevice, st);
         if (e != hipSuccess) return e;
         V = vcopy;
     }
     constexpr size_t smem = (size_t)ANS * 2 * ABN * D * 2;
-    auto kern = prefill_attn_kernel<DT, D>;
-    static bool raised = false;
+    auto kern = kf.rows ? prefill_attn_kernel<DT, D, true> : prefill_attn_kernel<DT, D, false>;
+    static bool raised_for[2] = {false, false};
+    bool &raised = raised_for[kf.rows != 0];
     if (smem > 48 * 1024 && !raised) {
         e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
@@ -415,7 +434,7 @@ hipError_t launch_attn(const h2o_config &cfg, double scale, const void *Q, const
     const float c2 = (float)(scale * 1.4426950408889634);
     hipLaunchKernelGGL(kern, dim3((unsigned)((heads + 63) / 64) * 64 * nblk), dim3(ANW * 64), smem, st,
                        static_cast<const char *>(Q), static_cast<const char *>(K),
-                       static_cast<const char *>(V), nq, nk, heads, c2, lse2, lse_nat,
+                       static_cast<const char *>(V), kf, vf, nq, nk, heads, c2, lse2, lse_nat,
                        static_cast<char *>(out));
     return hipGetLastError();
 }
@@ -429,13 +448,14 @@ size_t h2o_attn_vcopy_bytes(const h2o_config &cfg, int n)
 }
 
 hipError_t h2o_launch_prefill_attention(const h2o_config &cfg, double scale, const void *Q,
-                                        const void *K, const void *V, int nq, int nk, void *vcopy,
-                                        float *lse2, float *lse_nat, void *out, hipStream_t st)
+                                        const void *K, const void *V, const FrontRows &Kf, const FrontRows &Vf,
+                                        int nq, int nk, void *vcopy, float *lse2, float *lse_nat, void *out,
+                                        hipStream_t st)
 {
     const int d = cfg.head_dim;
     if (nq < 1 || nq > nk) return hipErrorInvalidValue;
 #define H2O_ATTN(DT, D) \
-    launch_attn<DT, D>(cfg, scale, Q, K, V, nq, nk, vcopy, lse2, lse_nat, out, st)
+    launch_attn<DT, D>(cfg, scale, Q, K, V, Kf, Vf, nq, nk, vcopy, lse2, lse_nat, out, st)
     if (cfg.dtype == H2O_F16) return d == 64 ? H2O_ATTN(H2O_F16, 64) : H2O_ATTN(H2O_F16, 128);
     return d == 64 ? H2O_ATTN(H2O_BF16, 64) : H2O_ATTN(H2O_BF16, 128);
 #undef H2O_ATTN

@@ -75,10 +75,14 @@ constexpr int NLB = 4;         // row-statistic buffers (pass 2; read one phase 
 // the shape for a full chip.  Four (128 rows, one group, one barrier per tile, the
 // overlap left to the workgroups that share a CU) is for grids that do not fill it:
 // the longest block then has half the work per tile.
-template <int DT, int D, int MB, int NWV, bool COLSUM>
+//
+// The first kf.rows keys of a head may sit elsewhere (FrontRows).  Stationary rows are
+// simply loaded from where they are; streamed ones (pass 1, TWO) are copied tile by tile
+// from one or the other, and row by row in the one tile that has rows of both.
+template <int DT, int D, int MB, int NWV, bool TWO, bool COLSUM>
 __device__ __forceinline__ void prefill_pass(
-    const char *__restrict__ Qg, const char *__restrict__ Kg, int nq, int nk, int heads, float c2,
-    float *__restrict__ lse2, float *__restrict__ colsum)
+    const char *__restrict__ Qg, const char *__restrict__ Kg, const FrontRows &kf, int nq, int nk, int heads,
+    float c2, float *__restrict__ lse2, float *__restrict__ colsum)
 {
     constexpr int ES = DT == H2O_F32 ? 4 : 2;
     constexpr int ROWB = D * ES;          // bytes per row
@@ -137,15 +141,22 @@ __device__ __forceinline__ void prefill_pass(
     // pass 2's first key block sees every query tile
     const int blk = COLSUM ? ord : nblk - 1 - ord;
     const int s0 = blk * SROWS;
-    const char *Sg = (COLSUM ? Kg : Qg) + (size_t)head * ns * ROWB;     // stationary operand
-    const char *Tg = (COLSUM ? Qg : Kg) + (size_t)head * nt * ROWB;     // streamed operand
+    const int nf = kf.rows;                          // keys that sit in front
+    const char *Kh = Kg + (size_t)head * (nk - nf) * ROWB;
+    const char *Kfh = kf.front + (size_t)head * kf.stride * ROWB;
+    const char *Sg = COLSUM ? Kh : Qg + (size_t)head * nq * ROWB;       // stationary operand
+    const char *Tg = COLSUM ? Qg + (size_t)head * nq * ROWB : Kh;       // streamed operand
 
     const int srow = s0 + wave * 32 + l32;           // this lane's stationary row
     // Rows past the end are clamped to the last row (in bounds) and zeroed after arrival.
     uint4 st[NF];
+    {
+        const int r = min(srow, ns - 1);
+        const char *row = !COLSUM ? Sg + (size_t)r * ROWB
+                          : r < nf ? Kfh + (size_t)r * ROWB : Kh + (size_t)(r - nf) * ROWB;
 #pragma unroll
-    for (int f = 0; f < NF; ++f)
-        st[f] = *reinterpret_cast<const uint4 *>(Sg + (size_t)min(srow, ns - 1) * ROWB + (2 * f + half) * 16);
+        for (int f = 0; f < NF; ++f) st[f] = *reinterpret_cast<const uint4 *>(row + (2 * f + half) * 16);
+    }
     if (srow >= ns) {
 #pragma unroll
         for (int f = 0; f < NF; ++f) st[f] = make_uint4(0, 0, 0, 0);
@@ -174,7 +185,8 @@ __device__ __forceinline__ void prefill_pass(
         goff[c] = r * ROWB;
         gchunk[c] = ((pos ^ ((r >> RSH) & KMASK)) * 16u);
     }
-    const i32x4 rsrc = make_rsrc(Tg, (unsigned)nt * ROWB);
+    const i32x4 rsrc = make_rsrc(Tg, (unsigned)(COLSUM ? nt : nt - nf) * ROWB);
+    const i32x4 rsrc_f = make_rsrc(TWO ? Kfh : Tg, TWO ? (unsigned)nf * ROWB : 0u);
     const i32x4 rsrc_lse = make_rsrc(lse2 + (size_t)head * nq, (unsigned)nq * 4u);
     // the low 32 bits of a generic pointer into LDS are the LDS byte offset
     const unsigned lds_w = __builtin_amdgcn_readfirstlane(
@@ -185,14 +197,29 @@ __device__ __forceinline__ void prefill_pass(
     // i = index of the tile in this block's sequence (selects the buffers)
     auto fetch = [&](int tile, int tb, int lb) {
         const unsigned t0 = (unsigned)tile * (BN * ROWB);
-        if (t0 + BN * ROWB <= (unsigned)nt * ROWB) {           // whole tile inside the operand
+        if (TWO && tile * BN < nf) {
+            if (tile * BN + BN <= nf) {                        // whole tile in front
+#pragma unroll
+                for (int c = 0; c < CPT; ++c)
+                    dma16(rsrc_f, goff[c] + gchunk[c], t0, lds_w + tb * TILEB + c * NWV * 1024);
+            } else {                                           // rows of both
+#pragma unroll
+                for (int c = 0; c < CPT; ++c) {
+                    const unsigned off = min(t0 + goff[c], last_row_off), edge = (unsigned)nf * ROWB;
+                    const unsigned to = lds_w + tb * TILEB + c * NWV * 1024;
+                    if (off < edge) dma16(rsrc_f, off + gchunk[c], 0u, to);
+                    else dma16(rsrc, off - edge + gchunk[c], 0u, to);
+                }
+            }
+        } else if (t0 + BN * ROWB <= (unsigned)nt * ROWB) {    // whole tile inside the operand
 #pragma unroll
             for (int c = 0; c < CPT; ++c)
-                dma16(rsrc, goff[c] + gchunk[c], t0, lds_w + tb * TILEB + c * NWV * 1024);
+                dma16(rsrc, goff[c] + gchunk[c], TWO ? t0 - (unsigned)nf * ROWB : t0,
+                      lds_w + tb * TILEB + c * NWV * 1024);
         } else {
 #pragma unroll
             for (int c = 0; c < CPT; ++c)
-                dma16(rsrc, min(t0 + goff[c], last_row_off) + gchunk[c], 0u,
+                dma16(rsrc, min(t0 + goff[c], last_row_off) - (TWO ? (unsigned)nf * ROWB : 0u) + gchunk[c], 0u,
                       lds_w + tb * TILEB + c * NWV * 1024);
         }
         if constexpr (COLSUM) {
@@ -408,23 +435,24 @@ __device__ __forceinline__ void prefill_pass(
 
 template <int DT, int D, int MB, bool COLSUM>
 __global__ __launch_bounds__(8 * 64, 4) void prefill_pass_kernel(
-    const char *__restrict__ Qg, const char *__restrict__ Kg, int nq, int nk, int heads, float c2,
+    const char *__restrict__ Qg, const char *__restrict__ Kg, FrontRows kf, int nq, int nk, int heads, float c2,
     float *__restrict__ lse2, float *__restrict__ colsum)
 {
-    prefill_pass<DT, D, MB, 8, COLSUM>(Qg, Kg, nq, nk, heads, c2, lse2, colsum);
+    prefill_pass<DT, D, MB, 8, false, COLSUM>(Qg, Kg, kf, nq, nk, heads, c2, lse2, colsum);
 }
 
-template <int DT, int D, int MB, bool COLSUM>
+template <int DT, int D, int MB, bool TWO, bool COLSUM>
 __global__ __launch_bounds__(4 * 64, 4) void prefill_pass4_kernel(
-    const char *__restrict__ Qg, const char *__restrict__ Kg, int nq, int nk, int heads, float c2,
+    const char *__restrict__ Qg, const char *__restrict__ Kg, FrontRows kf, int nq, int nk, int heads, float c2,
     float *__restrict__ lse2, float *__restrict__ colsum)
 {
-    prefill_pass<DT, D, MB, 4, COLSUM>(Qg, Kg, nq, nk, heads, c2, lse2, colsum);
+    prefill_pass<DT, D, MB, 4, TWO, COLSUM>(Qg, Kg, kf, nq, nk, heads, c2, lse2, colsum);
 }
 
-template <int DT, int D, int NWV, bool COLSUM>
-hipError_t launch_pass(const h2o_config &cfg, double scale, const void *Q, const void *K, int nq,
-                       int nk, float *lse2, float *colsum, hipStream_t st)
+// TWO: streamed rows in two places (pass 1 with keys in front, four waves)
+template <int DT, int D, int NWV, bool TWO, bool COLSUM>
+hipError_t launch_pass(const h2o_config &cfg, double scale, const void *Q, const void *K, const FrontRows &kf,
+                       int nq, int nk, float *lse2, float *colsum, hipStream_t st)
 {
     constexpr int SROWS = NWV * 32;
     constexpr int ES = DT == H2O_F32 ? 4 : 2;
@@ -434,7 +462,7 @@ hipError_t launch_pass(const h2o_config &cfg, double scale, const void *Q, const
     const int heads = cfg.batch * cfg.heads;
     const int nblk = ((COLSUM ? nk : nq) + SROWS - 1) / SROWS;
     const float c2 = (float)(scale * 1.4426950408889634);
-    auto kern = NWV == 8 ? prefill_pass_kernel<DT, D, MB, COLSUM> : prefill_pass4_kernel<DT, D, MB, COLSUM>;
+    auto kern = NWV == 8 ? prefill_pass_kernel<DT, D, MB, COLSUM> : prefill_pass4_kernel<DT, D, MB, TWO, COLSUM>;
     if (smem > 48 * 1024) {
         static bool raised = false;
         if (!raised) {
@@ -447,14 +475,16 @@ hipError_t launch_pass(const h2o_config &cfg, double scale, const void *Q, const
     hipLaunchKernelGGL(kern,
                        dim3((unsigned)((heads + 63) / 64) * 64 * nblk),
                        dim3(NWV * 64), smem, st, static_cast<const char *>(Q),
-                       static_cast<const char *>(K), nq, nk, heads, c2, lse2, colsum);
+                       static_cast<const char *>(K), kf, nq, nk, heads, c2, lse2, colsum);
     return hipGetLastError();
 }
 
 template <int DT, int D, bool COLSUM>
-hipError_t pick_waves(const h2o_config &cfg, double scale, const void *Q, const void *K, int nq,
-                      int nk, float *lse2, float *colsum, hipStream_t st)
+hipError_t pick_waves(const h2o_config &cfg, double scale, const void *Q, const void *K, const FrontRows &kf,
+                      int nq, int nk, float *lse2, float *colsum, hipStream_t st)
 {
+    if constexpr (!COLSUM)
+        if (kf.rows) return launch_pass<DT, D, 4, true, COLSUM>(cfg, scale, Q, K, kf, nq, nk, lse2, colsum, st);
     // Eight waves pay off when the grid fills the chip several times over with long streams:
     // the line is drawn on blocks x streamed rows.  Both passes, us, eight / four waves:
     //   16-bit, d = 128   32 heads x 512: 26.5 / 19.7, 32 x 1531: 59 / 51, 32 x 4096 (2.1 M):
@@ -466,39 +496,39 @@ hipError_t pick_waves(const h2o_config &cfg, double scale, const void *Q, const 
     const long long blocks8 = (long long)cfg.batch * cfg.heads * (((COLSUM ? nk : nq) + 255) / 256);
     constexpr long long LINE = DT != H2O_F32 && D == 128 ? 3000000 : 16000000;
     if (blocks8 * (COLSUM ? nq : nk) > LINE)
-        return launch_pass<DT, D, 8, COLSUM>(cfg, scale, Q, K, nq, nk, lse2, colsum, st);
-    return launch_pass<DT, D, 4, COLSUM>(cfg, scale, Q, K, nq, nk, lse2, colsum, st);
+        return launch_pass<DT, D, 8, false, COLSUM>(cfg, scale, Q, K, kf, nq, nk, lse2, colsum, st);
+    return launch_pass<DT, D, 4, false, COLSUM>(cfg, scale, Q, K, kf, nq, nk, lse2, colsum, st);
 }
 
 template <bool COLSUM>
-hipError_t dispatch(const h2o_config &cfg, double scale, const void *Q, const void *K, int nq,
-                    int nk, float *lse2, float *colsum, hipStream_t st)
+hipError_t dispatch(const h2o_config &cfg, double scale, const void *Q, const void *K, const FrontRows &kf,
+                    int nq, int nk, float *lse2, float *colsum, hipStream_t st)
 {
     const int d = cfg.head_dim;
     switch (cfg.dtype) {
     case H2O_F32:
-        return d == 64 ? pick_waves<H2O_F32, 64, COLSUM>(cfg, scale, Q, K, nq, nk, lse2, colsum, st)
-                       : pick_waves<H2O_F32, 128, COLSUM>(cfg, scale, Q, K, nq, nk, lse2, colsum, st);
+        return d == 64 ? pick_waves<H2O_F32, 64, COLSUM>(cfg, scale, Q, K, kf, nq, nk, lse2, colsum, st)
+                       : pick_waves<H2O_F32, 128, COLSUM>(cfg, scale, Q, K, kf, nq, nk, lse2, colsum, st);
     case H2O_F16:
-        return d == 64 ? pick_waves<H2O_F16, 64, COLSUM>(cfg, scale, Q, K, nq, nk, lse2, colsum, st)
-                       : pick_waves<H2O_F16, 128, COLSUM>(cfg, scale, Q, K, nq, nk, lse2, colsum, st);
+        return d == 64 ? pick_waves<H2O_F16, 64, COLSUM>(cfg, scale, Q, K, kf, nq, nk, lse2, colsum, st)
+                       : pick_waves<H2O_F16, 128, COLSUM>(cfg, scale, Q, K, kf, nq, nk, lse2, colsum, st);
     default:
-        return d == 64 ? pick_waves<H2O_BF16, 64, COLSUM>(cfg, scale, Q, K, nq, nk, lse2, colsum, st)
-                       : pick_waves<H2O_BF16, 128, COLSUM>(cfg, scale, Q, K, nq, nk, lse2, colsum, st);
+        return d == 64 ? pick_waves<H2O_BF16, 64, COLSUM>(cfg, scale, Q, K, kf, nq, nk, lse2, colsum, st)
+                       : pick_waves<H2O_BF16, 128, COLSUM>(cfg, scale, Q, K, kf, nq, nk, lse2, colsum, st);
     }
 }
 
 }  // namespace
 
 hipError_t h2o_launch_prefill_lse(const h2o_config &cfg, double scale, const void *Q,
-                                  const void *K, int nq, int nk, float *lse, hipStream_t st)
+                                  const void *K, const FrontRows &Kf, int nq, int nk, float *lse, hipStream_t st)
 {
-    return dispatch<false>(cfg, scale, Q, K, nq, nk, lse, nullptr, st);
+    return dispatch<false>(cfg, scale, Q, K, Kf, nq, nk, lse, nullptr, st);
 }
 
 hipError_t h2o_launch_prefill_colsum(const h2o_config &cfg, double scale, const void *Q,
-                                     const void *K, int nq, int nk, const float *lse,
+                                     const void *K, const FrontRows &Kf, int nq, int nk, const float *lse,
                                      float *colsum, hipStream_t st)
 {
-    return dispatch<true>(cfg, scale, Q, K, nq, nk, const_cast<float *>(lse), colsum, st);
+    return dispatch<true>(cfg, scale, Q, K, Kf, nq, nk, const_cast<float *>(lse), colsum, st);
 }

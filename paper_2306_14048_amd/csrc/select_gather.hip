@@ -83,13 +83,20 @@ __device__ inline int block_exclusive_scan(int v, int *scratch)
 // Measured, one workgroup per head and byte digits -> this: 32 heads, 3277 of 16 384
 // tokens, f16 d = 128: 134 -> 45 us (keys in LDS: 54) for 110 MB; 128 heads, 819 of
 // 4096: 42 -> 29 us; 512 heads, 410 of 2048: 48 -> 45 us (a copy's rate: 4.9 TB/s).
-template <int ROWB, int QDT, bool PAT, int KEYS>
+//
+// COMPACT: the cache itself is the front of the candidate list: entries j < n_occ are its
+// slots (in position order, with their scores), the others the tokens Kp, Vp at positions
+// t_new - m + (j - n_occ).  One workgroup per head then moves rows inside the cache: the
+// entry kept in slot s is never in front of it (j >= s), so filling the slots in ascending
+// rounds, every round's reads before its writes, never overwrites what is still to be read.
+// (The list used to be copied together first, rows and all, and gathered back from there:
+// 34 + 26 us per 1024-token chunk at 128 heads x 819 slots.)
+template <int ROWB, int QDT, bool PAT, int KEYS, bool COMPACT>
 __global__ __launch_bounds__(SG_NT) void select_gather_kernel(
     const char *__restrict__ Kp, const char *__restrict__ Vp, const float *__restrict__ score,
     const float *__restrict__ base, const int32_t *__restrict__ pos_in, int n, int t_new,
-    char *__restrict__ Kc, char *__restrict__ Vc, float *__restrict__ acc_g,
-    int32_t *__restrict__ pos_g, int k, int heavy, int recent, int rank, int protect, int stride,
-    int parts, int part_slots)
+    char *Kc, char *Vc, float *acc_g, int32_t *pos_g, int k, int heavy, int recent, int rank, int protect,
+    int stride, int parts, int part_slots, int n_occ)
 {
     extern __shared__ __align__(16) unsigned char smem[];
     int *sel_l = reinterpret_cast<int *>(smem);        // [part_slots] slot -> candidate
@@ -106,8 +113,14 @@ __global__ __launch_bounds__(SG_NT) void select_gather_kernel(
     const int32_t *pin = pos_in ? pos_in + (size_t)head * n : nullptr;
     const size_t hoff = (size_t)head * k;
     // the score of entry j as it will be stored, and its position
-    auto sc_of = [&](int j) { return bs ? bs[j] + sc_in[j] : sc_in[j]; };
-    auto pos_of = [&](int j) { return pin ? pin[j] : j; };
+    auto sc_of = [&](int j) {
+        if constexpr (COMPACT) return (j < n_occ ? acc_g[hoff + j] : 0.f) + sc_in[j];
+        else return bs ? bs[j] + sc_in[j] : sc_in[j];
+    };
+    auto pos_of = [&](int j) {
+        if constexpr (COMPACT) return j < n_occ ? pos_g[hoff + j] : t_new - (n - j);
+        else return pin ? pin[j] : j;
+    };
 
     // what ranks an older token: its score, or (averaged ranking) its score over
     // the n - j prompt queries that scored it
@@ -175,9 +188,9 @@ __global__ __launch_bounds__(SG_NT) void select_gather_kernel(
             const int total = block_sum(cnt, scan_l);
             overflow = total > k;
             want = overflow ? k : k - total;
-        } else if (pin) {
+        } else if (COMPACT || pin) {
             int cnt = 0;
-            for (int j = tid; j < n; j += SG_NT) cnt += pin[j] < t_new - recent;
+            for (int j = tid; j < n; j += SG_NT) cnt += pos_of(j) < t_new - recent;
             older = block_sum(cnt, scan_l);
         }
         auto is_cand = [&](int j) {
@@ -280,6 +293,53 @@ __global__ __launch_bounds__(SG_NT) void select_gather_kernel(
     }
     __syncthreads();
 
+    if constexpr (COMPACT) {
+        // in rounds: reads (waited for, so that no wave's write can pass another's read), a
+        // barrier, writes; the next round reads behind everything written so far
+        constexpr int LPR = ROWB / 16, RPR = SG_NT / LPR, UNR = 8;
+        const int li = tid % LPR, rsub = tid / LPR;
+        for (int s0 = 0; s0 < k; s0 += SG_NT) {
+            const int s = s0 + tid, j = s < k ? sel_l[s] : -1;
+            const int p = j >= 0 ? pos_of(j) : -1;
+            const float a = j >= 0 ? sc_of(j) : 0.f;
+            asm volatile("s_waitcnt vmcnt(0)" ::"v"(p), "v"(a) : "memory");
+            __syncthreads();
+            if (s < k) {
+                pos_g[hoff + s] = p;
+                acc_g[hoff + s] = a;
+            }
+        }
+        const char *Kn = Kp + (size_t)head * (n - n_occ) * ROWB, *Vn = Vp + (size_t)head * (n - n_occ) * ROWB;
+        char *Kh = Kc + hoff * ROWB, *Vh = Vc + hoff * ROWB;
+        for (int s0 = 0; s0 < k; s0 += UNR * RPR) {
+            int j[UNR];
+            uint4 kv[UNR], vv[UNR];
+#pragma unroll
+            for (int u = 0; u < UNR; ++u) {
+                const int s = s0 + u * RPR + rsub;
+                j[u] = s < k ? sel_l[s] : -1;
+                if (j[u] == s && s < n_occ) j[u] = -1;         // stays where it is
+                const size_t off = (size_t)(j[u] < n_occ ? max(j[u], 0) : j[u] - n_occ) * ROWB + li * 16;
+                kv[u] = *reinterpret_cast<const uint4 *>((j[u] < n_occ ? Kh : Kn) + off);
+                vv[u] = *reinterpret_cast<const uint4 *>((j[u] < n_occ ? Vh : Vn) + off);
+            }
+#pragma unroll
+            for (int u = 0; u < UNR; ++u)
+                asm volatile("" : "+v"(kv[u].x), "+v"(kv[u].y), "+v"(kv[u].z), "+v"(kv[u].w), "+v"(vv[u].x),
+                             "+v"(vv[u].y), "+v"(vv[u].z), "+v"(vv[u].w));
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            __syncthreads();
+#pragma unroll
+            for (int u = 0; u < UNR; ++u) {
+                const int s = s0 + u * RPR + rsub;
+                if (j[u] >= 0) {
+                    *reinterpret_cast<uint4 *>(Kh + (size_t)s * ROWB + li * 16) = kv[u];
+                    *reinterpret_cast<uint4 *>(Vh + (size_t)s * ROWB + li * 16) = vv[u];
+                }
+            }
+        }
+        return;
+    }
     // bookkeeping of this workgroup's slots
     for (int s = sb + tid; s < se; s += SG_NT) {
         const int j = sel_l[s - sb];
@@ -380,16 +440,20 @@ hipError_t h2o_launch_mark_free(const h2o_cache &c, hipStream_t st)
     return hipGetLastError();
 }
 
-hipError_t h2o_launch_select_gather(const h2o_cache &c, const void *K, const void *V,
-                                    const float *score, const float *base, const int32_t *pos_in,
-                                    int n, int t_new, hipStream_t st)
+namespace {
+
+// Launches the compression of n candidates per head.  COMPACT: see the kernel (16-bit and
+// binary32 storage only: a chunked prompt is refused on a 4-bit cache).
+template <bool COMPACT>
+hipError_t launch_select(const h2o_cache &c, const void *K, const void *V, const float *score, const float *base,
+                         const int32_t *pos_in, int n, int t_new, int n_occ, hipStream_t st)
 {
     const int heads = c.cfg.batch * c.cfg.heads;
     const int rowb = c.cfg.head_dim * c.esize;
     const char *Kp = static_cast<const char *>(K), *Vp = static_cast<const char *>(V);
     // Workgroups per head: enough to give every CU two, but at least 32 slots each
     // (one round of the row copy).
-    int parts = (2 * 256 + heads - 1) / heads;
+    int parts = COMPACT ? 1 : (2 * 256 + heads - 1) / heads;
     if (const int most = (c.k + 31) / 32; parts > most) parts = most;
     const int part_slots = (c.k + parts - 1) / parts;
     parts = (c.k + part_slots - 1) / part_slots;
@@ -410,13 +474,13 @@ hipError_t h2o_launch_select_gather(const h2o_cache &c, const void *K, const voi
         }
         hipLaunchKernelGGL(kern, dim3((unsigned)heads * parts), dim3(SG_NT), smem, st, Kp, Vp, score, base,
                            pos_in, n, t_new, c.K, c.V, c.acc, c.pos, c.k, c.cfg.heavy, c.cfg.recent,
-                           c.cfg.rank, c.cfg.protect, c.cfg.stride, parts, part_slots);
+                           c.cfg.rank, c.cfg.protect, c.cfg.stride, parts, part_slots, n_occ);
         return hipGetLastError();
     };
 #define H2O_SG1(RB, QDT, PAT, KEYS)                                                             \
     do {                                                                                        \
         static bool raised = false;                                                             \
-        return launch(select_gather_kernel<RB, QDT, PAT, KEYS>, raised);                        \
+        return launch(select_gather_kernel<RB, QDT, PAT, KEYS, COMPACT>, raised);               \
     } while (0)
 #define H2O_SG(RB, QDT)                                                                         \
     do {                                                                                        \
@@ -427,12 +491,14 @@ hipError_t h2o_launch_select_gather(const h2o_cache &c, const void *K, const voi
         if (keys == SG_KEYS_LDS) H2O_SG1(RB, QDT, true, SG_KEYS_LDS);                           \
         H2O_SG1(RB, QDT, true, SG_KEYS_NONE);                                                   \
     } while (0)
-    if (c.cfg.kv_bits == 4) {
-        const int d = c.cfg.head_dim;
-        switch (c.cfg.dtype) {
-        case H2O_F32: if (d == 64) H2O_SG(256, H2O_F32); else H2O_SG(512, H2O_F32); break;
-        case H2O_F16: if (d == 64) H2O_SG(128, H2O_F16); else H2O_SG(256, H2O_F16); break;
-        default: if (d == 64) H2O_SG(128, H2O_BF16); else H2O_SG(256, H2O_BF16); break;
+    if constexpr (!COMPACT) {
+        if (c.cfg.kv_bits == 4) {
+            const int d = c.cfg.head_dim;
+            switch (c.cfg.dtype) {
+            case H2O_F32: if (d == 64) H2O_SG(256, H2O_F32); else H2O_SG(512, H2O_F32); break;
+            case H2O_F16: if (d == 64) H2O_SG(128, H2O_F16); else H2O_SG(256, H2O_F16); break;
+            default: if (d == 64) H2O_SG(128, H2O_BF16); else H2O_SG(256, H2O_BF16); break;
+            }
         }
     }
     switch (rowb) {
@@ -443,6 +509,21 @@ hipError_t h2o_launch_select_gather(const h2o_cache &c, const void *K, const voi
     }
 #undef H2O_SG
 #undef H2O_SG1
+}
+
+}  // namespace
+
+hipError_t h2o_launch_select_gather(const h2o_cache &c, const void *K, const void *V,
+                                    const float *score, const float *base, const int32_t *pos_in,
+                                    int n, int t_new, hipStream_t st)
+{
+    return launch_select<false>(c, K, V, score, base, pos_in, n, t_new, 0, st);
+}
+
+hipError_t h2o_launch_compact(const h2o_cache &c, const void *Kn, const void *Vn, const float *score, int m,
+                              int n_occ, hipStream_t st)
+{
+    return launch_select<true>(c, Kn, Vn, score, nullptr, nullptr, n_occ + m, c.t + m, n_occ, st);
 }
 
 // ---- cache + chunk -> one candidate list per head ---------------------------------
