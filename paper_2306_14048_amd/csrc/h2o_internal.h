@@ -90,6 +90,29 @@ hipError_t h2o_launch_rolled_positions(const h2o_cache &c, int32_t *rolled, hipS
 // flags[B*Hh]: 0 for a head whose bookkeeping is consistent, else a bit mask (h2o.h)
 hipError_t h2o_launch_validate(const h2o_cache &c, int32_t *flags, hipStream_t st);
 
+// The prompt kernels hand out workgroups as (head, block) with a head on one XCD: 8 XCDs take
+// head groups of 8 * hg heads, hg at most 8 and no larger than the heads need (a grid padded to
+// whole groups of 64 heads made 8 heads wait behind seven times as many empty workgroups).
+static __host__ __device__ inline int head_group(int heads) { return heads >= 64 ? 8 : (heads + 7) / 8; }
+static inline long long head_slots(int heads)
+{
+    const int step = 8 * head_group(heads);
+    return (long long)(heads + step - 1) / step * step;
+}
+
+// Whether two groups of four waves share a block of 128 rows and halve its streamed rows (one
+// workgroup per CU then, instead of two or three): while blocks leave CUs idle, and the
+// stream is long enough to be worth joining two parts.  Both scoring passes / attention, f16,
+// d = 128, us, one -> two groups: 8 heads x 1024 31 -> 26 / 25 -> 21, 8 x 4096 101 -> 80 / 83 -> 67,
+// 32 x 1531 (384 blocks) 47 -> 40 / 40 -> 34, 32 x 2048 (512) 63 -> 57 / 57 -> 52; past the line:
+// 32 x 300 15.8 -> 15.8 / 10.4 -> 11.0, 128 x 300 (384) 19 -> 23 / 16 -> 20, 128 x 512 (512) 30 -> 30 /
+// 25 -> 26, 32 x 3000 (768) 110 -> 123 / 95 -> 106.
+static inline bool two_groups(int heads, int rows, int streamed)
+{
+    const long long blocks = (long long)heads * ((rows + 127) / 128);
+    return streamed >= 480 && blocks <= (streamed >= 1500 ? 512 : 384);
+}
+
 // ---- element types ----------------------------------------------------------
 // Raw storage views: f32 -> float, f16 -> _Float16, bf16 -> uint16_t bit pattern.
 template <int DT> struct Elem;

@@ -88,7 +88,7 @@ __device__ inline float other_half(float x)
     return __uint_as_float(r[0] == own ? r[1] : r[0]);
 }
 
-constexpr int ANW = 4;       // waves per workgroup
+constexpr int ARW = 4;       // waves over a workgroup's rows
 constexpr int ANS = 2;       // stages (key tile + value tile each); copies run one tile ahead
 constexpr int ABN = 64;      // keys per tile
 
@@ -104,8 +104,12 @@ __device__ inline uint2 read_keys4(const unsigned char *lds)
 // ---- attention -------------------------------------------------------------------
 // TWO: the first kf.rows keys and values of a head sit elsewhere (FrontRows): a tile is
 // copied from one place or the other, and row by row in the one tile that has rows of both.
-template <int DT, int D, bool TWO>
-__global__ __launch_bounds__(ANW * 64, 2) void prefill_attn_kernel(
+//
+// G: groups of four waves over the same 128 queries.  With two, a tile is 128 keys and each
+// group takes 64 of them; the two partial results are joined at the end.  For grids that
+// leave CUs idle: the longest block has half the steps.
+template <int DT, int D, bool TWO, int G>
+__global__ __launch_bounds__(ARW * G * 64, 2) void prefill_attn_kernel(
     const char *__restrict__ Qg, const char *__restrict__ Kg, const char *__restrict__ Vg,
     FrontRows kf, FrontRows vf, int nq, int nk, int heads, float c2, float *__restrict__ lse2, float *__restrict__ lse_nat,
     char *__restrict__ Og)
@@ -116,7 +120,9 @@ __global__ __launch_bounds__(ANW * 64, 2) void prefill_attn_kernel(
     constexpr int MB = ABN / 32;           // 32-key blocks per tile
     constexpr int NDB = D / 32;            // 32-dim blocks of the output
     constexpr int KS = ABN / 16;           // MFMA steps of the second product per tile
-    constexpr int TILEK = ABN * ROWB;      // key tile bytes
+    constexpr int ANW = ARW * G;           // waves per workgroup
+    constexpr int SBN = ABN * G;           // keys per tile, all groups
+    constexpr int TILEK = SBN * ROWB;      // key tile bytes
     constexpr int STAGE = 2 * TILEK;       // key tile + value tile
     // XOR swizzle of 16-byte chunks inside a row (see the scoring passes)
     constexpr int CPRK = ROWB / 16, RSHK = ROWB >= 256 ? 0 : 1, KMASKK = (CPRK < 16 ? CPRK : 16) - 1;
@@ -124,9 +130,9 @@ __global__ __launch_bounds__(ANW * 64, 2) void prefill_attn_kernel(
     // rows x 64 bytes per 32 lanes, which have to fall into four different bank groups.
     constexpr int VSH = ROWB >= 256 ? 0 : 1, VMASK = ROWB >= 256 ? 3 : 1;
     constexpr int NT = ANW * 64;
-    constexpr int SROWS = ANW * 32;
-    constexpr int CPTK = ABN * CPRK / NT;
-    static_assert(ABN * CPRK % NT == 0 && CPTK >= 1, "copy split");
+    constexpr int SROWS = ARW * 32;
+    constexpr int CPTK = SBN * CPRK / NT;
+    static_assert(SBN * CPRK % NT == 0 && CPTK >= 1, "copy split");
 
     extern __shared__ __align__(16) unsigned char smem[];   // [ANS][STAGE]
 
@@ -134,22 +140,23 @@ __global__ __launch_bounds__(ANW * 64, 2) void prefill_attn_kernel(
     // (the wave index as a scalar: branches on it are then uniform for the compiler
     // too, which otherwise keeps a second copy of the accumulators around them)
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int rw = wave % ARW, grp = G > 1 ? wave / ARW : 0;
     const int half = lane >> 5, l32 = lane & 31;
     const int nblk = (nq + SROWS - 1) / SROWS;
     // a head lives on one XCD (one L2); heaviest (last) row blocks first
-    constexpr int HG = 8;
+    const int hg = head_group(heads);
     const int xcd = blockIdx.x & 7, turn = blockIdx.x >> 3;
-    const int group = turn / (HG * nblk), idx = turn % (HG * nblk);
-    const int head = (group * HG + idx % HG) * 8 + xcd;
+    const int group = turn / (hg * nblk), idx = turn % (hg * nblk);
+    const int head = (group * hg + idx % hg) * 8 + xcd;
     if (head >= heads) return;
-    const int blk = nblk - 1 - idx / HG;
+    const int blk = nblk - 1 - idx / hg;
     const int s0 = blk * SROWS;
     const char *Qh = Qg + (size_t)head * nq * ROWB;
     const int nf = TWO ? kf.rows : 0;
     const char *Kh = Kg + (size_t)head * (nk - nf) * ROWB;
     const char *Vh = Vg + (size_t)head * (nk - nf) * ROWB;
 
-    const int srow = s0 + wave * 32 + l32;           // this lane's query
+    const int srow = s0 + rw * 32 + l32;             // this lane's query
     uint4 st[NF];
 #pragma unroll
     for (int f = 0; f < NF; ++f)
@@ -160,7 +167,7 @@ __global__ __launch_bounds__(ANW * 64, 2) void prefill_attn_kernel(
     }
 
     // key tiles of this block (>= 1): up to the one that holds the last query's own key
-    const int T = min((nk + ABN - 1) / ABN, (off + s0 + SROWS + ABN - 1) / ABN);
+    const int T = min((nk + SBN - 1) / SBN, (off + s0 + SROWS + SBN - 1) / SBN);
 
     // copy plan: instruction c of wave w fills LDS chunks [(c*ANW + w)*64, +64)
     unsigned koff[CPTK], kchunk[CPTK], vchunk[CPTK];
@@ -188,9 +195,9 @@ __global__ __launch_bounds__(ANW * 64, 2) void prefill_attn_kernel(
         const unsigned base = lds_w + stg * STAGE;
         // (rows past the end, only in a ragged last tile, repeat row nk-1: masked)
         auto tile = [&](const i32x4 &rsrc, const i32x4 &rsrc_f, int t, const unsigned *chunk, unsigned lds) {
-            const unsigned t0 = (unsigned)t * (ABN * ROWB);
+            const unsigned t0 = (unsigned)t * (SBN * ROWB);
             if (TWO && t0 < edge) {
-                if (t0 + ABN * ROWB <= edge) {                 // whole tile in front
+                if (t0 + SBN * ROWB <= edge) {                 // whole tile in front
 #pragma unroll
                     for (int c = 0; c < CPTK; ++c) dma16(rsrc_f, koff[c] + chunk[c], t0, lds + c * ANW * 1024);
                 } else {                                       // rows of both
@@ -201,7 +208,7 @@ __global__ __launch_bounds__(ANW * 64, 2) void prefill_attn_kernel(
                         else dma16(rsrc, off - edge + chunk[c], 0u, lds + c * ANW * 1024);
                     }
                 }
-            } else if (t0 + ABN * ROWB <= (unsigned)nk * ROWB) {
+            } else if (t0 + SBN * ROWB <= (unsigned)nk * ROWB) {
 #pragma unroll
                 for (int c = 0; c < CPTK; ++c) dma16(rsrc, koff[c] + chunk[c], t0 - edge, lds + c * ANW * 1024);
             } else {
@@ -269,9 +276,9 @@ __global__ __launch_bounds__(ANW * 64, 2) void prefill_attn_kernel(
         constexpr bool MASKED = decltype(masked_tag)::value;
         constexpr bool LAST = decltype(last_tag)::value;
         fetch(u + 1, stg ^ 1);                               // into the stage of iteration u-1
-        const unsigned char *sb = smem + stg * STAGE;
-        const int r0 = u * ABN;
-        const int w0 = s0 + wave * 32;
+        const unsigned char *sb = smem + stg * STAGE + grp * (ABN * ROWB);     // this group's rows of the tiles
+        const int r0 = u * SBN + grp * ABN;
+        const int w0 = s0 + rw * 32;
         // keys r0.. are visible to this wave only if r0 <= its last query
         const bool live = !LAST && (!MASKED || r0 <= off + w0 + 31);
         f32x16 sacc[MB];
@@ -337,9 +344,10 @@ __global__ __launch_bounds__(ANW * 64, 2) void prefill_attn_kernel(
 #pragma unroll
                 for (int v = 0; v < 16; v += 2) mx = fmaxf(fmaxf(mx, sacc[mb][v]), sacc[mb][v + 1]);
             mx = fmaxf(mx, other_half(mx));              // both halves of a query use one reference
-            // mx is finite from the first tile on: key 0 is visible to every query
+            // mx is finite from the first group's first tile on: key 0 is visible to every query
             if (__builtin_amdgcn_ballot_w64(mx > m_run) != 0) {      // rescale only when a maximum moved
                 float alpha = __builtin_amdgcn_exp2f((m_run - mx) * c2);         // 0 on the first tile
+                if (G > 1 && m_run == mx) alpha = 1.f;     // (a query of the second group may have seen no key yet)
                 l_run *= alpha;
                 // in place (written as an instruction so that the branch leaves the
                 // accumulator in the registers it already occupies).  The compiler does
@@ -353,7 +361,7 @@ __global__ __launch_bounds__(ANW * 64, 2) void prefill_attn_kernel(
                         asm volatile("v_mul_f32 %0, %0, %1" : "+v"(oacc[db][v]) : "v"(alpha));
                 m_run = mx;
             }
-            const float nms = -m_run * c2;
+            const float nms = G > 1 && m_run == -INFINITY ? 0.f : -m_run * c2;
             float sum0 = 0.f, sum1 = 0.f;
 #pragma unroll
             for (int mb = 0; mb < MB; ++mb)
@@ -376,10 +384,34 @@ __global__ __launch_bounds__(ANW * 64, 2) void prefill_attn_kernel(
         wg_barrier();
     };
     {
-        const int t_diag0 = min(T, (off + s0 + 1) / ABN);   // tiles every query of the block sees in full
+        const int t_diag0 = min(T, (off + s0 + 1) / SBN);   // tiles every query of the block sees in full
         for (int u = 0; u < t_diag0; ++u) step(u, std::false_type{}, std::false_type{});
         for (int u = t_diag0; u < T; ++u) step(u, std::true_type{}, std::false_type{});
         step(T, std::false_type{}, std::true_type{});
+    }
+
+    // ---- the groups' parts of a query, brought to the larger reference ----------------
+    if constexpr (G > 1) {
+        float *part = reinterpret_cast<float *>(smem) + (size_t)rw * (NDB * 16 + 2) * 64 + lane;   // (stages are done with)
+        if (grp == 1) {
+            part[0] = m_run;
+            part[64] = l_run;
+#pragma unroll
+            for (int db = 0; db < NDB; ++db)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) part[(2 + db * 16 + v) * 64] = oacc[db][v];
+        }
+        wg_barrier();
+        if (grp == 1) return;
+        // (group 0 has key 0: its reference is finite; group 1 may have seen nothing: weight 0)
+        const float m1 = part[0], mx = fmaxf(m_run, m1);
+        const float f0 = __builtin_amdgcn_exp2f((m_run - mx) * c2), f1 = __builtin_amdgcn_exp2f((m1 - mx) * c2);
+        l_run = l_run * f0 + part[64] * f1;
+#pragma unroll
+        for (int db = 0; db < NDB; ++db)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) oacc[db][v] = oacc[db][v] * f0 + part[(2 + db * 16 + v) * 64] * f1;
+        m_run = mx;
     }
 
     // ---- normalise and store ------------------------------------------------------
@@ -405,7 +437,7 @@ __global__ __launch_bounds__(ANW * 64, 2) void prefill_attn_kernel(
     }
 }
 
-template <int DT, int D>
+template <int DT, int D, int G>
 hipError_t launch_attn(const h2o_config &cfg, double scale, const void *Q, const void *K,
                        const void *V, const FrontRows &kf, const FrontRows &vf, int nq, int nk, void *vcopy,
                        float *lse2, float *lse_nat, void *out, hipStream_t st)
@@ -420,8 +452,10 @@ hipError_t launch_attn(const h2o_config &cfg, double scale, const void *Q, const
         if (e != hipSuccess) return e;
         V = vcopy;
     }
-    constexpr size_t smem = (size_t)ANS * 2 * ABN * D * 2;
-    auto kern = kf.rows ? prefill_attn_kernel<DT, D, true> : prefill_attn_kernel<DT, D, false>;
+    constexpr int ANW = ARW * G;
+    constexpr size_t smem = (size_t)ANS * 2 * ABN * G * D * 2;
+    static_assert(G == 1 || smem >= (size_t)ARW * (D / 32 * 16 + 2) * 256, "the stages hold a group's parts");
+    auto kern = kf.rows ? prefill_attn_kernel<DT, D, true, G> : prefill_attn_kernel<DT, D, false, G>;
     static bool raised_for[2] = {false, false};
     bool &raised = raised_for[kf.rows != 0];
     if (smem > 48 * 1024 && !raised) {
@@ -430,9 +464,9 @@ hipError_t launch_attn(const h2o_config &cfg, double scale, const void *Q, const
         if (e != hipSuccess) return e;
         raised = true;
     }
-    const int nblk = (nq + ANW * 32 - 1) / (ANW * 32);
+    const int nblk = (nq + ARW * 32 - 1) / (ARW * 32);
     const float c2 = (float)(scale * 1.4426950408889634);
-    hipLaunchKernelGGL(kern, dim3((unsigned)((heads + 63) / 64) * 64 * nblk), dim3(ANW * 64), smem, st,
+    hipLaunchKernelGGL(kern, dim3((unsigned)head_slots(heads) * nblk), dim3(ANW * 64), smem, st,
                        static_cast<const char *>(Q), static_cast<const char *>(K),
                        static_cast<const char *>(V), kf, vf, nq, nk, heads, c2, lse2, lse_nat,
                        static_cast<char *>(out));
@@ -454,8 +488,10 @@ hipError_t h2o_launch_prefill_attention(const h2o_config &cfg, double scale, con
 {
     const int d = cfg.head_dim;
     if (nq < 1 || nq > nk) return hipErrorInvalidValue;
-#define H2O_ATTN(DT, D) \
-    launch_attn<DT, D>(cfg, scale, Q, K, V, Kf, Vf, nq, nk, vcopy, lse2, lse_nat, out, st)
+    const bool few = two_groups(cfg.batch * cfg.heads, nq, nk);
+#define H2O_ATTN(DT, D)                                                                                   \
+    (few ? launch_attn<DT, D, 2>(cfg, scale, Q, K, V, Kf, Vf, nq, nk, vcopy, lse2, lse_nat, out, st)      \
+         : launch_attn<DT, D, 1>(cfg, scale, Q, K, V, Kf, Vf, nq, nk, vcopy, lse2, lse_nat, out, st))
     if (cfg.dtype == H2O_F16) return d == 64 ? H2O_ATTN(H2O_F16, 64) : H2O_ATTN(H2O_F16, 128);
     return d == 64 ? H2O_ATTN(H2O_BF16, 64) : H2O_ATTN(H2O_BF16, 128);
 #undef H2O_ATTN

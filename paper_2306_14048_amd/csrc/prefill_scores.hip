@@ -79,7 +79,11 @@ constexpr int NLB = 4;         // row-statistic buffers (pass 2; read one phase 
 // The first kf.rows keys of a head may sit elsewhere (FrontRows).  Stationary rows are
 // simply loaded from where they are; streamed ones (pass 1, TWO) are copied tile by tile
 // from one or the other, and row by row in the one tile that has rows of both.
-template <int DT, int D, int MB, int NWV, bool TWO, bool COLSUM>
+//
+// G (four-wave shape): groups of four waves over the same 128 stationary rows.  With two, a
+// tile has twice the rows and each group takes half of them; the parts are joined at the
+// end.  For grids that leave CUs idle: the longest block has half the steps.
+template <int DT, int D, int MB, int RWV, int G, bool TWO, bool COLSUM>
 __device__ __forceinline__ void prefill_pass(
     const char *__restrict__ Qg, const char *__restrict__ Kg, const FrontRows &kf, int nq, int nk, int heads,
     float c2, float *__restrict__ lse2, float *__restrict__ colsum)
@@ -87,7 +91,9 @@ __device__ __forceinline__ void prefill_pass(
     constexpr int ES = DT == H2O_F32 ? 4 : 2;
     constexpr int ROWB = D * ES;          // bytes per row
     constexpr int NF = ROWB / 32;         // 16-byte fragments per row per lane half
-    constexpr int BN = 32 * MB;           // streamed rows per tile
+    constexpr int NWV = RWV * G;          // waves per workgroup
+    constexpr int GN = 32 * MB;           // streamed rows per tile and group
+    constexpr int BN = GN * G;            // streamed rows per tile
     constexpr int LROW = ROWB;            // LDS row pitch (chunks are XOR-swizzled instead of padded)
     constexpr int TILEB = BN * LROW;
     // Swizzle: 16-byte chunk c of tile row r is stored at chunk position
@@ -99,12 +105,12 @@ __device__ __forceinline__ void prefill_pass(
     constexpr int CPR = ROWB / 16;        // 16-byte chunks per row
     constexpr int CHUNKS = BN * CPR;      // 16-byte chunks per tile
     constexpr int NT = NWV * 64;          // threads per workgroup
-    constexpr int SROWS = NWV * 32;       // stationary rows per workgroup
+    constexpr int SROWS = RWV * 32;       // stationary rows per workgroup
     constexpr int CPT = CHUNKS / NT;      // tile-copy instructions per wave per tile
     constexpr int CPF = CPT + (COLSUM ? 1 : 0);   // copy instructions per wave per fetch
     constexpr int LPW = BN / NWV;         // row statistics each wave copies per tile
     static_assert(CHUNKS % NT == 0 && CPT >= 1, "every thread moves the same number of chunks");
-    static_assert(SROWS % BN == 0 && BN % NWV == 0, "tiles divide the workgroup's rows");
+    static_assert(SROWS % BN == 0 && BN % NWV == 0 && LPW <= 64, "tiles divide the workgroup's rows");
 
     extern __shared__ __align__(16) unsigned char smem[];
     unsigned char *tile_l = smem;                                        // [NTB][TILEB]
@@ -114,8 +120,9 @@ __device__ __forceinline__ void prefill_pass(
     // (the wave index as a scalar: branches on it are then uniform for the compiler too)
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int half = lane >> 5, l32 = lane & 31;
-    constexpr bool SKEW = NWV == 8;       // two wave groups one phase apart
+    constexpr bool SKEW = RWV == 8;       // two wave groups one phase apart
     const int grp = SKEW ? wave >> 2 : 0; // ping-pong group
+    const int rw = wave % RWV, part = G > 1 ? wave / RWV : 0;   // its 32 stationary rows, its part of a tile
     // The nq queries are the LAST nq positions of the nk keys (nq == nk for a whole
     // prompt; nq < nk when a chunk of new tokens attends to nk - nq cached tokens in
     // front of it): query row i sits at key position off + i and sees keys <= off + i.
@@ -127,16 +134,16 @@ __device__ __forceinline__ void prefill_pass(
     // has its own L2.  All blocks of a head share the streamed operand, so a head
     // lives on ONE XCD (ids that agree modulo 8) and its blocks run close together
     // in time: the operand is then fetched from HBM about once instead of once
-    // per block.  On an XCD, heads are taken in groups of HG (about as many
+    // per block.  On an XCD, heads are taken in groups of hg (about as many
     // workgroups as the XCD holds at once); inside a group the order is by block
     // weight, heaviest first over all its heads, so that the kernel does not end
     // on a few long blocks.
-    constexpr int HG = 8;
+    const int hg = head_group(heads);
     const int xcd = blockIdx.x & 7, turn = blockIdx.x >> 3;
-    const int group = turn / (HG * nblk), idx = turn % (HG * nblk);
-    const int head = (group * HG + idx % HG) * 8 + xcd;
+    const int group = turn / (hg * nblk), idx = turn % (hg * nblk);
+    const int head = (group * hg + idx % hg) * 8 + xcd;
     if (head >= heads) return;                       // padding of the last head group
-    const int ord = idx / HG;
+    const int ord = idx / hg;
     // heaviest blocks first: pass 1's last row block sees every key tile,
     // pass 2's first key block sees every query tile
     const int blk = COLSUM ? ord : nblk - 1 - ord;
@@ -147,7 +154,7 @@ __device__ __forceinline__ void prefill_pass(
     const char *Sg = COLSUM ? Kh : Qg + (size_t)head * nq * ROWB;       // stationary operand
     const char *Tg = COLSUM ? Qg + (size_t)head * nq * ROWB : Kh;       // streamed operand
 
-    const int srow = s0 + wave * 32 + l32;           // this lane's stationary row
+    const int srow = s0 + rw * 32 + l32;             // this lane's stationary row
     // Rows past the end are clamped to the last row (in bounds) and zeroed after arrival.
     uint4 st[NF];
     {
@@ -193,7 +200,6 @@ __device__ __forceinline__ void prefill_pass(
         (unsigned)reinterpret_cast<size_t>(tile_l) + wave * 1024);
     const unsigned lds_lse = (unsigned)reinterpret_cast<size_t>(lse_l);
     const unsigned last_row_off = (unsigned)(nt - 1) * ROWB;
-    const bool lse_lane = lane / LPW == wave;        // (lane < BN follows from wave < NWV)
     // i = index of the tile in this block's sequence (selects the buffers)
     auto fetch = [&](int tile, int tb, int lb) {
         const unsigned t0 = (unsigned)tile * (BN * ROWB);
@@ -223,9 +229,16 @@ __device__ __forceinline__ void prefill_pass(
                       lds_w + tb * TILEB + c * NWV * 1024);
         }
         if constexpr (COLSUM) {
-            // lane l writes LDS word l of the buffer; statistics past nq read as 0
-            // (end of the descriptor) or as the next head's and are masked later
-            if (lse_lane) dma4(rsrc_lse, (unsigned)lane * 4u, (unsigned)tile * (BN * 4u), lds_lse + lb * (BN * 4));
+            // wave w copies the words [w * LPW, (w + 1) * LPW) of the buffer; statistics past
+            // nq read as 0 (end of the descriptor) and are masked later
+            // (two groups: clamped to the last one, a tile reaches twice as far)
+            const unsigned to = lds_lse + lb * (BN * 4) + wave * (LPW * 4);
+            if (lane < LPW) {
+                if constexpr (G > 1)
+                    dma4(rsrc_lse, (unsigned)min(tile * BN + wave * LPW + lane, nq - 1) * 4u, 0u, to);
+                else
+                    dma4(rsrc_lse, (unsigned)(wave * LPW + lane) * 4u, (unsigned)tile * (BN * 4u), to);
+            }
         }
     };
 
@@ -268,15 +281,15 @@ __device__ __forceinline__ void prefill_pass(
         constexpr bool MASKED = decltype(masked_tag)::value;
         const int tb2 = tb == 0 ? NTB - 1 : tb - 1;               // (tb + 2) % 3
         fetch(min(tile + 2, t_end - 1), tb2, (lb + 2) & (NLB - 1));
-        const int r0 = tile * BN;
-        const int w0 = s0 + wave * 32;            // first stationary row of this wave
+        const int r0 = tile * BN + part * GN;     // first row of this wave's part of the tile
+        const int w0 = s0 + rw * 32;              // first stationary row of this wave
         // pass 1: keys r0.. are visible to the queries at positions >= r0; pass 2:
         // the queries up to position off+r0+BN-1 see the keys up to there
-        const bool live = !MASKED || (COLSUM ? off + r0 + BN - 1 >= w0 : r0 <= off + w0 + 31);
+        const bool live = !MASKED || (COLSUM ? off + r0 + GN - 1 >= w0 : r0 <= off + w0 + 31);
         // Of the tiles that touch the block's diagonal, a wave's own 32 rows straddle
         // only one; those in front of it are fully visible to the wave and need no
         // mask arithmetic (wave-uniform test).
-        const bool clear = COLSUM ? (off + r0 >= w0 + 31 && r0 + BN <= nq) : (r0 + BN - 1 <= off + w0);
+        const bool clear = COLSUM ? (off + r0 >= w0 + 31 && r0 + GN <= nq) : (r0 + GN - 1 <= off + w0);
         f32x16 acc[MB];
         if (live) {
             __builtin_amdgcn_s_setprio(2);
@@ -284,7 +297,7 @@ __device__ __forceinline__ void prefill_pass(
             for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
                 for (int v = 0; v < 16; ++v) acc[mb][v] = 0.f;
-            const unsigned char *tbp = tile_l + tb * TILEB;
+            const unsigned char *tbp = tile_l + tb * TILEB + part * (GN * LROW);
             auto fragment = [&](int f, int mb) {
                 const int row = mb * 32 + l32;
                 return *reinterpret_cast<const uint4 *>(
@@ -363,7 +376,7 @@ __device__ __forceinline__ void prefill_pass(
             } else {
                 // streamed rows are queries i (at position off + i), this lane's row is
                 // key j = srow: need j <= off + i, i < nq
-                const float *ll = lse_l + lb * BN;
+                const float *ll = lse_l + lb * BN + part * GN;
                 float sum0 = 0.f, sum1 = 0.f;
 #pragma unroll
                 for (int mb = 0; mb < MB; ++mb)
@@ -421,6 +434,22 @@ __device__ __forceinline__ void prefill_pass(
     if (SKEW && grp == 0) wg_barrier();    // the barrier the second group spent at the start
     dma_wait_upto<0>();                    // trailing repeat requests land before the LDS is released
 
+    if constexpr (G > 1) {
+        // the second group's part of every row (the tiles are done with)
+        float2 *join = reinterpret_cast<float2 *>(smem) + rw * 64 + lane;
+        wg_barrier();
+        if (part == 1) *join = COLSUM ? make_float2(c_run, 0.f) : make_float2(m_run, l_run);
+        wg_barrier();
+        if (part == 1) return;
+        const float2 o = *join;
+        if constexpr (COLSUM) {
+            c_run += o.x;
+        } else {
+            const float M = fmaxf(m_run, o.x), ms = M == -INFINITY ? 0.f : M;     // (a lane half may have seen no key)
+            l_run = l_run * __builtin_amdgcn_exp2f((m_run - ms) * c2) + o.y * __builtin_amdgcn_exp2f((o.x - ms) * c2);
+            m_run = M;
+        }
+    }
     if constexpr (!COLSUM) {
         const float m2 = __shfl_xor(m_run, 32, 64), l2 = __shfl_xor(l_run, 32, 64);
         const float M = fmaxf(m_run, m2);            // finite: key 0 is visible to every query
@@ -438,31 +467,31 @@ __global__ __launch_bounds__(8 * 64, 4) void prefill_pass_kernel(
     const char *__restrict__ Qg, const char *__restrict__ Kg, FrontRows kf, int nq, int nk, int heads, float c2,
     float *__restrict__ lse2, float *__restrict__ colsum)
 {
-    prefill_pass<DT, D, MB, 8, false, COLSUM>(Qg, Kg, kf, nq, nk, heads, c2, lse2, colsum);
+    prefill_pass<DT, D, MB, 8, 1, false, COLSUM>(Qg, Kg, kf, nq, nk, heads, c2, lse2, colsum);
 }
 
-template <int DT, int D, int MB, bool TWO, bool COLSUM>
-__global__ __launch_bounds__(4 * 64, 4) void prefill_pass4_kernel(
+template <int DT, int D, int MB, int G, bool TWO, bool COLSUM>
+__global__ __launch_bounds__(4 * G * 64, G == 1 ? 4 : 2) void prefill_pass4_kernel(
     const char *__restrict__ Qg, const char *__restrict__ Kg, FrontRows kf, int nq, int nk, int heads, float c2,
     float *__restrict__ lse2, float *__restrict__ colsum)
 {
-    prefill_pass<DT, D, MB, 4, TWO, COLSUM>(Qg, Kg, kf, nq, nk, heads, c2, lse2, colsum);
+    prefill_pass<DT, D, MB, 4, G, TWO, COLSUM>(Qg, Kg, kf, nq, nk, heads, c2, lse2, colsum);
 }
 
 // TWO: streamed rows in two places (pass 1 with keys in front, four waves)
-template <int DT, int D, int NWV, bool TWO, bool COLSUM>
+template <int DT, int D, int RWV, int G, bool TWO, bool COLSUM>
 hipError_t launch_pass(const h2o_config &cfg, double scale, const void *Q, const void *K, const FrontRows &kf,
                        int nq, int nk, float *lse2, float *colsum, hipStream_t st)
 {
-    constexpr int SROWS = NWV * 32;
+    constexpr int SROWS = RWV * 32, NWV = RWV * G;
     constexpr int ES = DT == H2O_F32 ? 4 : 2;
-    constexpr int MB = (D * ES >= 512) ? 1 : 2;      // keep the two tile buffers under 48 KiB
-    constexpr int BN = 32 * MB;
+    constexpr int MB = (D * ES >= 512) ? 1 : 2;      // keep a group's tile buffers at 48 KiB
+    constexpr int BN = 32 * MB * G;
     constexpr size_t smem = NTB * (size_t)BN * (D * ES) + NLB * BN * sizeof(float);
     const int heads = cfg.batch * cfg.heads;
     const int nblk = ((COLSUM ? nk : nq) + SROWS - 1) / SROWS;
     const float c2 = (float)(scale * 1.4426950408889634);
-    auto kern = NWV == 8 ? prefill_pass_kernel<DT, D, MB, COLSUM> : prefill_pass4_kernel<DT, D, MB, TWO, COLSUM>;
+    auto kern = RWV == 8 ? prefill_pass_kernel<DT, D, MB, COLSUM> : prefill_pass4_kernel<DT, D, MB, G, TWO, COLSUM>;
     if (smem > 48 * 1024) {
         static bool raised = false;
         if (!raised) {
@@ -473,7 +502,7 @@ hipError_t launch_pass(const h2o_config &cfg, double scale, const void *Q, const
         }
     }
     hipLaunchKernelGGL(kern,
-                       dim3((unsigned)((heads + 63) / 64) * 64 * nblk),
+                       dim3((unsigned)head_slots(heads) * nblk),
                        dim3(NWV * 64), smem, st, static_cast<const char *>(Q),
                        static_cast<const char *>(K), kf, nq, nk, heads, c2, lse2, colsum);
     return hipGetLastError();
@@ -483,8 +512,11 @@ template <int DT, int D, bool COLSUM>
 hipError_t pick_waves(const h2o_config &cfg, double scale, const void *Q, const void *K, const FrontRows &kf,
                       int nq, int nk, float *lse2, float *colsum, hipStream_t st)
 {
+    const bool few = two_groups(cfg.batch * cfg.heads, COLSUM ? nk : nq, COLSUM ? nq : nk);
     if constexpr (!COLSUM)
-        if (kf.rows) return launch_pass<DT, D, 4, true, COLSUM>(cfg, scale, Q, K, kf, nq, nk, lse2, colsum, st);
+        if (kf.rows)
+            return few ? launch_pass<DT, D, 4, 2, true, COLSUM>(cfg, scale, Q, K, kf, nq, nk, lse2, colsum, st)
+                       : launch_pass<DT, D, 4, 1, true, COLSUM>(cfg, scale, Q, K, kf, nq, nk, lse2, colsum, st);
     // Eight waves pay off when the grid fills the chip several times over with long streams:
     // the line is drawn on blocks x streamed rows.  Both passes, us, eight / four waves:
     //   16-bit, d = 128   32 heads x 512: 26.5 / 19.7, 32 x 1531: 59 / 51, 32 x 4096 (2.1 M):
@@ -496,8 +528,9 @@ hipError_t pick_waves(const h2o_config &cfg, double scale, const void *Q, const 
     const long long blocks8 = (long long)cfg.batch * cfg.heads * (((COLSUM ? nk : nq) + 255) / 256);
     constexpr long long LINE = DT != H2O_F32 && D == 128 ? 3000000 : 16000000;
     if (blocks8 * (COLSUM ? nq : nk) > LINE)
-        return launch_pass<DT, D, 8, false, COLSUM>(cfg, scale, Q, K, kf, nq, nk, lse2, colsum, st);
-    return launch_pass<DT, D, 4, false, COLSUM>(cfg, scale, Q, K, kf, nq, nk, lse2, colsum, st);
+        return launch_pass<DT, D, 8, 1, false, COLSUM>(cfg, scale, Q, K, kf, nq, nk, lse2, colsum, st);
+    return few ? launch_pass<DT, D, 4, 2, false, COLSUM>(cfg, scale, Q, K, kf, nq, nk, lse2, colsum, st)
+               : launch_pass<DT, D, 4, 1, false, COLSUM>(cfg, scale, Q, K, kf, nq, nk, lse2, colsum, st);
 }
 
 template <bool COLSUM>

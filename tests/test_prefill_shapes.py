@@ -19,6 +19,8 @@ ROW_TOL = {"f16": 2 * 2.0 ** -11, "bf16": 2 * 2.0 ** -8}
     ("bf16", 128, 64, 2999),                                                  # four waves, just below
     ("f16", 128, 3, 1), ("f16", 64, 3, 127), ("bf16", 128, 9, 128), ("f16", 128, 2, 129),
     ("f32", 64, 2, 130), ("f32", 128, 2, 257), ("bf16", 64, 2, 513),
+    ("f16", 128, 8, 1100), ("bf16", 128, 12, 1531), ("bf16", 64, 8, 1029), ("f16", 64, 3, 480),   # two groups
+    ("f32", 128, 4, 900), ("f32", 64, 5, 1027), ("f16", 128, 2, 641), ("f16", 128, 17, 479),
 ])
 def test_column_sums_and_rows(dt, d, heads, n):
     from paper_2306_14048_amd import binding as hb, synth
