@@ -18,7 +18,7 @@ constexpr int SG_NT = 512;
 constexpr int SG_NW = SG_NT / 64;
 constexpr int SG_BITS = 11;                 // radix digit: 11 + 11 + 10 bits
 constexpr int SG_BINS = 1 << SG_BITS;
-constexpr int SG_LDS_KEYS = 30720;          // ranking keys kept in LDS up to this many candidates (120 KiB)
+constexpr int SG_LDS_KEYS = 28672;          // ranking keys kept in LDS up to this many candidates (112 KiB)
 // where the ranking keys live during the selection
 constexpr int SG_KEYS_NONE = 0, SG_KEYS_LDS = 1;   // (any larger value: that many registers per thread)
 
@@ -43,24 +43,16 @@ __device__ inline int block_sum(int v, int *scratch)
     return tot;
 }
 
-// Exclusive prefix sum of one int per thread over the workgroup.  `scratch` holds SG_NW ints.
-__device__ inline int block_exclusive_scan(int v, int *scratch)
+// Inclusive prefix sum over the lanes of a wave.
+__device__ inline unsigned wave_inclusive_scan(unsigned v)
 {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    int inc = v;
+    const int lane = threadIdx.x & 63;
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) {
-        const int y = __shfl_up(inc, o, 64);
-        if (lane >= o) inc += y;
+        const unsigned y = (unsigned)__shfl_up((int)v, o, 64);
+        if (lane >= o) v += y;
     }
-    __syncthreads();                       // scratch may still be read from a previous scan
-    if (lane == 63) scratch[wave] = inc;
-    __syncthreads();
-    int base = 0;
-#pragma unroll
-    for (int w = 0; w < SG_NW; ++w)
-        if (w < wave) base += scratch[w];
-    return base + inc - v;
+    return v;
 }
 
 // Entry j of a head's n candidates is the token at position pos_in[j] (ascending;
@@ -80,9 +72,11 @@ __device__ inline int block_exclusive_scan(int v, int *scratch)
 // from ballots; the ranking keys are formed once and kept in KEYS registers per
 // thread (all reads in flight at once, no LDS latency in the sweeps), in LDS for
 // longer prompts, and beyond SG_LDS_KEYS candidates formed again for every sweep.
-// Measured, one workgroup per head and byte digits -> this: 32 heads, 3277 of 16 384
-// tokens, f16 d = 128: 134 -> 45 us (keys in LDS: 54) for 110 MB; 128 heads, 819 of
-// 4096: 42 -> 29 us; 512 heads, 410 of 2048: 48 -> 45 us (a copy's rate: 4.9 TB/s).
+// The selection is issue-bound (every workgroup makes all of it), hence the keys that carry
+// their kind and the digits that cost one barrier each.  Measured, one workgroup per head
+// and byte digits -> this: 32 heads, 3277 of 16 384 tokens, f16 d = 128: 134 -> 37 us for
+// 110 MB (keys in LDS: 54; kinds tested per entry, five barriers per digit: 45); 128 heads,
+// 819 of 4096: 42 -> 29 us; 512 heads, 410 of 2048: 48 -> 44 us (a copy's rate: 5.0 TB/s).
 //
 // COMPACT: the cache itself is the front of the candidate list: entries j < n_occ are its
 // slots (in position order, with their scores), the others the tokens Kp, Vp at positions
@@ -92,7 +86,7 @@ __device__ inline int block_exclusive_scan(int v, int *scratch)
 // (The list used to be copied together first, rows and all, and gathered back from there:
 // 34 + 26 us per 1024-token chunk at 128 heads x 819 slots.)
 template <int ROWB, int QDT, bool PAT, int KEYS, bool COMPACT>
-__global__ __launch_bounds__(SG_NT) void select_gather_kernel(
+__global__ __launch_bounds__(SG_NT, 4) void select_gather_kernel(
     const char *__restrict__ Kp, const char *__restrict__ Vp, const float *__restrict__ score,
     const float *__restrict__ base, const int32_t *__restrict__ pos_in, int n, int t_new,
     char *Kc, char *Vc, float *acc_g, int32_t *pos_g, int k, int heavy, int recent, int rank, int protect,
@@ -101,8 +95,7 @@ __global__ __launch_bounds__(SG_NT) void select_gather_kernel(
     extern __shared__ __align__(16) unsigned char smem[];
     int *sel_l = reinterpret_cast<int *>(smem);        // [part_slots] slot -> candidate
     unsigned *key_l = reinterpret_cast<unsigned *>(sel_l + part_slots);   // [n] (SG_KEYS_LDS)
-    __shared__ unsigned hist[SG_BINS];
-    __shared__ unsigned sh_prefix, sh_need;
+    __shared__ __align__(16) unsigned hist[3][SG_BINS];      // one per digit
     __shared__ int scan_l[2 * SG_NW];
 
     const int head = blockIdx.x / parts, tid = threadIdx.x;
@@ -133,43 +126,49 @@ __global__ __launch_bounds__(SG_NT) void select_gather_kernel(
     const int j0 = min(n, wave * run), j1 = min(n, j0 + run);
     constexpr bool IN_REGS = KEYS > SG_KEYS_LDS;
     unsigned key_r[IN_REGS ? KEYS : 1];
-    // f(entry, its key) for every entry of the wave's run, one per lane, ascending; lanes
-    // past the run's end get entry n
+    // what an entry is (set once the candidates are known): see below
+    struct { int older; bool overflow; } kinds = {0, false};
+    auto kind_of = [&](int j, unsigned key) -> unsigned {
+        if constexpr (PAT) {
+            const bool cov = j < n && is_protected(pos_of(j), t_new - 1, recent, protect, stride);
+            return cov == kinds.overflow ? key : cov ? ~0u : 0u;
+        } else {
+            return j < kinds.older ? key : ~0u;
+        }
+    };
+    // f(entry, its key) for every entry of the wave's run, one per lane, ascending.  A key
+    // also says what the entry is: KEY_OUT = none (past the run's end, or not to be kept),
+    // KEY_SURE = kept outright, any other value = a candidate, so that the sweeps test
+    // nothing but the key.
+    constexpr unsigned KEY_OUT = 0u, KEY_SURE = ~0u;
+    auto candidate_key = [&](float v, int j) {
+        return min(max(order_key(ranked(v, j)), 1u), KEY_SURE - 1u);   // (the ends are NaNs)
+    };
     auto sweep = [&](auto f) {
         if constexpr (IN_REGS) {
 #pragma unroll
             for (int i = 0; i < KEYS; ++i) {
                 if (j0 + i * 64 >= j1) break;          // wave-uniform
-                const int j = j0 + i * 64 + lane;
-                f(j < j1 ? j : n, key_r[i]);
+                f(j0 + i * 64 + lane, key_r[i]);
             }
         } else {
             for (int b = j0; b < j1; b += 64) {
                 const int j = b + lane;
-                unsigned key = 0;
+                unsigned key = KEY_OUT;
                 if (j < j1) {
                     if constexpr (KEYS == SG_KEYS_LDS) key = key_l[j];
-                    else key = order_key(ranked(sc_of(j), j));
+                    else key = kind_of(j, candidate_key(sc_of(j), j));
                 }
-                f(j < j1 ? j : n, key);
+                f(j, key);
             }
         }
     };
 
     for (int s = sb + tid; s < se; s += SG_NT) sel_l[s - sb] = n <= k && s < n ? s : -1;
+    for (int b = tid; b < 3 * SG_BINS / 4; b += SG_NT)
+        reinterpret_cast<uint4 *>(hist[0])[b] = make_uint4(0, 0, 0, 0);
 
     if (n > k) {
-        if constexpr (IN_REGS) {
-#pragma unroll
-            for (int i = 0; i < KEYS; ++i) {
-                const int j = min(j0 + i * 64 + lane, n - 1);
-                key_r[i] = order_key(ranked(sc_of(j), j));
-            }
-        } else if constexpr (KEYS == SG_KEYS_LDS) {
-            // (written and read by the same wave)
-#pragma unroll 8
-            for (int j = j0 + lane; j < j1; j += 64) key_l[j] = order_key(ranked(sc_of(j), j));
-        }
         // Which entries compete.  With the recent window (protect 0) the candidates are
         // the entries in front of the last `recent` positions; positions ascend, so they
         // are a prefix [0, older) and `heavy` of them are kept.  With a sparse-attention
@@ -193,15 +192,40 @@ __global__ __launch_bounds__(SG_NT) void select_gather_kernel(
             for (int j = tid; j < n; j += SG_NT) cnt += pos_of(j) < t_new - recent;
             older = block_sum(cnt, scan_l);
         }
-        auto is_cand = [&](int j) {
-            if constexpr (PAT) return covered(j) == overflow;
-            else return j < older;
-        };
-        auto always = [&](int j) {
-            if constexpr (PAT) return !overflow && covered(j);
-            else return j >= older;
-        };
-        unsigned thr = 0, need = 0;                    // keep keys > thr, and `need` of those == thr
+        kinds.older = older;
+        kinds.overflow = overflow;
+        if constexpr (IN_REGS) {
+            // every score requested before the first is looked at
+            float v[KEYS];
+#pragma unroll
+            for (int i = 0; i < KEYS; ++i) v[i] = sc_in[min(j0 + i * 64 + lane, n - 1)];
+            if constexpr (COMPACT) {
+#pragma unroll
+                for (int i = 0; i < KEYS; ++i) {
+                    const int j = min(j0 + i * 64 + lane, n - 1);
+                    const float a = acc_g[hoff + min(j, max(n_occ, 1) - 1)];
+                    v[i] = (j < n_occ ? a : 0.f) + v[i];
+                }
+            } else if (bs) {
+#pragma unroll
+                for (int i = 0; i < KEYS; ++i) v[i] = bs[min(j0 + i * 64 + lane, n - 1)] + v[i];
+            }
+            if (rank == H2O_RANK_AVERAGED) {
+#pragma unroll
+                for (int i = 0; i < KEYS; ++i) v[i] = ranked(v[i], min(j0 + i * 64 + lane, n - 1));
+            }
+#pragma unroll
+            for (int i = 0; i < KEYS; ++i) {
+                const int j = j0 + i * 64 + lane;
+                const unsigned key = kind_of(j, min(max(order_key(v[i]), 1u), KEY_SURE - 1u));
+                key_r[i] = j < j1 ? key : KEY_OUT;
+            }
+        } else if constexpr (KEYS == SG_KEYS_LDS) {
+            // (written and read by the same wave)
+#pragma unroll 8
+            for (int j = j0 + lane; j < j1; j += 64) key_l[j] = kind_of(j, candidate_key(sc_of(j), j));
+        }
+        unsigned thr = KEY_SURE - 1u, need = 0;        // keep keys > thr, and `need` of those == thr
         if (want > 0) {
             // radix select: the want-th largest key among the candidates (there are more
             // than `want` of them: n exceeds the budget).  Three digits of 11, 11 and 10
@@ -214,34 +238,35 @@ __global__ __launch_bounds__(SG_NT) void select_gather_kernel(
             for (int d = 0; d < 3; ++d) {
                 const int shift = d == 0 ? 21 : d == 1 ? 10 : 0;
                 const unsigned dmask = d == 2 ? 1023u : 2047u;
-                for (int b = tid; b < SG_BINS; b += SG_NT) hist[b] = 0;
-                __syncthreads();
-                sweep([&](int j, unsigned key) {
-                    if (j < n && (key & mask) == prefix && is_cand(j))
-                        atomicAdd(&hist[(key >> shift) & dmask], 1u);
+                if (d == 0) __syncthreads();           // the counters are zero (and keys in LDS written)
+                sweep([&](int, unsigned key) {
+                    if (((key ^ prefix) & mask) == 0 && key - 1u < KEY_SURE - 1u)
+                        atomicAdd(&hist[d][(key >> shift) & dmask], 1u);
                 });
                 __syncthreads();
-                // the bin in which the count from the top reaches `need`: thread r looks at
-                // the bins SG_BINS - 1 - 4r and the three below, the scan gives it the count
-                // of all higher bins
+                // The bin in which the count from the top reaches `need`.  Every wave finds it for
+                // itself (one barrier per digit): a lane adds up 32 bins, highest lane first, a
+                // scan finds the lane in which `need` is reached, a second one its bin.
+                unsigned mine = 0;
                 {
-                    static_assert(SG_BINS == 4 * SG_NT, "four bins per thread");
-                    const int top = SG_BINS - 4 - 4 * tid;
-                    const uint4 h = *reinterpret_cast<const uint4 *>(hist + top);
-                    const unsigned c[4] = {h.w, h.z, h.y, h.x};
-                    unsigned above = (unsigned)block_exclusive_scan((int)(c[0] + c[1] + c[2] + c[3]), scan_l);
+                    const uint4 *h = reinterpret_cast<const uint4 *>(hist[d] + SG_BINS - 32 - 32 * lane);
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        if (above < need && above + c[i] >= need) {
-                            sh_prefix = prefix | ((unsigned)(top + 3 - i) << shift);
-                            sh_need = need - above;     // still needed inside that bin
-                        }
-                        above += c[i];
+                    for (int i = 0; i < 8; ++i) {
+                        const uint4 x = h[(i + lane) & 7];      // (spread over the banks)
+                        mine += (x.x + x.y) + (x.z + x.w);
                     }
                 }
-                __syncthreads();
-                prefix = sh_prefix;
-                need = sh_need;
+                unsigned upto = wave_inclusive_scan(mine);
+                const int at = __builtin_amdgcn_readfirstlane(
+                    __ffsll((long long)__ballot(upto >= need)) - 1);
+                const unsigned above = __builtin_amdgcn_readlane((int)(upto - mine), at);
+                const int first = SG_BINS - 1 - 32 * at;        // highest of its bins
+                mine = lane < 32 ? hist[d][first - lane] : 0;
+                upto = above + wave_inclusive_scan(mine);
+                const int bin = __builtin_amdgcn_readfirstlane(
+                    __ffsll((long long)__ballot(upto >= need)) - 1);
+                need -= (unsigned)__builtin_amdgcn_readlane((int)(upto - mine), bin);   // still needed inside that bin
+                prefix |= (unsigned)(first - bin) << shift;
                 mask |= dmask << shift;
             }
             thr = prefix;
@@ -249,22 +274,10 @@ __global__ __launch_bounds__(SG_NT) void select_gather_kernel(
         // Ranks in position order.  A wave first counts, in its run, the entries that are kept
         // outright and those at the threshold, then (knowing how many of both the waves in
         // front have) it assigns slots.
-        auto look = [&](int j, unsigned key, bool &sure, bool &equal) {
-            sure = equal = false;
-            if (j < n) {
-                sure = always(j);
-                if (!sure && want > 0 && is_cand(j)) {
-                    sure = key > thr;
-                    equal = key == thr;
-                }
-            }
-        };
         int sure_cnt = 0, eq_cnt = 0;
-        sweep([&](int j, unsigned key) {
-            bool sure, equal;
-            look(j, key, sure, equal);
-            sure_cnt += __popcll(__ballot(sure));
-            eq_cnt += __popcll(__ballot(equal));
+        sweep([&](int, unsigned key) {
+            sure_cnt += __popcll(__ballot(key > thr));
+            eq_cnt += __popcll(__ballot(key == thr));
         });
         __syncthreads();
         if (lane == 0) { scan_l[wave] = sure_cnt; scan_l[SG_NW + wave] = eq_cnt; }
@@ -280,15 +293,16 @@ __global__ __launch_bounds__(SG_NT) void select_gather_kernel(
         slot += max(0, e - eq_first);
         const unsigned long long below = (1ull << lane) - 1ull;
         sweep([&](int j, unsigned key) {
-            bool sure, equal;
-            look(j, key, sure, equal);
-            const unsigned long long eqs = __ballot(equal);
-            const bool keep = sure || (equal && e + __popcll(eqs & below) >= eq_first);
+            const unsigned long long eqs = __ballot(key == thr);
+            bool keep = key > thr;
+            if (eqs) {                                 // wave-uniform, rare
+                keep = keep || (key == thr && e + __popcll(eqs & below) >= eq_first);
+                e += __popcll(eqs);
+            }
             const unsigned long long kept = __ballot(keep);
             const int mine = slot + __popcll(kept & below);
             if (keep && mine >= sb && mine < se) sel_l[mine - sb] = j;
             slot += __popcll(kept);
-            e += __popcll(eqs);
         });
     }
     __syncthreads();
@@ -468,7 +482,8 @@ hipError_t launch_select(const h2o_cache &c, const void *K, const void *V, const
     auto launch = [&](auto kern, bool &raised) -> hipError_t {
         if (smem > 40 * 1024 && !raised) {
             const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
-                                                     hipFuncAttributeMaxDynamicSharedMemorySize, 140 * 1024);
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize,
+                                                     (SG_LDS_KEYS + H2O_MAX_BUDGET) * 4);
             if (e != hipSuccess) return e;
             raised = true;
         }

@@ -1,6 +1,6 @@
 """The prompt compression at the edges of its dispatch: where the ranking keys move from
 8 to 32 registers per thread (4096 candidates), to LDS (16 384) and to being formed again
-for every sweep (30 720), with one and with many workgroups per head.  Bit for bit
+for every sweep (28 672), with one and with many workgroups per head.  Bit for bit
 against a stable sort on the host (the kernel does no arithmetic but the rank value)."""
 import pytest
 import torch
@@ -36,10 +36,10 @@ def kept_by_sorting(score, heavy, recent, averaged, protect, stride):
     (513, 600, 33, 30, False, 0, True),        # one workgroup per head
     (16384, 2, 1700, 1577, False, 0, True),
     (16385, 2, 1700, 1577, True, 0, False),
-    (30720, 1, 2048, 2048, False, 0, True),
-    (30721, 1, 2048, 2048, False, 0, True),
+    (28672, 1, 2048, 2048, False, 0, True),
+    (28673, 1, 2048, 2048, False, 0, True),
     (5000, 2, 300, 31, True, 1, True),
-    (30721, 1, 300, 33, False, 1, True),
+    (28673, 1, 300, 33, False, 1, True),
     (2500, 2, 0, 70, False, 0, False),         # window only
     (2500, 2, 70, 0, False, 0, True),          # no window
 ])
