@@ -465,9 +465,11 @@ hipError_t launch_select(const h2o_cache &c, const void *K, const void *V, const
     const int heads = c.cfg.batch * c.cfg.heads;
     const int rowb = c.cfg.head_dim * c.esize;
     const char *Kp = static_cast<const char *>(K), *Vp = static_cast<const char *>(V);
-    // Workgroups per head: enough to give every CU two, but at least 32 slots each
-    // (one round of the row copy).
-    int parts = COMPACT ? 1 : (2 * 256 + heads - 1) / heads;
+    // Workgroups per head: enough to give every CU one, but at least 32 slots each (one round
+    // of the row copy).  Two per CU were slower (us, reset included, one / two / four: 32
+    // heads, 306 of 1531 10.1 / 11.5 / 11.4; 3277 of 16 384 32.0 / 32.6 / 50; 8 heads 21 / 26 / 45;
+    // 128 heads, 819 of 4096 22.2 / 22.8 / 26.5): each makes the whole selection.
+    int parts = COMPACT ? 1 : (256 + heads - 1) / heads;
     if (const int most = (c.k + 31) / 32; parts > most) parts = most;
     const int part_slots = (c.k + parts - 1) / parts;
     parts = (c.k + part_slots - 1) / part_slots;
