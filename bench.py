@@ -424,7 +424,7 @@ def main():
         tf = fl / (min(prefill_ms) * 1e-3) / 1e12
         mfma_roofline = {"bound": "mfma", "achieved": tf, "peak": MFMA_PEAK_TFLOPS, "unit": "TFLOP/s",
                          "frac": tf / MFMA_PEAK_TFLOPS, "traffic": None,
-                         "kernel": "whole chunked prompt phase: per chunk concat_kernel + two "
+                         "kernel": "whole chunked prompt phase: per chunk two "
                                    "prefill_pass_kernel launches + select_gather_kernel",
                          "flops": fl, "ms": min(prefill_ms), "chunk": chunks[0][0].shape[2],
                          "chunks": len(chunks)}

@@ -228,8 +228,8 @@ int h2o_prefill_scores_noalloc(h2o_cache *cache, const void *Q, const void *K,
 
 /* Device bytes of scratch h2o_prefill_chunk needs for chunks of up to m tokens
  * (cache + chunk as one candidate list: K and V rows, old scores, positions,
- * column sums, row statistics, slot order; with_output != 0: also the transposed
- * V the attention output needs).  Returns 0 for invalid arguments, when heavy + recent
+ * column sums, row statistics, slot order; with_output != 0: also room for a copy of
+ * V).  Returns 0 for invalid arguments, when heavy + recent
  * + m exceeds H2O_MAX_PROMPT, and for with_output on a binary32 configuration. */
 size_t h2o_prefill_chunk_workspace_bytes(const h2o_config *cfg, int32_t m, int32_t with_output);
 
@@ -262,8 +262,8 @@ int h2o_prefill_chunk(h2o_cache *cache, const void *Q, const void *K, const void
 
 /*
  * Device bytes of scratch h2o_prefill_attention / h2o_prefill_attention_scores
- * need for a prompt of n tokens (a transposed copy of V padded to whole tiles,
- * then the scratch of h2o_prefill_workspace_bytes).  Returns 0 for invalid
+ * need for a prompt of n tokens (room for a copy of V padded to whole tiles, used
+ * when `out` overlaps V, then the scratch of h2o_prefill_workspace_bytes).  Returns 0 for invalid
  * arguments and for H2O_F32 (16-bit element types only).
  */
 size_t h2o_prefill_attention_workspace_bytes(const h2o_config *cfg, int32_t n);

@@ -7,10 +7,10 @@
 //   pass 2 (column sums)    : c_j   = sum_{i>=j} exp(scale * <Q_i, K_j> - LSE_i)
 //
 // Both passes are the same dense contraction QK^T and run on the matrix cores;
-// they differ in which operand stays in registers.  A workgroup of NWV waves owns
-// 32*NWV "stationary" rows (queries in pass 1, keys in pass 2; 32 per wave, kept
-// in registers as MFMA B-operand fragments) and streams tiles of the other
-// operand through LDS (double buffered) as A-operand fragments.  Eight waves
+// they differ in which operand stays in registers.  A workgroup's waves own 32
+// "stationary" rows each (queries in pass 1, keys in pass 2; kept in registers as
+// MFMA B-operand fragments) and stream tiles of the other operand through LDS
+// as A-operand fragments.  Eight waves (four in the shape for smaller grids)
 // share one streamed tile: the copy into LDS and its address arithmetic are paid
 // once per 256 stationary rows, which matters because the matrix pipe, the
 // vector ALU (one exponential per product) and the vector memory path are all
@@ -71,7 +71,7 @@ constexpr int NLB = 4;         // row-statistic buffers (pass 2; read one phase 
 // so whenever one group is in its matrix phase the other is in its vector
 // phase ("ping-pong").  s_setprio lets the matrix phase win the issue slot.
 //
-// NWV: waves per workgroup.  Eight (256 stationary rows, two workgroups per CU) is
+// RWV: waves over a workgroup's rows.  Eight (256 stationary rows, two workgroups per CU) is
 // the shape for a full chip.  Four (128 rows, one group, one barrier per tile, the
 // overlap left to the workgroups that share a CU) is for grids that do not fill it:
 // the longest block then has half the work per tile.
