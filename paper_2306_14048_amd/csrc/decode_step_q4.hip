@@ -558,17 +558,15 @@ hipError_t launch_q4(const h2o_cache &c, int waves, const void *q, const void *k
                      void *out, hipStream_t st)
 {
     const size_t smem = lds_of<D, SPL>(waves);
-    auto launch = [&](auto kern, bool &raised) -> hipError_t {
-        if (smem > 48 * 1024 && !raised) {
-            const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
-                                                     hipFuncAttributeMaxDynamicSharedMemorySize, 150 * 1024);
+    auto launch = [&](auto kern, std::atomic<uint64_t> &raised) -> hipError_t {
+        if (smem > 48 * 1024) {
+            const hipError_t e = allow_lds(reinterpret_cast<const void *>(kern), 150 * 1024, raised);
             if (e != hipSuccess) return e;
-            raised = true;
         }
         hipLaunchKernelGGL(kern, dim3(c.cfg.batch * c.cfg.heads), dim3(waves * 64), smem, st, H2O_DECODE_ARGS);
         return hipGetLastError();
     };
-    static bool raised_window = false, raised_pattern = false;
+    static std::atomic<uint64_t> raised_window{0}, raised_pattern{0};
     if (c.cfg.protect == H2O_PROTECT_RECENT) return launch(decode_q4_kernel<DT, D, SPL, false>, raised_window);
     return launch(decode_q4_kernel<DT, D, SPL, true>, raised_pattern);
 }

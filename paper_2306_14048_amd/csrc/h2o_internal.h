@@ -3,6 +3,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include <atomic>
 #include "h2o.h"
 
 struct h2o_cache {
@@ -111,6 +112,20 @@ static inline bool two_groups(int heads, int rows, int streamed)
 {
     const long long blocks = (long long)heads * ((rows + 127) / 128);
     return streamed >= 480 && blocks <= (streamed >= 1500 ? 512 : 384);
+}
+
+// Lets a kernel have up to `bytes` of dynamic LDS on the current device (the attribute belongs
+// to a device's copy of the kernel); `done` remembers the devices, one per kernel.
+static inline hipError_t allow_lds(const void *kern, int bytes, std::atomic<uint64_t> &done)
+{
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    const uint64_t bit = dev >= 0 && dev < 64 ? 1ull << dev : 0;
+    if (done.load(std::memory_order_relaxed) & bit) return hipSuccess;
+    e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+    if (e == hipSuccess) done.fetch_or(bit, std::memory_order_relaxed);
+    return e;
 }
 
 // ---- element types ----------------------------------------------------------

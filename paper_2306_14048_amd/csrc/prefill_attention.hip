@@ -456,13 +456,10 @@ hipError_t launch_attn(const h2o_config &cfg, double scale, const void *Q, const
     constexpr size_t smem = (size_t)ANS * 2 * ABN * G * D * 2;
     static_assert(G == 1 || smem >= (size_t)ARW * (D / 32 * 16 + 2) * 256, "the stages hold a group's parts");
     auto kern = kf.rows ? prefill_attn_kernel<DT, D, true, G> : prefill_attn_kernel<DT, D, false, G>;
-    static bool raised_for[2] = {false, false};
-    bool &raised = raised_for[kf.rows != 0];
-    if (smem > 48 * 1024 && !raised) {
-        e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+    static std::atomic<uint64_t> raised[2] = {};
+    if (smem > 48 * 1024) {
+        e = allow_lds(reinterpret_cast<const void *>(kern), (int)smem, raised[kf.rows != 0]);
         if (e != hipSuccess) return e;
-        raised = true;
     }
     const int nblk = (nq + ARW * 32 - 1) / (ARW * 32);
     const float c2 = (float)(scale * 1.4426950408889634);

@@ -493,13 +493,9 @@ hipError_t launch_pass(const h2o_config &cfg, double scale, const void *Q, const
     const float c2 = (float)(scale * 1.4426950408889634);
     auto kern = RWV == 8 ? prefill_pass_kernel<DT, D, MB, COLSUM> : prefill_pass4_kernel<DT, D, MB, G, TWO, COLSUM>;
     if (smem > 48 * 1024) {
-        static bool raised = false;
-        if (!raised) {
-            hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
-                                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-            if (e != hipSuccess) return e;
-            raised = true;
-        }
+        static std::atomic<uint64_t> raised{0};
+        const hipError_t e = allow_lds(reinterpret_cast<const void *>(kern), (int)smem, raised);
+        if (e != hipSuccess) return e;
     }
     hipLaunchKernelGGL(kern,
                        dim3((unsigned)head_slots(heads) * nblk),

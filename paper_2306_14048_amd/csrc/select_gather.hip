@@ -481,13 +481,11 @@ hipError_t launch_select(const h2o_cache &c, const void *K, const void *V, const
                      : n <= SG_LDS_KEYS          ? SG_KEYS_LDS
                                                  : SG_KEYS_NONE;
     const size_t smem = (size_t)part_slots * sizeof(int) + (keys == SG_KEYS_LDS && n > c.k ? (size_t)n * 4 : 0);
-    auto launch = [&](auto kern, bool &raised) -> hipError_t {
-        if (smem > 40 * 1024 && !raised) {
-            const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
-                                                     hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                     (SG_LDS_KEYS + H2O_MAX_BUDGET) * 4);
+    auto launch = [&](auto kern, std::atomic<uint64_t> &raised) -> hipError_t {
+        if (smem > 32 * 1024) {
+            const hipError_t e =
+                allow_lds(reinterpret_cast<const void *>(kern), (SG_LDS_KEYS + H2O_MAX_BUDGET) * 4, raised);
             if (e != hipSuccess) return e;
-            raised = true;
         }
         hipLaunchKernelGGL(kern, dim3((unsigned)heads * parts), dim3(SG_NT), smem, st, Kp, Vp, score, base,
                            pos_in, n, t_new, c.K, c.V, c.acc, c.pos, c.k, c.cfg.heavy, c.cfg.recent,
@@ -496,7 +494,7 @@ hipError_t launch_select(const h2o_cache &c, const void *K, const void *V, const
     };
 #define H2O_SG1(RB, QDT, PAT, KEYS)                                                             \
     do {                                                                                        \
-        static bool raised = false;                                                             \
+        static std::atomic<uint64_t> raised{0};                                                 \
         return launch(select_gather_kernel<RB, QDT, PAT, KEYS, COMPACT>, raised);               \
     } while (0)
 #define H2O_SG(RB, QDT)                                                                         \
