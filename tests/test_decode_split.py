@@ -97,3 +97,47 @@ def test_scratch_sizes_and_refusals():
     assert lib.h2o_cache_set_step_scratch(None, buf.data_ptr(), need) == hb.H2O_EINVAL
     assert lib.h2o_cache_set_step_scratch(c.handle, buf.data_ptr(), need) == hb.H2O_OK
     c.close()
+
+
+def test_split_steps_and_chunks_in_a_captured_graph():
+    """Reset, a prompt in two chunks and split steps captured once and replayed, with eager
+    work on another cache in between: every replay equals the eager run bit for bit."""
+    from paper_2306_14048_amd import binding as hb
+    dev, d, heads, m, T = torch.device("cuda:0"), 128, 4, 700, 3
+    g = torch.Generator().manual_seed(8)
+    pieces = [tuple(torch.randn(1, heads, m, d, generator=g).half().to(dev) for _ in range(3)) for _ in range(2)]
+    steps = [tuple(torch.randn(1, heads, d, generator=g).half().to(dev) for _ in range(3)) for _ in range(T)]
+
+    def run(cache, chunk_out, step_out):
+        cache.reset()
+        for (Q, K, V), o in zip(pieces, chunk_out):
+            cache.prefill_chunk(Q, K, V, out=o)
+        for (q, k, v), o in zip(steps, step_out):
+            cache.decode_step(q, k, v, o)
+
+    def buffers():
+        return [torch.empty(1, heads, m, d, dtype=torch.float16, device=dev) for _ in range(2)], \
+               [torch.empty(1, heads, d, dtype=torch.float16, device=dev) for _ in range(T)]
+
+    caches = [hb.H2OCache(1, heads, d, 500, 500, torch.float16, device=dev) for _ in range(2)]
+    assert hb.h2o_step_scratch_bytes(caches[0].cfg) > 0
+    want = buffers()
+    run(caches[0], *want)
+    got = buffers()
+    run(caches[1], *got)                          # workspaces are allocated outside the capture
+    graph = torch.cuda.CUDAGraph()
+    stream = torch.cuda.Stream()
+    stream.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.graph(graph, stream=stream):
+        run(caches[1], *got)
+    for _ in range(3):
+        for x in got[0] + got[1]:
+            x.zero_()
+        graph.replay()
+        run(caches[0], *want)                     # eager work in between
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip(want[0] + want[1], got[0] + got[1]))
+        assert all(torch.equal(a.view(torch.uint8), b.view(torch.uint8))
+                   for a, b in zip(caches[0].views(), caches[1].views()))
+    for c in caches:
+        c.close()
