@@ -221,7 +221,7 @@ __global__ __launch_bounds__(FNT) void decode_finish_kernel(
     }
     const T v_self = reinterpret_cast<const T *>(vn_g)[(size_t)head * D + tid % D];
     const int li = lane % LPR;
-    const uint4 row = *reinterpret_cast<const uint4 *>(((lane / LPR) & 1 ? vn_g : kn_g) + (size_t)head * ROWB + li * 16);
+    uint4 row = *reinterpret_cast<const uint4 *>(((lane / LPR) & 1 ? vn_g : kn_g) + (size_t)head * ROWB + li * 16);
 
     // the outputs of the parts (column tid % D; the first D threads use them)
     constexpr int OPF = 8;
@@ -249,6 +249,7 @@ __global__ __launch_bounds__(FNT) void decode_finish_kernel(
         ow_l[lane] = (float)(st.sum * f / den);
     }
     const bool plain = __ballot(f != 1.0) == 0;      // (every wave finds the same)
+    pin(row);                                        // the new token has arrived before any wave writes `out` (over it, perhaps)
     __syncthreads();
 
     // ---- scores and the eviction candidates (as in the one-workgroup kernels)

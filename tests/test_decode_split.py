@@ -83,6 +83,26 @@ def test_split_step_matches_one_workgroup(dt, d, batch, heads, n, heavy, recent,
         c.close()
 
 
+def test_split_step_output_over_its_inputs():
+    from paper_2306_14048_amd import binding as hb
+    dev, d, heads, k = torch.device("cuda:0"), 128, 6, 1400
+    g = torch.Generator().manual_seed(4)
+    K, V = (torch.randn(1, heads, k, d, generator=g).half().to(dev) for _ in range(2))
+    score = torch.rand(1, heads, k, generator=g).to(dev)
+    q, kn, vn = (torch.randn(1, heads, d, generator=g).half().to(dev) for _ in range(3))
+    ref = None
+    for over in (None, 0, 1, 2):
+        c = hb.H2OCache(1, heads, d, k // 2, k // 2, torch.float16, device=dev)
+        c.prefill_select(K, V, score)
+        args = [q.clone(), kn.clone(), vn.clone()]
+        out = torch.empty_like(q) if over is None else args[over]
+        c.decode_step(*args, out)
+        got = [out.clone(), *(x.clone() for x in c.views())]
+        ref = got if ref is None else ref
+        assert all(torch.equal(a, b) for a, b in zip(got, ref)), over
+        c.close()
+
+
 def test_scratch_sizes_and_refusals():
     from paper_2306_14048_amd import binding as hb
     assert hb.h2o_step_scratch_bytes(hb.make_config(16, 32, 128, 1000, 1000, hb.H2O_F16)) == 0   # many heads
