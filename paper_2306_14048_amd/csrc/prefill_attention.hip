@@ -424,10 +424,10 @@ __global__ __launch_bounds__(ARW * G * 64, 2) void prefill_attn_kernel(
         for (int db = 0; db < NDB; ++db)
 #pragma unroll
             for (int g = 0; g < 4; ++g) {
-                typename E::T o4[4];
-#pragma unroll
-                for (int e = 0; e < 4; ++e) o4[e] = E::from_f(oacc[db][4 * g + e] * inv);
-                *reinterpret_cast<uint2 *>(orow + 32 * db + 8 * g + 4 * half) = *reinterpret_cast<const uint2 *>(o4);
+                // (a pair per conversion: element by element, bf16 took a branch for NaNs on every one)
+                *reinterpret_cast<uint2 *>(orow + 32 * db + 8 * g + 4 * half) =
+                    make_uint2(pack2<DT>(oacc[db][4 * g] * inv, oacc[db][4 * g + 1] * inv),
+                               pack2<DT>(oacc[db][4 * g + 2] * inv, oacc[db][4 * g + 3] * inv));
             }
         if (half == 0) {
             const float l2 = m_run * c2 + __builtin_amdgcn_logf(l_tot);      // log2 of the row's normaliser
