@@ -40,15 +40,23 @@ struct PartStat { double shift, sum, s_self, unused; };
 // Scratch of one cache: e[heads][k], stat[heads][32], o[heads][32][d]
 struct Scratch { double *e; PartStat *stat; float *o; };
 
+// How a step is split: `parts` workgroups per head, `per` slots each (parts <= 1: it is not).
+struct Plan { int parts, per; };
+
 // The one-workgroup kernel's body without the bookkeeping: see decode_resident_kernel
 // for the plan of the loads (all requests first, straight-line, none conditional) and
 // for slot ownership.  Requires per <= U * RPI and 1 <= slots of every part.
 template <int DT, int D, int U>
-__global__ __launch_bounds__(PNW * 64, 4) void decode_part_kernel(
-    const char *__restrict__ Kc, const char *__restrict__ Vc, const char *__restrict__ q_g,
-    const char *__restrict__ kn_g, int k, int n_occ, int per, int parts, double scale,
-    double *__restrict__ e_g, PartStat *__restrict__ stat_g, float *__restrict__ o_g)
+__global__ __launch_bounds__(PNW * 64, 4) void decode_part_kernel(const StepArgs args, const Scratch scratch, const Plan plan)
 {
+    const char *__restrict__ Kc = args.K, *__restrict__ Vc = args.V;
+    const char *__restrict__ q_g = args.q, *__restrict__ kn_g = args.kn;
+    double *__restrict__ e_g = scratch.e;
+    PartStat *__restrict__ stat_g = scratch.stat;
+    float *__restrict__ o_g = scratch.o;
+    const int k = args.k, n_occ = args.n_occ, per = plan.per, parts = plan.parts;
+    const double scale = args.scale;
+    args_here(args);
     using E = Elem<DT>;
     using T = typename E::T;
     constexpr int EPL = E::EPL;
@@ -196,13 +204,20 @@ __global__ __launch_bounds__(PNW * 64, 4) void decode_part_kernel(
 // (20 bytes per slot): every load is requested before the first use, and what depends on
 // the parts (factors, normaliser) is worked out by one lane per part.
 template <int DT, int D, bool PAT>
-__global__ __launch_bounds__(FNT) void decode_finish_kernel(
-    char *__restrict__ Kc, char *__restrict__ Vc, float *__restrict__ acc_g,
-    int32_t *__restrict__ pos_g, const char *__restrict__ kn_g, const char *__restrict__ vn_g,
-    char *__restrict__ out_g, int k, int n_occ, int t, int recent, int rank, int protect, int stride,
-    int per, int parts, const double *__restrict__ e_g, const PartStat *__restrict__ stat_g,
-    const float *__restrict__ o_g)
+__global__ __launch_bounds__(FNT) void decode_finish_kernel(const StepArgs args, const Scratch scratch, const Plan plan)
 {
+    char *__restrict__ Kc = args.K;
+    char *__restrict__ Vc = args.V;
+    float *__restrict__ acc_g = args.acc;
+    int32_t *__restrict__ pos_g = args.pos;
+    const char *__restrict__ kn_g = args.kn, *__restrict__ vn_g = args.vn;
+    char *__restrict__ out_g = args.out;
+    const double *__restrict__ e_g = scratch.e;
+    const PartStat *__restrict__ stat_g = scratch.stat;
+    const float *__restrict__ o_g = scratch.o;
+    const int k = args.k, n_occ = args.n_occ, t = args.t, recent = args.recent, rank = args.rank, protect = args.protect,
+              stride = args.stride, per = plan.per, parts = plan.parts;
+    args_here(args);
     using E = Elem<DT>;
     using T = typename E::T;
     constexpr int EPL = E::EPL, LPR = D / EPL;
@@ -330,8 +345,6 @@ __global__ __launch_bounds__(FNT) void decode_finish_kernel(
 
 // How a step over n_occ slots is split (parts <= 1: it is not).  Rows of `rpw` per
 // wave and load; a part holds at most `umax` rounds.
-struct Plan { int parts, per; };
-
 Plan plan_of(int heads, int n_occ, int rpw, bool f32)
 {
     const int rpi = PNW * rpw, umax = rpw * 13 <= 64 ? 13 : 8;
@@ -386,12 +399,11 @@ hipError_t launch(const h2o_cache &c, const void *q, const void *kn, const void 
 {
     constexpr int RPW = 64 / (D / Elem<DT>::EPL);
     constexpr int RPI = PNW * RPW;
-    const int heads = c.cfg.batch * c.cfg.heads, occ = c.t < c.k ? c.t : c.k;
+    const int heads = c.cfg.batch * c.cfg.heads;
     const Scratch s = carve(c);
+    const StepArgs args = step_args(c, q, kn, vn, out);
     auto part = [&](auto kern) {
-        hipLaunchKernelGGL(kern, dim3((unsigned)heads * p.parts), dim3(PNW * 64), 0, st, c.K, c.V,
-                           static_cast<const char *>(q), static_cast<const char *>(kn), c.k, occ, p.per, p.parts,
-                           c.scale, s.e, s.stat, s.o);
+        hipLaunchKernelGGL(kern, dim3((unsigned)heads * p.parts), dim3(PNW * 64), 0, st, args, s, p);
     };
     const int rounds = p.per / RPI;
     if (rounds <= 4) part(decode_part_kernel<DT, D, 4>);
@@ -404,10 +416,7 @@ hipError_t launch(const h2o_cache &c, const void *q, const void *kn, const void 
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     auto finish = [&](auto kern) {
-        hipLaunchKernelGGL(kern, dim3(heads), dim3(FNT), 0, st, c.K, c.V, c.acc, c.pos,
-                           static_cast<const char *>(kn), static_cast<const char *>(vn), static_cast<char *>(out),
-                           c.k, occ, c.t, c.cfg.recent, c.cfg.rank, c.cfg.protect, c.cfg.stride, p.per, p.parts, s.e,
-                           s.stat, s.o);
+        hipLaunchKernelGGL(kern, dim3(heads), dim3(FNT), 0, st, args, s, p);
     };
     if (c.cfg.protect == H2O_PROTECT_RECENT) finish(decode_finish_kernel<DT, D, false>);
     else finish(decode_finish_kernel<DT, D, true>);

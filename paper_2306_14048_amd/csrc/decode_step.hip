@@ -54,13 +54,18 @@ namespace {
 // PAT: a sparse-attention pattern is the protected set (cfg.protect != 0); the plain
 // recent-window build carries none of that code.
 template <int DT, int D, int NW, int U, bool PAT>
-__global__ __launch_bounds__(NW * 64, 4) void decode_resident_kernel(
-    char *__restrict__ Kc, char *__restrict__ Vc, float *__restrict__ acc_g,
-    int32_t *__restrict__ pos_g, const char *__restrict__ q_g,
-    const char *__restrict__ kn_g, const char *__restrict__ vn_g,
-    char *__restrict__ out_g, int k, int n_occ, int t, int recent, double scale, int rank, int protect,
-    int stride)
+__global__ __launch_bounds__(NW * 64, 4) void decode_resident_kernel(const StepArgs args)
 {
+    char *__restrict__ Kc = args.K;
+    char *__restrict__ Vc = args.V;
+    float *__restrict__ acc_g = args.acc;
+    int32_t *__restrict__ pos_g = args.pos;
+    const char *__restrict__ q_g = args.q, *__restrict__ kn_g = args.kn, *__restrict__ vn_g = args.vn;
+    char *__restrict__ out_g = args.out;
+    const int k = args.k, n_occ = args.n_occ, t = args.t, recent = args.recent, rank = args.rank, protect = args.protect,
+              stride = args.stride;
+    const double scale = args.scale;
+    args_here(args);
     using E = Elem<DT>;
     using T = typename E::T;
     constexpr int EPL = E::EPL;          // elements per lane per 16-byte load
@@ -305,13 +310,18 @@ __global__ __launch_bounds__(NW * 64, 4) void decode_resident_kernel(
 // only known after the last key chunk).  Scores and positions are read one
 // chunk ahead of their use.  Softmax shift and overflow fallback as above.
 template <int DT, int D, int NW, int U, bool PAT>
-__global__ __launch_bounds__(NW * 64, 4) void decode_chunked_kernel(
-    char *__restrict__ Kc, char *__restrict__ Vc, float *__restrict__ acc_g,
-    int32_t *__restrict__ pos_g, const char *__restrict__ q_g,
-    const char *__restrict__ kn_g, const char *__restrict__ vn_g,
-    char *__restrict__ out_g, int k, int n_occ, int t, int recent, double scale, int rank, int protect,
-    int stride, int chunks)
+__global__ __launch_bounds__(NW * 64, 4) void decode_chunked_kernel(const StepArgs args, int chunks)
 {
+    char *__restrict__ Kc = args.K;
+    char *__restrict__ Vc = args.V;
+    float *__restrict__ acc_g = args.acc;
+    int32_t *__restrict__ pos_g = args.pos;
+    const char *__restrict__ q_g = args.q, *__restrict__ kn_g = args.kn, *__restrict__ vn_g = args.vn;
+    char *__restrict__ out_g = args.out;
+    const int k = args.k, n_occ = args.n_occ, t = args.t, recent = args.recent, rank = args.rank, protect = args.protect,
+              stride = args.stride;
+    const double scale = args.scale;
+    args_here(args);
     using E = Elem<DT>;
     using T = typename E::T;
     constexpr int EPL = E::EPL;
@@ -573,11 +583,6 @@ inline hipError_t raise_lds_limit(const void *kern, size_t smem, std::atomic<uin
     return smem > 48 * 1024 ? allow_lds(kern, 150 * 1024, raised) : hipSuccess;
 }
 
-#define H2O_DECODE_ARGS                                                                         \
-    c.K, c.V, c.acc, c.pos, static_cast<const char *>(q), static_cast<const char *>(kn),        \
-        static_cast<const char *>(vn), static_cast<char *>(out), c.k, (c.t < c.k ? c.t : c.k),  \
-        c.t, c.cfg.recent, c.scale, c.cfg.rank, c.cfg.protect, c.cfg.stride
-
 template <int DT, int D, int NW, int U>
 hipError_t launch_resident(const h2o_cache &c, const void *q, const void *kn, const void *vn,
                            void *out, hipStream_t st)
@@ -591,7 +596,7 @@ hipError_t launch_resident(const h2o_cache &c, const void *q, const void *kn, co
         static std::atomic<uint64_t> raised{0};
         hipError_t e = raise_lds_limit(reinterpret_cast<const void *>(kern), smem, raised);
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(kern, dim3(c.cfg.batch * c.cfg.heads), dim3(NW * 64), smem, st, H2O_DECODE_ARGS);
+        hipLaunchKernelGGL(kern, dim3(c.cfg.batch * c.cfg.heads), dim3(NW * 64), smem, st, step_args(c, q, kn, vn, out));
         return hipGetLastError();
     }
     auto kern = decode_resident_kernel<DT, D, NW, U, false>;
@@ -599,7 +604,7 @@ hipError_t launch_resident(const h2o_cache &c, const void *q, const void *kn, co
     hipError_t e = raise_lds_limit(reinterpret_cast<const void *>(kern), smem, raised);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(kern, dim3(c.cfg.batch * c.cfg.heads), dim3(NW * 64), smem, st,
-                       H2O_DECODE_ARGS);
+                       step_args(c, q, kn, vn, out));
     return hipGetLastError();
 }
 
@@ -620,7 +625,7 @@ hipError_t launch_chunked(const h2o_cache &c, const void *q, const void *kn, con
         static std::atomic<uint64_t> raised{0};
         hipError_t e = raise_lds_limit(reinterpret_cast<const void *>(kern), smem, raised);
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(kern, dim3(c.cfg.batch * c.cfg.heads), dim3(NW * 64), smem, st, H2O_DECODE_ARGS,
+        hipLaunchKernelGGL(kern, dim3(c.cfg.batch * c.cfg.heads), dim3(NW * 64), smem, st, step_args(c, q, kn, vn, out),
                            chunks);
         return hipGetLastError();
     }
@@ -629,7 +634,7 @@ hipError_t launch_chunked(const h2o_cache &c, const void *q, const void *kn, con
     hipError_t e = raise_lds_limit(reinterpret_cast<const void *>(kern), smem, raised);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(kern, dim3(c.cfg.batch * c.cfg.heads), dim3(NW * 64), smem, st,
-                       H2O_DECODE_ARGS, chunks);
+                       step_args(c, q, kn, vn, out), chunks);
     return hipGetLastError();
 }
 

@@ -129,13 +129,18 @@ template <int DT, int D, int SPL> struct Ring {
 // a sparse-attention pattern as the protected set (the plain recent window's build
 // carries none of that code).
 template <int DT, int D, int SPL, bool PAT>
-__global__ __launch_bounds__(MAX_WAVES * 64, 4) void decode_q4_kernel(
-    char *__restrict__ Kc, char *__restrict__ Vc, float *__restrict__ acc_g,
-    int32_t *__restrict__ pos_g, const char *__restrict__ q_g,
-    const char *__restrict__ kn_g, const char *__restrict__ vn_g,
-    char *__restrict__ out_g, int k, int n_occ, int t, int recent, double scale, int rank, int protect,
-    int stride)
+__global__ __launch_bounds__(MAX_WAVES * 64, 4) void decode_q4_kernel(const StepArgs args)
 {
+    char *__restrict__ Kc = args.K;
+    char *__restrict__ Vc = args.V;
+    float *__restrict__ acc_g = args.acc;
+    int32_t *__restrict__ pos_g = args.pos;
+    const char *__restrict__ q_g = args.q, *__restrict__ kn_g = args.kn, *__restrict__ vn_g = args.vn;
+    char *__restrict__ out_g = args.out;
+    const int k = args.k, n_occ = args.n_occ, t = args.t, recent = args.recent, rank = args.rank, protect = args.protect,
+              stride = args.stride;
+    const double scale = args.scale;
+    args_here(args);
     using E = Elem<DT>;
     using T = typename E::T;
     using L = Ring<DT, D, SPL>;
@@ -576,11 +581,6 @@ template <int DT, int D, int SPL> constexpr size_t lds_of(int waves)
     return ((sizeof(Shared<D>) + 15) & ~(size_t)15) + (size_t)waves * Ring<DT, D, SPL>::BYTES;
 }
 
-#define H2O_DECODE_ARGS                                                                         \
-    c.K, c.V, c.acc, c.pos, static_cast<const char *>(q), static_cast<const char *>(kn),        \
-        static_cast<const char *>(vn), static_cast<char *>(out), c.k, (c.t < c.k ? c.t : c.k),  \
-        c.t, c.cfg.recent, c.scale, c.cfg.rank, c.cfg.protect, c.cfg.stride
-
 template <int DT, int D, int SPL>
 hipError_t launch_q4(const h2o_cache &c, int waves, const void *q, const void *kn, const void *vn,
                      void *out, hipStream_t st)
@@ -591,7 +591,7 @@ hipError_t launch_q4(const h2o_cache &c, int waves, const void *q, const void *k
             const hipError_t e = allow_lds(reinterpret_cast<const void *>(kern), 150 * 1024, raised);
             if (e != hipSuccess) return e;
         }
-        hipLaunchKernelGGL(kern, dim3(c.cfg.batch * c.cfg.heads), dim3(waves * 64), smem, st, H2O_DECODE_ARGS);
+        hipLaunchKernelGGL(kern, dim3(c.cfg.batch * c.cfg.heads), dim3(waves * 64), smem, st, step_args(c, q, kn, vn, out));
         return hipGetLastError();
     };
     static std::atomic<uint64_t> raised_window{0}, raised_pattern{0};

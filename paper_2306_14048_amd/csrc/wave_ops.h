@@ -13,6 +13,13 @@ __device__ inline void lds_barrier()
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
+// All of a step's arguments are read here, in one go: left to itself the compiler reads some of
+// them where they are first used, a memory latency in the middle of the step.
+__device__ inline void args_here(const StepArgs &a)
+{
+    asm volatile("" ::"s"(a.scale), "s"(a.k), "s"(a.n_occ), "s"(a.t), "s"(a.recent), "s"(a.rank), "s"(a.protect));
+}
+
 // 128-bit load of a cache row piece with the non-temporal hint: the cache is
 // streamed once per step, and hinting that lifts the achieved read bandwidth by
 // 12-14 % on this part (measured with a plain streaming-read kernel).
