@@ -14,8 +14,6 @@
 
 namespace {
 
-constexpr int SG_NT = 512;
-constexpr int SG_NW = SG_NT / 64;
 constexpr int SG_BITS = 11;                 // radix digit: 11 + 11 + 10 bits
 constexpr int SG_BINS = 1 << SG_BITS;
 constexpr int SG_LDS_KEYS = 28672;          // ranking keys kept in LDS up to this many candidates (112 KiB)
@@ -25,34 +23,34 @@ constexpr int SG_KEYS_NONE = 0, SG_KEYS_LDS = 1;   // (any larger value: that ma
 __device__ inline unsigned order_key(float x)
 {
     const unsigned u = __float_as_uint(x);
-    return (u & 0x80000000u) ? ~u : (u | 0x80000000u);   // monotone in x
+    return u ^ ((unsigned)((int)u >> 31) | 0x80000000u);   // monotone in x
 }
 
-// Sum over the workgroup of one int per thread (every thread gets it).  `scratch`
-// holds SG_NW ints.
-__device__ inline int block_sum(int v, int *scratch)
+// Inclusive prefix sum over the lanes of a wave: DPP moves (six shuffles through LDS, each
+// waiting for the one before, took 800 cycles, twice per digit).
+__device__ inline unsigned wave_inclusive_scan(unsigned v)
 {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+    v += (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xf, 0xf, true);    // row_shr:1
+    v += (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xf, 0xf, true);    // row_shr:2
+    v += (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xf, 0xf, true);    // row_shr:4
+    v += (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xf, 0xf, true);    // row_shr:8
+    v += (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xa, 0xf, false);   // row_bcast:15 into rows 1, 3
+    v += (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xc, 0xf, false);   // row_bcast:31 into rows 2, 3
+    return v;
+}
+
+// Sum over the workgroup of one non-negative int per thread (every thread gets it).  `scratch`
+// holds NW ints (waves of the workgroup).
+template <int NW> __device__ inline int block_sum(int v, int *scratch)
+{
+    const unsigned w = wave_inclusive_scan((unsigned)v);
     __syncthreads();                       // scratch may still be read from a previous use
-    if ((threadIdx.x & 63) == 0) scratch[threadIdx.x >> 6] = v;
+    if ((threadIdx.x & 63) == 63) scratch[threadIdx.x >> 6] = (int)w;
     __syncthreads();
     int tot = 0;
 #pragma unroll
-    for (int w = 0; w < SG_NW; ++w) tot += scratch[w];
+    for (int i = 0; i < NW; ++i) tot += scratch[i];
     return tot;
-}
-
-// Inclusive prefix sum over the lanes of a wave.
-__device__ inline unsigned wave_inclusive_scan(unsigned v)
-{
-    const int lane = threadIdx.x & 63;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const unsigned y = (unsigned)__shfl_up((int)v, o, 64);
-        if (lane >= o) v += y;
-    }
-    return v;
 }
 
 // Entry j of a head's n candidates is the token at position pos_in[j] (ascending;
@@ -73,12 +71,17 @@ __device__ inline unsigned wave_inclusive_scan(unsigned v)
 // thread (all reads in flight at once, no LDS latency in the sweeps), in LDS for
 // longer prompts, and beyond SG_LDS_KEYS candidates formed again for every sweep.
 // The selection is issue-bound (every workgroup makes all of it), hence the keys that carry
-// their kind and the digits that cost one barrier each.  Measured, one workgroup per head
-// and byte digits -> this (kernel alone, three prompts in turn, so that rows come from HBM): 32
-// heads, 3277 of 16 384 tokens, f16 d = 128: 134 -> 37 us for 110 MB (keys in LDS: 54; kinds
-// tested per entry, five barriers per digit: 45); 128 heads, 819 of 4096: 42 -> 29 us; 512 heads,
-// 410 of 2048: 52 us for 221 MB (4.2 TB/s; a large copy: 4.7; one prompt repeatedly, its rows in
-// the last-level cache, 48 -> 42).
+// their kind and the digits that cost one barrier each; what a wave does after the sweeps is
+// latency, hence scans in registers, no slots for entries that other workgroups copy, and
+// bookkeeping that is requested in front of the row copy and stored behind it.  Cycles of 32 heads,
+// 3277 of 16 384: 33 500 for the selection and 2100 for the bookkeeping with shuffles and a ballot
+// per tie test, 26 300 and 0 now, then 33 000 for the rows (110 MB, 8 TB/s of read + write).
+// Measured (reset included, three prompts in turn, so that rows come from HBM; us, before that
+// / now; one workgroup per head and byte digits before both): 32 heads, 3277 of 16 384 tokens, f16 d =
+// 128: 39.7 / 35.4 (134); 128 heads, 819 of 4096 30.5 / 29.0 (42); 512 heads, 410 of 2048 54.2 / 52.8; 64 heads, 900
+// of 9000 24.7 / 21.8; 32 heads, 2048 of 30 000 102 / 60; 16 heads, 4000 of 60 000 188 / 104.
+// (Tried: four counters per bin of the first digit, no gain, so the atomics' queue is not what
+// that sweep waits for.)
 //
 // COMPACT: the cache itself is the front of the candidate list: entries j < n_occ are its
 // slots (in position order, with their scores), the others the tokens Kp, Vp at positions
@@ -86,14 +89,17 @@ __device__ inline unsigned wave_inclusive_scan(unsigned v)
 // entry kept in slot s is never in front of it (j >= s), so filling the slots in ascending
 // rounds, every round's reads before its writes, never overwrites what is still to be read.
 // (The list used to be copied together first, rows and all, and gathered back from there:
-// 34 + 26 us per 1024-token chunk at 128 heads x 819 slots.)
-template <int ROWB, int QDT, bool PAT, int KEYS, bool COMPACT>
+// 34 + 26 us per 1024-token chunk at 128 heads x 819 slots.)  Rounds overlap: the next one's reads are
+// in flight while one is written (a whole call, us: 8 heads x 2048 tokens on 4000 slots 186 -> 172, 32 x 1024 on
+// 819 77.1 -> 74.8, 256 x 512 on 410, d = 64, 84.3 -> 82.3).
+template <int ROWB, int QDT, bool PAT, int KEYS, bool COMPACT, int SG_NT>
 __global__ __launch_bounds__(SG_NT, 4) void select_gather_kernel(
     const char *__restrict__ Kp, const char *__restrict__ Vp, const float *__restrict__ score,
     const float *__restrict__ base, const int32_t *__restrict__ pos_in, int n, int t_new,
     char *Kc, char *Vc, float *acc_g, int32_t *pos_g, int k, int heavy, int recent, int rank, int protect,
     int stride, int parts, int part_slots, int n_occ)
 {
+    constexpr int SG_NW = SG_NT / 64;
     extern __shared__ __align__(16) unsigned char smem[];
     int *sel_l = reinterpret_cast<int *>(smem);        // [part_slots] slot -> candidate
     unsigned *key_l = reinterpret_cast<unsigned *>(sel_l + part_slots);   // [n] (SG_KEYS_LDS)
@@ -105,7 +111,7 @@ __global__ __launch_bounds__(SG_NT, 4) void select_gather_kernel(
     const int se = min(k, sb + part_slots);
     const float *sc_in = score + (size_t)head * n;
     const float *bs = base ? base + (size_t)head * n : nullptr;
-    const int32_t *pin = pos_in ? pos_in + (size_t)head * n : nullptr;
+    const int32_t *pos_src = pos_in ? pos_in + (size_t)head * n : nullptr;
     const size_t hoff = (size_t)head * k;
     // the score of entry j as it will be stored, and its position
     auto sc_of = [&](int j) {
@@ -114,7 +120,7 @@ __global__ __launch_bounds__(SG_NT, 4) void select_gather_kernel(
     };
     auto pos_of = [&](int j) {
         if constexpr (COMPACT) return j < n_occ ? pos_g[hoff + j] : t_new - (n - j);
-        else return pin ? pin[j] : j;
+        else return pos_src ? pos_src[j] : j;
     };
 
     // what ranks an older token: its score, or (averaged ranking) its score over
@@ -186,13 +192,14 @@ __global__ __launch_bounds__(SG_NT, 4) void select_gather_kernel(
         if constexpr (PAT) {
             int cnt = 0;
             for (int j = tid; j < n; j += SG_NT) cnt += covered(j);
-            const int total = block_sum(cnt, scan_l);
+            const int total = block_sum<SG_NW>(cnt, scan_l);
             overflow = total > k;
             want = overflow ? k : k - total;
-        } else if (COMPACT || pin) {
+        } else if (COMPACT ? recent > n - n_occ : pos_src != nullptr) {
+            // (COMPACT with a window inside the chunk: the chunk's positions are consecutive)
             int cnt = 0;
             for (int j = tid; j < n; j += SG_NT) cnt += pos_of(j) < t_new - recent;
-            older = block_sum(cnt, scan_l);
+            older = block_sum<SG_NW>(cnt, scan_l);
         }
         kinds.older = older;
         kinds.overflow = overflow;
@@ -219,8 +226,11 @@ __global__ __launch_bounds__(SG_NT, 4) void select_gather_kernel(
 #pragma unroll
             for (int i = 0; i < KEYS; ++i) {
                 const int j = j0 + i * 64 + lane;
-                const unsigned key = kind_of(j, min(max(order_key(v[i]), 1u), KEY_SURE - 1u));
-                key_r[i] = j < j1 ? key : KEY_OUT;
+                key_r[i] = min(max(order_key(v[i]), 1u), KEY_SURE - 1u);
+                if (PAT || j0 + i * 64 + 64 > min(older, j1)) {       // wave-uniform: not candidates throughout
+                    const unsigned key = kind_of(j, key_r[i]);
+                    key_r[i] = j < j1 ? key : KEY_OUT;
+                }
             }
         } else if constexpr (KEYS == SG_KEYS_LDS) {
             // (written and read by the same wave)
@@ -241,10 +251,19 @@ __global__ __launch_bounds__(SG_NT, 4) void select_gather_kernel(
                 const int shift = d == 0 ? 21 : d == 1 ? 10 : 0;
                 const unsigned dmask = d == 2 ? 1023u : 2047u;
                 if (d == 0) __syncthreads();           // the counters are zero (and keys in LDS written)
-                sweep([&](int, unsigned key) {
-                    if (((key ^ prefix) & mask) == 0 && key - 1u < KEY_SURE - 1u)
-                        atomicAdd(&hist[d][(key >> shift) & dmask], 1u);
-                });
+                // (a key that agrees with the digits found so far is a candidate, unless those are
+                // all zeros or all ones, which the two marks agree with as well)
+                if (d > 0 && prefix != 0 && prefix != mask) {
+                    const unsigned known = prefix >> (shift + (d == 1 ? 11 : 10));
+                    sweep([&](int, unsigned key) {
+                        if (key >> (shift + (d == 1 ? 11 : 10)) == known) atomicAdd(&hist[d][(key >> shift) & dmask], 1u);
+                    });
+                } else {
+                    sweep([&](int, unsigned key) {
+                        if (((key ^ prefix) & mask) == 0 && key - 1u < KEY_SURE - 1u)
+                            atomicAdd(&hist[d][(key >> shift) & dmask], 1u);
+                    });
+                }
                 __syncthreads();
                 // The bin in which the count from the top reaches `need`.  Every wave finds it for
                 // itself (one barrier per digit): a lane adds up 32 bins, highest lane first, a
@@ -293,75 +312,125 @@ __global__ __launch_bounds__(SG_NT, 4) void select_gather_kernel(
         // among equal scores the higher positions are kept: the last `need` of them
         const int eq_first = eq_total - (int)need;
         slot += max(0, e - eq_first);
-        const unsigned long long below = (1ull << lane) - 1ull;
-        sweep([&](int j, unsigned key) {
-            const unsigned long long eqs = __ballot(key == thr);
-            bool keep = key > thr;
-            if (eqs) {                                 // wave-uniform, rare
-                keep = keep || (key == thr && e + __popcll(eqs & below) >= eq_first);
-                e += __popcll(eqs);
+        // Waves whose slots belong to other workgroups are done.
+        const int mine_end = slot + sure_cnt + max(0, min(eq_cnt, e + eq_cnt - eq_first));
+        if (slot < se && mine_end > sb) {
+            if (eq_first == 0) {
+                // every entry at the threshold is kept (nearly always: scores are distinct)
+                sweep([&](int j, unsigned key) {
+                    const bool keep = key >= thr;
+                    const unsigned long long kept = __ballot(keep);
+                    const int mine = (int)__builtin_amdgcn_mbcnt_hi(
+                        (unsigned)(kept >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)kept, (unsigned)slot));
+                    if (keep && mine >= sb && mine < se) sel_l[mine - sb] = j;
+                    slot += __popcll(kept);
+                });
+            } else {
+                const unsigned long long below = (1ull << lane) - 1ull;
+                sweep([&](int j, unsigned key) {
+                    const unsigned long long eqs = __ballot(key == thr);
+                    bool keep = key > thr;
+                    if (eqs) {                         // wave-uniform, rare
+                        keep = keep || (key == thr && e + __popcll(eqs & below) >= eq_first);
+                        e += __popcll(eqs);
+                    }
+                    const unsigned long long kept = __ballot(keep);
+                    const int mine = slot + __popcll(kept & below);
+                    if (keep && mine >= sb && mine < se) sel_l[mine - sb] = j;
+                    slot += __popcll(kept);
+                });
             }
-            const unsigned long long kept = __ballot(keep);
-            const int mine = slot + __popcll(kept & below);
-            if (keep && mine >= sb && mine < se) sel_l[mine - sb] = j;
-            slot += __popcll(kept);
-        });
+        }
     }
     __syncthreads();
 
     if constexpr (COMPACT) {
-        // in rounds: reads (waited for, so that no wave's write can pass another's read), a
-        // barrier, writes; the next round reads behind everything written so far
-        constexpr int LPR = ROWB / 16, RPR = SG_NT / LPR, UNR = 8;
+        // In rounds of slots: reads (waited for), a barrier, writes.  No wave's write can then pass
+        // another's read: round r writes slots that only rounds up to r read.  The next round's
+        // reads lie behind what this round writes, so they are requested first and are in flight
+        // while this round is written.
+        constexpr int LPR = ROWB / 16, RPR = SG_NT / LPR, UNR = 4, ROUND = UNR * RPR;
+        constexpr int OWN = H2O_MAX_BUDGET / SG_NT;
         const int li = tid % LPR, rsub = tid / LPR;
-        for (int s0 = 0; s0 < k; s0 += SG_NT) {
-            const int s = s0 + tid, j = s < k ? sel_l[s] : -1;
-            const int p = j >= 0 ? pos_of(j) : -1;
-            const float a = j >= 0 ? sc_of(j) : 0.f;
-            asm volatile("s_waitcnt vmcnt(0)" ::"v"(p), "v"(a) : "memory");
-            __syncthreads();
-            if (s < k) {
-                pos_g[hoff + s] = p;
-                acc_g[hoff + s] = a;
-            }
-        }
         const char *Kn = Kp + (size_t)head * (n - n_occ) * ROWB, *Vn = Vp + (size_t)head * (n - n_occ) * ROWB;
         char *Kh = Kc + hoff * ROWB, *Vh = Vc + hoff * ROWB;
-        for (int s0 = 0; s0 < k; s0 += UNR * RPR) {
-            int j[UNR];
-            uint4 kv[UNR], vv[UNR];
+        int p[OWN];
+        float a[OWN];
+#pragma unroll
+        for (int i = 0; i < OWN; ++i) {
+            if (i * SG_NT >= k) break;
+            const int s = i * SG_NT + tid, j = s < k ? max(sel_l[s], 0) : 0;
+            p[i] = pos_of(j);
+            a[i] = sc_of(j);
+        }
+        struct Rows { int j[UNR]; uint4 k[UNR], v[UNR]; };
+        auto request = [&](Rows &r, int s0) {
 #pragma unroll
             for (int u = 0; u < UNR; ++u) {
                 const int s = s0 + u * RPR + rsub;
-                j[u] = s < k ? sel_l[s] : -1;
-                if (j[u] == s && s < n_occ) j[u] = -1;         // stays where it is
-                const size_t off = (size_t)(j[u] < n_occ ? max(j[u], 0) : j[u] - n_occ) * ROWB + li * 16;
-                kv[u] = *reinterpret_cast<const uint4 *>((j[u] < n_occ ? Kh : Kn) + off);
-                vv[u] = *reinterpret_cast<const uint4 *>((j[u] < n_occ ? Vh : Vn) + off);
+                int j = s < k ? sel_l[s] : -1;
+                if (j == s && s < n_occ) j = -1;               // stays where it is
+                const size_t off = (size_t)(j < n_occ ? max(j, 0) : j - n_occ) * ROWB + li * 16;
+                r.j[u] = j;
+                r.k[u] = *reinterpret_cast<const uint4 *>((j < n_occ ? Kh : Kn) + off);
+                r.v[u] = *reinterpret_cast<const uint4 *>((j < n_occ ? Vh : Vn) + off);
             }
+        };
+        auto write = [&](Rows &r, int s0) {
 #pragma unroll
-            for (int u = 0; u < UNR; ++u)
-                asm volatile("" : "+v"(kv[u].x), "+v"(kv[u].y), "+v"(kv[u].z), "+v"(kv[u].w), "+v"(vv[u].x),
-                             "+v"(vv[u].y), "+v"(vv[u].z), "+v"(vv[u].w));
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-            __syncthreads();
+            for (int u = 0; u < UNR; ++u) { pin(r.k[u]); pin(r.v[u]); }      // (they have arrived)
+            lds_barrier();
 #pragma unroll
             for (int u = 0; u < UNR; ++u) {
                 const int s = s0 + u * RPR + rsub;
-                if (j[u] >= 0) {
-                    *reinterpret_cast<uint4 *>(Kh + (size_t)s * ROWB + li * 16) = kv[u];
-                    *reinterpret_cast<uint4 *>(Vh + (size_t)s * ROWB + li * 16) = vv[u];
+                if (r.j[u] >= 0) {
+                    *reinterpret_cast<uint4 *>(Kh + (size_t)s * ROWB + li * 16) = r.k[u];
+                    *reinterpret_cast<uint4 *>(Vh + (size_t)s * ROWB + li * 16) = r.v[u];
                 }
             }
+        };
+        Rows even, odd;
+        request(even, 0);
+#pragma unroll
+        for (int i = 0; i < OWN; ++i) {
+            if (i * SG_NT >= k) break;
+            asm volatile("" ::"v"(p[i]), "v"(a[i]));
+        }
+        lds_barrier();                       // every wave has its positions and scores
+#pragma unroll
+        for (int i = 0; i < OWN; ++i) {
+            if (i * SG_NT >= k) break;
+            const int s = i * SG_NT + tid;
+            if (s < k) {
+                const bool any = sel_l[s] >= 0;
+                pos_g[hoff + s] = any ? p[i] : -1;
+                acc_g[hoff + s] = any ? a[i] : 0.f;
+            }
+        }
+        for (int s0 = 0; s0 < k; s0 += 2 * ROUND) {
+            request(odd, s0 + ROUND);        // (past the end: row 0, not written)
+            write(even, s0);
+            request(even, s0 + 2 * ROUND);
+            write(odd, s0 + ROUND);
         }
         return;
     }
-    // bookkeeping of this workgroup's slots
-    for (int s = sb + tid; s < se; s += SG_NT) {
-        const int j = sel_l[s - sb];
-        pos_g[hoff + s] = j >= 0 ? pos_of(j) : -1;
-        acc_g[hoff + s] = j >= 0 ? sc_of(j) : 0.f;
-    }
+    // bookkeeping of this workgroup's slots: requested here, stored behind the row copy (beyond the
+    // first SG_NT slots: all of it there)
+    const int own = sb + tid < se ? sel_l[tid] : -1;
+    const int own_pos = pos_of(max(own, 0));
+    const float own_score = sc_of(max(own, 0));
+    auto store_bookkeeping = [&] {
+        if (sb + tid < se) {
+            pos_g[hoff + sb + tid] = own >= 0 ? own_pos : -1;
+            acc_g[hoff + sb + tid] = own >= 0 ? own_score : 0.f;
+        }
+        for (int s = sb + tid + SG_NT; s < se; s += SG_NT) {
+            const int j = sel_l[s - sb];
+            pos_g[hoff + s] = j >= 0 ? pos_of(j) : -1;
+            acc_g[hoff + s] = j >= 0 ? sc_of(j) : 0.f;
+        }
+    };
     if constexpr (QDT >= 0) {
         // quantising gather: D/8 lanes per row, 8 elements each; an aligned group of 8
         // lanes is one group of 64 elements
@@ -395,6 +464,7 @@ __global__ __launch_bounds__(SG_NT, 4) void select_gather_kernel(
                 }
             }
         }
+        store_bookkeeping();
         return;
     }
     // gather rows: LPR lanes copy one row of ROWB bytes
@@ -425,6 +495,7 @@ __global__ __launch_bounds__(SG_NT, 4) void select_gather_kernel(
             }
         }
     }
+    store_bookkeeping();
 }
 
 // Marks every slot free (acc = 0, pos = -1).  Slot 0 of every head is what a step on an
@@ -483,13 +554,18 @@ hipError_t launch_select(const h2o_cache &c, const void *K, const void *V, const
     if (const int most = (c.k + 31) / 32; parts > most) parts = most;
     const int part_slots = (c.k + parts - 1) / parts;
     parts = (c.k + part_slots - 1) / part_slots;
-    // Keys in registers: 8 per thread up to 4096 candidates, 32 up to 16 384 (window mode;
-    // the pattern modes, whose sweeps also test the pattern, keep them in LDS).
+    // Sixteen waves per workgroup instead of eight where every workgroup has a CU to itself and the
+    // selection is long (us, eight / sixteen waves, reset included: 32 heads, 3277 of 16 384
+    // 39.6 / 37.7, 16 heads binary32, 1000 of 8192 18.9 / 17.6, 32 heads, 2048 of 30 000 102 / 66; 128 heads, 819 of
+    // 4096 30.5 / 31.3, 8 heads, 800 of 4096 11.3 / 11.9; two workgroups to a CU: 512 heads, 410 of 2048 54.4 / 60.7).
     const bool window = c.cfg.protect == H2O_PROTECT_RECENT;
-    const int keys = window && n <= 8 * SG_NT    ? 8
-                     : window && n <= 32 * SG_NT ? 32
-                     : n <= SG_LDS_KEYS          ? SG_KEYS_LDS
-                                                 : SG_KEYS_NONE;
+    const bool wide = n > 4096 && (long long)heads * parts <= 256;
+    // Keys in registers: 8 per thread up to 4096 (sixteen waves: 8192) candidates, 32 (16) up to
+    // 16 384 (window mode; the pattern modes, whose sweeps also test the pattern, keep them in LDS).
+    const int keys = window && n <= (wide ? 8192 : 4096) ? 8
+                     : window && n <= 16384              ? 32
+                     : n <= SG_LDS_KEYS                  ? SG_KEYS_LDS
+                                                         : SG_KEYS_NONE;
     const size_t smem = (size_t)part_slots * sizeof(int) + (keys == SG_KEYS_LDS && n > c.k ? (size_t)n * 4 : 0);
     auto launch = [&](auto kern, std::atomic<uint64_t> &raised) -> hipError_t {
         if (smem > 32 * 1024) {
@@ -497,15 +573,17 @@ hipError_t launch_select(const h2o_cache &c, const void *K, const void *V, const
                 allow_lds(reinterpret_cast<const void *>(kern), (SG_LDS_KEYS + H2O_MAX_BUDGET) * 4, raised);
             if (e != hipSuccess) return e;
         }
-        hipLaunchKernelGGL(kern, dim3((unsigned)heads * parts), dim3(SG_NT), smem, st, Kp, Vp, score, base,
+        hipLaunchKernelGGL(kern, dim3((unsigned)heads * parts), dim3(wide ? 1024 : 512), smem, st, Kp, Vp, score, base,
                            pos_in, n, t_new, c.K, c.V, c.acc, c.pos, c.k, c.cfg.heavy, c.cfg.recent,
                            c.cfg.rank, c.cfg.protect, c.cfg.stride, parts, part_slots, n_occ);
         return hipGetLastError();
     };
 #define H2O_SG1(RB, QDT, PAT, KEYS)                                                             \
     do {                                                                                        \
-        static std::atomic<uint64_t> raised{0};                                                 \
-        return launch(select_gather_kernel<RB, QDT, PAT, KEYS, COMPACT>, raised);               \
+        static std::atomic<uint64_t> raised{0}, raised_wide{0};                                 \
+        constexpr int WKEYS = KEYS == 32 ? 16 : KEYS;                                           \
+        return wide ? launch(select_gather_kernel<RB, QDT, PAT, WKEYS, COMPACT, 1024>, raised_wide) \
+                    : launch(select_gather_kernel<RB, QDT, PAT, KEYS, COMPACT, 512>, raised);   \
     } while (0)
 #define H2O_SG(RB, QDT)                                                                         \
     do {                                                                                        \
