@@ -289,7 +289,7 @@ __device__ __forceinline__ void prefill_pass(
         // Of the tiles that touch the block's diagonal, a wave's own 32 rows straddle
         // only one; those in front of it are fully visible to the wave and need no
         // mask arithmetic (wave-uniform test).
-        const bool clear = COLSUM ? (off + r0 >= w0 + 31 && r0 + GN <= nq) : (r0 + GN - 1 <= off + w0);
+        const bool clear = !COLSUM && r0 + GN - 1 <= off + w0;
         f32x16 acc[MB];
         if (live) {
             __builtin_amdgcn_s_setprio(2);
@@ -347,13 +347,12 @@ __device__ __forceinline__ void prefill_pass(
                 // the scale is folded into the exponent's fma
                 if constexpr (MASKED) {
                     if (!clear) {
+                        const int last = off + srow - r0 - 4 * half;     // last visible row of this lane's
 #pragma unroll
                         for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-                            for (int v = 0; v < 16; ++v) {
-                                const int j = r0 + mb * 32 + 8 * (v >> 2) + 4 * half + (v & 3);
-                                if (j > off + srow) acc[mb][v] = -INFINITY;
-                            }
+                            for (int v = 0; v < 16; ++v)
+                                if (mb * 32 + 8 * (v >> 2) + (v & 3) > last) acc[mb][v] = -INFINITY;
                     }
                 }
                 float mx = m_run;
@@ -378,28 +377,42 @@ __device__ __forceinline__ void prefill_pass(
                 // key j = srow: need j <= off + i, i < nq
                 const float *ll = lse_l + lb * BN + part * GN;
                 float sum0 = 0.f, sum1 = 0.f;
+                // this lane's rows of the tile from `first` on and in front of `end` count
+                const int first = srow - off - r0 - 4 * half, end = nq - r0 - 4 * half;
+                auto add_up = [&](auto first_tag, auto end_tag) {
 #pragma unroll
-                for (int mb = 0; mb < MB; ++mb)
+                    for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-                    for (int gq = 0; gq < 4; ++gq) {
-                        const float4 l4 = *reinterpret_cast<const float4 *>(ll + mb * 32 + 8 * gq + 4 * half);
-                        const float lv[4] = {l4.x, l4.y, l4.z, l4.w};
-                        float x[4];
+                        for (int gq = 0; gq < 4; ++gq) {
+                            const float4 l4 = *reinterpret_cast<const float4 *>(ll + mb * 32 + 8 * gq + 4 * half);
+                            const float lv[4] = {l4.x, l4.y, l4.z, l4.w};
+                            float x[4];
 #pragma unroll
-                        for (int e = 0; e < 4; ++e)
-                            x[e] = fmaf(acc[mb][4 * gq + e], c2, -lv[e]);
-                        if constexpr (MASKED) {
-                            if (!clear) {
-#pragma unroll
-                                for (int e = 0; e < 4; ++e) {
-                                    const int i = r0 + mb * 32 + 8 * gq + 4 * half + e;
-                                    if (off + i < srow || i >= nq) x[e] = -INFINITY;
-                                }
+                            for (int e = 0; e < 4; ++e) {
+                                x[e] = fmaf(acc[mb][4 * gq + e], c2, -lv[e]);
+                                if constexpr (decltype(first_tag)::value)
+                                    x[e] = mb * 32 + 8 * gq + e < first ? -INFINITY : x[e];
+                                if constexpr (decltype(end_tag)::value)
+                                    x[e] = mb * 32 + 8 * gq + e >= end ? -INFINITY : x[e];
                             }
+                            sum0 += __builtin_amdgcn_exp2f(x[0]) + __builtin_amdgcn_exp2f(x[2]);
+                            sum1 += __builtin_amdgcn_exp2f(x[1]) + __builtin_amdgcn_exp2f(x[3]);
                         }
-                        sum0 += __builtin_amdgcn_exp2f(x[0]) + __builtin_amdgcn_exp2f(x[2]);
-                        sum1 += __builtin_amdgcn_exp2f(x[1]) + __builtin_amdgcn_exp2f(x[3]);
-                    }
+                };
+                // (what a tile needs is the same for the whole wave; tested per element, a masked
+                // tile took three times the instructions: both passes 1 to 6 % slower, 256
+                // heads x 300 24.3 us against 22.8, 32 x 1531 40.8 / 39.0, 128 x 4096 555 / 549)
+                if constexpr (!MASKED) {
+                    add_up(std::false_type{}, std::false_type{});
+                } else if constexpr (ROWB >= 512) {               // (no registers left for three ways)
+                    add_up(std::true_type{}, std::true_type{});
+                } else if (r0 + GN > nq) {
+                    add_up(std::true_type{}, std::true_type{});
+                } else if (off + r0 < w0 + 31) {
+                    add_up(std::true_type{}, std::false_type{});
+                } else {
+                    add_up(std::false_type{}, std::false_type{});
+                }
                 c_run += sum0 + sum1;
             }
         }
