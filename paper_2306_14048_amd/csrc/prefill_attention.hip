@@ -108,11 +108,14 @@ __device__ inline uint2 read_keys4(const unsigned char *lds)
 // G: groups of four waves over the same 128 queries.  With two, a tile is 128 keys and each
 // group takes 64 of them; the two partial results are joined at the end.  For grids that
 // leave CUs idle: the longest block has half the steps.
-template <int DT, int D, bool TWO, int G>
+// SKEW: the groups run one phase apart, with a barrier between a step's MFMAs and its softmax.  Group
+// g copies its own half of a tile at the start of its step u - 1 into rows that it has read
+// last in step u - 2, and waits for them in front of the barrier that ends the step.
+template <int DT, int D, bool TWO, int G, bool SKEW>
 __global__ __launch_bounds__(ARW * G * 64, 2) void prefill_attn_kernel(
     const char *__restrict__ Qg, const char *__restrict__ Kg, const char *__restrict__ Vg,
-    FrontRows kf, FrontRows vf, int nq, int nk, int heads, float c2, float *__restrict__ lse2, float *__restrict__ lse_nat,
-    char *__restrict__ Og)
+    FrontRows kf, FrontRows vf, int nq, int nk, int heads, float c2, float *__restrict__ lse2,
+    float *__restrict__ lse_nat, char *__restrict__ Og)
 {
     const int off = nk - nq;               // key position of query 0
     constexpr int ROWB = D * 2;            // bytes per Q/K row
@@ -169,11 +172,15 @@ __global__ __launch_bounds__(ARW * G * 64, 2) void prefill_attn_kernel(
     // key tiles of this block (>= 1): up to the one that holds the last query's own key
     const int T = min((nk + SBN - 1) / SBN, (off + s0 + SROWS + SBN - 1) / SBN);
 
-    // copy plan: instruction c of wave w fills LDS chunks [(c*ANW + w)*64, +64)
+    // Copy plan: instruction c of a wave fills 64 chunks of LDS, the waves side by side; groups that
+    // run one phase apart copy the rows that they read themselves, so that only their own waves
+    // wait for them.
+    const int first_copy = SKEW ? grp * CPTK * ARW + rw : wave;
+    constexpr int copy_step = SKEW ? ARW : ANW;
     unsigned koff[CPTK], kchunk[CPTK], vchunk[CPTK];
 #pragma unroll
     for (int c = 0; c < CPTK; ++c) {
-        const unsigned q = (unsigned)(c * ANW + wave) * 64u + lane;
+        const unsigned q = (unsigned)(first_copy + c * copy_step) * 64u + lane;
         const unsigned r = q / CPRK, pos = q % CPRK;
         koff[c] = r * ROWB;
         kchunk[c] = (pos ^ ((r >> RSHK) & KMASKK)) * 16u;
@@ -185,7 +192,7 @@ __global__ __launch_bounds__(ARW * G * 64, 2) void prefill_attn_kernel(
     const i32x4 rsrc_vf = TWO ? make_rsrc(vf.front + (size_t)head * vf.stride * ROWB, (unsigned)nf * ROWB) : rsrc_v;
     const unsigned edge = (unsigned)nf * ROWB;
     const unsigned lds_w = __builtin_amdgcn_readfirstlane(
-        (unsigned)reinterpret_cast<size_t>(smem) + wave * 1024);
+        (unsigned)reinterpret_cast<size_t>(smem) + first_copy * 1024);
     const unsigned last_row_off = (unsigned)(nk - 1) * ROWB;
     // stage u holds what matrix phase u reads: key tile u and value tile u-1
     // (indices clamped to existing tiles: the first stage's value tile and the
@@ -199,22 +206,22 @@ __global__ __launch_bounds__(ARW * G * 64, 2) void prefill_attn_kernel(
             if (TWO && t0 < edge) {
                 if (t0 + SBN * ROWB <= edge) {                 // whole tile in front
 #pragma unroll
-                    for (int c = 0; c < CPTK; ++c) dma16(rsrc_f, koff[c] + chunk[c], t0, lds + c * ANW * 1024);
+                    for (int c = 0; c < CPTK; ++c) dma16(rsrc_f, koff[c] + chunk[c], t0, lds + c * copy_step * 1024);
                 } else {                                       // rows of both
 #pragma unroll
                     for (int c = 0; c < CPTK; ++c) {
                         const unsigned off = min(t0 + koff[c], last_row_off);
-                        if (off < edge) dma16(rsrc_f, off + chunk[c], 0u, lds + c * ANW * 1024);
-                        else dma16(rsrc, off - edge + chunk[c], 0u, lds + c * ANW * 1024);
+                        if (off < edge) dma16(rsrc_f, off + chunk[c], 0u, lds + c * copy_step * 1024);
+                        else dma16(rsrc, off - edge + chunk[c], 0u, lds + c * copy_step * 1024);
                     }
                 }
             } else if (t0 + SBN * ROWB <= (unsigned)nk * ROWB) {
 #pragma unroll
-                for (int c = 0; c < CPTK; ++c) dma16(rsrc, koff[c] + chunk[c], t0 - edge, lds + c * ANW * 1024);
+                for (int c = 0; c < CPTK; ++c) dma16(rsrc, koff[c] + chunk[c], t0 - edge, lds + c * copy_step * 1024);
             } else {
 #pragma unroll
                 for (int c = 0; c < CPTK; ++c)
-                    dma16(rsrc, min(t0 + koff[c], last_row_off) - edge + chunk[c], 0u, lds + c * ANW * 1024);
+                    dma16(rsrc, min(t0 + koff[c], last_row_off) - edge + chunk[c], 0u, lds + c * copy_step * 1024);
             }
         };
         tile(rsrc_k, rsrc_kf, kt, kchunk, base);
@@ -267,6 +274,7 @@ __global__ __launch_bounds__(ARW * G * 64, 2) void prefill_attn_kernel(
     for (int f = 0; f < NF; ++f)
         asm volatile("" ::"v"(st[f].x), "v"(st[f].y), "v"(st[f].z), "v"(st[f].w));
     wg_barrier();
+    if (SKEW && grp == 1) wg_barrier();     // the second group runs one phase behind
 
     int stg = 0;
     // Iteration u: matrix phase = P.V of tile u-1 and Q.K of tile u, vector phase
@@ -324,6 +332,8 @@ __global__ __launch_bounds__(ARW * G * 64, 2) void prefill_attn_kernel(
             __builtin_amdgcn_sched_barrier(0);
         }
         __builtin_amdgcn_s_setprio(0);
+        // (m_run as an operand: the softmax, which starts from it, stays behind the barrier)
+        if constexpr (SKEW) asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" : "+v"(m_run) : : "memory");
 
         if (live) {
             if constexpr (MASKED) {
@@ -381,7 +391,10 @@ __global__ __launch_bounds__(ARW * G * 64, 2) void prefill_attn_kernel(
         live_prev = live;
         stg ^= 1;
         dma_wait_upto<0>();                    // the next iteration's stage has landed
-        wg_barrier();
+        if constexpr (SKEW)
+            asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" : "+v"(m_run), "+v"(l_run) : : "memory");
+        else
+            wg_barrier();
     };
     {
         const int t_diag0 = min(T, (off + s0 + 1) / SBN);   // tiles every query of the block sees in full
@@ -389,6 +402,7 @@ __global__ __launch_bounds__(ARW * G * 64, 2) void prefill_attn_kernel(
         for (int u = t_diag0; u < T; ++u) step(u, std::true_type{}, std::false_type{});
         step(T, std::false_type{}, std::true_type{});
     }
+    if (SKEW && grp == 0) wg_barrier();     // the barrier the second group spent at the start
 
     // ---- the groups' parts of a query, brought to the larger reference ----------------
     if constexpr (G > 1) {
@@ -437,7 +451,7 @@ __global__ __launch_bounds__(ARW * G * 64, 2) void prefill_attn_kernel(
     }
 }
 
-template <int DT, int D, int G>
+template <int DT, int D, int G, bool SKEW>
 hipError_t launch_attn(const h2o_config &cfg, double scale, const void *Q, const void *K,
                        const void *V, const FrontRows &kf, const FrontRows &vf, int nq, int nk, void *vcopy,
                        float *lse2, float *lse_nat, void *out, hipStream_t st)
@@ -455,7 +469,7 @@ hipError_t launch_attn(const h2o_config &cfg, double scale, const void *Q, const
     constexpr int ANW = ARW * G;
     constexpr size_t smem = (size_t)ANS * 2 * ABN * G * D * 2;
     static_assert(G == 1 || smem >= (size_t)ARW * (D / 32 * 16 + 2) * 256, "the stages hold a group's parts");
-    auto kern = kf.rows ? prefill_attn_kernel<DT, D, true, G> : prefill_attn_kernel<DT, D, false, G>;
+    auto kern = kf.rows ? prefill_attn_kernel<DT, D, true, G, SKEW> : prefill_attn_kernel<DT, D, false, G, SKEW>;
     static std::atomic<uint64_t> raised[2] = {};
     if (smem > 48 * 1024) {
         e = allow_lds(reinterpret_cast<const void *>(kern), (int)smem, raised[kf.rows != 0]);
@@ -486,9 +500,17 @@ hipError_t h2o_launch_prefill_attention(const h2o_config &cfg, double scale, con
     const int d = cfg.head_dim;
     if (nq < 1 || nq > nk) return hipErrorInvalidValue;
     const bool few = two_groups(cfg.batch * cfg.heads, nq, nk, false, d);
-#define H2O_ATTN(DT, D)                                                                                   \
-    (few ? launch_attn<DT, D, 2>(cfg, scale, Q, K, V, Kf, Vf, nq, nk, vcopy, lse2, lse_nat, out, st)      \
-         : launch_attn<DT, D, 1>(cfg, scale, Q, K, V, Kf, Vf, nq, nk, vcopy, lse2, lse_nat, out, st))
+    // Two groups one phase apart: while one is in its MFMAs the other is in its softmax.  That takes a
+    // second barrier per tile, which short streams behind more blocks than CUs do not pay back
+    // (d = 128, f16, us, together / apart): to 256 blocks 8 heads x 4096 66 / 61, 16 x 1531 28.6 / 26.7, 32 x 1000
+    // 21.5 / 20.6, 8 x 500 14.0 / 13.8, a chunk of 1024 on 410 cached ones, 32 heads, 66.5 / 61.2 (the whole call);
+    // more: 32 x 1531 37.3 / 36.5, 32 x 1100 24.6 / 23.5, 32 x 1400 28.6 / 28.6, 40 x 900 23.1 / 23.6, 64 x 640
+    // 20.3 / 20.8; d = 64, 32 x 1200 16.8 / 15.6, 64 x 700 13.6 / 15.2.
+    const bool apart = few && ((long long)cfg.batch * cfg.heads * ((nq + ARW * 32 - 1) / (ARW * 32)) <= 256 || nk >= 1100);
+#define H2O_ATTN(DT, D)                                                                                         \
+    (apart ? launch_attn<DT, D, 2, true>(cfg, scale, Q, K, V, Kf, Vf, nq, nk, vcopy, lse2, lse_nat, out, st)    \
+     : few ? launch_attn<DT, D, 2, false>(cfg, scale, Q, K, V, Kf, Vf, nq, nk, vcopy, lse2, lse_nat, out, st)   \
+           : launch_attn<DT, D, 1, false>(cfg, scale, Q, K, V, Kf, Vf, nq, nk, vcopy, lse2, lse_nat, out, st))
     if (cfg.dtype == H2O_F16) return d == 64 ? H2O_ATTN(H2O_F16, 64) : H2O_ATTN(H2O_F16, 128);
     return d == 64 ? H2O_ATTN(H2O_BF16, 64) : H2O_ATTN(H2O_BF16, 128);
 #undef H2O_ATTN
