@@ -83,7 +83,8 @@ constexpr int NLB = 4;         // row-statistic buffers (pass 2; read one phase 
 // G (four-wave shape): groups of four waves over the same 128 stationary rows.  With two, a
 // tile has twice the rows and each group takes half of them; the parts are joined at the
 // end.  For grids that leave CUs idle: the longest block has half the steps.
-template <int DT, int D, int MB, int RWV, int G, bool TWO, bool COLSUM>
+// SKEW: the two halves of eight waves run one phase apart.
+template <int DT, int D, int MB, int RWV, int G, bool TWO, bool COLSUM, bool SKEW>
 __device__ __forceinline__ void prefill_pass(
     const char *__restrict__ Qg, const char *__restrict__ Kg, const FrontRows &kf, int nq, int nk, int heads,
     float c2, float *__restrict__ lse2, float *__restrict__ colsum)
@@ -120,7 +121,7 @@ __device__ __forceinline__ void prefill_pass(
     // (the wave index as a scalar: branches on it are then uniform for the compiler too)
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int half = lane >> 5, l32 = lane & 31;
-    constexpr bool SKEW = RWV == 8;       // two wave groups one phase apart
+    static_assert(!SKEW || NWV == 8, "two groups of four waves");
     const int grp = SKEW ? wave >> 2 : 0; // ping-pong group
     const int rw = wave % RWV, part = G > 1 ? wave / RWV : 0;   // its 32 stationary rows, its part of a tile
     // The nq queries are the LAST nq positions of the nk keys (nq == nk for a whole
@@ -480,19 +481,19 @@ __global__ __launch_bounds__(8 * 64, 4) void prefill_pass_kernel(
     const char *__restrict__ Qg, const char *__restrict__ Kg, FrontRows kf, int nq, int nk, int heads, float c2,
     float *__restrict__ lse2, float *__restrict__ colsum)
 {
-    prefill_pass<DT, D, MB, 8, 1, false, COLSUM>(Qg, Kg, kf, nq, nk, heads, c2, lse2, colsum);
+    prefill_pass<DT, D, MB, 8, 1, false, COLSUM, true>(Qg, Kg, kf, nq, nk, heads, c2, lse2, colsum);
 }
 
-template <int DT, int D, int MB, int G, bool TWO, bool COLSUM>
+template <int DT, int D, int MB, int G, bool TWO, bool COLSUM, bool SKEW>
 __global__ __launch_bounds__(4 * G * 64, G == 1 ? 4 : 2) void prefill_pass4_kernel(
     const char *__restrict__ Qg, const char *__restrict__ Kg, FrontRows kf, int nq, int nk, int heads, float c2,
     float *__restrict__ lse2, float *__restrict__ colsum)
 {
-    prefill_pass<DT, D, MB, 4, G, TWO, COLSUM>(Qg, Kg, kf, nq, nk, heads, c2, lse2, colsum);
+    prefill_pass<DT, D, MB, 4, G, TWO, COLSUM, SKEW>(Qg, Kg, kf, nq, nk, heads, c2, lse2, colsum);
 }
 
 // TWO: streamed rows in two places (pass 1 with keys in front, four waves)
-template <int DT, int D, int RWV, int G, bool TWO, bool COLSUM>
+template <int DT, int D, int RWV, int G, bool TWO, bool COLSUM, bool SKEW = false>
 hipError_t launch_pass(const h2o_config &cfg, double scale, const void *Q, const void *K, const FrontRows &kf,
                        int nq, int nk, float *lse2, float *colsum, hipStream_t st)
 {
@@ -504,7 +505,7 @@ hipError_t launch_pass(const h2o_config &cfg, double scale, const void *Q, const
     const int heads = cfg.batch * cfg.heads;
     const int nblk = ((COLSUM ? nk : nq) + SROWS - 1) / SROWS;
     const float c2 = (float)(scale * 1.4426950408889634);
-    auto kern = RWV == 8 ? prefill_pass_kernel<DT, D, MB, COLSUM> : prefill_pass4_kernel<DT, D, MB, G, TWO, COLSUM>;
+    auto kern = RWV == 8 ? prefill_pass_kernel<DT, D, MB, COLSUM> : prefill_pass4_kernel<DT, D, MB, G, TWO, COLSUM, SKEW>;
     if (smem > 48 * 1024) {
         static std::atomic<uint64_t> raised{0};
         const hipError_t e = allow_lds(reinterpret_cast<const void *>(kern), (int)smem, raised);
@@ -547,9 +548,19 @@ hipError_t pick_waves(const h2o_config &cfg, double scale, const void *Q, const 
 {
     const int rows = COLSUM ? nk : nq, streamed = COLSUM ? nq : nk;
     const bool few = two_groups(cfg.batch * cfg.heads, rows, streamed, DT == H2O_F32, D);
+    // The two groups one phase apart, as the halves of eight waves are: one barrier more per tile, which
+    // short streams, the rest of a second round of blocks and binary32 (a pass is its MFMAs there) do not pay
+    // back.  Both passes, f16, d = 128, us, together / apart: to 256 blocks 8 heads x 4096 81.8 / 74.1, 16 x 1531
+    // 35.2 / 33.4, 32 x 1000 27.0 / 26.0, 32 x 700 21.4 / 21.8, 8 x 500 17.8 / 18.5; more: 32 x 1531 37.8 / 40.0, 24 x 2048
+    // 44.9 / 45.0, 24 x 2500 65.4 / 64.2, 8 x 6000 120.6 / 110.0, 16 x 4000 113 / 104; d = 64 8 x 4096 61.6 / 60.3, 16 x 4000
+    // 70.8 / 71.4, 32 x 700 17.3 / 17.8; binary32 16 x 1500 209 / 213.
+    constexpr bool CAN = DT != H2O_F32 && D == 128;
+    const bool apart = CAN && few &&
+                       (streamed >= 2500 || (streamed >= 800 && (long long)cfg.batch * cfg.heads * ((rows + 127) / 128) <= 256));
     if constexpr (!COLSUM)
         if (kf.rows)
-            return few ? launch_pass<DT, D, 4, 2, true, COLSUM>(cfg, scale, Q, K, kf, nq, nk, lse2, colsum, st)
+            return apart ? launch_pass<DT, D, 4, 2, true, COLSUM, CAN>(cfg, scale, Q, K, kf, nq, nk, lse2, colsum, st)
+                   : few ? launch_pass<DT, D, 4, 2, true, COLSUM>(cfg, scale, Q, K, kf, nq, nk, lse2, colsum, st)
                        : launch_pass<DT, D, 4, 1, true, COLSUM>(cfg, scale, Q, K, kf, nq, nk, lse2, colsum, st);
     // Eight waves pay off when the grid fills the chip several times over with long streams:
     // the line is drawn on blocks x streamed rows.  Both passes, us, eight / four waves:
@@ -564,7 +575,8 @@ hipError_t pick_waves(const h2o_config &cfg, double scale, const void *Q, const 
     constexpr long long LINE = DT != H2O_F32 && D == 128 ? 3000000 : 16000000;
     if (blocks8 * streamed > LINE || (!few && eight_fill_the_chip<DT, D>(blocks8, rows, streamed)))
         return launch_pass<DT, D, 8, 1, false, COLSUM>(cfg, scale, Q, K, kf, nq, nk, lse2, colsum, st);
-    return few ? launch_pass<DT, D, 4, 2, false, COLSUM>(cfg, scale, Q, K, kf, nq, nk, lse2, colsum, st)
+    return apart ? launch_pass<DT, D, 4, 2, false, COLSUM, CAN>(cfg, scale, Q, K, kf, nq, nk, lse2, colsum, st)
+           : few ? launch_pass<DT, D, 4, 2, false, COLSUM>(cfg, scale, Q, K, kf, nq, nk, lse2, colsum, st)
                : launch_pass<DT, D, 4, 1, false, COLSUM>(cfg, scale, Q, K, kf, nq, nk, lse2, colsum, st);
 }
 

@@ -35,3 +35,20 @@ def test_attention_rows_and_normalisers(dt, d, heads, n):
         assert float(err.max()) <= tol, "head %d: %g" % (h, float(err.max()))
         ref = torch.logsumexp(s, -1)
         assert torch.all((lse[h].double() - ref).abs() <= 1e-5 * (1 + ref.abs()))
+
+
+@pytest.mark.parametrize("dt,heads,n", [
+    ("f16", 2, 799), ("f16", 2, 800), ("bf16", 3, 833), ("f16", 1, 900), ("bf16", 36, 801), ("f16", 37, 897),
+    ("f16", 13, 2500),            # 260 blocks, a long stream
+])
+def test_column_sums_of_groups_apart(dt, heads, n):
+    from paper_2306_14048_amd import binding as hb
+    g = torch.Generator(device="cuda").manual_seed(n)
+    Q, K = (torch.randn(1, heads, n, 128, generator=g, device="cuda").to(DT[dt]) for _ in range(2))
+    cfg = hb.make_config(1, heads, 128, 8, 8, DT[dt])
+    got = hb.prefill_colsum(cfg, Q, K)[0].double()
+    hidden = torch.ones(n, n, dtype=torch.bool, device="cuda").triu(1)
+    for h in range(heads):
+        s = (Q[0, h].double() @ K[0, h].double().t() / 128 ** 0.5).masked_fill(hidden, float("-inf"))
+        ref = torch.softmax(s, -1).sum(0)
+        assert torch.all((got[h] - ref).abs() <= 3e-5 * ref + 1e-30), "head %d" % h
