@@ -68,6 +68,7 @@ constexpr int DPP_XOR1 = 0xB1;         // quad_perm [1,0,3,2]
 constexpr int DPP_XOR2 = 0x4E;         // quad_perm [2,3,0,1]
 constexpr int DPP_HALF_MIRROR = 0x141; // lane i <-> 7-i inside each 8 lanes
 constexpr int DPP_MIRROR = 0x140;      // lane i <-> 15-i inside each 16 lanes
+constexpr int DPP_ROR8 = 0x128;        // lane i <-> i^8 inside each 16 lanes (a rotation by 8)
 
 template <int CTRL> __device__ inline int dpp(int v)
 {
@@ -83,6 +84,24 @@ template <int CTRL> __device__ inline unsigned long long dpp(unsigned long long 
     return ((unsigned long long)hi << 32) | lo;
 }
 
+// Sum of a over the lanes l and l ^ M, M = 8, 16 or 32, in registers: the swap of a register with
+// itself leaves this lane's value in one result and the partner's in the other.  (A shuffle
+// through LDS takes some 130 cycles, and these stand in the tail of a step, where nothing
+// else is left to do: 300 to 400 cycles of a step's 4600 on 8 heads x 64 slots.)
+template <int M> __device__ inline float pair_sum(float a)
+{
+    const unsigned u = __float_as_uint(a);
+    if constexpr (M == 8) {
+        return a + __int_as_float(dpp<DPP_ROR8>(__float_as_int(a)));
+    } else if constexpr (M == 16) {
+        const auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+        return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+    } else {
+        static_assert(M == 32, "");
+        const auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+        return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+    }
+}
 // After the xor-1 and xor-2 steps all four lanes of a quad agree, so the two
 // mirror steps act as xor-4 and xor-8: every lane ends with its group's total.
 template <int LANES> __device__ inline double group_sum(double a)
@@ -138,9 +157,10 @@ template <int EPL, int LPR, int D>
 __device__ inline void wave_output_to_lds(float (&o)[EPL], float *o_l, int wave, int sub, int li)
 {
 #pragma unroll
-    for (int m = LPR; m < 64; m <<= 1) {
-#pragma unroll
-        for (int i = 0; i < EPL; ++i) o[i] += __shfl_xor(o[i], m, 64);
+    for (int i = 0; i < EPL; ++i) {
+        if constexpr (LPR <= 8) o[i] = pair_sum<8>(o[i]);
+        if constexpr (LPR <= 16) o[i] = pair_sum<16>(o[i]);
+        o[i] = pair_sum<32>(o[i]);
     }
     if (sub == 0) {
 #pragma unroll
