@@ -147,6 +147,45 @@ static inline bool two_groups(int heads, int rows, int streamed, bool f32, int d
     return streamed >= (d == 128 ? 600 : 480) && blocks <= (streamed >= 1500 ? 512 : 384);
 }
 
+// How a compression of n candidates per head into k slots is laid out: workgroups per head, slots
+// of each, and whether they have sixteen waves instead of eight.
+constexpr int SG_LDS_KEYS = 28672;     // ranking keys kept in LDS up to this many candidates (112 KiB)
+struct SelectPlan { int parts, part_slots; bool wide; };
+static inline SelectPlan select_plan(int heads, int k, int n, bool in_place)
+{
+    // Workgroups per head: enough to give every CU one, but at least 32 slots each (one round of
+    // the row copy); in place one, which alone knows what it has read.
+    int parts = in_place ? 1 : (256 + heads - 1) / heads;
+    // Beyond SG_LDS_KEYS candidates every sweep reads the scores again.  A head's workgroups go to
+    // different XCDs, so each XCD reads those of parts / 8 of the heads (all from 8 parts on):
+    // that many have to stay in its 4 MB L2.  us, parts halved / not (eight waves): 32 heads, 2048 of 40 000
+    // (2.6 / 5.1 MB) 123 / 180 (one workgroup per head 138), 64 heads 131 / 185, 64 heads, 200 of 28 673
+    // (1.8 / 3.7 MB) 76 / 114; 16 heads, 2048 of 40 000 (2.6 MB as it is) 119 / 117.
+    if (n > SG_LDS_KEYS)
+        while (parts > 1 && (long long)heads * (parts < 8 ? parts : 8) * n * 4 > 8 * (3LL << 20)) parts /= 2;
+    // Every workgroup makes the whole selection.  Beyond 4096 candidates that is most of the time, and
+    // rounding up, which puts a second one on some CUs, costs more than the CUs that rounding down leaves
+    // idle.  f16, d = 128, us, reset included, up with eight waves / down with sixteen: 12 heads, 840 of 4200 14.2 /
+    // 11.5, 1600 of 8000 17.4 / 13.2, 3276 of 16 384 23.8 / 19.4, 4000 of 20 000 73 / 31, 4096 of 60 000 152 / 87; 24 heads 15.6 / 12.8,
+    // 19.1 / 16.5, 30.5 / 27.0, 82 / 39; 56 heads 18.6 / 17.0, 27.9 / 24.7, 57.7 / 47.1, 113 / 62; 112 heads 25.9 / 24.5, 49.6 /
+    // 41.6, 102 / 86, 180 / 123; 192 heads 42.2 / 41.7, 74.8 / 70.9, 145 / 138, 234 / 178.  Up to 4096 the row copy weighs as
+    // much, and two workgroups of eight waves on a CU copy faster than one (144 heads, 4-bit rows, 1500
+    // of 2048, rounded up / down, eight waves: 80 / 90; 32 heads, 306 of 1531 10.1 with one per CU, 11.5 with two).
+    if (n > 4096 && (long long)heads * parts > 256) parts = heads < 256 ? 256 / heads : 1;
+    if (const int most = (k + 31) / 32; parts > most) parts = most;
+    const int part_slots = (k + parts - 1) / parts;
+    parts = (k + part_slots - 1) / part_slots;
+    // Sixteen waves where the selection is long and a workgroup has its CU to itself: one for every CU, or
+    // more than 64 KiB of keys in LDS.  Sixteen over eight waves at the same workgroups (time, 1 to 256
+    // heads, 64 to 4096 slots): to 8192 candidates 0.87 .. 1.01 (d = 64, binary32 and averaged ranking too; 4-bit
+    // rows 0.87 .. 1.07, mean 0.96; a pattern 0.80 .. 0.99), to 16 384 0.86 .. 1.01 (4-bit 0.86 .. 1.04; pattern 0.72 .. 0.95), to
+    // 28 672 0.68 .. 0.94, beyond 0.56 .. 0.84; in place 0.5 to 12 us less per call.  257 to 1024 heads: to 8192 0.86 .. 1.09,
+    // to 16 384 1.00 .. 1.36 (pattern 0.70 .. 0.93), to 28 672 0.66 .. 0.87, beyond 0.61 .. 0.86 (pattern 0.92 .. 1.04).  Up to
+    // 4096: 128 heads, 819 of 4096 30.5 us against 31.3, 8 heads, 800 of 4096 11.3 / 11.9, in place 0.3 to 1.7 us more.
+    const bool wide = n > 4096 && ((long long)heads * parts <= 256 || n > 16384);
+    return {parts, part_slots, wide};
+}
+
 // Rounds per chunk of the one-workgroup step beyond its registers: of umax, umax - 2, umax - 4
 // and umax - 6 the one that wastes the fewest rounds on the last chunk (rounds past the
 // occupied slots re-read the last row), the deepest of equals.

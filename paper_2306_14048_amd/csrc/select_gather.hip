@@ -16,7 +16,6 @@ namespace {
 
 constexpr int SG_BITS = 11;                 // radix digit: 11 + 11 + 10 bits
 constexpr int SG_BINS = 1 << SG_BITS;
-constexpr int SG_LDS_KEYS = 28672;          // ranking keys kept in LDS up to this many candidates (112 KiB)
 // where the ranking keys live during the selection
 constexpr int SG_KEYS_NONE = 0, SG_KEYS_LDS = 1;   // (any larger value: that many registers per thread)
 
@@ -538,28 +537,9 @@ hipError_t launch_select(const h2o_cache &c, const void *K, const void *V, const
     const int heads = c.cfg.batch * c.cfg.heads;
     const int rowb = c.cfg.head_dim * c.esize;
     const char *Kp = static_cast<const char *>(K), *Vp = static_cast<const char *>(V);
-    // Workgroups per head: enough to give every CU one, but at least 32 slots each (one round
-    // of the row copy).  Two per CU were slower: each makes the whole selection (us, one / two / four,
-    // reset included, one prompt repeatedly with its keys also passed as values, so that rows
-    // come from the last-level cache and half of them are read: 32 heads, 306 of 1531 10.1 / 11.5 /
-    // 11.4; 3277 of 16 384 32.0 / 32.6 / 50; 8 heads 21 / 26 / 45; 128 heads, 819 of 4096 22.2 / 22.8 / 26.5).
-    int parts = COMPACT ? 1 : (256 + heads - 1) / heads;
-    // Beyond SG_LDS_KEYS candidates every sweep reads the scores again.  A head's workgroups go to
-    // different XCDs, so each XCD reads those of parts / 8 of the heads (all from 8 parts on):
-    // that many have to stay in its 4 MB L2.  us, parts halved / not: 32 heads, 2048 of 40 000
-    // (2.6 / 5.1 MB) 123 / 180 (one workgroup per head 138), 64 heads 131 / 185, 64 heads, 200 of 28 673
-    // (1.8 / 3.7 MB) 76 / 114; 16 heads, 2048 of 40 000 (2.6 MB as it is) 119 / 117.
-    if (n > SG_LDS_KEYS)
-        while (parts > 1 && (long long)heads * (parts < 8 ? parts : 8) * n * 4 > 8 * (3LL << 20)) parts /= 2;
-    if (const int most = (c.k + 31) / 32; parts > most) parts = most;
-    const int part_slots = (c.k + parts - 1) / parts;
-    parts = (c.k + part_slots - 1) / part_slots;
-    // Sixteen waves per workgroup instead of eight where every workgroup has a CU to itself and the
-    // selection is long (us, eight / sixteen waves, reset included: 32 heads, 3277 of 16 384
-    // 39.6 / 37.7, 16 heads binary32, 1000 of 8192 18.9 / 17.6, 32 heads, 2048 of 30 000 102 / 66; 128 heads, 819 of
-    // 4096 30.5 / 31.3, 8 heads, 800 of 4096 11.3 / 11.9; two workgroups to a CU: 512 heads, 410 of 2048 54.4 / 60.7).
-    const bool window = c.cfg.protect == H2O_PROTECT_RECENT;
-    const bool wide = n > 4096 && (long long)heads * parts <= 256;
+    const SelectPlan plan = select_plan(heads, c.k, n, COMPACT);
+    const int parts = plan.parts, part_slots = plan.part_slots;
+    const bool window = c.cfg.protect == H2O_PROTECT_RECENT, wide = plan.wide;
     // Keys in registers: 8 per thread up to 4096 (sixteen waves: 8192) candidates, 32 (16) up to
     // 16 384 (window mode; the pattern modes, whose sweeps also test the pattern, keep them in LDS).
     const int keys = window && n <= (wide ? 8192 : 4096) ? 8
@@ -578,21 +558,25 @@ hipError_t launch_select(const h2o_cache &c, const void *K, const void *V, const
                            c.cfg.rank, c.cfg.protect, c.cfg.stride, parts, part_slots, n_occ);
         return hipGetLastError();
     };
-#define H2O_SG1(RB, QDT, PAT, KEYS)                                                             \
+    // (eight waves never see more than 16 384 candidates)
+#define H2O_SG1(RB, QDT, PAT, KEYS, NT)                                                         \
     do {                                                                                        \
-        static std::atomic<uint64_t> raised{0}, raised_wide{0};                                 \
-        constexpr int WKEYS = KEYS == 32 ? 16 : KEYS;                                           \
-        return wide ? launch(select_gather_kernel<RB, QDT, PAT, WKEYS, COMPACT, 1024>, raised_wide) \
-                    : launch(select_gather_kernel<RB, QDT, PAT, KEYS, COMPACT, 512>, raised);   \
+        static std::atomic<uint64_t> raised{0};                                                 \
+        return launch(select_gather_kernel<RB, QDT, PAT, KEYS, COMPACT, NT>, raised);           \
     } while (0)
 #define H2O_SG(RB, QDT)                                                                         \
     do {                                                                                        \
-        if (window && keys == 8) H2O_SG1(RB, QDT, false, 8);                                    \
-        if (window && keys == 32) H2O_SG1(RB, QDT, false, 32);                                  \
-        if (window && keys == SG_KEYS_LDS) H2O_SG1(RB, QDT, false, SG_KEYS_LDS);                \
-        if (window) H2O_SG1(RB, QDT, false, SG_KEYS_NONE);                                      \
-        if (keys == SG_KEYS_LDS) H2O_SG1(RB, QDT, true, SG_KEYS_LDS);                           \
-        H2O_SG1(RB, QDT, true, SG_KEYS_NONE);                                                   \
+        if (!wide) {                                                                            \
+            if (window && keys == 8) H2O_SG1(RB, QDT, false, 8, 512);                           \
+            if (window) H2O_SG1(RB, QDT, false, 32, 512);                                       \
+            H2O_SG1(RB, QDT, true, SG_KEYS_LDS, 512);                                           \
+        }                                                                                       \
+        if (window && keys == 8) H2O_SG1(RB, QDT, false, 8, 1024);                              \
+        if (window && keys == 32) H2O_SG1(RB, QDT, false, 16, 1024);                            \
+        if (window && keys == SG_KEYS_LDS) H2O_SG1(RB, QDT, false, SG_KEYS_LDS, 1024);          \
+        if (window) H2O_SG1(RB, QDT, false, SG_KEYS_NONE, 1024);                                \
+        if (keys == SG_KEYS_LDS) H2O_SG1(RB, QDT, true, SG_KEYS_LDS, 1024);                     \
+        H2O_SG1(RB, QDT, true, SG_KEYS_NONE, 1024);                                             \
     } while (0)
     if constexpr (!COMPACT) {
         if (c.cfg.kv_bits == 4) {

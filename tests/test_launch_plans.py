@@ -1,0 +1,63 @@
+"""The host rules that lay a launch out, over the whole range of sizes they are asked for
+(compiled from the library's own header, no GPU needed)."""
+import os
+import subprocess
+
+import pytest
+
+from paper_2306_14048_amd import build as hb
+
+MAIN = r"""
+#include <math.h>
+#include <stdio.h>
+#include "h2o_internal.h"
+int main()
+{
+    int what, a, b, c, d;
+    while (scanf("%d %d %d %d %d", &what, &a, &b, &c, &d) == 5) {
+        const SelectPlan p = select_plan(a, b, c, d != 0);
+        printf("%d %d %d\n", p.parts, p.part_slots, (int)p.wide);
+    }
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def plans(tmp_path_factory):
+    """plans(list of (rule, a, b, c, d)) -> the rule's answers, a tuple of ints each"""
+    d = tmp_path_factory.mktemp("plans")
+    src, exe = str(d / "plans.hip"), str(d / "plans")
+    with open(src, "w") as f:
+        f.write(MAIN)
+    flags = [f for f in hb.FLAGS if f not in ("-fPIC", "-fvisibility=hidden", "-O3")]
+    subprocess.run(["hipcc", *flags, "-O1", src, "-o", exe], check=True, capture_output=True)
+
+    def ask(queries):
+        text = "\n".join(" ".join(str(int(x)) for x in q) for q in queries)
+        env = dict(os.environ, HIP_VISIBLE_DEVICES="")
+        out = subprocess.run([exe], input=text, capture_output=True, text=True, check=True, env=env).stdout
+        return [tuple(int(x) for x in line.split()) for line in out.splitlines()]
+    return ask
+
+
+def test_selection_gives_every_workgroup_a_cu(plans):
+    """Beyond 4096 candidates a workgroup's time is its selection: never two on one of the 256 CUs while
+    heads could be spread otherwise, and then sixteen waves, whatever the head count."""
+    q = [(0, h, k, n, 0) for h in [*range(1, 258), 300, 512, 3584] for k in (1, 64, 700, 1000, 3277, 4096)
+         for n in (4097, 8193, 16384, 16385, 28672, 28673, 40000, 65536) if n > k]
+    for (_, h, k, n, _), (parts, slots, wide) in zip(q, plans(q)):
+        assert parts >= 1 and parts * slots >= k and (parts - 1) * slots < k, (h, k, n)
+        assert parts == 1 or h * parts <= 256, (h, k, n, parts)
+        assert wide == (h <= 256 or n > 16384), (h, k, n)
+        if n <= 28672 and h <= 128 and k >= 8192 // h:       # nor are CUs left idle that a head could use
+            assert h * (parts + 1) > 256 or parts * slots < k + slots, (h, k, n, parts)
+
+
+def test_selection_of_few_candidates_and_in_place(plans):
+    q = [(0, h, k, n, 0) for h in range(1, 300) for k in (1, 64, 700, 3277) for n in (k + 1, 4096)]
+    for (_, h, k, n, _), (parts, slots, wide) in zip(q, plans(q)):
+        assert not wide and parts * slots >= k > (parts - 1) * slots, (h, k, n)
+        assert parts <= (256 + h - 1) // h and (parts == 1 or slots >= 16), (h, k, n)
+    q = [(0, h, k, n, 1) for h in (1, 12, 56, 128, 256, 257, 3584) for k in (64, 4096) for n in (4096, 4097, 16385, 69000)]
+    for (_, h, k, n, _), (parts, slots, wide) in zip(q, plans(q)):
+        assert (parts, slots) == (1, k) and wide == (n > 4096 and (h <= 256 or n > 16384)), (h, k, n)
