@@ -18,7 +18,7 @@ DT = {"f32": torch.float32, "f16": torch.float16, "bf16": torch.bfloat16}
     ("f16", 128, 2, 0, 64, (100, 64, 10), {}),                         # window only: every row moves
     ("bf16", 128, 2, 60, 61, (150, 150), dict(rank=1)),
     ("f16", 128, 2, 150, 20, (400, 333), dict(protect=1, stride=7)),
-    ("f16", 128, 2, 2048, 2048, (4200, 1500), {}),                     # keys in 32 registers
+    ("f16", 128, 2, 2048, 2048, (4200, 1500), {}),                     # sixteen waves, 8 keys
     ("bf16", 128, 160, 256, 256, (600, 2048), {}),                     # column sums with eight waves
 ])
 def test_in_place_chunk_matches_the_copying_way(dt, d, heads, heavy, recent, chunks, more):
