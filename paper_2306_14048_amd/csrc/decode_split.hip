@@ -76,7 +76,7 @@ __global__ __launch_bounds__(PNW * 64, 4) void decode_part_kernel(const StepArgs
     __shared__ double part_l[PNW * OWN * PITCH];
     __shared__ double red_sum[PNW], red_max[PNW];
     __shared__ float p_l[PNW * OWN];
-    __shared__ float o_l[PNW * D];
+    __shared__ __align__(16) float o_l[PNW * D];
     double *part_w = part_l + wave * OWN * PITCH;
     float *p_w = p_l + wave * OWN;
 

@@ -84,21 +84,17 @@ template <int CTRL> __device__ inline unsigned long long dpp(unsigned long long 
     return ((unsigned long long)hi << 32) | lo;
 }
 
-// Sum of a over the lanes l and l ^ M, M = 8, 16 or 32, in registers: the swap of a register with
-// itself leaves this lane's value in one result and the partner's in the other.  (A shuffle
-// through LDS takes some 130 cycles, and these stand in the tail of a step, where nothing
-// else is left to do: 300 to 400 cycles of a step's 4600 on 8 heads x 64 slots.)
-template <int M> __device__ inline float pair_sum(float a)
+// Sums of a and of b over the lanes l and l ^ M, M = 16 or 32: lanes with bit M clear get a's, the
+// others b's.  The swap hands each half what it adds up, so a sum costs half a swap and half an addition.
+template <int M> __device__ inline float pair_sums(float a, float b)
 {
-    const unsigned u = __float_as_uint(a);
-    if constexpr (M == 8) {
-        return a + __int_as_float(dpp<DPP_ROR8>(__float_as_int(a)));
-    } else if constexpr (M == 16) {
-        const auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+    const unsigned u = __float_as_uint(a), v = __float_as_uint(b);
+    if constexpr (M == 16) {
+        const auto r = __builtin_amdgcn_permlane16_swap(u, v, false, false);
         return __uint_as_float(r[0]) + __uint_as_float(r[1]);
     } else {
         static_assert(M == 32, "");
-        const auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+        const auto r = __builtin_amdgcn_permlane32_swap(u, v, false, false);
         return __uint_as_float(r[0]) + __uint_as_float(r[1]);
     }
 }
@@ -153,18 +149,35 @@ __device__ inline double wave_sum(double v)
 }
 // Adds this lane's fp32 partial output (EPL columns of row group `sub`) into the
 // workgroup's output row, multiplies nothing: o_l[wave][column] gets the wave's sum.
+//
+// Each step halves the columns a lane is left with (up to 8 lanes per row: the first keeps them
+// all), and at the end every lane stores its own one or two.  In registers, because a shuffle through LDS takes
+// some 130 cycles and these stand in the tail of a step, where nothing else is left to do: 300 to
+// 400 cycles of a step's 4600 on 8 heads x 64 slots.  (All columns in all lanes, a register swapped with itself, takes
+// three times the instructions: with fourteen workgroups per CU those count, 3584 heads x 1 slot 12.1 us
+// against 11.3.)
 template <int EPL, int LPR, int D>
 __device__ inline void wave_output_to_lds(float (&o)[EPL], float *o_l, int wave, int sub, int li)
 {
+    static_assert(LPR == 8 || LPR == 16 || LPR == 32, "");
+    constexpr int H = LPR <= 16 ? EPL / 2 : EPL, Q = H / 2;
+    const int lane = sub * LPR + li;
+    int col = li * EPL;
+    if constexpr (LPR == 8) {
 #pragma unroll
-    for (int i = 0; i < EPL; ++i) {
-        if constexpr (LPR <= 8) o[i] = pair_sum<8>(o[i]);
-        if constexpr (LPR <= 16) o[i] = pair_sum<16>(o[i]);
-        o[i] = pair_sum<32>(o[i]);
+        for (int i = 0; i < EPL; ++i) o[i] += __int_as_float(dpp<DPP_ROR8>(__float_as_int(o[i])));
     }
-    if (sub == 0) {
+    if constexpr (LPR <= 16) {
 #pragma unroll
-        for (int i = 0; i < EPL; ++i) o_l[wave * D + li * EPL + i] = o[i];
+        for (int i = 0; i < H; ++i) o[i] = pair_sums<16>(o[i], o[i + H]);
+        col += lane & 16 ? H : 0;
+    }
+#pragma unroll
+    for (int i = 0; i < Q; ++i) o[i] = pair_sums<32>(o[i], o[i + Q]);
+    col += lane & 32 ? Q : 0;
+    if (LPR > 8 || !(lane & 8)) {
+#pragma unroll
+        for (int i = 0; i < Q; ++i) o_l[wave * D + col + i] = o[i];
     }
 }
 

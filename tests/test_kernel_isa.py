@@ -8,6 +8,9 @@ assembly hipcc emits for gfx950 (no GPU needed).
   results stay right, the two groups then take turns and the pass is ~10 % slower).
   Every steady-state loop must therefore have its exponentials between its barriers.
 * The kernels the benchmark times must not spill registers to scratch memory.
+* A step's output sums halve the columns a lane is left with at every exchange between lanes;
+  with all columns in all lanes they take three times the instructions, which steps of many
+  heads and few slots pay for.
 """
 import os
 import re
@@ -111,3 +114,19 @@ def test_benchmarked_kernels_do_not_spill(scores_asm, tmp_path):
             assert m["vgpr_spill_count"] == 0 and m["vgpr_count"] <= 128, (name, m)
             checked += 1
     assert checked >= 8
+
+
+def test_output_sums_halve_their_columns(tmp_path):
+    checked = 0
+    for src in ("decode_step.hip", "decode_split.hip"):
+        for name, blocks in functions(device_asm(src, tmp_path)).items():
+            m = re.search(r"decode_(?:resident|chunked|part)_kernelILi(\d)ELi(\d+)E", name)
+            if not m:
+                continue
+            f32, d = m[1] == "0", int(m[2])
+            # columns of a lane: 4 or 8; exchanges over 16 lanes (rows of up to 16 lanes) and over 32
+            want = {(True, 64): 2 + 1, (True, 128): 2, (False, 64): 4 + 2, (False, 128): 4 + 2}[(f32, d)]
+            ops = [x.split()[0] for ins in blocks for x in ins]
+            assert sum(o.startswith("v_permlane") for o in ops) == want, name
+            checked += 1
+    assert checked >= 100
