@@ -147,6 +147,31 @@ static inline bool two_groups(int heads, int rows, int streamed, bool f32, int d
     return streamed >= (d == 128 ? 600 : 480) && blocks <= (streamed >= 1500 ? 512 : 384);
 }
 
+// Whether the attention's two groups (two_groups) run one phase apart: while one is in its MFMAs the
+// other is in its softmax.  That takes a second barrier per tile and, at d = 64, 143 registers
+// instead of 127, with which a second workgroup does not fit on the CU any more; blocks beyond the CUs then wait
+// for a whole round where the groups in step would have run beside them.  What counts is the grid with its
+// empty workgroups (slots: heads go to XCDs eight at a time, one head's blocks all to one XCD), for causal
+// streams of some tiles up to two rounds of it.  Apart / together (time of the attention alone, 1 to 400
+// heads; d = 128: both 16-bit types):
+//   d = 128  to 256 slots from 1100 keys on 0.90 .. 0.98, below 0.95 .. 1.01; more slots from 1100 on 0.90 .. 1.01
+//            (mean 0.97; 1 head x 65 536 0.91), below 1.00 .. 1.04
+//   d = 64   to 256 slots 0.88 .. 1.02.  More, whole prompts: 33 heads x 860 tokens (231 blocks, 280 slots) 0.93, 36 x 800 0.99, 50 x
+//            560 1.06; to 352 slots x 1100 to 1500 0.91 .. 0.97, 33 x 1150 (297 blocks) 0.95, 36 x 1100 (324) 1.02, 36 x 1200 1.03; from
+//            1500 on to 512 slots 0.88 .. 0.98, from 4000 on to 576 0.89 .. 0.98; more slots 36 x 1650 (520) 1.11, 20 x
+//            3000 (576) 1.04, 12 x 5000 (640) 1.04, 1 x 16 000 (1000) 1.17, 1 x 65 536 (4096) 1.23;
+//            chunks behind many cached tokens (all blocks equally heavy): to 256 0.95 .. 1.01, more 0.99 .. 1.14
+static inline bool groups_apart(int heads, int nq, int nk, int d)
+{
+    const long long row_blocks = (nq + 127) / 128, blocks = heads * row_blocks, slots = head_slots(heads) * row_blocks;
+    if (slots <= 256) return true;
+    if (d == 128) return nk >= 1100;
+    if (2LL * nk >= 3LL * nq) return false;
+    if (nk < 1100) return nk >= 800 && blocks <= 256;
+    if (nk < 1500) return slots <= 352 || blocks <= 320;
+    return slots <= (nk < 4000 ? 512 : 576);
+}
+
 // How a compression of n candidates per head into k slots is laid out: workgroups per head, slots
 // of each, and whether they have sixteen waves instead of eight.
 constexpr int SG_LDS_KEYS = 28672;     // ranking keys kept in LDS up to this many candidates (112 KiB)

@@ -500,13 +500,7 @@ hipError_t h2o_launch_prefill_attention(const h2o_config &cfg, double scale, con
     const int d = cfg.head_dim;
     if (nq < 1 || nq > nk) return hipErrorInvalidValue;
     const bool few = two_groups(cfg.batch * cfg.heads, nq, nk, false, d);
-    // Two groups one phase apart: while one is in its MFMAs the other is in its softmax.  That takes a
-    // second barrier per tile, which short streams behind more blocks than CUs do not pay back
-    // (d = 128, f16, us, together / apart): to 256 blocks 8 heads x 4096 66 / 61, 16 x 1531 28.6 / 26.7, 32 x 1000
-    // 21.5 / 20.6, 8 x 500 14.0 / 13.8, a chunk of 1024 on 410 cached ones, 32 heads, 66.5 / 61.2 (the whole call);
-    // more: 32 x 1531 37.3 / 36.5, 32 x 1100 24.6 / 23.5, 32 x 1400 28.6 / 28.6, 40 x 900 23.1 / 23.6, 64 x 640
-    // 20.3 / 20.8; d = 64, 32 x 1200 16.8 / 15.6, 64 x 700 13.6 / 15.2.
-    const bool apart = few && ((long long)cfg.batch * cfg.heads * ((nq + ARW * 32 - 1) / (ARW * 32)) <= 256 || nk >= 1100);
+    const bool apart = few && groups_apart(cfg.batch * cfg.heads, nq, nk, d);
 #define H2O_ATTN(DT, D)                                                                                         \
     (apart ? launch_attn<DT, D, 2, true>(cfg, scale, Q, K, V, Kf, Vf, nq, nk, vcopy, lse2, lse_nat, out, st)    \
      : few ? launch_attn<DT, D, 2, false>(cfg, scale, Q, K, V, Kf, Vf, nq, nk, vcopy, lse2, lse_nat, out, st)   \

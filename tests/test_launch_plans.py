@@ -15,8 +15,12 @@ int main()
 {
     int what, a, b, c, d;
     while (scanf("%d %d %d %d %d", &what, &a, &b, &c, &d) == 5) {
-        const SelectPlan p = select_plan(a, b, c, d != 0);
-        printf("%d %d %d\n", p.parts, p.part_slots, (int)p.wide);
+        if (what == 0) {
+            const SelectPlan p = select_plan(a, b, c, d != 0);
+            printf("%d %d %d\n", p.parts, p.part_slots, (int)p.wide);
+        } else {
+            printf("%d %d %d\n", (int)two_groups(a, b, c, false, d), (int)groups_apart(a, b, c, d), (int)head_slots(a));
+        }
     }
 }
 """
@@ -61,3 +65,28 @@ def test_selection_of_few_candidates_and_in_place(plans):
     q = [(0, h, k, n, 1) for h in (1, 12, 56, 128, 256, 257, 3584) for k in (64, 4096) for n in (4096, 4097, 16385, 69000)]
     for (_, h, k, n, _), (parts, slots, wide) in zip(q, plans(q)):
         assert (parts, slots) == (1, k) and wide == (n > 4096 and (h <= 256 or n > 16384)), (h, k, n)
+
+
+def test_attention_groups_apart_have_a_cu_of_their_own(plans):
+    """At d = 64 the groups one phase apart leave no room for a second workgroup on their CU: few more
+    block slots than two rounds of the CUs, and one round where blocks are equally heavy.  (All blocks of
+    a head run on one XCD: a single long prompt has eight times its blocks in slots.)"""
+    q = [(1, h, nq, nq + old, d) for d in (64, 128) for h in [*range(1, 66), 96, 128, 192, 256, 320, 400, 512]
+         for nq in (1, 100, 128, 256, 500, 800, 1024, 1100, 1200, 1531, 1650, 2048, 2300, 3000, 5000, 8200, 16000, 65536)
+         for old in (0, 410, 2000, 4000)]
+    some = {64: 0, 128: 0}
+    for (_, h, nq, nk, d), (few, apart, heads8) in zip(q, plans(q)):
+        slots = heads8 * ((nq + 127) // 128)
+        if not few or not apart:
+            continue
+        some[d] += 1
+        if d == 64:
+            assert slots <= (512 if nk < 4000 else 576), (h, nq, nk)
+            assert slots <= 256 or 2 * nk < 3 * nq, (h, nq, nk)
+        else:
+            assert slots <= 256 or nk >= 1100, (h, nq, nk, d)
+    assert min(some.values()) > 300
+    want = {(1, 16000, 64): 0, (1, 65536, 64): 0, (20, 3000, 64): 0, (36, 1650, 64): 0, (8, 8000, 64): 1, (32, 1531, 64): 1,
+            (1, 65536, 128): 1, (32, 1531, 128): 1, (36, 800, 128): 0, (320, 100, 64): 0, (8, 500, 64): 1}
+    got = plans([(1, h, n, n, d) for h, n, d in want])
+    assert [g[1] for g in got] == list(want.values())

@@ -13,6 +13,14 @@ DT = {"f16": torch.float16, "bf16": torch.bfloat16}
     ("f16", 128, 43, 768),        # 258: together
     ("bf16", 64, 30, 1099),       # 270, below the line of the stream: together
     ("bf16", 128, 30, 1100),      # at it: apart
+    ("f16", 64, 33, 860),         # 231 blocks in a grid of 280: apart
+    ("bf16", 64, 50, 560),        # 250 in 280, a short stream: together
+    ("f16", 64, 33, 1150),        # 297: apart
+    ("bf16", 64, 36, 1100),       # 324 in 360: together
+    ("f16", 64, 36, 1531),        # 432 in 480: apart
+    ("f16", 64, 36, 1650),        # 468 in 520: together
+    ("bf16", 64, 1, 9216),        # 72 in 576: apart
+    ("f16", 64, 1, 9217),         # 73 in 584: together
 ])
 def test_attention_rows_and_normalisers(dt, d, heads, n):
     from paper_2306_14048_amd import binding as hb
