@@ -378,8 +378,9 @@ __device__ __forceinline__ void prefill_pass(
                 // key j = srow: need j <= off + i, i < nq
                 const float *ll = lse_l + lb * BN + part * GN;
                 float sum0 = 0.f, sum1 = 0.f;
-                // this lane's rows of the tile from `first` on and in front of `end` count
-                const int first = srow - off - r0 - 4 * half, end = nq - r0 - 4 * half;
+                // `count` of this lane's rows of the stream count, from row `first` of the tile on
+                const int first = srow - off - r0 - 4 * half;
+                const unsigned count = max(0, nq + off - srow);
                 auto add_up = [&](auto first_tag, auto end_tag) {
 #pragma unroll
                     for (int mb = 0; mb < MB; ++mb)
@@ -391,10 +392,11 @@ __device__ __forceinline__ void prefill_pass(
 #pragma unroll
                             for (int e = 0; e < 4; ++e) {
                                 x[e] = fmaf(acc[mb][4 * gq + e], c2, -lv[e]);
-                                if constexpr (decltype(first_tag)::value)
-                                    x[e] = mb * 32 + 8 * gq + e < first ? -INFINITY : x[e];
+                                const int row = mb * 32 + 8 * gq + e;
                                 if constexpr (decltype(end_tag)::value)
-                                    x[e] = mb * 32 + 8 * gq + e >= end ? -INFINITY : x[e];
+                                    x[e] = (unsigned)(row - first) >= count ? -INFINITY : x[e];
+                                else if constexpr (decltype(first_tag)::value)
+                                    x[e] = row < first ? -INFINITY : x[e];
                             }
                             sum0 += __builtin_amdgcn_exp2f(x[0]) + __builtin_amdgcn_exp2f(x[2]);
                             sum1 += __builtin_amdgcn_exp2f(x[1]) + __builtin_amdgcn_exp2f(x[3]);
@@ -402,10 +404,13 @@ __device__ __forceinline__ void prefill_pass(
                 };
                 // (what a tile needs is the same for the whole wave; tested per element, a masked
                 // tile took three times the instructions: both passes 1 to 6 % slower, 256
-                // heads x 300 24.3 us against 22.8, 32 x 1531 40.8 / 39.0, 128 x 4096 555 / 549)
+                // heads x 300 24.3 us against 22.8, 32 x 1531 40.8 / 39.0, 128 x 4096 555 / 549.  binary32,
+                // d = 128, has no registers for three ways and takes both ends as one range: two comparisons
+                // per element had made it 2 % slower where several workgroups share a CU, 256 heads x 300
+                // 96.1 us, now 93.6, tested per element 93.8; 128 x 300 79.1 / 78.2 / 81.0)
                 if constexpr (!MASKED) {
                     add_up(std::false_type{}, std::false_type{});
-                } else if constexpr (ROWB >= 512) {               // (no registers left for three ways)
+                } else if constexpr (ROWB >= 512) {
                     add_up(std::true_type{}, std::true_type{});
                 } else if (r0 + GN > nq) {
                     add_up(std::true_type{}, std::true_type{});

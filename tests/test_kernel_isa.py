@@ -130,3 +130,20 @@ def test_output_sums_halve_their_columns(tmp_path):
             assert sum(o.startswith("v_permlane") for o in ops) == want, name
             checked += 1
     assert checked >= 100
+
+
+def test_masks_of_the_column_sums_take_one_comparison_per_product(scores_asm):
+    """A masked tile tests both ends of the stream as one range."""
+    checked = 0
+    for name, blocks in functions(scores_asm).items():
+        # (name ends: G, TWO, COLSUM, SKEW / COLSUM)
+        if not re.search(r"prefill_pass_kernelILi\dELi\d+ELi\dELb1EEE|prefill_pass4_kernelILi\dELi\d+ELi\dELi\dELb0ELb1ELb\dE", name):
+            continue
+        f32_128 = "ILi0ELi128E" in name
+        for ins in blocks:
+            ops = [x.split()[0] for x in ins]
+            exps, cmps = (sum(o.startswith(p) for o in ops) for p in ("v_exp_f32", "v_cmp"))
+            if exps >= 16:
+                assert cmps <= (16 if f32_128 else 32) + 2, (name, cmps, exps)
+                checked += 1
+    assert checked >= 40
