@@ -1,8 +1,8 @@
 """Properties of the compiled kernels that no numerical test can see, checked on the
 assembly hipcc emits for gfx950 (no GPU needed).
 
-* The prompt-scoring passes run two wave groups one phase apart: a step is
-  `matrix phase, barrier, vector phase, barrier`.  Pass 1's vector phase touches no
+* The prompt-scoring passes and the prompt attention run two wave groups one phase apart: a step
+  is `matrix phase, barrier, vector phase, barrier`.  Pass 1's vector phase touches no
   memory, so only a data dependence on the closing barrier keeps the compiler from
   scheduling its arithmetic behind that barrier (a build did exactly that: the
   results stay right, the two groups then take turns and the pass is ~10 % slower).
@@ -75,9 +75,17 @@ def scores_asm(tmp_path_factory):
     return device_asm("prefill_scores.hip", tmp_path_factory.mktemp("isa"))
 
 
+@pytest.fixture(scope="module")
+def attention_asm(tmp_path_factory):
+    return device_asm("prefill_attention.hip", tmp_path_factory.mktemp("isa"))
+
+
 def test_vector_phase_of_the_scoring_passes_sits_between_the_barriers(scores_asm):
-    fns = {n: b for n, b in functions(scores_asm).items() if "prefill_pass_kernel" in n}
-    assert len(fns) == 12                                   # 3 element types x 2 head dims x 2 passes
+    # eight waves: 3 element types x 2 head dims x 2 passes; two groups of four waves one phase apart (16-bit,
+    # d = 128, last template argument set): 2 types x (column sums, statistics with keys in one and in two places)
+    fns = {n: b for n, b in functions(scores_asm).items()
+           if "prefill_pass_kernel" in n or re.search(r"prefill_pass4_kernelI\w+?Lb1EEEv", n)}
+    assert len(fns) == 12 + 6
     for name, blocks in fns.items():
         loops = 0
         for ins in blocks:
@@ -95,6 +103,29 @@ def test_vector_phase_of_the_scoring_passes_sits_between_the_barriers(scores_asm
                 "%s: %d exponentials between the barriers, %d behind the second" % (
                     name, len(between), len([i for i in exps if i > second]))
         assert loops >= 1, name                             # the unmasked steady-state loop was found
+
+
+def test_phases_of_the_attention_groups_sit_between_their_barriers(attention_asm):
+    """The attention with its groups one phase apart: all matrix instructions of a step in front of its
+    middle barrier, the softmax behind it and in front of the closing one."""
+    fns = {n: b for n, b in functions(attention_asm).items() if re.search(r"prefill_attn_kernelI\w+?ELb1EEEv", n)}
+    assert len(fns) == 2 * 2 * 2                            # types, head dims, keys in one and in two places
+    for name, blocks in fns.items():
+        middle = closing = 0
+        for ins in blocks:
+            ops = [x.split()[0] for x in ins]
+            bars, mfmas, exps = ([i for i, o in enumerate(ops) if f(o)] for f in
+                                 (lambda o: o == "s_barrier", lambda o: "mfma" in o, lambda o: o.startswith("v_exp_f32")))
+            assert len(bars) <= 1 or not (mfmas or len(exps) >= 32), name
+            if mfmas and bars:
+                assert max(mfmas) < bars[0] and all(i > bars[0] for i in exps), name
+                middle += 1
+            elif mfmas:
+                assert not exps, name
+            elif len(exps) >= 32:                           # a tile's exponentials
+                assert len(exps) == 32 and (not bars or max(exps) < bars[0]), name
+                closing += len(bars)                        # (a masked tile's barrier is in the next block)
+        assert middle >= 1 and closing >= 1, (name, middle, closing)
 
 
 def test_benchmarked_kernels_do_not_spill(scores_asm, tmp_path):
