@@ -10,6 +10,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import warnings
 
 import torch
 
@@ -53,11 +54,16 @@ class H2OError(RuntimeError):
         super().__init__("%s: %s (%d)" % (where, h2o_status_str(status), status))
 
 
-if not os.path.exists(LIB_PATH) or not os.path.exists(os.path.join(_PKG, "_step_call.so")):
-    raise ImportError("libh2o_hip.so or _step_call.so is not built; run `python -m paper_2306_14048_amd.build` "
+if not os.path.exists(LIB_PATH):
+    raise ImportError("libh2o_hip.so is not built; run `python -m paper_2306_14048_amd.build` "
                       "(there is no CPU fallback)")
 _lib = ctypes.CDLL(LIB_PATH)
-from . import _step_call  # noqa: E402  (built with the library and linked against it)
+try:
+    from . import _step_call  # built with the library and linked against it, for one Python and one torch
+except ImportError as _e:
+    _step_call = None
+    warnings.warn("the native step call is not usable here (%s): steps are called through ctypes, with 2 us more "
+                  "of host time each; `python -m paper_2306_14048_amd.build` builds it" % _e)
 
 _vp, _i32, _sz = ctypes.c_void_p, ctypes.c_int32, ctypes.c_size_t
 _cfgp = ctypes.POINTER(h2o_config)
@@ -293,7 +299,7 @@ class H2OCache:
         self.nbytes = nbytes
         self.mem = torch.empty(nbytes, dtype=torch.uint8, device=self.device)
         self.handle = h2o_cache_init(self.cfg, self.mem, nbytes, stream)
-        self._step_spec = _step_call.step_spec(self.mem, *self._step_shape, self.cfg.dtype)
+        self._step_spec = _step_call and _step_call.step_spec(self.mem, *self._step_shape, self.cfg.dtype)
         self._ws = None
         # scratch for steps that are split over several workgroups per head (0 for most shapes;
         # 2.8 MB for 64 heads x 3277 slots, d = 128); not part of nbytes, which is the cache's own size
@@ -387,15 +393,27 @@ class H2OCache:
         h2o_prefill_select(self.handle, K, V, score, n, stream)
 
     def decode_step(self, q, k_new, v_new, out, stream=None):
-        # The call every generated token makes: checks and call in one native function (host
-        # time per step 5.4 us with the checks in Python and ctypes, of which the launch was 2.4).
-        rc = _step_call.decode_step(self._step_spec, self.handle, q, k_new, v_new, out,
-                                    stream if stream is None else _stream(stream))
-        if rc == H2O_OK:
+        # The call every generated token makes: checks and call in one native function.  What that
+        # does not take (a tensor subclass), or all of it without the function: the checks of _expect in one
+        # condition and the entry point called with the pointers right away.
+        if self._step_spec is not None:
+            rc = _step_call.decode_step(self._step_spec, self.handle, q, k_new, v_new, out,
+                                        stream if stream is None else _stream(stream))
+            if rc == H2O_OK:
+                return
+            if rc < 0:
+                raise H2OError(rc, "h2o_decode_step")
+        shape, dtype, device = self._step_shape, self.dtype, self.mem.device
+        for x in (q, k_new, v_new, out):
+            if not (isinstance(x, torch.Tensor) and x.dtype == dtype and x.shape == shape
+                    and x.device == device and x.is_contiguous()):
+                break
+        else:
+            rc = _lib.h2o_decode_step(self.handle, q.data_ptr(), k_new.data_ptr(), v_new.data_ptr(),
+                                      out.data_ptr(), _stream(stream))
+            if rc != H2O_OK:
+                raise H2OError(rc, "h2o_decode_step")
             return
-        if rc < 0:
-            raise H2OError(rc, "h2o_decode_step")
-        shape, dtype = self._step_shape, self.dtype           # not the plain case
         for x, nm in ((q, "q"), (k_new, "k_new"), (v_new, "v_new"), (out, "out")):
             self._expect(x, shape, dtype, nm)                 # says what is wrong
         h2o_decode_step(self.handle, q, k_new, v_new, out, stream)

@@ -56,7 +56,8 @@ def _build_step_call() -> None:
         ["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-fvisibility=hidden", "-Wall", "-D__HIP_PLATFORM_AMD__",
          "-DUSE_ROCM", "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI]
         + [x for i in inc for x in ("-isystem", i)]
-        + [os.path.join(CSRC, "step_call.cpp"), "-o", tmp, "-L", PKG, "-l:libh2o_hip.so", "-Wl,-rpath,$ORIGIN", "-L", lib,
+        # (-z now: another torch without one of its symbols fails the import, not a step)
+        + [os.path.join(CSRC, "step_call.cpp"), "-o", tmp, "-L", PKG, "-l:libh2o_hip.so", "-Wl,-rpath,$ORIGIN", "-Wl,-z,now", "-L", lib,
            "-ltorch_python", "-ltorch_cpu", "-lc10_hip", "-lc10"])
     os.replace(tmp, STEP_CALL)
 

@@ -1,5 +1,8 @@
 """The native call of a generation step: what it takes itself, what it leaves to the
 general way, and that both ways are the same step."""
+import subprocess
+import sys
+
 import pytest
 import torch
 
@@ -36,9 +39,21 @@ def test_only_exact_plain_tensors_are_taken(hb):
         hb._step_call.step_spec(None, B, Hh, D, hb.H2O_F16)
 
 
+def test_binding_without_the_native_call():
+    """The library alone is enough: the import says that steps are slower and goes on."""
+    code = ("import sys, warnings\n"
+            "sys.modules['paper_2306_14048_amd._step_call'] = None\n"
+            "with warnings.catch_warnings(record=True) as w:\n"
+            "    warnings.simplefilter('always')\n"
+            "    from paper_2306_14048_amd import binding\n"
+            "assert binding._step_call is None and 'native step call' in str(w[-1].message), w\n"
+            "assert binding.h2o_status_str(0)\n")
+    subprocess.run([sys.executable, "-c", code], check=True)
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("dtype", [torch.float32, torch.float16, torch.bfloat16])
-def test_native_and_general_call_are_the_same_step(hb, dtype):
+def test_native_and_general_call_are_the_same_step(hb, dtype, monkeypatch):
     dev = torch.device("cuda:0")
     gen = torch.Generator(device=dev).manual_seed(3)
     draw = lambda *s: torch.randn(s, generator=gen, device=dev).to(dtype)  # noqa: E731
@@ -49,7 +64,12 @@ def test_native_and_general_call_are_the_same_step(hb, dtype):
     side = torch.cuda.Stream()
 
     def run(way):
-        c = hb.H2OCache(B, Hh, D, HEAVY, RECENT, dtype, device=dev)
+        with monkeypatch.context() as m:
+            if way == "without the native call":
+                m.setattr(hb, "_step_call", None)
+            c = hb.H2OCache(B, Hh, D, HEAVY, RECENT, dtype, device=dev)
+        if way in ("subclass", "without the native call"):      # one condition, not a call per tensor
+            monkeypatch.setattr(c, "_expect", None, raising=False)
         torch.cuda.synchronize()
         outs = []
         for q, k, v in steps:
@@ -60,6 +80,8 @@ def test_native_and_general_call_are_the_same_step(hb, dtype):
                 hb.h2o_decode_step(c.handle, q, k, v, out)
             elif way == "subclass":                              # not the plain case: checked and called in Python
                 c.decode_step(q.as_subclass(Sub), k, v, out)
+            elif way == "without the native call":
+                c.decode_step(q, k, v, out)
             elif way == "stream object":
                 c.decode_step(q, k, v, out, side)
             elif way == "raw stream":
@@ -75,7 +97,7 @@ def test_native_and_general_call_are_the_same_step(hb, dtype):
             c.decode_step(*steps[0], outs[0])                    # closed
         return outs + state
     ref = run("native")
-    for way in ("entry point", "subclass", "stream object", "raw stream", "current stream"):
+    for way in ("entry point", "subclass", "without the native call", "stream object", "raw stream", "current stream"):
         for a, b in zip(ref, run(way)):
             assert torch.equal(a, b), way
 
