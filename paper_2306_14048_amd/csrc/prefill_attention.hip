@@ -32,11 +32,16 @@
 // 8 consecutive keys, so P^T goes from the accumulator registers into the second
 // product without any shuffle and the V^T fragment is two 64-bit LDS reads.
 //
-// Schedule.  One barrier per tile; the copy of tile u+1 into the other stage runs while
-// tile u is worked on.  Two workgroups share a CU (64 KB of LDS and 2 x 4 waves at ~200
-// registers each), and drift apart by themselves: while one multiplies the other is in
-// its softmax.  A first version had 8 waves and 256 queries per workgroup, one
-// workgroup per CU, its two wave groups held one phase apart by the barriers; measured
+// Schedule.  The copy of tile u+1 into the other stage runs while tile u is worked on.  Three forms:
+//   one group of 4 waves: one barrier per tile.  Two workgroups share a CU (64 KB of LDS and 2 x 4
+//     waves at ~200 registers each), and drift apart by themselves: while one multiplies the other
+//     is in its softmax.
+//   two groups together: for grids that leave CUs idle the keys of a tile are shared out to two groups
+//     of 4 waves (two_groups); one barrier per tile still, and nothing keeps the groups of a
+//     workgroup, mostly alone on its CU, out of each other's phase.
+//   two groups one phase apart (groups_apart, SKEW below): two barriers per tile, and the second group
+//     enters the loop one barrier late, so that one group multiplies while the other is in its softmax.
+// An early version kept the halves of 8 waves with 256 queries one phase apart; one group of 4 measured
 // against it (us, attention only, d = 128, f16): 8 heads x 300 tokens 14.8 -> 10.5, 32 x
 // 1531 46 -> 41, 32 x 4096 153 -> 148, 128 x 4096 574 -> 563 (976 TFLOP/s), 3584 x 256 242 -> 191:
 // short and few prompts gain most (half the work on the longest block), long ones lose
@@ -292,8 +297,9 @@ __global__ __launch_bounds__(ARW * G * 64, 2) void prefill_attn_kernel(
         f32x16 sacc[MB];
         __builtin_amdgcn_s_setprio(2);
         // The waves that share a SIMD are in no fixed phase relation (they may all be in
-        // their softmax), so a wave hides the LDS latency of its operand reads itself: they
-        // run PF fragments ahead of the MFMAs that use them (a ring of PF register quadruples).
+        // their softmax; with SKEW one of them is), so a wave hides the LDS latency of its operand
+        // reads itself: they run PF fragments ahead of the MFMAs that use them (a ring of PF
+        // register quadruples).
         constexpr int PF = 4;
         if (live_prev) {
             constexpr int N = KS * NDB;

@@ -72,9 +72,9 @@ constexpr int NLB = 4;         // row-statistic buffers (pass 2; read one phase 
 // phase ("ping-pong").  s_setprio lets the matrix phase win the issue slot.
 //
 // RWV: waves over a workgroup's rows.  Eight (256 stationary rows, two workgroups per CU) is
-// the shape for a full chip.  Four (128 rows, one group, one barrier per tile, the
-// overlap left to the workgroups that share a CU) is for grids that do not fill it:
-// the longest block then has half the work per tile.
+// the shape for a full chip.  Four (128 rows) is for grids that do not fill it: the longest
+// block then has half the work per tile.  Without SKEW its waves meet at one barrier per tile and
+// the overlap is left to the workgroups that share a CU.
 //
 // The first kf.rows keys of a head may sit elsewhere (FrontRows).  Stationary rows are
 // simply loaded from where they are; streamed ones (pass 1, TWO) are copied tile by tile
@@ -83,7 +83,9 @@ constexpr int NLB = 4;         // row-statistic buffers (pass 2; read one phase 
 // G (four-wave shape): groups of four waves over the same 128 stationary rows.  With two, a
 // tile has twice the rows and each group takes half of them; the parts are joined at the
 // end.  For grids that leave CUs idle: the longest block has half the steps.
-// SKEW: the two halves of eight waves run one phase apart.
+// SKEW: the two halves of eight waves, of one shape or of two groups of four, run one phase apart: two
+// barriers per tile, the second half one barrier behind.  (Two groups have a CU to themselves, no other
+// workgroup overlaps with them.)
 template <int DT, int D, int MB, int RWV, int G, bool TWO, bool COLSUM, bool SKEW>
 __device__ __forceinline__ void prefill_pass(
     const char *__restrict__ Qg, const char *__restrict__ Kg, const FrontRows &kf, int nq, int nk, int heads,
@@ -273,8 +275,8 @@ __device__ __forceinline__ void prefill_pass(
     // Buffer life times: the tile two ahead is requested at the start of the
     // matrix phase into the buffer of the previous tile, which both groups have
     // finished reading (the later group's matrix phase of that tile ended at the
-    // barrier this group has just passed).  Row statistics are read in the vector
-    // phase, one barrier later, hence one buffer more.  Before either barrier a
+    // barrier this group has just passed; without SKEW everybody's did).  Row statistics are read in the
+    // vector phase, one barrier later, hence one buffer more.  Before either barrier a
     // wave waits until only its newest request is outstanding, so that by the
     // barrier in front of any matrix phase every wave's share of that tile has
     // landed.
@@ -554,11 +556,12 @@ hipError_t pick_waves(const h2o_config &cfg, double scale, const void *Q, const 
     const int rows = COLSUM ? nk : nq, streamed = COLSUM ? nq : nk;
     const bool few = two_groups(cfg.batch * cfg.heads, rows, streamed, DT == H2O_F32, D);
     // The two groups one phase apart, as the halves of eight waves are: one barrier more per tile, which
-    // short streams, the rest of a second round of blocks and binary32 (a pass is its MFMAs there) do not pay
-    // back.  Both passes, f16, d = 128, us, together / apart: to 256 blocks 8 heads x 4096 81.8 / 74.1, 16 x 1531
-    // 35.2 / 33.4, 32 x 1000 27.0 / 26.0, 32 x 700 21.4 / 21.8, 8 x 500 17.8 / 18.5; more: 32 x 1531 37.8 / 40.0, 24 x 2048
-    // 44.9 / 45.0, 24 x 2500 65.4 / 64.2, 8 x 6000 120.6 / 110.0, 16 x 4000 113 / 104; d = 64 8 x 4096 61.6 / 60.3, 16 x 4000
-    // 70.8 / 71.4, 32 x 700 17.3 / 17.8; binary32 16 x 1500 209 / 213.
+    // short streams and binary32 (a pass is its MFMAs there) do not pay back.  Apart / together, time of
+    // both passes, whole prompts, both 16-bit types, d = 128, 1 to 256 heads:
+    //   to 256 blocks  2500 rows on 0.89 .. 0.95, 1100 on 0.91 .. 0.97, 800 on 0.96 .. 1.03, below 1.00 .. 1.04
+    //   to 512         2500 rows on 0.91 .. 0.98, 1100 on 0.93 .. 1.06 by how the last round of blocks fills (mean
+    //                  0.99: 16 heads x 2300 0.93, 32 x 1531 1.04; left together), below 1.03 .. 1.08
+    // d = 64 8 heads x 4096 61.6 us together / 60.3 apart, 16 x 4000 70.8 / 71.4, 32 x 700 17.3 / 17.8; binary32 16 x 1500 209 / 213.
     constexpr bool CAN = DT != H2O_F32 && D == 128;
     const bool apart = CAN && few &&
                        (streamed >= 2500 || (streamed >= 800 && (long long)cfg.batch * cfg.heads * ((rows + 127) / 128) <= 256));

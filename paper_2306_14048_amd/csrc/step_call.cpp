@@ -1,7 +1,7 @@
 // The Python call of a generation step: tensor checks and the call of h2o_decode_step in one
 // native function, because a small step is as short as the call that starts it.  8 heads x 64 slots,
-// binary32, all measured in one process: host time per call 3.5 us, of which h2o_decode_step itself is 3.1 (most of
-// it the launch), 5.7 us with the checks in Python and ctypes; on the GPU 2.8 us from launch to launch in
+// binary32, all measured in one process: host time per call 3.5 us, 3.1 of them in here (the launch is
+// most of that), 5.7 us with the checks in Python and ctypes; on the GPU 2.8 us from launch to launch in
 // a replayed graph.  (A profiler's kernel duration of the same step is 3.6 us, 3.1 at least: its
 // begin and end stamps enclose more than the step.)
 //
