@@ -35,6 +35,13 @@
 // 205 34.9 -> 30.2 (4.3 TB/s), x 64 25.4 -> 14.7; 4096 x 410 70.8 -> 57.1 (5.1 TB/s); 32 x 2000
 // 17.7 -> 12.1; binary32 elements 512 x 410 13.8 -> 10.0.
 //
+// What a step of few slots waits for is one chain: arguments, q, its digits, logits, normaliser, output, the sums over
+// the waves (32 heads x 410: 4.8 us between the first and the last stamp, every wave nearly alone on its SIMD).
+// Taken out of that chain: a division by the number of waves (0.3 us), the quantiser's second
+// four elements per lane (0.2), the reads of the final sums one after the other (0.45), the scores behind the
+// output.  Steps in a graph, before -> this, us, one cache / caches in turn: 512 heads x 410 9.6 -> 8.4 / 12.0 ->
+// 10.6, 32 x 410 6.15 -> 5.5 / 6.9 -> 5.9, 3584 x 205 29.3 -> 27.4 / 30.2 -> 28.7, 512 x 2000 32.5 -> 31.6 / 35.7 -> 34.9.
+//
 // Memory plan.  A wave owns blocks of 64 consecutive slots, one slot per lane.  A
 // block's stored rows are one contiguous image of 64 * 80 (or 48) bytes; the K images of a
 // wave's blocks followed by the V images are copied straight into a ring of LDS buffers of
@@ -96,6 +103,17 @@ __device__ inline void exponents_above(float a, float b, int &ea, int &eb)
     ea = exponent_above(__int_as_float(max(__builtin_amdgcn_readlane(v, 0), __builtin_amdgcn_readlane(v, 16))));
     eb = exponent_above(__int_as_float(max(__builtin_amdgcn_readlane(v, 32), __builtin_amdgcn_readlane(v, 48))));
 }
+// the same for one value per lane
+__device__ inline int exponent_above_wave(float a)
+{
+    int v = __float_as_int(a);
+    v = max(v, dpp<DPP_XOR1>(v));
+    v = max(v, dpp<DPP_XOR2>(v));
+    v = max(v, dpp<DPP_HALF_MIRROR>(v));
+    v = max(v, dpp<DPP_MIRROR>(v));
+    return exponent_above(__int_as_float(max(max(__builtin_amdgcn_readlane(v, 0), __builtin_amdgcn_readlane(v, 16)),
+                                             max(__builtin_amdgcn_readlane(v, 32), __builtin_amdgcn_readlane(v, 48)))));
+}
 // exact power of two, |n| <= 1022
 __device__ inline double pow2(int n) { return __hiloint2double((1023 + n) << 20, 0); }
 
@@ -113,6 +131,7 @@ template <int D> struct Shared {
     double red_sum[MAX_WAVES], red_max[MAX_WAVES], red_key[MAX_WAVES];
     double min_sum[2][MAX_WAVES];              // sum p m_g over a wave's slots
     double s_self, qsum[2];                    // the token's own logit; scale * sum q per group
+    int q_exp[2];                              // |q| < 2^q_exp in each group
     unsigned new_row[96];                      // the new token as stored: words, scales, mins
 };
 template <int DT, int D, int SPL> struct Ring {
@@ -194,8 +213,9 @@ __global__ __launch_bounds__(MAX_WAVES * 64, 4) void decode_q4_kernel(const Step
             dma16_stream(item < SPL ? rsrc_k : rsrc_v, min(first + i * 1024u, occ_bytes - 16u),
                          mine_b + (item % NB) * L::IMG + i * 1024);
     };
+    constexpr int KFIRST = SPL < NB ? SPL : NB;     // K images among the first NB
 #pragma unroll
-    for (int i = 0; i < NB; ++i) fetch(i);
+    for (int i = 0; i < KFIRST; ++i) fetch(i);
     int my_slot[SPL];
     bool owner[SPL];
     {
@@ -211,8 +231,9 @@ __global__ __launch_bounds__(MAX_WAVES * 64, 4) void decode_q4_kernel(const Step
         }
     }
 
+
     // ---- q: the token's own logit, group sums, digits --------------------------------
-    dma_wait_upto<NB * IPB + META_COPIES>();    // (wave 0: its three copies have landed)
+    dma_wait_upto<KFIRST * IPB + META_COPIES>();    // (wave 0: its three copies have landed)
     lds_barrier();
     const T *q_l = reinterpret_cast<const T *>(sh.raw[0]), *kn_l = reinterpret_cast<const T *>(sh.raw[1]),
             *vn_l = reinterpret_cast<const T *>(sh.raw[2]);
@@ -224,7 +245,10 @@ __global__ __launch_bounds__(MAX_WAVES * 64, 4) void decode_q4_kernel(const Step
         sh.red_key[tid] = __longlong_as_double((long long)NO_CANDIDATE);
         sh.min_sum[0][tid] = sh.min_sum[1][tid] = 0.0;
     }
-    auto job = [&](int j) { return wave == (j + 2) % nw; };      // (waves 0 and 1 cut the digits)
+    // (waves 0 and 1 cut the digits; job j goes to wave (j + 2) mod waves, from a table: a division by a
+    // number of waves that is only known here takes 300 ns)
+    const unsigned jobs = (unsigned)(nw <= 4 ? 0x1032210210100000ull >> (16 * (nw - 1)) : 0x5432543254320432ull >> (16 * (nw - 5)));
+    auto job = [&](int j) { return wave == (int)((jobs >> (4 * j)) & 15u); };
     if (job(0)) {
         double a = 0.0;
 #pragma unroll
@@ -241,22 +265,25 @@ __global__ __launch_bounds__(MAX_WAVES * 64, 4) void decode_q4_kernel(const Step
         const double a = NG == 2 ? wave_sum((double)E::to_f(q_l[D - 64 + lane])) : 0.0;
         if (lane == 0) sh.qsum[1] = a * scale;
     }
-    if (job(3)) {
-        float n8[8];
-        load8<DT>(((lane / QL) == 1 ? vn_l : kn_l) + (lane % QL) * 8, n8);
+    if (job(3)) {                               // four elements per lane: the longest of the jobs
+        const T *x = ((lane / (2 * QL)) == 1 ? vn_l : kn_l) + (lane % (2 * QL)) * 4;
+        const float n4[4] = {E::to_f(x[0]), E::to_f(x[1]), E::to_f(x[2]), E::to_f(x[3])};
         float new_scale, new_min;
-        const unsigned new_word = q4_quantise8(n8, new_scale, new_min);
-        if (lane < 32) {
-            sh.new_row[lane] = new_word;
-            sh.new_row[32 + lane] = __float_as_uint(new_scale);
-            sh.new_row[64 + lane] = __float_as_uint(new_min);
+        const unsigned new_half = q4_quantise<16>(n4, new_scale, new_min);
+        if (lane < 4 * QL) {
+            reinterpret_cast<unsigned short *>(sh.new_row)[lane] = (unsigned short)new_half;
+            if (!(lane & 1)) {
+                sh.new_row[32 + lane / 2] = __float_as_uint(new_scale);
+                sh.new_row[64 + lane / 2] = __float_as_uint(new_min);
+            }
         }
     }
-    int qe[2];                                  // |q| < 2^qe in each group
-    exponents_above(fabsf(E::to_f(q_l[lane])), fabsf(E::to_f(q_l[D - 64 + lane])), qe[0], qe[1]);
-    for (int e = tid; e < D; e += nthr) {
+    for (int e = tid; e < D; e += nthr) {       // (a wave has the 64 elements of one group)
+        const float q_e = E::to_f(q_l[e]);
+        const int qe = exponent_above_wave(fabsf(q_e));
+        if (lane == 0) sh.q_exp[e >> 6] = qe;
         // rounded first: the low word of what is left is then exactly one in [0, 2^32)
-        const double x = rint((double)E::to_f(q_l[e]) * pow2(54 - (e < 64 ? qe[0] : qe[1])));
+        const double x = rint((double)q_e * pow2(54 - qe));
         const double hi = floor(x * 0x1p-32);
         const unsigned lo = (unsigned)fma(hi, -0x1p32, x);
         const unsigned long long bias = 0x0080808080808080ull;
@@ -267,6 +294,12 @@ __global__ __launch_bounds__(MAX_WAVES * 64, 4) void decode_q4_kernel(const Step
         for (int i = 0; i < 8; ++i) sh.digit[i][at] = (signed char)(d >> (8 * i));
     }
     lds_barrier();
+    // The first value images are only requested here: a copy is issued no faster than the CU's share of the
+    // stream comes in, and a wave that issues them all at the start gets to q 1 to 2 us later (512 heads x 410
+    // slots, 24 caches in turn: all at the start 12.0 us per step, here 11.1, behind the logits 10.4; but 1024
+    // heads 19.2 / 18.1 / 18.3, 3584 x 205 30.2 / 30.0 / 31.2).
+#pragma unroll
+    for (int i = KFIRST; i < NB; ++i) fetch(i);
     i32x4 aq[NG];
 #pragma unroll
     for (int m = 0; m < NG; ++m) {
@@ -281,7 +314,7 @@ __global__ __launch_bounds__(MAX_WAVES * 64, 4) void decode_q4_kernel(const Step
     const double s_self = sh.s_self, qsum[2] = {sh.qsum[0], sh.qsum[1]};
     // (digits cannot hold an infinity or a NaN in q: the logits are then not numbers)
     const bool q_finite = fabs(qsum[0] + qsum[1]) <= 1.79769313486231570815e+308;
-    const double digit_unit = !q_finite ? (double)NAN : used ? pow2((my_group ? qe[1] : qe[0]) - 54 + ((quarter & 1) ? 32 : 0)) * scale : 0.0;
+    const double digit_unit = !q_finite ? (double)NAN : used ? pow2(sh.q_exp[my_group] - 54 + ((quarter & 1) ? 32 : 0)) * scale : 0.0;
     const double min_unit = used && !(quarter & 1) ? qsum[my_group] : 0.0;
 
     // ---- logits ------------------------------------------------------------------------
@@ -303,7 +336,7 @@ __global__ __launch_bounds__(MAX_WAVES * 64, 4) void decode_q4_kernel(const Step
     // copies issued behind item i by the time it is waited for
     constexpr auto behind = [](int i) {
         const int last = i + NB - 1 < 2 * SPL - 1 ? i + NB - 1 : 2 * SPL - 1;
-        return (last - i) * IPB + (i < NB ? META_COPIES : 0);
+        return (last - i) * IPB + (i < KFIRST ? META_COPIES : 0);
     };
     for_blocks([&](auto tag) {
         constexpr int s = decltype(tag)::value;
@@ -379,6 +412,40 @@ __global__ __launch_bounds__(MAX_WAVES * 64, 4) void decode_q4_kernel(const Step
     float p_j[SPL];
 #pragma unroll
     for (int s = 0; s < SPL; ++s) p_j[s] = (float)(e_j[s] / den);          // 0 for unoccupied rows
+
+    // ---- score update (Algorithm 2, accumulate line: binary32 add of the binary32
+    // probability) and the eviction candidate: smallest (rank value, position) outside
+    // the window
+    // (with a sparse-attention pattern as the protected set the candidates are the slots
+    // it does not cover; the minimum over all slots is reduced alongside for the case
+    // that it covers them all, in the LDS words of the overflow path, idle by now)
+    dma_wait_upto<(SPL < NB ? SPL : NB) * IPB>();           // (behind the bookkeeping: value images)
+    unsigned long long key = NO_CANDIDATE, key_all = NO_CANDIDATE;
+    int key_slot = -1, key_all_slot = -1;
+    float acc_j[SPL];
+#pragma unroll
+    for (int s = 0; s < SPL; ++s) {
+        const int pos_j = *reinterpret_cast<const int *>(mine_l + L::META + s * 512 + lane * 4);
+        acc_j[s] = *reinterpret_cast<const float *>(mine_l + L::META + s * 512 + 256 + lane * 4);
+        acc_j[s] += p_j[s];
+        if (owner[s]) {
+            const unsigned long long c =
+                ((unsigned long long)__float_as_uint(rank_value(acc_j[s], pos_j, t, rank)) << 32) |
+                (unsigned)pos_j;
+            if (PAT ? !is_protected(pos_j, t, recent, protect, stride) : pos_j <= t - recent) {
+                if (c < key) { key = c; key_slot = my_slot[s]; }
+            }
+            if (PAT && c < key_all) { key_all = c; key_all_slot = my_slot[s]; }
+        }
+    }
+    {
+        const double kw = wave_min_f64(__longlong_as_double((long long)key));
+        if (lane == 0) sh.red_key[wave] = kw;
+    }
+    if constexpr (PAT) {
+        const double ka = wave_min_f64(__longlong_as_double((long long)key_all));
+        if (lane == 0) sh.red_max[wave] = ka;
+    }
 
     // ---- output ------------------------------------------------------------------------
     // (the weights of a block have exponents of their own, one per group: the scales of later
@@ -473,7 +540,6 @@ __global__ __launch_bounds__(MAX_WAVES * 64, 4) void decode_q4_kernel(const Step
         }
         refill(SPL + s);
     });
-    dma_wait_upto<0>();                         // the bookkeeping as well
     {
         // the wave's columns, in its first buffer (every image has been read)
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
@@ -490,49 +556,27 @@ __global__ __launch_bounds__(MAX_WAVES * 64, 4) void decode_q4_kernel(const Step
         if ((lane & 31) == 0 && (lane >> 5) < NG) sh.min_sum[lane >> 5][wave] = mg;
     }
 
-    // ---- score update (Algorithm 2, accumulate line: binary32 add of the binary32
-    // probability) and the eviction candidate: smallest (rank value, position) outside
-    // the window
-    // (with a sparse-attention pattern as the protected set the candidates are the slots
-    // it does not cover; the minimum over all slots is reduced alongside for the case
-    // that it covers them all, in the LDS words of the overflow path, idle by now)
-    unsigned long long key = NO_CANDIDATE, key_all = NO_CANDIDATE;
-    int key_slot = -1, key_all_slot = -1;
-    float acc_j[SPL];
-#pragma unroll
-    for (int s = 0; s < SPL; ++s) {
-        const int pos_j = *reinterpret_cast<const int *>(mine_l + L::META + s * 512 + lane * 4);
-        acc_j[s] = *reinterpret_cast<const float *>(mine_l + L::META + s * 512 + 256 + lane * 4);
-        acc_j[s] += p_j[s];
-        if (owner[s]) {
-            const unsigned long long c =
-                ((unsigned long long)__float_as_uint(rank_value(acc_j[s], pos_j, t, rank)) << 32) |
-                (unsigned)pos_j;
-            if (PAT ? !is_protected(pos_j, t, recent, protect, stride) : pos_j <= t - recent) {
-                if (c < key) { key = c; key_slot = my_slot[s]; }
-            }
-            if (PAT && c < key_all) { key_all = c; key_all_slot = my_slot[s]; }
-        }
-    }
-    {
-        const double kw = wave_min_f64(__longlong_as_double((long long)key));
-        if (lane == 0) sh.red_key[wave] = kw;
-    }
-    if constexpr (PAT) {
-        const double ka = wave_min_f64(__longlong_as_double((long long)key_all));
-        if (lane == 0) sh.red_max[wave] = ka;
-    }
     lds_barrier();
 
     // ---- write-back ---------------------------------------------------------------------
     for (int e = tid; e < D; e += nthr) {
+        // (all reads first, over every wave there can be: these sums end the step)
+        const unsigned char *w0 = smem + ((sizeof(Shared<D>) + 15) & ~(size_t)15) + (size_t)e * 8;
+        double mins[MAX_WAVES], parts[WIDE ? 2 : 1][MAX_WAVES];
+#pragma unroll
+        for (int w = 0; w < MAX_WAVES; ++w) {
+            mins[w] = sh.min_sum[e / 64][w];
+            const unsigned char *at = w0 + (size_t)min(w, nw - 1) * L::BYTES;
+            parts[0][w] = *reinterpret_cast<const double *>(at);
+            if constexpr (WIDE) parts[1][w] = *reinterpret_cast<const double *>(at + D * 8);
+        }
         double r = (double)p_self * (double)E::to_f(vn_l[e]);
 #pragma unroll
-        for (int w = 0; w < MAX_WAVES; ++w) r += sh.min_sum[e / 64][w];
-        const unsigned char *w0 = smem + ((sizeof(Shared<D>) + 15) & ~(size_t)15) + (size_t)e * 8;
-        for (int w = 0; w < nw; ++w) {
-            r += *reinterpret_cast<const double *>(w0 + (size_t)w * L::BYTES);
-            if (WIDE) r += *reinterpret_cast<const double *>(w0 + (size_t)w * L::BYTES + D * 8);
+        for (int w = 0; w < MAX_WAVES; ++w) r += mins[w];
+#pragma unroll
+        for (int w = 0; w < MAX_WAVES; ++w) {
+            r += w < nw ? parts[0][w] : 0.0;
+            if constexpr (WIDE) r += w < nw ? parts[1][w] : 0.0;
         }
         reinterpret_cast<T *>(out_g)[(size_t)head * D + e] = E::from_f((float)r);
     }

@@ -451,8 +451,8 @@ __global__ __launch_bounds__(SG_NT, 4) void select_gather_kernel(
             load8<QDT>(reinterpret_cast<const T *>(Kp + off) + l * 8, kx);
             load8<QDT>(reinterpret_cast<const T *>(Vp + off) + l * 8, vx);
             float ks, km, vs, vm;
-            const unsigned kw = q4_quantise8(kx, ks, km);
-            const unsigned vw = q4_quantise8(vx, vs, vm);
+            const unsigned kw = q4_quantise<8>(kx, ks, km);
+            const unsigned vw = q4_quantise<8>(vx, vs, vm);
             if (j >= 0) {
                 char *kr = Kc + (hoff + s) * QROWB, *vr = Vc + (hoff + s) * QROWB;
                 *reinterpret_cast<unsigned *>(kr + l * 4) = kw;

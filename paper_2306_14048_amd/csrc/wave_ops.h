@@ -208,28 +208,34 @@ __device__ inline bool is_protected(int p, int t, int recent, int protect, int s
 
 // ---- 4-bit group-wise storage ------------------------------------------------------
 //
-// A lane holds 8 consecutive elements of a row (exact binary32 images); the 8
-// lanes of an aligned group of 8 together hold one quantisation group of 64.
-// Returns the lane's 8 codes packed into one word (element i in bits 4i..4i+3)
+// A lane holds 64 / LANES consecutive elements of a row (exact binary32 images); the LANES
+// lanes of an aligned group together hold one quantisation group of 64.
+// Returns the lane's codes packed into one word (element i in bits 4i..4i+3)
 // and the group's (scale, min).  Every operation is a single correctly rounded
 // binary32 operation, in the order the storage format is defined in.
-__device__ inline unsigned q4_quantise8(const float (&x)[8], float &scale, float &mn)
+template <int LANES>
+__device__ inline unsigned q4_quantise(const float (&x)[64 / LANES], float &scale, float &mn)
 {
+    static_assert(LANES == 8 || LANES == 16, "");
     float lo = x[0], hi = x[0];
 #pragma unroll
-    for (int i = 1; i < 8; ++i) { lo = fminf(lo, x[i]); hi = fmaxf(hi, x[i]); }
+    for (int i = 1; i < 64 / LANES; ++i) { lo = fminf(lo, x[i]); hi = fmaxf(hi, x[i]); }
     lo = fminf(lo, __int_as_float(dpp<DPP_XOR1>(__float_as_int(lo))));
     hi = fmaxf(hi, __int_as_float(dpp<DPP_XOR1>(__float_as_int(hi))));
     lo = fminf(lo, __int_as_float(dpp<DPP_XOR2>(__float_as_int(lo))));
     hi = fmaxf(hi, __int_as_float(dpp<DPP_XOR2>(__float_as_int(hi))));
     lo = fminf(lo, __int_as_float(dpp<DPP_HALF_MIRROR>(__float_as_int(lo))));
     hi = fmaxf(hi, __int_as_float(dpp<DPP_HALF_MIRROR>(__float_as_int(hi))));
+    if constexpr (LANES == 16) {
+        lo = fminf(lo, __int_as_float(dpp<DPP_MIRROR>(__float_as_int(lo))));
+        hi = fmaxf(hi, __int_as_float(dpp<DPP_MIRROR>(__float_as_int(hi))));
+    }
     mn = lo;
     scale = __fdiv_rn(__fsub_rn(hi, lo), 15.0f);
     unsigned word = 0;
     if (scale > 0.0f) {
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
+        for (int i = 0; i < 64 / LANES; ++i) {
             float c = rintf(__fdiv_rn(__fsub_rn(x[i], lo), scale));   // half to even
             c = fminf(fmaxf(c, 0.0f), 15.0f);
             word |= (unsigned)c << (4 * i);

@@ -22,6 +22,13 @@ def test_q4_block_edges(d, k, heads, dt):
         q4_case(1, heads, d, k - 3, 6, (k + 1) // 2, k // 2, torch_dt[dt], 1.0, 81 + k)   # fills, then evicts
 
 
+@pytest.mark.parametrize("waves", range(1, 9))
+def test_q4_shared_work_with_every_number_of_waves(waves):
+    """Which wave sums, cuts digits and quantises the new token depends on how many there are."""
+    k, heads = 64 * waves - 5, 520 if waves == 1 else 2          # (few heads: at least two waves)
+    q4_case(1, heads, 64, k + 3, 4, (k + 1) // 2, k // 2, torch_dt["f16"], 1.0, 90 + waves)
+
+
 def dequantised(x):
     g = x.float().unflatten(-1, (-1, 64))
     mn, mx = g.amin(-1, keepdim=True), g.amax(-1, keepdim=True)
