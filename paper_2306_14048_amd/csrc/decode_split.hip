@@ -98,6 +98,7 @@ __global__ __launch_bounds__(PNW * 64, 4) void decode_part_kernel(const StepArgs
     for (int u = 0; u < U; ++u) {
         off[u] = (unsigned)min(u * RPI + row0, last) * ROWB + (unsigned)li * 16u;
         buf[u] = load_stream(Kb + off[u]);
+        in_step(u, U);
     }
     __builtin_amdgcn_sched_barrier(0);
 

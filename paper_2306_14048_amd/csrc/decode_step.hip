@@ -116,6 +116,7 @@ __global__ __launch_bounds__(NW * 64, 4) void decode_resident_kernel(const StepA
     for (int u = 0; u < U; ++u) {
         off[u] = (unsigned)min(u * RPI + row0, last) * ROWB + (unsigned)li * 16u;
         buf[u] = load_stream(Kb + off[u]);
+        if (NW == 8) in_step(u, U);
     }
     // the owned slot's bookkeeping (unconditional, clamped: a conditional load
     // would be merged with its default right here and stall on the whole stream)

@@ -30,6 +30,18 @@ __device__ inline uint4 load_stream(const char *p)
     return make_uint4(t.x, t.y, t.z, t.w);
 }
 
+// Behind every second of `count` first requests of a wave, in kernels with two waves per SIMD: the workgroup's
+// waves issue them in step.  Left alone the first wave of every SIMD issues all of its own before the second, whose first
+// row then arrives after the first's last; their arithmetic takes turns instead of sharing the SIMD.
+__device__ inline void in_step(int u, int count)
+{
+    if ((u & 1) && u + 1 < count) {
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+    }
+}
+
 // Marks the point from which a loaded row may be unpacked: inside a loop the
 // compiler otherwise moves the unpacking of 16-bit pairs to the end of the
 // previous iteration, right behind the loads, and with it the wait for them.
