@@ -3,7 +3,7 @@
 // One workgroup per head leaves most of the chip idle when there are fewer heads
 // than CUs, and a head's cache then streams at the rate of one CU (about 130 GB/s):
 // 64 heads x 3277 slots (bf16, d = 128, 110 MB) took 41.5 us, 2.6 TB/s; split it takes
-// 26.4 us: 19-21 us for the parts (5.1-5.8 TB/s) and 5 us for joining them.  Here `parts`
+// 24.3 us: 15-18 us for the parts (6.0-7.1 TB/s), 1.8 between the launches and 3-4 for joining them.  Here `parts`
 // workgroups share a head, each with a run of its slots, and a second, short launch
 // puts the parts together.  What one part needs of the others (the softmax normaliser)
 // is only needed for the scores and for the final scale of the output, so nothing in
@@ -369,25 +369,29 @@ Plan plan_of(int heads, int n_occ, int rpw, bool f32)
 {
     const int rpi = PNW * rpw, umax = rpw * 13 <= 64 ? 13 : 8;
     // Where the line lies.  A budget that the one-workgroup kernel holds in registers is
-    // bound by the latency of one pass over it, which a second launch (4.5 us) only adds
-    // to.  Beyond it, measured (us per step, one workgroup / split; every 15 to 60 slots of
-    // 1 to 32 heads up to 1100 slots, and of up to 255 heads up to 4096):
-    //   16-bit, d = 128     8 heads: 481 8.7 / 9.2, 571 8.6 / 9.1, 586 9.6 / 9.0, 700 9.3 / 8.8, 900 12.0 / 8.8; 32: 571 9.1 /
-    //                       9.0, 4096 47 / 17;  64: 520 9.5 / 10.5, 900 14.4 / 11.2;  128: 520 10.4 / 12.3, 1000 16.2 / 15.4,
-    //                       4096 55 / 51;  192: 1000 18 / 23, 4096 63 / 73
-    //   binary32, d = 64    8 heads: 513 6.8 / 8.1, 811 8.0 / 8.4, 856 8.4 / 8.7, 871 9.4 / 8.9, 1000 9.6 / 8.4;  64: 900 12.4 / 10.7;
-    //                       128: 902 14.4 / 14.2, 1976 27.1 / 27.7, 4096 52.7 / 49.2
-    //   binary32, d = 128   8 heads: 257 7.4 / 8.8, 300 9.0 / 8.3, 345 8.1 / 8.5, 409 8.3 / 8.8, 417 9.0 / 8.5, 433 10.9 / 8.6;
-    //                       64: 450 13.0 / 10.6;  128: 520 15.9 / 15.6, 4096 110 / 91;  192: 127 / 136
-    //   16-bit, d = 64      8 heads: 513 8.7 / 9.1, 633 9.0 / 9.0, 700 7.2 / 8.6, 768 7.1 / 8.8, 783 10.7 / 9.0, 1000 9.7 / 8.7;
-    //                       96: 700 8.0 / 10.7;  128: 1000 18 / 11.4
-    // With that last row size the one-workgroup kernel's time depends on its ring: 8 and 2 rounds
-    // are slow, 6 and 4 fast (255 heads: 1000 slots, ring 8, 20.2 / 16.0; 2048 40 / 27; 1061, ring 6, 13.0 /
+    // bound by the latency of one pass over it, which a second launch (1.8 us between the two and
+    // 3 in the second) only adds to.  Beyond it, split / one workgroup (time of a step in a graph, 1 to 255
+    // heads, 27 budgets up to 3300, and 12 more on either side of every line):
+    //   16-bit, d = 128     33 to 96 heads: 481 0.86 .. 0.95, 571 0.83 .. 0.91, 700 0.83 .. 0.92, 865 0.65 .. 0.77; 128: 481 0.93, 520
+    //                       and 545 1.01, 571 0.97, from 600 on 0.87 .. 0.96; 160: 0.97 .. 1.07; 200: 0.96 .. 1.22
+    //   binary32, d = 64    33 to 96 heads: 520 to 571 0.88 .. 0.98, 600 to 865 0.71 .. 0.94; 128: 600 0.95, 700 1.00, 811 1.01, 865 0.92;
+    //                       160: 0.97 .. 1.14; 200: 1.01 .. 1.29
+    //   binary32, d = 128   33 to 96 heads: 257 0.91 .. 1.07, 300 0.80 .. 0.89, 417 0.77 .. 0.84; 128: 300 0.97, 345 0.97, 417 0.93; 160:
+    //                       0.96 .. 1.11; 200: 1.03 .. 1.31
+    //   16-bit, d = 64      to 160 heads: 520 to 640 0.79 .. 0.91, 700 and 768 1.01 .. 1.12, 783 to 865 (from 33 heads on) 0.59 ..
+    //                       0.77; 200 and 255: 0.83 .. 0.96, 700 and 768 1.20 .. 1.25
+    // Up to 32 heads the lines of the first three lie higher than what now measures (0.76 .. 0.97 from 481, 600 and
+    // 300 slots on): sizes below them are promised to need no scratch.
+    // With 128-byte rows the one-workgroup kernel's time depends on its ring: 8 and 2 rounds
+    // are slow, 6 and 4 fast (255 heads: 1000 slots, ring 8, 20.2 us / split 16.0; 2048 40 / 27; 1061, ring 6, 13.0 /
     // 17.1; 1793 20.8 / 25.3; 1183, ring 4, 16.0 / 18.4;  160 heads: ring 6 1793 17.5 / 18.7, ring 4 1183 14.6 /
     // 14.0, 2708 29.5 / 24.4, 200 heads 1183 15.1 / 16.9;  128 heads: ring 6 1061 11.3 / 12.6, 1793 17.0 / 15.2).
     const int resident = rpi * (umax > 8 ? 15 : 8), rounds = (n_occ + rpi - 1) / rpi;
     int most_heads = 128;
-    const int least_slots = heads > 32 ? (rpw == 2 ? 450 : 900) : rpw == 2 ? 417 : rpw == 8 ? 769 : f32 ? 865 : 577;
+    const int least_slots = rpw == 8 ? 0
+                            : rpw == 2 ? (heads > 32 ? 300 : 417)
+                            : f32      ? (heads <= 32 ? 865 : heads <= 96 ? 577 : 900)
+                                       : (heads <= 32 ? 577 : heads <= 96 ? 0 : 571);
     if (rpw == 8) {
         const int ring = chunk_ring(rounds, umax);
         most_heads = ring == 6 ? (rounds > 18 ? 128 : 0) : ring == 4 ? 160 : 255;
