@@ -165,14 +165,6 @@ __global__ __launch_bounds__(ARW * G * 64, 2) void prefill_attn_kernel(
     const char *Vh = Vg + (size_t)head * (nk - nf) * ROWB;
 
     const int srow = s0 + rw * 32 + l32;             // this lane's query
-    uint4 st[NF];
-#pragma unroll
-    for (int f = 0; f < NF; ++f)
-        st[f] = *reinterpret_cast<const uint4 *>(Qh + (size_t)min(srow, nq - 1) * ROWB + (2 * f + half) * 16);
-    if (srow >= nq) {
-#pragma unroll
-        for (int f = 0; f < NF; ++f) st[f] = make_uint4(0, 0, 0, 0);
-    }
 
     // key tiles of this block (>= 1): up to the one that holds the last query's own key
     const int T = min((nk + SBN - 1) / SBN, (off + s0 + SROWS + SBN - 1) / SBN);
@@ -199,11 +191,8 @@ __global__ __launch_bounds__(ARW * G * 64, 2) void prefill_attn_kernel(
     const unsigned lds_w = __builtin_amdgcn_readfirstlane(
         (unsigned)reinterpret_cast<size_t>(smem) + first_copy * 1024);
     const unsigned last_row_off = (unsigned)(nk - 1) * ROWB;
-    // stage u holds what matrix phase u reads: key tile u and value tile u-1
-    // (indices clamped to existing tiles: the first stage's value tile and the
-    // last stage's key tile are never read)
+    // stage u holds what matrix phase u reads: key tile u (u < T) and value tile u-1 (u > 0)
     auto fetch = [&](int u, int stg) {
-        const int kt = min(u, T - 1), vt = min(max(u - 1, 0), T - 1);
         const unsigned base = lds_w + stg * STAGE;
         // (rows past the end, only in a ragged last tile, repeat row nk-1: masked)
         auto tile = [&](const i32x4 &rsrc, const i32x4 &rsrc_f, int t, const unsigned *chunk, unsigned lds) {
@@ -229,9 +218,23 @@ __global__ __launch_bounds__(ARW * G * 64, 2) void prefill_attn_kernel(
                     dma16(rsrc, min(t0 + koff[c], last_row_off) - edge + chunk[c], 0u, lds + c * copy_step * 1024);
             }
         };
-        tile(rsrc_k, rsrc_kf, kt, kchunk, base);
-        tile(rsrc_v, rsrc_vf, vt, vchunk, base + TILEK);
+        if (u < T) tile(rsrc_k, rsrc_kf, u, kchunk, base);
+        if (u > 0) tile(rsrc_v, rsrc_vf, u - 1, vchunk, base + TILEK);
     };
+    // The block's queries, through LDS as well (a fragment load straight from memory has 64 lanes on 32 rows: four
+    // times the address work of whole rows, and two groups would load them twice), in stage 1, swizzled like key rows.
+    static_assert(SROWS * ROWB <= STAGE, "a block's queries fit a stage");
+    {
+        const i32x4 rsrc_q = make_rsrc(Qh, (unsigned)nq * ROWB);
+        const unsigned to = __builtin_amdgcn_readfirstlane((unsigned)reinterpret_cast<size_t>(smem) + STAGE + wave * 1024);
+#pragma unroll
+        for (int c = 0; c < SROWS * CPRK / NT; ++c) {
+            const unsigned q = (unsigned)(c * ANW + wave) * 64u + lane, r = q / CPRK, pos = q % CPRK;
+            dma16(rsrc_q, (unsigned)min(s0 + (int)r, nq - 1) * ROWB + (pos ^ ((r >> RSHK) & KMASKK)) * 16u, 0u,
+                  to + c * ANW * 1024);
+        }
+    }
+    fetch(0, 0);
 
     // LDS read offsets.  Key rows are visited so that MFMA row 16a + 8b + 4c + e
     // of a 32-row block is key 16a + 8c + 4b + e (bits 2 and 3 exchanged): the
@@ -273,12 +276,21 @@ __global__ __launch_bounds__(ARW * G * 64, 2) void prefill_attn_kernel(
     uint4 pfrag[KS];                        // probabilities of the previous tile, packed 16-bit
     bool live_prev = false;
 
-    fetch(0, 0);
     dma_wait_upto<0>();
-#pragma unroll
-    for (int f = 0; f < NF; ++f)
-        asm volatile("" ::"v"(st[f].x), "v"(st[f].y), "v"(st[f].z), "v"(st[f].w));
     wg_barrier();
+    uint4 st[NF];
+    {
+        const int row = rw * 32 + l32;
+        const unsigned char *q = smem + STAGE + row * ROWB;
+#pragma unroll
+        for (int f = 0; f < NF; ++f)
+            st[f] = *reinterpret_cast<const uint4 *>(q + (((2 * f + half) ^ ((row >> RSHK) & KMASKK)) * 16));
+    }
+    if (srow >= nq) {
+#pragma unroll
+        for (int f = 0; f < NF; ++f) st[f] = make_uint4(0, 0, 0, 0);
+    }
+    wg_barrier();                           // every wave has its queries: stage 1 may be filled
     if (SKEW && grp == 1) wg_barrier();     // the second group runs one phase behind
 
     int stg = 0;
@@ -288,7 +300,7 @@ __global__ __launch_bounds__(ARW * G * 64, 2) void prefill_attn_kernel(
     auto step = [&](int u, auto masked_tag, auto last_tag) {
         constexpr bool MASKED = decltype(masked_tag)::value;
         constexpr bool LAST = decltype(last_tag)::value;
-        fetch(u + 1, stg ^ 1);                               // into the stage of iteration u-1
+        if constexpr (!LAST) fetch(u + 1, stg ^ 1);          // into the stage of iteration u-1
         const unsigned char *sb = smem + stg * STAGE + grp * (ABN * ROWB);     // this group's rows of the tiles
         const int r0 = u * SBN + grp * ABN;
         const int w0 = s0 + rw * 32;
@@ -411,49 +423,68 @@ __global__ __launch_bounds__(ARW * G * 64, 2) void prefill_attn_kernel(
     if (SKEW && grp == 0) wg_barrier();     // the barrier the second group spent at the start
 
     // ---- the groups' parts of a query, brought to the larger reference ----------------
+    // Each group hands the other half of the output dims and finishes the rest.
+    constexpr int FDB = NDB / G;            // 32-dim blocks that a wave finishes
     if constexpr (G > 1) {
-        float *part = reinterpret_cast<float *>(smem) + (size_t)rw * (NDB * 16 + 2) * 64 + lane;   // (stages are done with)
-        if (grp == 1) {
-            part[0] = m_run;
-            part[64] = l_run;
+        constexpr int PART = (FDB * 16 + 2) * 64;
+        float *parts = reinterpret_cast<float *>(smem) + (size_t)rw * 2 * PART + lane;    // (stages are done with)
+        float *mine = parts + grp * PART;
+        const float *other = parts + (1 - grp) * PART;
+        auto hand_over = [&](auto first) {
+            mine[0] = m_run;
+            mine[64] = l_run;
 #pragma unroll
-            for (int db = 0; db < NDB; ++db)
+            for (int db = 0; db < FDB; ++db)
 #pragma unroll
-                for (int v = 0; v < 16; ++v) part[(2 + db * 16 + v) * 64] = oacc[db][v];
-        }
+                for (int v = 0; v < 16; ++v) mine[(2 + db * 16 + v) * 64] = oacc[decltype(first)::value + db][v];
+        };
+        if (grp == 0) hand_over(std::integral_constant<int, FDB>{});
+        else hand_over(std::integral_constant<int, 0>{});
         wg_barrier();
-        if (grp == 1) return;
         // (group 0 has key 0: its reference is finite; group 1 may have seen nothing: weight 0)
-        const float m1 = part[0], mx = fmaxf(m_run, m1);
+        const float m1 = other[0], mx = fmaxf(m_run, m1);
         const float f0 = __builtin_amdgcn_exp2f((m_run - mx) * c2), f1 = __builtin_amdgcn_exp2f((m1 - mx) * c2);
-        l_run = l_run * f0 + part[64] * f1;
+        l_run = l_run * f0 + other[64] * f1;
+        auto take_over = [&](auto first) {
 #pragma unroll
-        for (int db = 0; db < NDB; ++db)
+            for (int db = 0; db < FDB; ++db)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) oacc[db][v] = oacc[db][v] * f0 + part[(2 + db * 16 + v) * 64] * f1;
+                for (int v = 0; v < 16; ++v) {
+                    constexpr int F = decltype(first)::value;
+                    oacc[F + db][v] = oacc[F + db][v] * f0 + other[(2 + db * 16 + v) * 64] * f1;
+                }
+        };
+        if (grp == 0) take_over(std::integral_constant<int, 0>{});
+        else take_over(std::integral_constant<int, FDB>{});
         m_run = mx;
     }
 
     // ---- normalise and store ------------------------------------------------------
     const float l_tot = l_run + other_half(l_run);
     const float inv = 1.0f / l_tot;
-    if (srow < nq) {
-        using E = Elem<DT>;
-        typename E::T *orow = reinterpret_cast<typename E::T *>(Og) + ((size_t)head * nq + srow) * D;
+    using E = Elem<DT>;
+    typename E::T *orow = reinterpret_cast<typename E::T *>(Og) + ((size_t)head * nq + srow) * D;
+    // The lane halves hold 4 dims each of every 8: they exchange so that one has all 8 of one group of
+    // dims and the other those of the next, and 16 bytes go out at a time.  (A pair per conversion: element by
+    // element, bf16 took a branch for NaNs on every one.)
+    auto finish = [&](auto first) {
 #pragma unroll
-        for (int db = 0; db < NDB; ++db)
+        for (int db = decltype(first)::value; db < decltype(first)::value + FDB; ++db)
 #pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                // (a pair per conversion: element by element, bf16 took a branch for NaNs on every one)
-                *reinterpret_cast<uint2 *>(orow + 32 * db + 8 * g + 4 * half) =
-                    make_uint2(pack2<DT>(oacc[db][4 * g] * inv, oacc[db][4 * g + 1] * inv),
-                               pack2<DT>(oacc[db][4 * g + 2] * inv, oacc[db][4 * g + 3] * inv));
+            for (int g = 0; g < 4; g += 2) {
+                auto pair = [&](int v) { return pack2<DT>(oacc[db][v] * inv, oacc[db][v + 1] * inv); };
+                const auto x = __builtin_amdgcn_permlane32_swap(pair(4 * g), pair(4 * g + 4), false, false);
+                const auto y = __builtin_amdgcn_permlane32_swap(pair(4 * g + 2), pair(4 * g + 6), false, false);
+                if (srow < nq)
+                    *reinterpret_cast<uint4 *>(orow + 32 * db + 8 * (g + half)) = make_uint4(x[0], y[0], x[1], y[1]);
             }
-        if (half == 0) {
-            const float l2 = m_run * c2 + __builtin_amdgcn_logf(l_tot);      // log2 of the row's normaliser
-            lse2[(size_t)head * nq + srow] = l2;
-            if (lse_nat) lse_nat[(size_t)head * nq + srow] = l2 * 0.69314718055994531f;
-        }
+    };
+    if (G == 1 || grp == 0) finish(std::integral_constant<int, 0>{});
+    else finish(std::integral_constant<int, (G > 1 ? FDB : 0)>{});
+    if (srow < nq && half == 0 && grp == 0) {
+        const float l2 = m_run * c2 + __builtin_amdgcn_logf(l_tot);      // log2 of the row's normaliser
+        lse2[(size_t)head * nq + srow] = l2;
+        if (lse_nat) lse_nat[(size_t)head * nq + srow] = l2 * 0.69314718055994531f;
     }
 }
 
