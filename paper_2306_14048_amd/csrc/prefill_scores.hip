@@ -112,6 +112,11 @@ __device__ __forceinline__ void prefill_pass(
     constexpr int CPT = CHUNKS / NT;      // tile-copy instructions per wave per tile
     constexpr int CPF = CPT + (COLSUM ? 1 : 0);   // copy instructions per wave per fetch
     constexpr int LPW = BN / NWV;         // row statistics each wave copies per tile
+    // Pieces in which a wave's stationary rows fit its share of two tile buffers.  Loaded directly: where these are more
+    // than two, or two halves of a 128-byte row (512 heads x 2048, d = 64, 410 us, copied 415), and binary32 rows without
+    // a second group (a block is its matrix instructions there: 256 x 300, d = 128, 93.7 / 94.9, 8 x 256, d = 64, 25.8 / 25.1).
+    constexpr int SROUNDS = NWV * 16 / BN;
+    constexpr bool STAGED = (SROUNDS == 1 || (SROUNDS == 2 && ROWB >= 256)) && (DT != H2O_F32 || G > 1);
     static_assert(CHUNKS % NT == 0 && CPT >= 1, "every thread moves the same number of chunks");
     static_assert(SROWS % BN == 0 && BN % NWV == 0 && LPW <= 64, "tiles divide the workgroup's rows");
 
@@ -158,18 +163,18 @@ __device__ __forceinline__ void prefill_pass(
     const char *Tg = COLSUM ? Qg + (size_t)head * nq * ROWB : Kh;       // streamed operand
 
     const int srow = s0 + rw * 32 + l32;             // this lane's stationary row
-    // Rows past the end are clamped to the last row (in bounds) and zeroed after arrival.
     uint4 st[NF];
-    {
+    // Rows past the end are clamped to the last row (in bounds) and zeroed after arrival.
+    if constexpr (!STAGED) {
         const int r = min(srow, ns - 1);
         const char *row = !COLSUM ? Sg + (size_t)r * ROWB
                           : r < nf ? Kfh + (size_t)r * ROWB : Kh + (size_t)(r - nf) * ROWB;
 #pragma unroll
         for (int f = 0; f < NF; ++f) st[f] = *reinterpret_cast<const uint4 *>(row + (2 * f + half) * 16);
-    }
-    if (srow >= ns) {
+        if (srow >= ns) {
 #pragma unroll
-        for (int f = 0; f < NF; ++f) st[f] = make_uint4(0, 0, 0, 0);
+            for (int f = 0; f < NF; ++f) st[f] = make_uint4(0, 0, 0, 0);
+        }
     }
 
     const int ntile_all = (nt + BN - 1) / BN;
@@ -249,18 +254,64 @@ __device__ __forceinline__ void prefill_pass(
     float c_run = 0.f;                      // pass 2: running column sum
 
     // Every block has at least one tile.  The first two are requested
-    // here; waiting for the first also completes the stationary loads above
-    // (vector loads finish in order).  Requests past the block's last tile repeat
+    // here.  Requests past the block's last tile repeat
     // that tile (harmless, keeps the request count per iteration constant).
-    fetch(t_begin, 0, 0);
-    fetch(min(t_begin + 1, t_end - 1), 1, 1);
-    dma_wait_upto<CPF>();
-    // tell the compiler that the stationary fragments have arrived (it cannot see
-    // the wait above), or it would re-wait for them, and with them for the tile
-    // copies in flight, in front of the MFMAs of every iteration
+    if constexpr (STAGED) {
+        // A wave's stationary rows go through its share of the tile buffers 1 and 2, SROUNDS pieces of each row in
+        // turn: copied row by row they take a quarter of the address work of fragment loads, where
+        // 64 lanes are on 32 rows (both passes, d = 128, us: 512 heads x 2048 654 -> 636, 3584 x 256 183 -> 166, 200 x 300 20.9
+        // -> 18.3, 32 x 1531 37.7 -> 34.7, 32 x 512 17.3 -> 15.1, 8 x 4096 70.9 -> 68.3).
+        constexpr int SEG = ROWB / SROUNDS, SCH = SEG / 16;        // bytes and chunks of a row per round
+        constexpr int SSH = SEG >= 256 ? 0 : SEG >= 128 ? 1 : 2, SMASK = SCH - 1;
+        constexpr int SCPT = 32 * SEG / 1024;                      // copies per wave and round
+        const i32x4 rsrc_s = make_rsrc(Sg, (unsigned)(COLSUM ? nk - nf : nq) * ROWB);
+        const i32x4 rsrc_sf = make_rsrc(COLSUM && nf ? Kfh : Sg, COLSUM ? (unsigned)nf * ROWB : 0u);
+        unsigned char *area = tile_l + TILEB + wave * (32 * SEG);
+        const unsigned area_lds = __builtin_amdgcn_readfirstlane((unsigned)reinterpret_cast<size_t>(area));
+        auto copy_rows = [&](int round) {
 #pragma unroll
-    for (int f = 0; f < NF; ++f)
-        asm volatile("" ::"v"(st[f].x), "v"(st[f].y), "v"(st[f].z), "v"(st[f].w));
+            for (int c = 0; c < SCPT; ++c) {
+                const unsigned q = (unsigned)c * 64u + lane, r = q / SCH, pos = q % SCH;
+                const int row = min(s0 + rw * 32 + (int)r, ns - 1);
+                const unsigned at = (unsigned)round * SEG + (pos ^ ((r >> SSH) & SMASK)) * 16u;
+                if (COLSUM && row < nf) dma16(rsrc_sf, (unsigned)row * ROWB + at, 0u, area_lds + c * 1024);
+                else dma16(rsrc_s, (unsigned)(COLSUM ? row - nf : row) * ROWB + at, 0u, area_lds + c * 1024);
+            }
+        };
+        copy_rows(0);
+        fetch(t_begin, 0, 0);
+#pragma unroll
+        for (int round = 0; round < SROUNDS; ++round) {
+            if (round == 0) dma_wait_upto<CPF>();
+            else dma_wait_upto<0>();
+#pragma unroll
+            for (int i = 0; i < NF / SROUNDS; ++i)
+                st[round * (NF / SROUNDS) + i] = *reinterpret_cast<const uint4 *>(
+                    area + l32 * SEG + (((2 * i + half) ^ ((l32 >> SSH) & SMASK)) * 16));
+            if (round + 1 < SROUNDS) {
+                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+                copy_rows(round + 1);
+            }
+        }
+        if (srow >= ns) {
+#pragma unroll
+            for (int f = 0; f < NF; ++f) st[f] = make_uint4(0, 0, 0, 0);
+        }
+        wg_barrier();                      // every wave has its rows: the buffers may be filled
+        fetch(min(t_begin + 1, t_end - 1), 1, 1);
+        dma_wait_upto<CPF>();
+    } else {
+        // (waiting for the first tile also completes the stationary loads above: vector loads finish in order)
+        fetch(t_begin, 0, 0);
+        fetch(min(t_begin + 1, t_end - 1), 1, 1);
+        dma_wait_upto<CPF>();
+        // tell the compiler that the stationary fragments have arrived (it cannot see
+        // the wait above), or it would re-wait for them, and with them for the tile
+        // copies in flight, in front of the MFMAs of every iteration
+#pragma unroll
+        for (int f = 0; f < NF; ++f)
+            asm volatile("" ::"v"(st[f].x), "v"(st[f].y), "v"(st[f].z), "v"(st[f].w));
+    }
     wg_barrier();
     if (grp == 1) wg_barrier();            // second group runs one phase behind
 
