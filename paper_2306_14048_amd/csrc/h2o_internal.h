@@ -181,13 +181,16 @@ static inline SelectPlan select_plan(int heads, int k, int n, bool in_place)
     // Workgroups per head: enough to give every CU one, but at least 32 slots each (one round of
     // the row copy); in place one, which alone knows what it has read.
     int parts = in_place ? 1 : (256 + heads - 1) / heads;
-    // Beyond SG_LDS_KEYS candidates every sweep reads the scores again.  A head's workgroups go to
-    // different XCDs, so each XCD reads those of parts / 8 of the heads (all from 8 parts on):
-    // that many have to stay in its 4 MB L2.  us, parts halved / not (eight waves): 32 heads, 2048 of 40 000
+    // Beyond SG_LDS_KEYS candidates every sweep reads the scores again.  Those that an XCD's workgroups read have to
+    // stay in its 4 MB L2: an eighth of the heads where heads come in eights (all workgroups of a head on one
+    // XCD), else parts / 8 of them, all from 8 parts on.  us, eights, halved by the other count / not: 32 heads,
+    // 2048 of 40 000 68.5 / 66.3, 64 heads, 2048 of 30 000 77.3 / 66.2, 16 heads, 4000 of 60 000 92.9 / 87.5.  Not
+    // in eights, parts halved / not (measured on such counts before eights were put on one XCD, eight waves): 32 heads, 2048 of 40 000
     // (2.6 / 5.1 MB) 123 / 180 (one workgroup per head 138), 64 heads 131 / 185, 64 heads, 200 of 28 673
     // (1.8 / 3.7 MB) 76 / 114; 16 heads, 2048 of 40 000 (2.6 MB as it is) 119 / 117.
     if (n > SG_LDS_KEYS)
-        while (parts > 1 && (long long)heads * (parts < 8 ? parts : 8) * n * 4 > 8 * (3LL << 20)) parts /= 2;
+        while (parts > 1 && (long long)heads * (heads % 8 == 0 ? 1 : parts < 8 ? parts : 8) * n * 4 > 8 * (3LL << 20))
+            parts /= 2;
     // Every workgroup makes the whole selection.  Beyond 4096 candidates that is most of the time, and
     // rounding up, which puts a second one on some CUs, costs more than the CUs that rounding down leaves
     // idle.  f16, d = 128, us, reset included, up with eight waves / down with sixteen: 12 heads, 840 of 4200 14.2 /

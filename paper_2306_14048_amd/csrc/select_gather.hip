@@ -38,6 +38,50 @@ __device__ inline unsigned wave_inclusive_scan(unsigned v)
     return v;
 }
 
+// The bin of a digit's histogram in which the count from the top reaches `need`, the count above that bin and its own.
+// Every wave adds up its share of the bins (highest first), a barrier, then every wave finds the share and
+// in it the bin: all counters are read once by the workgroup instead of once by each wave (1700 -> 900 cycles).
+// `sums` holds NW words that nothing else uses.
+struct BinAt { int bin; unsigned above, count; };
+template <int NW> __device__ inline BinAt find_bin(const unsigned *hist, unsigned need, unsigned *sums)
+{
+    constexpr int SHARE = SG_BINS / NW, PER = SHARE / 64;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    struct __align__(4 * PER) Bins { unsigned c[PER]; };          // ascending
+    auto bins_of = [&](int w) {
+        return *reinterpret_cast<const Bins *>(hist + SG_BINS - SHARE * w - PER * (lane + 1));
+    };
+    auto total = [](const Bins &b) {
+        unsigned t = 0;
+#pragma unroll
+        for (int i = 0; i < PER; ++i) t += b.c[i];
+        return t;
+    };
+    const unsigned share = wave_inclusive_scan(total(bins_of(wave)));
+    if (lane == 63) sums[wave] = share;
+    __syncthreads();
+    unsigned mine = lane < NW ? sums[lane] : 0;
+    unsigned upto = wave_inclusive_scan(mine);
+    const int w = __builtin_amdgcn_readfirstlane(__ffsll((long long)__ballot(upto >= need)) - 1);
+    unsigned above = __builtin_amdgcn_readlane((int)(upto - mine), w);
+    const Bins b = bins_of(w);
+    mine = total(b);
+    upto = above + wave_inclusive_scan(mine);
+    const int at = __builtin_amdgcn_readfirstlane(__ffsll((long long)__ballot(upto >= need)) - 1);
+    above = __builtin_amdgcn_readlane((int)(upto - mine), at);
+    int i = PER - 1;
+    unsigned count = __builtin_amdgcn_readlane((int)b.c[PER - 1], at);
+#pragma unroll
+    for (int next = PER - 2; next >= 0; --next) {
+        if (above + count < need) {                   // (all of it is wave-uniform)
+            above += count;
+            count = __builtin_amdgcn_readlane((int)b.c[next], at);
+            i = next;
+        }
+    }
+    return {SG_BINS - SHARE * w - PER * (at + 1) + i, above, count};
+}
+
 // Sum over the workgroup of one non-negative int per thread (every thread gets it).  `scratch`
 // holds NW ints (waves of the workgroup).
 template <int NW> __device__ inline int block_sum(int v, int *scratch)
@@ -70,15 +114,16 @@ template <int NW> __device__ inline int block_sum(int v, int *scratch)
 // thread (all reads in flight at once, no LDS latency in the sweeps), in LDS for
 // longer prompts, and beyond SG_LDS_KEYS candidates formed again for every sweep.
 // The selection is issue-bound (every workgroup makes all of it), hence the keys that carry
-// their kind and the digits that cost one barrier each; what a wave does after the sweeps is
+// their kind, a histogram that the workgroup reads once per digit, no digit behind one whose bin is kept
+// whole (nearly always the third) and one compare per key for the count; what a wave does after the sweeps is
 // latency, hence scans in registers, no slots for entries that other workgroups copy, and
 // bookkeeping that is requested in front of the row copy and stored behind it.  Cycles of 32 heads,
-// 3277 of 16 384: 33 500 for the selection and 2100 for the bookkeeping with shuffles and a ballot
-// per tie test, 26 300 and 0 now, then 33 000 for the rows (110 MB, 8 TB/s of read + write).
-// Measured (reset included, three prompts in turn, so that rows come from HBM; us, before that
-// / now; one workgroup per head and byte digits before both): 32 heads, 3277 of 16 384 tokens, f16 d =
-// 128: 39.7 / 35.4 (134); 128 heads, 819 of 4096 30.5 / 29.0 (42); 512 heads, 410 of 2048 54.2 / 52.8; 64 heads, 900
-// of 9000 24.7 / 21.8; 32 heads, 2048 of 30 000 102 / 60; 16 heads, 4000 of 60 000 188 / 104.
+// 3277 of 16 384: 29 000 for the selection with all three digits, every wave reading the whole histogram, two ballots
+// per key and the scores fetched by every XCD (8600 until they had come), 20 100 now (5500 until the scores have come, 4900
+// first sweep, 4400 second, 1100 to find each bin, 4500 count and slots), then 32 000 for the rows (110 MB, 8 TB/s of read + write).
+// This kernel alone (three prompts in turn, so that rows come from HBM; us, before that / now): 32 heads, 3277 of 16 384
+// tokens, f16 d = 128: 32.7 / 29.1; 306 of 1531 7.2 / 6.55; 128 heads, 819 of 4096 25.3 / 24.1; 512 heads, 410 of 2048 40.5 /
+// 39.6; 12 heads, 1600 of 8000 11.9 / 10.1.
 // (Tried: four counters per bin of the first digit, no gain, so the atomics' queue is not what
 // that sweep waits for.)
 //
@@ -104,9 +149,15 @@ __global__ __launch_bounds__(SG_NT, 4) void select_gather_kernel(
     unsigned *key_l = reinterpret_cast<unsigned *>(sel_l + part_slots);   // [n] (SG_KEYS_LDS)
     __shared__ __align__(16) unsigned hist[3][SG_BINS];      // one per digit
     __shared__ int scan_l[2 * SG_NW];
+    __shared__ unsigned sums_l[3][SG_NW];
 
-    const int head = blockIdx.x / parts, tid = threadIdx.x;
-    const int sb = (blockIdx.x % parts) * part_slots;  // this workgroup's slots [sb, se)
+    const int tid = threadIdx.x;
+    // Consecutive workgroups go to the 8 XCDs in turn.  All workgroups of a head read all of its scores: on one XCD
+    // (heads in eights) these come from memory once and from its L2 then, instead of once for each XCD.
+    const bool eights = parts > 1 && gridDim.x % (8 * parts) == 0;
+    const int turn = eights ? blockIdx.x >> 3 : blockIdx.x;
+    const int head = eights ? turn / parts * 8 + (blockIdx.x & 7) : turn / parts;
+    const int sb = turn % parts * part_slots;          // this workgroup's slots [sb, se)
     const int se = min(k, sb + part_slots);
     const float *sc_in = score + (size_t)head * n;
     const float *bs = base ? base + (size_t)head * n : nullptr;
@@ -237,19 +288,24 @@ __global__ __launch_bounds__(SG_NT, 4) void select_gather_kernel(
             for (int j = j0 + lane; j < j1; j += 64) key_l[j] = kind_of(j, candidate_key(sc_of(j), j));
         }
         unsigned thr = KEY_SURE - 1u, need = 0;        // keep keys > thr, and `need` of those == thr
+        bool whole = false;                            // ... or simply all keys >= thr
         if (want > 0) {
             // radix select: the want-th largest key among the candidates (there are more
             // than `want` of them: n exceeds the budget).  Three digits of 11, 11 and 10
             // bits: the first one (sign, exponent, two mantissa bits) already spreads
             // scores over dozens of bins, where 8 bits had put nearly all of them, and the
             // LDS atomics with them, into a handful.
+            // A digit whose bin is kept whole is the last one: every key from its lowest on is kept.
             unsigned prefix = 0, mask = 0;
             need = (unsigned)want;
+            __syncthreads();                           // the counters are zero (and keys in LDS written)
+            sweep([&](int, unsigned key) {
+                if (key - 1u < KEY_SURE - 1u) atomicAdd(&hist[0][key >> 21], 1u);
+            });
 #pragma unroll 1
             for (int d = 0; d < 3; ++d) {
                 const int shift = d == 0 ? 21 : d == 1 ? 10 : 0;
                 const unsigned dmask = d == 2 ? 1023u : 2047u;
-                if (d == 0) __syncthreads();           // the counters are zero (and keys in LDS written)
                 // (a key that agrees with the digits found so far is a candidate, unless those are
                 // all zeros or all ones, which the two marks agree with as well)
                 if (d > 0 && prefix != 0 && prefix != mask) {
@@ -257,57 +313,49 @@ __global__ __launch_bounds__(SG_NT, 4) void select_gather_kernel(
                     sweep([&](int, unsigned key) {
                         if (key >> (shift + (d == 1 ? 11 : 10)) == known) atomicAdd(&hist[d][(key >> shift) & dmask], 1u);
                     });
-                } else {
+                } else if (d > 0) {
                     sweep([&](int, unsigned key) {
                         if (((key ^ prefix) & mask) == 0 && key - 1u < KEY_SURE - 1u)
                             atomicAdd(&hist[d][(key >> shift) & dmask], 1u);
                     });
                 }
                 __syncthreads();
-                // The bin in which the count from the top reaches `need`.  Every wave finds it for
-                // itself (one barrier per digit): a lane adds up 32 bins, highest lane first, a
-                // scan finds the lane in which `need` is reached, a second one its bin.
-                unsigned mine = 0;
-                {
-                    const uint4 *h = reinterpret_cast<const uint4 *>(hist[d] + SG_BINS - 32 - 32 * lane);
-#pragma unroll
-                    for (int i = 0; i < 8; ++i) {
-                        const uint4 x = h[(i + lane) & 7];      // (spread over the banks)
-                        mine += (x.x + x.y) + (x.z + x.w);
-                    }
-                }
-                unsigned upto = wave_inclusive_scan(mine);
-                const int at = __builtin_amdgcn_readfirstlane(
-                    __ffsll((long long)__ballot(upto >= need)) - 1);
-                const unsigned above = __builtin_amdgcn_readlane((int)(upto - mine), at);
-                const int first = SG_BINS - 1 - 32 * at;        // highest of its bins
-                mine = lane < 32 ? hist[d][first - lane] : 0;
-                upto = above + wave_inclusive_scan(mine);
-                const int bin = __builtin_amdgcn_readfirstlane(
-                    __ffsll((long long)__ballot(upto >= need)) - 1);
-                need -= (unsigned)__builtin_amdgcn_readlane((int)(upto - mine), bin);   // still needed inside that bin
-                prefix |= (unsigned)(first - bin) << shift;
+                const BinAt at = find_bin<SG_NW>(hist[d], need, sums_l[d]);
+                need -= at.above;                      // still needed inside that bin
+                prefix |= (unsigned)at.bin << shift;
                 mask |= dmask << shift;
+                whole = at.count == need;
+                if (whole) break;
             }
-            thr = prefix;
+            thr = whole ? max(prefix, 1u) : prefix;
         }
         // Ranks in position order.  A wave first counts, in its run, the entries that are kept
         // outright and those at the threshold, then (knowing how many of both the waves in
         // front have) it assigns slots.
         int sure_cnt = 0, eq_cnt = 0;
-        sweep([&](int, unsigned key) {
-            sure_cnt += __popcll(__ballot(key > thr));
-            eq_cnt += __popcll(__ballot(key == thr));
-        });
+        if (whole) {
+            unsigned kept = 0;
+            sweep([&](int, unsigned key) { kept += key >= thr; });
+            sure_cnt = __builtin_amdgcn_readlane((int)wave_inclusive_scan(kept), 63);
+            need = 0;
+        } else {
+            sweep([&](int, unsigned key) {
+                sure_cnt += __popcll(__ballot(key > thr));
+                eq_cnt += __popcll(__ballot(key == thr));
+            });
+        }
         __syncthreads();
         if (lane == 0) { scan_l[wave] = sure_cnt; scan_l[SG_NW + wave] = eq_cnt; }
         __syncthreads();
-        int slot = 0, e = 0, eq_total = 0;
-#pragma unroll
-        for (int w = 0; w < SG_NW; ++w) {
-            if (w < wave) { slot += scan_l[w]; e += scan_l[SG_NW + w]; }
-            eq_total += scan_l[SG_NW + w];
-        }
+        // (entries of the waves in front, by a scan over the waves in the lanes)
+        auto in_front = [&](const int *counts, int &total) {
+            const unsigned mine = lane < SG_NW ? (unsigned)counts[lane] : 0u, upto = wave_inclusive_scan(mine);
+            total = __builtin_amdgcn_readlane((int)upto, SG_NW - 1);
+            return __builtin_amdgcn_readlane((int)(upto - mine), wave);
+        };
+        int eq_total = 0, sure_total;
+        int slot = in_front(scan_l, sure_total);
+        const int e = whole ? 0 : in_front(scan_l + SG_NW, eq_total);
         // among equal scores the higher positions are kept: the last `need` of them
         const int eq_first = eq_total - (int)need;
         slot += max(0, e - eq_first);
@@ -326,12 +374,13 @@ __global__ __launch_bounds__(SG_NT, 4) void select_gather_kernel(
                 });
             } else {
                 const unsigned long long below = (1ull << lane) - 1ull;
+                int eq = e;
                 sweep([&](int j, unsigned key) {
                     const unsigned long long eqs = __ballot(key == thr);
                     bool keep = key > thr;
                     if (eqs) {                         // wave-uniform, rare
-                        keep = keep || (key == thr && e + __popcll(eqs & below) >= eq_first);
-                        e += __popcll(eqs);
+                        keep = keep || (key == thr && eq + __popcll(eqs & below) >= eq_first);
+                        eq += __popcll(eqs);
                     }
                     const unsigned long long kept = __ballot(keep);
                     const int mine = slot + __popcll(kept & below);

@@ -41,6 +41,10 @@ def kept_by_sorting(score, heavy, recent, averaged, protect, stride):
     (28673, 30, 100, 103, False, 0, True),     # fewer workgroups per head: the scores stay in the L2
     (5000, 2, 300, 31, True, 1, True),
     (28673, 1, 300, 33, False, 1, True),
+    (1531, 16, 153, 153, False, 0, False),     # heads in eights: a head's workgroups on one XCD
+    (4097, 24, 400, 401, True, 0, True),
+    (16384, 8, 1700, 1577, False, 0, False),
+    (28673, 64, 700, 300, False, 0, True),
     (2500, 2, 0, 70, False, 0, False),         # window only
     (2500, 2, 70, 0, False, 0, True),          # no window
 ])
@@ -66,3 +70,33 @@ def test_select_branches(n, heads, heavy, recent, averaged, protect, tied):
         assert torch.equal(Kc[h].view(torch.int16), K[0, h, at].view(torch.int16))
         assert torch.equal(Vc[h].view(torch.int16), V[0, h, at].view(torch.int16))
     cache.close()
+
+
+@pytest.mark.parametrize("n", [700, 4097, 16385])          # eight waves; sixteen; keys in LDS
+@pytest.mark.parametrize("digit", [0, 1, 2])
+@pytest.mark.parametrize("spare", [0, 1])                  # the threshold's bin is kept whole, or all but one of it
+def test_select_last_digit(n, digit, spare):
+    """Scores that differ in one digit of the keys (11, 11 and 10 bits) only, at the ends and the middle of every
+    wave's share of the bins: the threshold is found at that digit, in a bin of several equal scores."""
+    from paper_2306_14048_amd import binding as hb
+    dev, d, recent = torch.device("cuda:0"), 64, 20
+    shift, bins = ((21, 1016), (10, 2048), (0, 1024))[digit]
+    edges = torch.arange(0, bins, 64).repeat_interleave(3) + torch.tensor([0, 31, 63]).repeat(len(range(0, bins, 64)))
+    edges = edges[edges < bins]                            # (below infinity)
+    base = 0 if digit == 0 else 0x3f800000
+    gen = torch.Generator().manual_seed(n + digit)
+    cand = n - recent
+    level = torch.randint(0, len(edges), (cand,), generator=gen)
+    score = torch.cat([(base + (edges[level] << shift)).int().view(torch.float32), torch.zeros(recent)])
+    from_top = torch.bincount(level, minlength=len(edges)).flip(0).cumsum(0)
+    most = int(len(edges) * min(0.5, 3700 / n))            # (budgets end at 4096)
+    for at in (most // 3, most):
+        heavy = int(from_top[at]) - spare
+        K = torch.randn(1, 8, n, d, generator=gen).half().to(dev)
+        cache = hb.H2OCache(1, 8, d, heavy, recent, torch.float16, device=dev)
+        cache.prefill_select(K, K, score.to(dev).expand(1, 8, n).contiguous())
+        want = kept_by_sorting(score, heavy, recent, False, 0, 1)
+        pos = cache.views()[3].cpu()[0].long()
+        for h in range(8):
+            assert torch.equal(pos[h], want), "head %d: kept positions differ" % h
+        cache.close()
