@@ -318,12 +318,15 @@ int h2o_prefill_chunk(h2o_cache *cache, const void *Q, const void *K, const void
         e = out ? h2o_launch_prefill_attention(cfg, scale, Q, K, V, kf, vf, m, ncat, vcopy, lse, nullptr, out, st)
                 : h2o_launch_prefill_lse(cfg, scale, Q, K, kf, m, ncat, lse, st);
         if (e != hipSuccess) return H2O_EHIP;
-        e = h2o_launch_prefill_colsum(cfg, scale, Q, K, kf, m, ncat, lse, colsum, st);
+        // (`order` is free here: the compression's arrival counts, cleared on the way)
+        const bool in_place = occ != 0 || cache->t != 0;
+        unsigned *arrived = in_place && compact_parts((int)heads, cache->k, cache->rowb) > 1
+                                ? reinterpret_cast<unsigned *>(order) : nullptr;
+        e = h2o_launch_prefill_colsum(cfg, scale, Q, K, kf, m, ncat, lse, colsum, st, arrived);
         if (e != hipSuccess) return H2O_EHIP;
         // (an empty cache: nothing to move, and several workgroups may share a head)
-        e = occ == 0 && cache->t == 0
-                ? h2o_launch_select_gather(*cache, K, V, colsum, nullptr, nullptr, m, m, st)
-                : h2o_launch_compact(*cache, K, V, colsum, m, occ, st);
+        e = in_place ? h2o_launch_compact(*cache, K, V, colsum, m, occ, arrived, st)
+                     : h2o_launch_select_gather(*cache, K, V, colsum, nullptr, nullptr, m, m, st);
         if (e != hipSuccess) return H2O_EHIP;
         cache->t += m;
         return H2O_OK;

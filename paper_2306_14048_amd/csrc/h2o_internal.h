@@ -72,12 +72,13 @@ struct FrontRows {
     int rows = 0, stride = 0;
 };
 // prompt scoring: the nq queries (rows of Q) are the last nq positions of the nk
-// keys; lse [B*Hh][nq] = log2 of the row normalisers, colsum [B*Hh][nk]
+// keys; lse [B*Hh][nq] = log2 of the row normalisers, colsum [B*Hh][nk]; zero (nullable): one word
+// per head that the column sums' launch clears for the one behind it
 hipError_t h2o_launch_prefill_lse(const h2o_config &cfg, double scale, const void *Q,
                                   const void *K, const FrontRows &Kf, int nq, int nk, float *lse, hipStream_t st);
 hipError_t h2o_launch_prefill_colsum(const h2o_config &cfg, double scale, const void *Q,
                                      const void *K, const FrontRows &Kf, int nq, int nk, const float *lse,
-                                     float *colsum, hipStream_t st);
+                                     float *colsum, hipStream_t st, unsigned *zero = nullptr);
 // causal attention of nq queries (the last nq of nk key positions) over nk keys: V
 // ([nk][d] per head) is copied to `vcopy` (h2o_attn_vcopy_bytes(cfg, nk) bytes) first if
 // `out` overlaps it,
@@ -94,9 +95,10 @@ hipError_t h2o_launch_select_gather(const h2o_cache &c, const void *K, const voi
                                     const float *score, const float *base, const int32_t *pos_in,
                                     int n, int t_new, hipStream_t st);
 // compression in place: the n_occ cached tokens (slots in position order) followed by the
-// m tokens Kn, Vn at positions t.. are the candidates, with column sums score[heads][n_occ + m]
+// m tokens Kn, Vn at positions t.. are the candidates, with column sums score[heads][n_occ + m];
+// arrived: one word per head, zero
 hipError_t h2o_launch_compact(const h2o_cache &c, const void *Kn, const void *Vn, const float *score,
-                              int m, int n_occ, hipStream_t st);
+                              int m, int n_occ, unsigned *arrived, hipStream_t st);
 // the n_occ cached tokens in position order followed by the m chunk tokens as one
 // candidate list; `order` (heads * k ints of scratch) is needed when the slots are
 // not in position order, nullptr when they are
@@ -212,6 +214,19 @@ static inline SelectPlan select_plan(int heads, int k, int n, bool in_place)
     // 4096: 128 heads, 819 of 4096 30.5 us against 31.3, 8 heads, 800 of 4096 11.3 / 11.9, in place 0.3 to 1.7 us more.
     const bool wide = n > 4096 && ((long long)heads * parts <= 256 || n > 16384);
     return {parts, part_slots, wide};
+}
+
+// Workgroups per head of the compression in place: each moves its own columns of the rows, 128 bytes of them (K and
+// V taken as one row) and 32 KiB of K's and V's together at least.  A head's rows go through one CU otherwise.  Whole chunked calls, us,
+// one workgroup / several: 32 heads x 819 slots of 256 bytes, chunks of 512, 370.6 / 349.0; 8 x 1000, 2048, 220.0 / 211.7;
+// 8 x 600, 256, averaged 414.5 / 400.0; 128 x 819, 1024, 676 / 672.  Below 128 KiB of K the rows are a round or two either
+// way: 56 x 300 158 / 161, 16 x 819 of 128 bytes 207.6 / 209.6.
+static inline int compact_parts(int heads, int k, int rowb)
+{
+    int parts = 1;
+    if ((size_t)k * rowb >= 131072)
+        while (parts < 2 * rowb / 128 && heads * parts * 2 <= 256 && (size_t)k * rowb / parts >= 65536) parts *= 2;
+    return parts;
 }
 
 // Rounds per chunk of the one-workgroup step beyond its registers: of umax, umax - 2, umax - 4

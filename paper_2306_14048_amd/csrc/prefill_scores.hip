@@ -89,7 +89,7 @@ constexpr int NLB = 4;         // row-statistic buffers (pass 2; read one phase 
 template <int DT, int D, int MB, int RWV, int G, bool TWO, bool COLSUM, bool SKEW>
 __device__ __forceinline__ void prefill_pass(
     const char *__restrict__ Qg, const char *__restrict__ Kg, const FrontRows &kf, int nq, int nk, int heads,
-    float c2, float *__restrict__ lse2, float *__restrict__ colsum)
+    float c2, float *__restrict__ lse2, float *__restrict__ colsum, unsigned *zero)
 {
     constexpr int ES = DT == H2O_F32 ? 4 : 2;
     constexpr int ROWB = D * ES;          // bytes per row
@@ -531,29 +531,30 @@ __device__ __forceinline__ void prefill_pass(
     } else {
         const float c = c_run + __shfl_xor(c_run, 32, 64);
         if (half == 0 && srow < nk) colsum[(size_t)head * nk + srow] = c;
+        if (zero && srow == 0) zero[head] = 0u;
     }
 }
 
 template <int DT, int D, int MB, bool COLSUM>
 __global__ __launch_bounds__(8 * 64, 4) void prefill_pass_kernel(
     const char *__restrict__ Qg, const char *__restrict__ Kg, FrontRows kf, int nq, int nk, int heads, float c2,
-    float *__restrict__ lse2, float *__restrict__ colsum)
+    float *__restrict__ lse2, float *__restrict__ colsum, unsigned *zero)
 {
-    prefill_pass<DT, D, MB, 8, 1, false, COLSUM, true>(Qg, Kg, kf, nq, nk, heads, c2, lse2, colsum);
+    prefill_pass<DT, D, MB, 8, 1, false, COLSUM, true>(Qg, Kg, kf, nq, nk, heads, c2, lse2, colsum, zero);
 }
 
 template <int DT, int D, int MB, int G, bool TWO, bool COLSUM, bool SKEW>
 __global__ __launch_bounds__(4 * G * 64, G == 1 ? 4 : 2) void prefill_pass4_kernel(
     const char *__restrict__ Qg, const char *__restrict__ Kg, FrontRows kf, int nq, int nk, int heads, float c2,
-    float *__restrict__ lse2, float *__restrict__ colsum)
+    float *__restrict__ lse2, float *__restrict__ colsum, unsigned *zero)
 {
-    prefill_pass<DT, D, MB, 4, G, TWO, COLSUM, SKEW>(Qg, Kg, kf, nq, nk, heads, c2, lse2, colsum);
+    prefill_pass<DT, D, MB, 4, G, TWO, COLSUM, SKEW>(Qg, Kg, kf, nq, nk, heads, c2, lse2, colsum, zero);
 }
 
 // TWO: streamed rows in two places (pass 1 with keys in front, four waves)
 template <int DT, int D, int RWV, int G, bool TWO, bool COLSUM, bool SKEW = false>
 hipError_t launch_pass(const h2o_config &cfg, double scale, const void *Q, const void *K, const FrontRows &kf,
-                       int nq, int nk, float *lse2, float *colsum, hipStream_t st)
+                       int nq, int nk, float *lse2, float *colsum, unsigned *zero, hipStream_t st)
 {
     constexpr int SROWS = RWV * 32, NWV = RWV * G;
     constexpr int ES = DT == H2O_F32 ? 4 : 2;
@@ -572,7 +573,7 @@ hipError_t launch_pass(const h2o_config &cfg, double scale, const void *Q, const
     hipLaunchKernelGGL(kern,
                        dim3((unsigned)head_slots(heads) * nblk),
                        dim3(NWV * 64), smem, st, static_cast<const char *>(Q),
-                       static_cast<const char *>(K), kf, nq, nk, heads, c2, lse2, colsum);
+                       static_cast<const char *>(K), kf, nq, nk, heads, c2, lse2, colsum, zero);
     return hipGetLastError();
 }
 
@@ -602,7 +603,7 @@ template <int DT, int D> bool eight_fill_the_chip(long long blocks8, int rows, i
 
 template <int DT, int D, bool COLSUM>
 hipError_t pick_waves(const h2o_config &cfg, double scale, const void *Q, const void *K, const FrontRows &kf,
-                      int nq, int nk, float *lse2, float *colsum, hipStream_t st)
+                      int nq, int nk, float *lse2, float *colsum, unsigned *zero, hipStream_t st)
 {
     const int rows = COLSUM ? nk : nq, streamed = COLSUM ? nq : nk;
     const bool few = two_groups(cfg.batch * cfg.heads, rows, streamed, DT == H2O_F32, D);
@@ -618,9 +619,9 @@ hipError_t pick_waves(const h2o_config &cfg, double scale, const void *Q, const 
                        (streamed >= 2500 || (streamed >= 800 && (long long)cfg.batch * cfg.heads * ((rows + 127) / 128) <= 256));
     if constexpr (!COLSUM)
         if (kf.rows)
-            return apart ? launch_pass<DT, D, 4, 2, true, COLSUM, CAN>(cfg, scale, Q, K, kf, nq, nk, lse2, colsum, st)
-                   : few ? launch_pass<DT, D, 4, 2, true, COLSUM>(cfg, scale, Q, K, kf, nq, nk, lse2, colsum, st)
-                       : launch_pass<DT, D, 4, 1, true, COLSUM>(cfg, scale, Q, K, kf, nq, nk, lse2, colsum, st);
+            return apart ? launch_pass<DT, D, 4, 2, true, COLSUM, CAN>(cfg, scale, Q, K, kf, nq, nk, lse2, colsum, zero, st)
+                   : few ? launch_pass<DT, D, 4, 2, true, COLSUM>(cfg, scale, Q, K, kf, nq, nk, lse2, colsum, zero, st)
+                       : launch_pass<DT, D, 4, 1, true, COLSUM>(cfg, scale, Q, K, kf, nq, nk, lse2, colsum, zero, st);
     // Eight waves pay off when the grid fills the chip several times over with long streams:
     // the line is drawn on blocks x streamed rows.  Both passes, us, eight / four waves:
     //   16-bit, d = 128   32 heads x 512: 26.5 / 19.7, 32 x 1531: 59 / 51, 32 x 4096 (2.1 M):
@@ -633,27 +634,27 @@ hipError_t pick_waves(const h2o_config &cfg, double scale, const void *Q, const 
     const long long blocks8 = (long long)cfg.batch * cfg.heads * ((rows + 255) / 256);
     constexpr long long LINE = DT != H2O_F32 && D == 128 ? 3000000 : 16000000;
     if (blocks8 * streamed > LINE || (!few && eight_fill_the_chip<DT, D>(blocks8, rows, streamed)))
-        return launch_pass<DT, D, 8, 1, false, COLSUM>(cfg, scale, Q, K, kf, nq, nk, lse2, colsum, st);
-    return apart ? launch_pass<DT, D, 4, 2, false, COLSUM, CAN>(cfg, scale, Q, K, kf, nq, nk, lse2, colsum, st)
-           : few ? launch_pass<DT, D, 4, 2, false, COLSUM>(cfg, scale, Q, K, kf, nq, nk, lse2, colsum, st)
-               : launch_pass<DT, D, 4, 1, false, COLSUM>(cfg, scale, Q, K, kf, nq, nk, lse2, colsum, st);
+        return launch_pass<DT, D, 8, 1, false, COLSUM>(cfg, scale, Q, K, kf, nq, nk, lse2, colsum, zero, st);
+    return apart ? launch_pass<DT, D, 4, 2, false, COLSUM, CAN>(cfg, scale, Q, K, kf, nq, nk, lse2, colsum, zero, st)
+           : few ? launch_pass<DT, D, 4, 2, false, COLSUM>(cfg, scale, Q, K, kf, nq, nk, lse2, colsum, zero, st)
+               : launch_pass<DT, D, 4, 1, false, COLSUM>(cfg, scale, Q, K, kf, nq, nk, lse2, colsum, zero, st);
 }
 
 template <bool COLSUM>
 hipError_t dispatch(const h2o_config &cfg, double scale, const void *Q, const void *K, const FrontRows &kf,
-                    int nq, int nk, float *lse2, float *colsum, hipStream_t st)
+                    int nq, int nk, float *lse2, float *colsum, unsigned *zero, hipStream_t st)
 {
     const int d = cfg.head_dim;
     switch (cfg.dtype) {
     case H2O_F32:
-        return d == 64 ? pick_waves<H2O_F32, 64, COLSUM>(cfg, scale, Q, K, kf, nq, nk, lse2, colsum, st)
-                       : pick_waves<H2O_F32, 128, COLSUM>(cfg, scale, Q, K, kf, nq, nk, lse2, colsum, st);
+        return d == 64 ? pick_waves<H2O_F32, 64, COLSUM>(cfg, scale, Q, K, kf, nq, nk, lse2, colsum, zero, st)
+                       : pick_waves<H2O_F32, 128, COLSUM>(cfg, scale, Q, K, kf, nq, nk, lse2, colsum, zero, st);
     case H2O_F16:
-        return d == 64 ? pick_waves<H2O_F16, 64, COLSUM>(cfg, scale, Q, K, kf, nq, nk, lse2, colsum, st)
-                       : pick_waves<H2O_F16, 128, COLSUM>(cfg, scale, Q, K, kf, nq, nk, lse2, colsum, st);
+        return d == 64 ? pick_waves<H2O_F16, 64, COLSUM>(cfg, scale, Q, K, kf, nq, nk, lse2, colsum, zero, st)
+                       : pick_waves<H2O_F16, 128, COLSUM>(cfg, scale, Q, K, kf, nq, nk, lse2, colsum, zero, st);
     default:
-        return d == 64 ? pick_waves<H2O_BF16, 64, COLSUM>(cfg, scale, Q, K, kf, nq, nk, lse2, colsum, st)
-                       : pick_waves<H2O_BF16, 128, COLSUM>(cfg, scale, Q, K, kf, nq, nk, lse2, colsum, st);
+        return d == 64 ? pick_waves<H2O_BF16, 64, COLSUM>(cfg, scale, Q, K, kf, nq, nk, lse2, colsum, zero, st)
+                       : pick_waves<H2O_BF16, 128, COLSUM>(cfg, scale, Q, K, kf, nq, nk, lse2, colsum, zero, st);
     }
 }
 
@@ -662,12 +663,12 @@ hipError_t dispatch(const h2o_config &cfg, double scale, const void *Q, const vo
 hipError_t h2o_launch_prefill_lse(const h2o_config &cfg, double scale, const void *Q,
                                   const void *K, const FrontRows &Kf, int nq, int nk, float *lse, hipStream_t st)
 {
-    return dispatch<false>(cfg, scale, Q, K, Kf, nq, nk, lse, nullptr, st);
+    return dispatch<false>(cfg, scale, Q, K, Kf, nq, nk, lse, nullptr, nullptr, st);
 }
 
 hipError_t h2o_launch_prefill_colsum(const h2o_config &cfg, double scale, const void *Q,
                                      const void *K, const FrontRows &Kf, int nq, int nk, const float *lse,
-                                     float *colsum, hipStream_t st)
+                                     float *colsum, hipStream_t st, unsigned *zero)
 {
-    return dispatch<true>(cfg, scale, Q, K, Kf, nq, nk, const_cast<float *>(lse), colsum, st);
+    return dispatch<true>(cfg, scale, Q, K, Kf, nq, nk, const_cast<float *>(lse), colsum, zero, st);
 }

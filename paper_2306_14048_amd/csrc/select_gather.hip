@@ -17,6 +17,8 @@ namespace {
 constexpr int SG_BITS = 11;                 // radix digit: 11 + 11 + 10 bits
 constexpr int SG_BINS = 1 << SG_BITS;
 // where the ranking keys live during the selection
+// the compression inside the cache: one workgroup per head, or several with some columns each
+constexpr int IN_PLACE = 1, IN_PLACE_COLUMNS = 2;
 constexpr int SG_KEYS_NONE = 0, SG_KEYS_LDS = 1;   // (any larger value: that many registers per thread)
 
 __device__ inline unsigned order_key(float x)
@@ -129,19 +131,19 @@ template <int NW> __device__ inline int block_sum(int v, int *scratch)
 //
 // COMPACT: the cache itself is the front of the candidate list: entries j < n_occ are its
 // slots (in position order, with their scores), the others the tokens Kp, Vp at positions
-// t_new - m + (j - n_occ).  One workgroup per head then moves rows inside the cache: the
+// t_new - m + (j - n_occ).  A workgroup then moves rows, or its columns of them, inside the cache: the
 // entry kept in slot s is never in front of it (j >= s), so filling the slots in ascending
 // rounds, every round's reads before its writes, never overwrites what is still to be read.
 // (The list used to be copied together first, rows and all, and gathered back from there:
 // 34 + 26 us per 1024-token chunk at 128 heads x 819 slots.)  Rounds overlap: the next one's reads are
 // in flight while one is written (a whole call, us: 8 heads x 2048 tokens on 4000 slots 186 -> 172, 32 x 1024 on
 // 819 77.1 -> 74.8, 256 x 512 on 410, d = 64, 84.3 -> 82.3).
-template <int ROWB, int QDT, bool PAT, int KEYS, bool COMPACT, int SG_NT>
+template <int ROWB, int QDT, bool PAT, int KEYS, int COMPACT, int SG_NT>
 __global__ __launch_bounds__(SG_NT, 4) void select_gather_kernel(
     const char *__restrict__ Kp, const char *__restrict__ Vp, const float *__restrict__ score,
     const float *__restrict__ base, const int32_t *__restrict__ pos_in, int n, int t_new,
     char *Kc, char *Vc, float *acc_g, int32_t *pos_g, int k, int heavy, int recent, int rank, int protect,
-    int stride, int parts, int part_slots, int n_occ)
+    int stride, int parts, int part_slots, int n_occ, unsigned *arrived)
 {
     constexpr int SG_NW = SG_NT / 64;
     extern __shared__ __align__(16) unsigned char smem[];
@@ -157,7 +159,7 @@ __global__ __launch_bounds__(SG_NT, 4) void select_gather_kernel(
     const bool eights = parts > 1 && gridDim.x % (8 * parts) == 0;
     const int turn = eights ? blockIdx.x >> 3 : blockIdx.x;
     const int head = eights ? turn / parts * 8 + (blockIdx.x & 7) : turn / parts;
-    const int sb = turn % parts * part_slots;          // this workgroup's slots [sb, se)
+    const int sb = COMPACT ? 0 : turn % parts * part_slots;     // this workgroup's slots [sb, se)
     const int se = min(k, sb + part_slots);
     const float *sc_in = score + (size_t)head * n;
     const float *bs = base ? base + (size_t)head * n : nullptr;
@@ -397,11 +399,7 @@ __global__ __launch_bounds__(SG_NT, 4) void select_gather_kernel(
         // another's read: round r writes slots that only rounds up to r read.  The next round's
         // reads lie behind what this round writes, so they are requested first and are in flight
         // while this round is written.
-        constexpr int LPR = ROWB / 16, RPR = SG_NT / LPR, UNR = 4, ROUND = UNR * RPR;
-        constexpr int OWN = H2O_MAX_BUDGET / SG_NT;
-        const int li = tid % LPR, rsub = tid / LPR;
-        const char *Kn = Kp + (size_t)head * (n - n_occ) * ROWB, *Vn = Vp + (size_t)head * (n - n_occ) * ROWB;
-        char *Kh = Kc + hoff * ROWB, *Vh = Vc + hoff * ROWB;
+        constexpr int LPR = ROWB / 16, OWN = H2O_MAX_BUDGET / SG_NT;
         int p[OWN];
         float a[OWN];
 #pragma unroll
@@ -411,6 +409,74 @@ __global__ __launch_bounds__(SG_NT, 4) void select_gather_kernel(
             p[i] = pos_of(j);
             a[i] = sc_of(j);
         }
+        auto bookkeeping_read = [&] {          // ... by every wave
+#pragma unroll
+            for (int i = 0; i < OWN; ++i) {
+                if (i * SG_NT >= k) break;
+                asm volatile("" ::"v"(p[i]), "v"(a[i]));
+            }
+            lds_barrier();
+        };
+        auto store_bookkeeping = [&] {
+#pragma unroll
+            for (int i = 0; i < OWN; ++i) {
+                if (i * SG_NT >= k) break;
+                const int s = i * SG_NT + tid;
+                if (s < k) {
+                    const bool any = sel_l[s] >= 0;
+                    pos_g[hoff + s] = any ? p[i] : -1;
+                    acc_g[hoff + s] = any ? a[i] : 0.f;
+                }
+            }
+        };
+        if constexpr (COMPACT == IN_PLACE_COLUMNS) {
+            // Several workgroups share a head, each moves its own columns (pieces of 16 bytes) of the row that K and V
+            // are together; a thread has one piece of every rpr-th slot.  All of them read the positions and
+            // scores; the last to have read them stores the new ones.
+            constexpr int UNR = 8;
+            const int cols = 2 * LPR / parts, rpr = SG_NT / cols, round = UNR * rpr;     // (powers of two)
+            const int piece = turn % parts * cols + (tid & (cols - 1)), rsub = tid >> (__ffs(cols) - 1);
+            const bool value = piece >= LPR;
+            const char *New = (value ? Vp : Kp) + (size_t)head * (n - n_occ) * ROWB + piece % LPR * 16;
+            char *Row = (value ? Vc : Kc) + hoff * ROWB + piece % LPR * 16;
+            struct Rows { int j[UNR]; uint4 x[UNR]; };
+            auto request = [&](Rows &r, int s0) {
+#pragma unroll
+                for (int u = 0; u < UNR; ++u) {
+                    const int s = s0 + u * rpr + rsub;
+                    int j = s < k ? sel_l[s] : -1;
+                    if (j == s && s < n_occ) j = -1;               // stays where it is
+                    r.j[u] = j;
+                    r.x[u] = *reinterpret_cast<const uint4 *>((j < n_occ ? Row : New) +
+                                                              (size_t)(j < n_occ ? max(j, 0) : j - n_occ) * ROWB);
+                }
+            };
+            auto write = [&](Rows &r, int s0) {
+#pragma unroll
+                for (int u = 0; u < UNR; ++u) pin(r.x[u]);         // (they have arrived)
+                lds_barrier();
+#pragma unroll
+                for (int u = 0; u < UNR; ++u)
+                    if (r.j[u] >= 0) *reinterpret_cast<uint4 *>(Row + (size_t)(s0 + u * rpr + rsub) * ROWB) = r.x[u];
+            };
+            __shared__ unsigned before;
+            Rows even, odd;
+            bookkeeping_read();
+            if (tid == 0) before = atomicAdd(arrived + head, 1u);
+            request(even, 0);
+            for (int s0 = 0; s0 < k; s0 += 2 * round) {
+                request(odd, s0 + round);        // (past the end: row 0, not written)
+                write(even, s0);
+                if (s0 == 0 && before == (unsigned)parts - 1) store_bookkeeping();     // (behind write's barrier)
+                request(even, s0 + 2 * round);
+                write(odd, s0 + round);
+            }
+            return;
+        }
+        constexpr int RPR = SG_NT / LPR, UNR = 4, ROUND = UNR * RPR;
+        const int li = tid % LPR, rsub = tid / LPR;
+        const char *Kn = Kp + (size_t)head * (n - n_occ) * ROWB, *Vn = Vp + (size_t)head * (n - n_occ) * ROWB;
+        char *Kh = Kc + hoff * ROWB, *Vh = Vc + hoff * ROWB;
         struct Rows { int j[UNR]; uint4 k[UNR], v[UNR]; };
         auto request = [&](Rows &r, int s0) {
 #pragma unroll
@@ -439,22 +505,8 @@ __global__ __launch_bounds__(SG_NT, 4) void select_gather_kernel(
         };
         Rows even, odd;
         request(even, 0);
-#pragma unroll
-        for (int i = 0; i < OWN; ++i) {
-            if (i * SG_NT >= k) break;
-            asm volatile("" ::"v"(p[i]), "v"(a[i]));
-        }
-        lds_barrier();                       // every wave has its positions and scores
-#pragma unroll
-        for (int i = 0; i < OWN; ++i) {
-            if (i * SG_NT >= k) break;
-            const int s = i * SG_NT + tid;
-            if (s < k) {
-                const bool any = sel_l[s] >= 0;
-                pos_g[hoff + s] = any ? p[i] : -1;
-                acc_g[hoff + s] = any ? a[i] : 0.f;
-            }
-        }
+        bookkeeping_read();
+        store_bookkeeping();
         for (int s0 = 0; s0 < k; s0 += 2 * ROUND) {
             request(odd, s0 + ROUND);        // (past the end: row 0, not written)
             write(even, s0);
@@ -579,15 +631,15 @@ namespace {
 
 // Launches the compression of n candidates per head.  COMPACT: see the kernel (16-bit and
 // binary32 storage only: a chunked prompt is refused on a 4-bit cache).
-template <bool COMPACT>
+template <int COMPACT>
 hipError_t launch_select(const h2o_cache &c, const void *K, const void *V, const float *score, const float *base,
-                         const int32_t *pos_in, int n, int t_new, int n_occ, hipStream_t st)
+                         const int32_t *pos_in, int n, int t_new, int n_occ, unsigned *arrived, hipStream_t st)
 {
     const int heads = c.cfg.batch * c.cfg.heads;
     const int rowb = c.cfg.head_dim * c.esize;
     const char *Kp = static_cast<const char *>(K), *Vp = static_cast<const char *>(V);
     const SelectPlan plan = select_plan(heads, c.k, n, COMPACT);
-    const int parts = plan.parts, part_slots = plan.part_slots;
+    const int parts = COMPACT == IN_PLACE_COLUMNS ? compact_parts(heads, c.k, rowb) : plan.parts, part_slots = plan.part_slots;
     const bool window = c.cfg.protect == H2O_PROTECT_RECENT, wide = plan.wide;
     // Keys in registers: 8 per thread up to 4096 (sixteen waves: 8192) candidates, 32 (16) up to
     // 16 384 (window mode; the pattern modes, whose sweeps also test the pattern, keep them in LDS).
@@ -604,7 +656,7 @@ hipError_t launch_select(const h2o_cache &c, const void *K, const void *V, const
         }
         hipLaunchKernelGGL(kern, dim3((unsigned)heads * parts), dim3(wide ? 1024 : 512), smem, st, Kp, Vp, score, base,
                            pos_in, n, t_new, c.K, c.V, c.acc, c.pos, c.k, c.cfg.heavy, c.cfg.recent,
-                           c.cfg.rank, c.cfg.protect, c.cfg.stride, parts, part_slots, n_occ);
+                           c.cfg.rank, c.cfg.protect, c.cfg.stride, parts, part_slots, n_occ, arrived);
         return hipGetLastError();
     };
     // (eight waves never see more than 16 384 candidates)
@@ -653,13 +705,14 @@ hipError_t h2o_launch_select_gather(const h2o_cache &c, const void *K, const voi
                                     const float *score, const float *base, const int32_t *pos_in,
                                     int n, int t_new, hipStream_t st)
 {
-    return launch_select<false>(c, K, V, score, base, pos_in, n, t_new, 0, st);
+    return launch_select<0>(c, K, V, score, base, pos_in, n, t_new, 0, nullptr, st);
 }
 
 hipError_t h2o_launch_compact(const h2o_cache &c, const void *Kn, const void *Vn, const float *score, int m,
-                              int n_occ, hipStream_t st)
+                              int n_occ, unsigned *arrived, hipStream_t st)
 {
-    return launch_select<true>(c, Kn, Vn, score, nullptr, nullptr, n_occ + m, c.t + m, n_occ, st);
+    return (arrived ? launch_select<IN_PLACE_COLUMNS> : launch_select<IN_PLACE>)(
+        c, Kn, Vn, score, nullptr, nullptr, n_occ + m, c.t + m, n_occ, arrived, st);
 }
 
 // ---- cache + chunk -> one candidate list per head ---------------------------------

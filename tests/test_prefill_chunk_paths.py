@@ -20,6 +20,16 @@ DT = {"f32": torch.float32, "f16": torch.float16, "bf16": torch.bfloat16}
     ("f16", 128, 2, 150, 20, (400, 333), dict(protect=1, stride=7)),
     ("f16", 128, 2, 2048, 2048, (4200, 1500), {}),                     # sixteen waves, 8 keys
     ("bf16", 128, 160, 256, 256, (600, 2048), {}),                     # column sums with eight waves
+    # several workgroups per head, with some columns of its rows each (128 KiB of keys on)
+    ("f16", 128, 8, 256, 256, (700, 3, 513), {}),                      # 4, at the line
+    ("f16", 128, 9, 256, 255, (700, 300), {}),                         # one, below it
+    ("f32", 128, 3, 300, 300, (700, 333, 1), {}),                      # 4 of 8
+    ("f32", 128, 2, 700, 801, (2000, 600), {}),                        # 8
+    ("f16", 64, 33, 512, 512, (1100, 500), dict(rank=1)),              # 2
+    ("bf16", 128, 65, 300, 400, (800, 300), {}),                       # 2 (heads)
+    ("f16", 128, 5, 800, 100, (1000, 777), dict(protect=1, stride=5)),
+    ("bf16", 128, 2, 0, 900, (1000, 300, 901), {}),                    # window only
+    ("bf16", 128, 16, 700, 500, (900, 700, 5000), {}),                 # fills up first; sixteen waves
 ])
 def test_in_place_chunk_matches_the_copying_way(dt, d, heads, heavy, recent, chunks, more):
     from paper_2306_14048_amd import binding as hb
