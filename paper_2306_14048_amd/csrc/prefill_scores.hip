@@ -551,6 +551,15 @@ __global__ __launch_bounds__(4 * G * 64, G == 1 ? 4 : 2) void prefill_pass4_kern
     prefill_pass<DT, D, MB, 4, G, TWO, COLSUM, SKEW>(Qg, Kg, kf, nq, nk, heads, c2, lse2, colsum, zero);
 }
 
+// Two groups of two waves: 64 stationary rows
+template <int DT, int D, bool TWO, bool COLSUM>
+__global__ __launch_bounds__(4 * 64, 2) void prefill_pass2_kernel(
+    const char *__restrict__ Qg, const char *__restrict__ Kg, FrontRows kf, int nq, int nk, int heads, float c2,
+    float *__restrict__ lse2, float *__restrict__ colsum, unsigned *zero)
+{
+    prefill_pass<DT, D, 1, 2, 2, TWO, COLSUM, false>(Qg, Kg, kf, nq, nk, heads, c2, lse2, colsum, zero);
+}
+
 // TWO: streamed rows in two places (pass 1 with keys in front, four waves)
 template <int DT, int D, int RWV, int G, bool TWO, bool COLSUM, bool SKEW = false>
 hipError_t launch_pass(const h2o_config &cfg, double scale, const void *Q, const void *K, const FrontRows &kf,
@@ -558,13 +567,17 @@ hipError_t launch_pass(const h2o_config &cfg, double scale, const void *Q, const
 {
     constexpr int SROWS = RWV * 32, NWV = RWV * G;
     constexpr int ES = DT == H2O_F32 ? 4 : 2;
-    constexpr int MB = (D * ES >= 512) ? 1 : 2;      // keep a group's tile buffers at 48 KiB
+    constexpr int MB = (D * ES >= 512 || RWV == 2) ? 1 : 2;      // keep a group's tile buffers at 48 KiB
     constexpr int BN = 32 * MB * G;
     constexpr size_t smem = NTB * (size_t)BN * (D * ES) + NLB * BN * sizeof(float);
     const int heads = cfg.batch * cfg.heads;
     const int nblk = ((COLSUM ? nk : nq) + SROWS - 1) / SROWS;
     const float c2 = (float)(scale * 1.4426950408889634);
-    auto kern = RWV == 8 ? prefill_pass_kernel<DT, D, MB, COLSUM> : prefill_pass4_kernel<DT, D, MB, G, TWO, COLSUM, SKEW>;
+    auto kern = [] {
+        if constexpr (RWV == 8) return prefill_pass_kernel<DT, D, MB, COLSUM>;
+        else if constexpr (RWV == 2) return prefill_pass2_kernel<DT, D, TWO, COLSUM>;
+        else return prefill_pass4_kernel<DT, D, MB, G, TWO, COLSUM, SKEW>;
+    }();
     if (smem > 48 * 1024) {
         static std::atomic<uint64_t> raised{0};
         const hipError_t e = allow_lds(reinterpret_cast<const void *>(kern), (int)smem, raised);
@@ -617,6 +630,17 @@ hipError_t pick_waves(const h2o_config &cfg, double scale, const void *Q, const 
     constexpr bool CAN = DT != H2O_F32 && D == 128;
     const bool apart = CAN && few &&
                        (streamed >= 2500 || (streamed >= 800 && (long long)cfg.batch * cfg.heads * ((rows + 127) / 128) <= 256));
+    // binary32 (a pass is its matrix instructions) on grids that leave CUs idle: blocks of 64 rows with two groups of two
+    // waves, so that the longest one has half the work.  Reset, both passes and selection, us, before / 64 rows: d = 64, 8 heads x 256
+    // 32.8 / 23.1, 8 x 64 20.0 / 18.0, 8 x 1500 117 / 76, 16 x 500 48.9 / 34.6, 56 x 512 (448 slots) 48.7 / 41.2, 128 x 256 (512)
+    // 33.9 / 31.9; d = 128, 8 x 256 52.4 / 33.0, 12 x 700 106 / 67, 32 x 1000 (512) 147 / 101, 128 x 300 (640) 87.5 / 65.3.
+    // The lines are the largest grids measured.
+    if constexpr (DT == H2O_F32)
+        if ((long long)head_slots(cfg.batch * cfg.heads) * ((rows + 63) / 64) <= (D == 64 ? 512 : 640)) {
+            if constexpr (!COLSUM)
+                if (kf.rows) return launch_pass<DT, D, 2, 2, true, COLSUM>(cfg, scale, Q, K, kf, nq, nk, lse2, colsum, zero, st);
+            return launch_pass<DT, D, 2, 2, false, COLSUM>(cfg, scale, Q, K, kf, nq, nk, lse2, colsum, zero, st);
+        }
     if constexpr (!COLSUM)
         if (kf.rows)
             return apart ? launch_pass<DT, D, 4, 2, true, COLSUM, CAN>(cfg, scale, Q, K, kf, nq, nk, lse2, colsum, zero, st)
