@@ -149,6 +149,34 @@ static inline bool two_groups(int heads, int rows, int streamed, bool f32, int d
     return streamed >= (d == 128 ? 600 : 480) && blocks <= (streamed >= 1500 ? 512 : 384);
 }
 
+// Whether a binary32 scoring pass takes blocks of 64 rows, two groups of two waves each, instead of 128 rows: on
+// grids that leave CUs idle the longest block then has half the work (a binary32 pass is its matrix
+// instructions).  Reset, both passes and selection, us, 128 rows / 64: d = 64, 8 heads x 256 32.8 / 23.1, 8 x 1500 117 / 76, 56 x
+// 512 (448 slots) 48.7 / 41.2, 128 x 256 (512) 33.9 / 31.9; d = 128, 8 x 256 52.4 / 33.0, 32 x 1000 (512) 147 / 101, 128 x 300 (640)
+// 87.5 / 65.3.  At d = 64 no grid up to 512 slots loses (0.58 .. 0.99).  At d = 128 a workgroup has its CU to itself (97 KiB of LDS), and a block
+// of 64 rows counts as half a round of the CUs (both passes alone, 64 rows / 128):
+//   to 32 streamed rows the second group has nothing to do: 8 to 256 heads x 1 .. 32 1.09 .. 1.17, 512 1.29 .. 1.44
+//   fewer rounds        264 to 320 heads x 100 and 128 0.83 .. 0.85, 136 to 192 x 129 .. 192 0.81 .. 0.96, one block per head to
+//                       640 heads 0.73 .. 0.97; but 264 to 320 x 65 (a second block of one row) 1.05 .. 1.07
+//   as many             blocks of a causal triangle are uneven, the light ones fill in: 128 heads x 129 .. 256 0.76 .. 0.91, 64 x
+//                       512 0.71; one or two blocks per head are not: 136 to 192 x 65 .. 128 0.98 .. 1.25, 200 to 256 1.10 .. 1.46.
+//                       Chunks behind cached tokens are the less so the more there are (the whole call, one pass on either side).
+//                       Statistics, to 352 slots 0.85 .. 0.92, then by streamed / rows: 1.6 .. 2.4 0.92 .. 0.98, 3 0.97 .. 1.03, 3.7
+//                       and more 1.05.  Column sums, by rows / streamed, at 280 to 320 slots 1.5 .. 2.7 0.83 .. 0.97, 2.9 and
+//                       more 1.06, at 352 1.6 0.88, 2.3 .. 2.6 1.02, at 416 to 512 1.7 .. 2 1.06 .. 1.10, 8 and more 1.06 .. 1.12
+// Beyond 512 and 640 slots nothing was measured.
+static inline bool small_blocks(int heads, int rows, int streamed, int d)
+{
+    const long long slots = head_slots(heads) * ((rows + 63) / 64), slots128 = head_slots(heads) * ((rows + 127) / 128);
+    if (d == 64) return slots <= 512;
+    if (streamed <= 32 || slots > 640) return false;
+    if (slots <= 256 || rows <= 64) return true;
+    const long long rounds = (slots + 255) / 256, rounds128 = 2 * ((slots128 + 255) / 256);
+    if (rounds < rounds128) return rows > 96;
+    if (rounds > rounds128 || rows <= 128) return false;
+    return streamed > rows ? slots <= 352 || 2LL * streamed < 5LL * rows : slots * rows < 820LL * streamed;
+}
+
 // Whether the attention's two groups (two_groups) run one phase apart: while one is in its MFMAs the
 // other is in its softmax.  That takes a second barrier per tile and, at d = 64, 143 registers
 // instead of 127, with which a second workgroup does not fit on the CU any more; blocks beyond the CUs then wait

@@ -630,13 +630,8 @@ hipError_t pick_waves(const h2o_config &cfg, double scale, const void *Q, const 
     constexpr bool CAN = DT != H2O_F32 && D == 128;
     const bool apart = CAN && few &&
                        (streamed >= 2500 || (streamed >= 800 && (long long)cfg.batch * cfg.heads * ((rows + 127) / 128) <= 256));
-    // binary32 (a pass is its matrix instructions) on grids that leave CUs idle: blocks of 64 rows with two groups of two
-    // waves, so that the longest one has half the work.  Reset, both passes and selection, us, before / 64 rows: d = 64, 8 heads x 256
-    // 32.8 / 23.1, 8 x 64 20.0 / 18.0, 8 x 1500 117 / 76, 16 x 500 48.9 / 34.6, 56 x 512 (448 slots) 48.7 / 41.2, 128 x 256 (512)
-    // 33.9 / 31.9; d = 128, 8 x 256 52.4 / 33.0, 12 x 700 106 / 67, 32 x 1000 (512) 147 / 101, 128 x 300 (640) 87.5 / 65.3.
-    // The lines are the largest grids measured.
     if constexpr (DT == H2O_F32)
-        if ((long long)head_slots(cfg.batch * cfg.heads) * ((rows + 63) / 64) <= (D == 64 ? 512 : 640)) {
+        if (small_blocks(cfg.batch * cfg.heads, rows, streamed, D)) {
             if constexpr (!COLSUM)
                 if (kf.rows) return launch_pass<DT, D, 2, 2, true, COLSUM>(cfg, scale, Q, K, kf, nq, nk, lse2, colsum, zero, st);
             return launch_pass<DT, D, 2, 2, false, COLSUM>(cfg, scale, Q, K, kf, nq, nk, lse2, colsum, zero, st);

@@ -18,6 +18,8 @@ int main()
         if (what == 0) {
             const SelectPlan p = select_plan(a, b, c, d != 0);
             printf("%d %d %d\n", p.parts, p.part_slots, (int)p.wide);
+        } else if (what == 2) {
+            printf("%d %d\n", (int)small_blocks(a, b, c, d), (int)head_slots(a));
         } else {
             printf("%d %d %d\n", (int)two_groups(a, b, c, false, d), (int)groups_apart(a, b, c, d), (int)head_slots(a));
         }
@@ -90,3 +92,32 @@ def test_attention_groups_apart_have_a_cu_of_their_own(plans):
             (1, 65536, 128): 1, (32, 1531, 128): 1, (36, 800, 128): 0, (320, 100, 64): 0, (8, 500, 64): 1}
     got = plans([(1, h, n, n, d) for h, n, d in want])
     assert [g[1] for g in got] == list(want.values())
+
+
+def test_binary32_blocks_of_64_rows(plans):
+    """At d = 128 a workgroup of 64 rows has a CU to itself: not where its second group has no rows, nor where
+    twice the blocks take more rounds of the 256 CUs, nor as many with all of them equally heavy."""
+    q = [(2, h, rows, st, d) for d in (64, 128) for h in [*range(1, 330, 3), 400, 512, 576, 640, 641, 1024]
+         for rows in (1, 16, 32, 33, 64, 65, 96, 97, 128, 129, 192, 200, 256, 300, 512, 700, 1024, 2500, 4096)
+         for st in {1, 16, 32, 33, 150, 400, rows, rows + 100, rows + 400, rows + 4000, max(1, rows - 100), max(1, rows - 400)}]
+    some = 0
+    for (_, h, rows, st, d), (small, heads8) in zip(q, plans(q)):
+        slots, slots128 = heads8 * ((rows + 63) // 64), heads8 * ((rows + 127) // 128)
+        if d == 64:
+            assert small == (slots <= 512), (h, rows, st)
+            continue
+        some += small
+        if small:
+            assert st > 32 and slots <= 640 and -(-slots // 256) <= 2 * -(-slots128 // 256), (h, rows, st)
+            assert rows <= 64 or rows > 128 or slots <= 256 or (rows > 96 and h > 256), (h, rows, st)
+        elif slots <= 256:
+            assert st <= 32, (h, rows, st)
+    assert some > 500
+    # (heads, rows, streamed) on either side: whole prompts, then statistics and column sums of chunks
+    want = {(8, 32, 32): 0, (512, 17, 17): 0, (8, 33, 33): 1, (640, 64, 64): 1, (641, 64, 64): 0, (128, 128, 128): 1,
+            (129, 65, 65): 0, (256, 100, 100): 0, (264, 96, 96): 0, (264, 97, 97): 1, (320, 128, 128): 1, (128, 129, 129): 1,
+            (192, 192, 192): 1, (200, 129, 129): 0, (128, 256, 256): 1, (128, 300, 300): 1, (32, 1000, 1000): 1, (32, 1300, 1300): 0,
+            (32, 700, 1700): 1, (128, 192, 292): 1, (128, 150, 550): 0, (48, 512, 912): 1, (64, 512, 1512): 0, (256, 100, 500): 0,
+            (64, 292, 192): 1, (128, 250, 150): 0, (32, 550, 300): 1, (32, 550, 150): 0, (40, 400, 150): 1, (64, 433, 33): 0}
+    got = plans([(2, h, rows, st, 128) for h, rows, st in want])
+    assert [g[0] for g in got] == list(want.values())
