@@ -1,5 +1,6 @@
-"""Column sums of binary32 prompts on small grids (blocks of 64 rows) at the edges of their tiles and of the
-rule's range, against float64.  Bar: the column sums' 3e-5 (three times the largest measured difference)."""
+"""Column sums of binary32 prompts on small grids (blocks of 64 rows) at the edges of their tiles and on both sides of
+every line of the rule (d = 64: 512 block slots; d = 128: 640, 32 tokens, two blocks per head beyond 128 heads and from 257
+heads on up to 96 tokens), against float64.  Bar: the column sums' 3e-5 (three times the largest measured difference)."""
 import pytest
 import torch
 
@@ -7,8 +8,9 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("d", [64, 128])
-@pytest.mark.parametrize("heads,n", [(1, 1), (3, 33), (8, 63), (8, 64), (9, 65), (2, 127), (5, 129), (8, 1000),
-                                     (64, 512), (64, 513), (80, 512), (80, 513)])
+@pytest.mark.parametrize("heads,n", [(1, 1), (3, 32), (3, 33), (8, 63), (8, 64), (9, 65), (2, 127), (5, 129), (8, 1000),
+                                     (64, 512), (64, 513), (64, 640), (64, 641), (65, 320), (65, 321), (128, 128), (129, 65),
+                                     (192, 129), (200, 129), (264, 96), (264, 97), (512, 32), (512, 33)])
 def test_binary32_column_sums_of_small_grids(d, heads, n):
     from paper_2306_14048_amd import binding as hb
     dev = torch.device("cuda:0")
