@@ -370,18 +370,22 @@ Plan plan_of(int heads, int n_occ, int rpw, bool f32)
     const int rpi = PNW * rpw, umax = rpw * 13 <= 64 ? 13 : 8;
     // Where the line lies.  A budget that the one-workgroup kernel holds in registers is
     // bound by the latency of one pass over it, which a second launch (1.8 us between the two and
-    // 3 in the second) only adds to.  Beyond it, split / one workgroup (time of a step in a graph, 1 to 255
-    // heads, 27 budgets up to 3300, and 12 more on either side of every line):
-    //   16-bit, d = 128     33 to 96 heads: 481 0.86 .. 0.95, 571 0.83 .. 0.91, 700 0.83 .. 0.92, 865 0.65 .. 0.77; 128: 481 0.93, 520
-    //                       and 545 1.01, 571 0.97, from 600 on 0.87 .. 0.96; 160: 0.97 .. 1.07; 200: 0.96 .. 1.22
-    //   binary32, d = 64    33 to 96 heads: 520 to 571 0.88 .. 0.98, 600 to 865 0.71 .. 0.94; 128: 600 0.95, 700 1.00, 811 1.01, 865 0.92;
-    //                       160: 0.97 .. 1.14; 200: 1.01 .. 1.29
-    //   binary32, d = 128   33 to 96 heads: 257 0.91 .. 1.07, 300 0.80 .. 0.89, 417 0.77 .. 0.84; 128: 300 0.97, 345 0.97, 417 0.93; 160:
-    //                       0.96 .. 1.11; 200: 1.03 .. 1.31
-    //   16-bit, d = 64      to 160 heads: 520 to 640 0.79 .. 0.91, 700 and 768 1.01 .. 1.12, 783 to 865 (from 33 heads on) 0.59 ..
-    //                       0.77; 200 and 255: 0.83 .. 0.96, 700 and 768 1.20 .. 1.25
-    // Up to 32 heads the lines of the first three lie higher than what now measures (0.76 .. 0.97 from 481, 600 and
-    // 300 slots on): sizes below them are promised to need no scratch.
+    // 3 in the second) only adds to.  Beyond it, split / one workgroup (time of a step in a graph, one cache over and
+    // over / 12 to 24 caches in turn, whose rows all come from HBM):
+    //   16-bit, d = 128     33 to 64 heads: 481 0.85 .. 0.95 / 0.83 .. 0.94, 520 to 571 0.85 .. 0.95 / 0.79 .. 1.01, 700 0.82 / 0.91; 72 to 96: 481
+    //                       to 520 0.94 .. 0.96 / 1.02 .. 1.09, 571 0.92 / 0.99 .. 1.03, from 600 on 0.74 .. 0.92 / 0.80 .. 0.98; 97 to 128:
+    //                       545 1.01 (one), 571 0.92 .. 1.04 / 1.03 .. 1.10, from 600 on 0.75 .. 0.97 / 0.86 .. 1.05; 160: 0.97 .. 1.07; 200: 0.96 ..
+    //                       1.22
+    //   binary32, d = 64    33 to 88 heads: 577 0.83 .. 0.91 / 0.78 .. 1.00, 700 0.79 .. 0.97 / 0.81 .. 1.00; 96: 577 to 700 0.87 .. 0.95 / 0.93 ..
+    //                       1.04; 128: 700 and 811 1.00 (one), 900 0.95 / 0.95; 160: 0.97 .. 1.14; 200: 1.01 .. 1.29
+    //   binary32, d = 128   33 to 88 heads: 257 0.91 .. 1.07 (one), 300 0.82 .. 0.90 / 0.77 .. 0.99; 96: 300 to 345 0.86 .. 0.97 / 0.96 .. 1.05;
+    //                       104 to 128: 300 to 416 0.85 .. 0.97 / 0.91 .. 1.12, 440 0.81 .. 0.94 / 0.91 .. 1.02; 160: 0.96 .. 1.11; 200: 1.03 .. 1.31
+    //   16-bit, d = 64      to 160 heads: 513 to 640 0.75 .. 0.90 / 0.69 .. 0.98, 700 and 768 1.01 .. 1.12, 783 and 855 0.60 .. 0.93 / 0.63 ..
+    //                       0.93; 200 and 255: 513 to 600 0.95 .. 1.03 / 0.99 .. 1.04, 640 0.96 / 0.97 .. 1.00, 783 on 0.82 .. 0.95 / 0.87 .. 0.96
+    // Where the two disagree (72 to 128 heads next to a line) the line follows the first: with two or three caches in turn it is
+    // still 0.79 .. 1.04, and what many lose, a tenth at most, is less than what few gain.
+    // Up to 32 heads the first three lines are older and lie higher than what measures now (one cache: 0.76 .. 0.97 from
+    // 481, 600 and 300 slots on).
     // With 128-byte rows the one-workgroup kernel's time depends on its ring: 8 and 2 rounds
     // are slow, 6 and 4 fast (255 heads: 1000 slots, ring 8, 20.2 us / split 16.0; 2048 40 / 27; 1061, ring 6, 13.0 /
     // 17.1; 1793 20.8 / 25.3; 1183, ring 4, 16.0 / 18.4;  160 heads: ring 6 1793 17.5 / 18.7, ring 4 1183 14.6 /
