@@ -29,6 +29,13 @@ def test_q4_shared_work_with_every_number_of_waves(waves):
     q4_case(1, heads, 64, k + 3, 4, (k + 1) // 2, k // 2, torch_dt["f16"], 1.0, 90 + waves)
 
 
+@pytest.mark.parametrize("waves", [1, 2, 3, 8])
+def test_q4_final_sums_of_binary32_elements(waves):
+    """Two sums per wave, read of two waves where there are no more, else of eight."""
+    k, heads = 64 * waves - 5, 520 if waves == 1 else 2
+    q4_case(1, heads, 128, k + 3, 4, (k + 1) // 2, k // 2, torch_dt["f32"], 1.0, 190 + waves)
+
+
 def dequantised(x):
     g = x.float().unflatten(-1, (-1, 64))
     mn, mx = g.amin(-1, keepdim=True), g.amax(-1, keepdim=True)
