@@ -427,6 +427,7 @@ __global__ __launch_bounds__(ARW * G * 64, 2) void prefill_attn_kernel(
     constexpr int FDB = NDB / G;            // 32-dim blocks that a wave finishes
     if constexpr (G > 1) {
         constexpr int PART = (FDB * 16 + 2) * 64;
+        static_assert(ARW * 2 * PART * (int)sizeof(float) <= ANS * STAGE && NDB % G == 0, "the stages hold what both groups hand over");
         float *parts = reinterpret_cast<float *>(smem) + (size_t)rw * 2 * PART + lane;    // (stages are done with)
         float *mine = parts + grp * PART;
         const float *other = parts + (1 - grp) * PART;
@@ -505,7 +506,6 @@ hipError_t launch_attn(const h2o_config &cfg, double scale, const void *Q, const
     }
     constexpr int ANW = ARW * G;
     constexpr size_t smem = (size_t)ANS * 2 * ABN * G * D * 2;
-    static_assert(G == 1 || smem >= (size_t)ARW * (D / 32 * 16 + 2) * 256, "the stages hold a group's parts");
     auto kern = kf.rows ? prefill_attn_kernel<DT, D, true, G, SKEW> : prefill_attn_kernel<DT, D, false, G, SKEW>;
     static std::atomic<uint64_t> raised[2] = {};
     if (smem > 48 * 1024) {
