@@ -464,12 +464,16 @@ __global__ __launch_bounds__(SG_NT, 4) void select_gather_kernel(
             bookkeeping_read();
             if (tid == 0) before = atomicAdd(arrived + head, 1u);
             request(even, 0);
-            for (int s0 = 0; s0 < k; s0 += 2 * round) {
-                request(odd, s0 + round);        // (past the end: row 0, not written)
-                write(even, s0);
-                if (s0 == 0 && before == (unsigned)parts - 1) store_bookkeeping();     // (behind write's barrier)
-                request(even, s0 + 2 * round);
-                write(odd, s0 + round);
+            // The first round in front of the loop: positions and scores are in registers no longer than to here (kept
+            // through the loop they spilled 23 registers, waited for with the rows in flight).
+            request(odd, round);                 // (past the end: row 0, not written)
+            write(even, 0);
+            if (before == (unsigned)parts - 1) store_bookkeeping();     // (behind write's barrier)
+            for (int s0 = round; s0 < k; s0 += 2 * round) {
+                request(even, s0 + round);
+                write(odd, s0);
+                request(odd, s0 + 2 * round);
+                write(even, s0 + round);
             }
             return;
         }

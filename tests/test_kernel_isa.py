@@ -147,6 +147,18 @@ def test_benchmarked_kernels_do_not_spill(scores_asm, tmp_path):
     assert checked >= 8
 
 
+def test_builds_of_the_selection_do_not_spill(tmp_path):
+    """Nor do those of a compression (a chunked prompt's is one with several workgroups per head inside the cache)."""
+    checked = Counter()
+    for name, m in metadata(device_asm("select_gather.hip", tmp_path)).items():
+        # row bytes, 4-bit type, pattern, keys, in place (0 no, 1 by one workgroup, 2 by columns), threads
+        shape = re.search(r"select_gather_kernelILi\d+ELi\w+ELb\dELi\d+ELi(\d)ELi(\d+)E", name)
+        if shape:
+            assert m["vgpr_spill_count"] == 0 and m["private_segment_fixed_size"] == 0, (name, m)
+            checked[shape[1]] += 1
+    assert checked["0"] >= 60 and checked["1"] == checked["2"] >= 27, checked
+
+
 def test_output_sums_halve_their_columns(tmp_path):
     checked = 0
     for src in ("decode_step.hip", "decode_split.hip"):
