@@ -245,10 +245,11 @@ static inline SelectPlan select_plan(int heads, int k, int n, bool in_place)
 }
 
 // Workgroups per head of the compression in place: each moves its own columns of the rows, 128 bytes of them (K and
-// V taken as one row) and 32 KiB of K's and V's together at least.  A head's rows go through one CU otherwise.  Whole chunked calls, us,
+// V taken as one row) and 64 KiB of K's and V's together at least.  A head's rows go through one CU otherwise.  Whole chunked calls, us,
 // one workgroup / several: 32 heads x 819 slots of 256 bytes, chunks of 512, 370.6 / 349.0; 8 x 1000, 2048, 220.0 / 211.7;
 // 8 x 600, 256, averaged 414.5 / 400.0; 128 x 819, 1024, 676 / 672.  Below 128 KiB of K the rows are a round or two either
-// way: 56 x 300 158 / 161, 16 x 819 of 128 bytes 207.6 / 209.6.
+// way: 56 x 300 158 / 161, 16 x 819 of 128 bytes 207.6 / 209.6.  (Every workgroup selects for itself; the scores that they all read
+// again beyond SG_LDS_KEYS candidates do not show: 127 heads x 1000, 29 000 tokens 29.76 / 29.86 ms, 20 x 1000, 31 000, a pattern 6.21 / 6.19.)
 static inline int compact_parts(int heads, int k, int rowb)
 {
     int parts = 1;

@@ -20,6 +20,8 @@ int main()
             printf("%d %d %d\n", p.parts, p.part_slots, (int)p.wide);
         } else if (what == 2) {
             printf("%d %d\n", (int)small_blocks(a, b, c, d), (int)head_slots(a));
+        } else if (what == 3) {
+            printf("%d\n", compact_parts(a, b, c));
         } else {
             printf("%d %d %d\n", (int)two_groups(a, b, c, false, d), (int)groups_apart(a, b, c, d), (int)head_slots(a));
         }
@@ -67,6 +69,22 @@ def test_selection_of_few_candidates_and_in_place(plans):
     q = [(0, h, k, n, 1) for h in (1, 12, 56, 128, 256, 257, 3584) for k in (64, 4096) for n in (4096, 4097, 16385, 69000)]
     for (_, h, k, n, _), (parts, slots, wide) in zip(q, plans(q)):
         assert (parts, slots) == (1, k) and wide == (n > 4096 and (h <= 256 or n > 16384)), (h, k, n)
+
+
+def test_columns_of_the_compression_in_place(plans):
+    """Workgroups per head: powers of two (columns are found with masks), lines of 128 bytes, K's columns or V's, at
+    least 64 KiB of rows each and no more than there are CUs."""
+    q = [(3, h, k, rowb, 0) for h in [*range(1, 270), 512, 3584] for rowb in (128, 256, 512)
+         for k in (1, 255, 256, 300, 511, 512, 513, 819, 1023, 1024, 1025, 2048, 4095, 4096)]
+    seen = set()
+    for (_, h, k, rowb, _), (parts,) in zip(q, plans(q)):
+        seen.add(parts)
+        assert parts & (parts - 1) == 0 and 1 <= parts <= 2 * rowb // 128, (h, k, rowb)
+        if parts > 1:
+            assert k * rowb >= 131072 and h * parts <= 256 and 2 * k * rowb // parts >= 65536, (h, k, rowb)
+        elif k * rowb >= 131072:
+            assert h > 128, (h, k, rowb)
+    assert seen == {1, 2, 4, 8}
 
 
 def test_attention_groups_apart_have_a_cu_of_their_own(plans):

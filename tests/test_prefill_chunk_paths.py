@@ -30,6 +30,10 @@ DT = {"f32": torch.float32, "f16": torch.float16, "bf16": torch.bfloat16}
     ("f16", 128, 5, 800, 100, (1000, 777), dict(protect=1, stride=5)),
     ("bf16", 128, 2, 0, 900, (1000, 300, 901), {}),                    # window only
     ("bf16", 128, 16, 700, 500, (900, 700, 5000), {}),                 # fills up first; sixteen waves
+    ("f16", 128, 2, 300, 300, (700, 17000), {}),                       # sixteen waves, keys in LDS
+    ("bf16", 128, 3, 300, 300, (700, 29000), {}),                      # ... keys formed per sweep, from scores read again
+    ("f16", 128, 2, 500, 100, (700, 17000, 29000), dict(protect=1, stride=37)),
+    ("f32", 64, 9, 400, 200, (700, 29000), dict(rank=1)),
 ])
 def test_in_place_chunk_matches_the_copying_way(dt, d, heads, heavy, recent, chunks, more):
     from paper_2306_14048_amd import binding as hb
