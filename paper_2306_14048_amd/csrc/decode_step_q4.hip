@@ -45,8 +45,9 @@
 // Memory plan.  A wave owns blocks of 64 consecutive slots, one slot per lane.  A
 // block's stored rows are one contiguous image of 64 * 80 (or 48) bytes; the K images of a
 // wave's blocks followed by the V images are copied straight into a ring of LDS buffers of
-// its own (no registers, no barriers), all of them up front when the ring holds them
-// (budgets up to 512: two workgroups per CU), with the slots' bookkeeping behind them.
+// its own (no registers, no barriers).  Requested are, at the start, the K images that the ring
+// holds and behind them the slots' bookkeeping, once q's digits are cut the V images that it
+// holds besides, and every other image when the buffer it goes to has been read.
 // Every global read of the kernel is such a copy, so that each wait names exactly the
 // copies it needs (a load that the compiler waits for would wait for all of them).
 #include "wave_ops.h"
@@ -188,8 +189,8 @@ __global__ __launch_bounds__(MAX_WAVES * 64, 4) void decode_q4_kernel(const Step
     char *Kb = Kc + hoff * ROWB;
     char *Vb = Vc + hoff * ROWB;
 
-    // ---- requests: q and the new token (wave 0), then the wave's images in the order they
-    // are used, then the bookkeeping.  Pieces past the occupied slots repeat the last
+    // ---- requests: q and the new token (wave 0), then the wave's first K images, then the
+    // bookkeeping (value images: behind q's digits).  Pieces past the occupied slots repeat the last
     // occupied piece (in bounds; what they hold is masked).
     if (wave == 0) {
         constexpr unsigned RB = D * sizeof(T);
@@ -230,7 +231,6 @@ __global__ __launch_bounds__(MAX_WAVES * 64, 4) void decode_q4_kernel(const Step
             dma4(rsrc_a, off, 0u, mine_b + L::META + s * 512 + 256);
         }
     }
-
 
     // ---- q: the token's own logit, group sums, digits --------------------------------
     dma_wait_upto<KFIRST * IPB + META_COPIES>();    // (wave 0: its three copies have landed)

@@ -10,8 +10,9 @@
 // they differ in which operand stays in registers.  A workgroup's waves own 32
 // "stationary" rows each (queries in pass 1, keys in pass 2; kept in registers as
 // MFMA B-operand fragments) and stream tiles of the other operand through LDS
-// as A-operand fragments.  Eight waves (four in the shape for smaller grids)
-// share one streamed tile: the copy into LDS and its address arithmetic are paid
+// as A-operand fragments.  Eight waves (four in the shape for smaller grids, two in
+// binary32's for the smallest; either may have a second group of waves for half of a
+// tile's rows) share one streamed tile: the copy into LDS and its address arithmetic are paid
 // once per 256 stationary rows, which matters because the matrix pipe, the
 // vector ALU (one exponential per product) and the vector memory path are all
 // close to saturated by this loop.  With the 32x32 MFMA
@@ -74,13 +75,14 @@ constexpr int NLB = 4;         // row-statistic buffers (pass 2; read one phase 
 // RWV: waves over a workgroup's rows.  Eight (256 stationary rows, two workgroups per CU) is
 // the shape for a full chip.  Four (128 rows) is for grids that do not fill it: the longest
 // block then has half the work per tile.  Without SKEW its waves meet at one barrier per tile and
-// the overlap is left to the workgroups that share a CU.
+// the overlap is left to the workgroups that share a CU.  Two (64 rows, with two groups) is binary32's shape for the
+// smallest grids (small_blocks): half the work again.
 //
 // The first kf.rows keys of a head may sit elsewhere (FrontRows).  Stationary rows are
 // simply loaded from where they are; streamed ones (pass 1, TWO) are copied tile by tile
 // from one or the other, and row by row in the one tile that has rows of both.
 //
-// G (four-wave shape): groups of four waves over the same 128 stationary rows.  With two, a
+// G (shapes of four and of two waves): groups of waves over the same 128 or 64 stationary rows.  With two, a
 // tile has twice the rows and each group takes half of them; the parts are joined at the
 // end.  For grids that leave CUs idle: the longest block has half the steps.
 // SKEW: the two halves of eight waves, of one shape or of two groups of four, run one phase apart: two
@@ -115,6 +117,9 @@ __device__ __forceinline__ void prefill_pass(
     // Pieces in which a wave's stationary rows fit its share of two tile buffers.  Loaded directly: where these are more
     // than two, or two halves of a 128-byte row (512 heads x 2048, d = 64, 410 us, copied 415), and binary32 rows without
     // a second group (a block is its matrix instructions there: 256 x 300, d = 128, 93.7 / 94.9, 8 x 256, d = 64, 25.8 / 25.1).
+    // Prompts of up to 32 tokens pay 0.1 to 0.5 us for it (a barrier and an LDS read in front of their one tile; both passes, direct /
+    // staged: f16, d = 128, 32 x 1 7.6 / 7.9, 32 x 17 7.7 / 7.75, d = 64 1024 x 17 9.8 / 10.4); leaving out that tile's second copy
+    // there gains 2 to 4 % and costs 65 to 300 tokens 0.5 to 1.
     constexpr int SROUNDS = NWV * 16 / BN;
     constexpr bool STAGED = (SROUNDS == 1 || (SROUNDS == 2 && ROWB >= 256)) && (DT != H2O_F32 || G > 1);
     static_assert(CHUNKS % NT == 0 && CPT >= 1, "every thread moves the same number of chunks");
