@@ -153,8 +153,8 @@ static inline bool two_groups(int heads, int rows, int streamed, bool f32, int d
 // grids that leave CUs idle the longest block then has half the work (a binary32 pass is its matrix
 // instructions).  Reset, both passes and selection, us, 128 rows / 64: d = 64, 8 heads x 256 32.8 / 23.1, 8 x 1500 117 / 76, 56 x
 // 512 (448 slots) 48.7 / 41.2, 128 x 256 (512) 33.9 / 31.9; d = 128, 8 x 256 52.4 / 33.0, 32 x 1000 (512) 147 / 101, 128 x 300 (640)
-// 87.5 / 65.3.  At d = 64 no grid up to 512 slots loses (0.58 .. 0.99).  At d = 128 a workgroup has its CU to itself (97 KiB of LDS), and a block
-// of 64 rows counts as half a round of the CUs (both passes alone, 64 rows / 128):
+// 87.5 / 65.3.  At d = 64 no grid up to 512 slots loses (0.58 .. 0.99).  At d = 128 a workgroup has its CU to itself (97 KiB of
+// LDS), and a block of 64 rows counts as half a round of the CUs (both passes alone, 64 rows / 128):
 //   to 32 streamed rows the second group has nothing to do: 8 to 256 heads x 1 .. 32 1.09 .. 1.17, 512 1.29 .. 1.44
 //   fewer rounds        264 to 320 heads x 100 and 128 0.83 .. 0.85, 136 to 192 x 129 .. 192 0.81 .. 0.96, one block per head to
 //                       640 heads 0.73 .. 0.97; but 264 to 320 x 65 (a second block of one row) 1.05 .. 1.07
